@@ -43,7 +43,7 @@ struct qoda_ctx {
   unsigned char *d_lut = nullptr;
   unsigned int *d_hist = nullptr, *d_status = nullptr;
   unsigned long long *d_pooled = nullptr;
-  int *d_type_exp = nullptr;
+  int *d_type_exp = nullptr, *d_walk = nullptr;
   short *d_dp_arg = nullptr;
   long long *d_dp_arg_off = nullptr;
   int *d_type_exp_next = nullptr;   // bucket scope: the weight scales the next gathering pass will use
@@ -244,7 +244,7 @@ Dev base_args(const qoda_ctx *c) {
   a.type_points = c->d_type_points;
   a.partial = c->d_partial; a.dpartial = c->d_dpartial; a.sumsq = c->d_sumsq;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
-  a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut;
+  a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.walk = c->d_walk;
   a.hist = c->d_hist; a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
   a.dp_arg = c->d_dp_arg; a.dp_arg_off = c->d_dp_arg_off;
   a.status = c->d_status; a.eta = c->d_eta;
@@ -283,7 +283,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_stiles, c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
-                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip};
+                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   qoda_ctx::Table *tabs[] = {&c->t_grad, &c->t_msg, &c->t_prev, &c->t_in, &c->t_x1, &c->t_y, &c->t_xh, &c->t_xn, &c->t_mean};
@@ -394,9 +394,17 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   // (workgroups the device holds) / K tiles per node, twice and four times that for the pairs and fours.  A launch of fewer than
   // four device-fills of full-length workgroups keeps full runs throughout: there the extra flushes of the short runs
   // cost more than the tail (measured on 0.4 k tiles per node: +20 % on the norm pass).
+  // Under bucket scope the table serves the quantize pass, which is bound by the vector ALU: what counts there is that
+  // every CU gets the same work, and a workgroup's tables and flush cost about a quarter of a tile.  Few tiles: single
+  // ones, then pairs (3096 tiles, K = 8: 167 us per round with runs of 8, 133 with 3, 119 with 1, 2 or 4; single ones also
+  // leave the most workgroups to a call for one node).  From 16 k tiles on, full runs that shorten at the end: 75 k tiles,
+  // K = 8: 1.93 ms with runs of 8, 1.96 with 4, 1.99 with 2, 2.17 with 1.
   std::vector<int4> stiles;
   {
-    const bool large = chunks * c->K >= 4ll * kSuperTile * kTaperWorkgroups;
+    const bool bucket = c->scope == kScopeBucket;
+    const long long total = chunks * c->K;
+    const int longest = !bucket || total > 16384 ? kSuperTile : total > 4096 ? 2 : 1;
+    const bool large = total >= (bucket ? 16384 : 4ll * kSuperTile * kTaperWorkgroups);
     const long long T = large ? (kTaperWorkgroups + c->K - 1) / c->K : 0;
     long long before = 0;   // tiles of the layers already listed
     for (int l = 0; l < c->L; ++l) {
@@ -404,7 +412,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
       for (int ch = 0; ch < n;) {
         const long long left = chunks - (before + ch);   // tiles from here to the end of the table
         const int want = left <= T ? 1 : left <= 3 * T ? 2 : left <= 7 * T ? 4 : kSuperTile;
-        const int len = std::min(want, n - ch);
+        const int len = std::min(std::min(want, longest), n - ch);
         stiles.push_back(make_int4(l, ch, len, 0));
         ch += len;
       }
@@ -441,6 +449,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_status, 2));   // the status word, and a word no kernel result depends on
   A(dev_alloc(&c->d_pooled, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_type_exp, (size_t)c->M));
+  A(dev_alloc(&c->d_walk, (size_t)c->M));
   if (c->scope == kScopeBucket) {   // the quantize pass gathers the fit's statistics itself
     A(dev_alloc(&c->d_type_exp_next, (size_t)c->M));
     A(dev_alloc(&c->d_type_skip, (size_t)c->M));

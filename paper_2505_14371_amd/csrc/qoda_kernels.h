@@ -63,6 +63,7 @@ struct Dev {
   float *lev;         // [M*256]
   float *rgap;        // [M*256]
   unsigned char *lut;  // [M*1024] level-search table: tau at the lower edge of the bin bits(u) >> 20
+  int *walk;          // [M] some interior level of the type lies inside a bin of lut
   unsigned int *hist;          // [K*L*2048]
   unsigned long long *pooled;  // [M*257]
   int *type_exp;               // [M]

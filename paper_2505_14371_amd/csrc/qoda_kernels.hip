@@ -583,10 +583,176 @@ __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
   quantize_tile<C1, PREV>(a, m, l, k, tile.y, lut, tab, tprev, red);
 }
 
+// ------------------------------------------------------------------------------------------------ octets in registers
+// The quantizer for a wave that holds a whole octet (8 blocks = 2048 coordinates; 32 values a lane): the form with the
+// fewest instructions.  Used where the pass is bound by the vector ALU or by latency and not, like k_quantize on large
+// models, by the memory system's rate for its mix of loads and stores.
+
+// Bits of word r of a record that hold the sign of a code (bit C1*jj of the little-endian string).
+template <int C1>
+constexpr unsigned int sign_bits(int r) {
+  unsigned int m = 0u;
+  for (int jj = 0; jj < 32; ++jj)
+    if ((C1 * jj) >> 5 == r) m |= 1u << ((C1 * jj) & 31);
+  return m;
+}
+
+// Append the codes of block bb (sign | index << 1, C1 bits each) to the record.  The codes of up to 32 bits are
+// assembled from the last one down, two instructions each: index by shift-and-or, sign by a funnel shift out of the value.
+template <int C1>
+__device__ __forceinline__ void insert_block(unsigned int (&D)[C1], const unsigned int (&h)[4], const float *x, int bb) {
+  constexpr int N = C1 <= 8 ? 4 : 2;   // codes per unit
+#pragma unroll
+  for (int q = 0; q < 4; q += N) {
+    unsigned int F = 0u;
+#pragma unroll
+    for (int j = N - 1; j >= 0; --j) {
+      F = (F << (C1 - 1)) | h[q + j];
+      F = __builtin_amdgcn_alignbit(F, f2u(x[q + j]), 31);   // (F << 1) | sign
+    }
+    const int pos = C1 * (4 * bb + q), r = pos >> 5, sh = pos & 31;
+    D[r] |= F << sh;
+    if (sh + N * C1 > 32) D[r + 1] |= F >> (32 - sh);
+  }
+}
+
+// Nothing of a block may be worked out before its turn or be left for later: with the blocks interleaved, or the
+// differences computed where the sum needs them, the compiler keeps more than 200 registers.  The block's values pass
+// through an empty statement that keeps its place.
+__device__ __forceinline__ void pin_block(float *x) {
+  asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+}
+
+// One octet from registers.  x: the lane's 32 values in order (zeros past the end of the layer: they give code 0 and
+// distance 0).  A block's four differences to the previous message (up to a sign that their square does not see) are
+// given to done(bb, diff) as soon as they are known; it may put new values into the block's place in x.
+// Tables: lut as in build_tables; tprev[code] = value the previous message's code stands for.
+//   WALK = false, layer norms    tab[tau] = {l_tau, 1/gap, norm * l_tau, norm * l_tau+1}: the decoder's product, taken once
+//                                per table entry
+//   WALK = true, or bucket norms tab[tau] = {l_tau, 1/gap, l_tau+1, -}
+// WALK: some level of the type lies inside a bin of lut, so a lane may have to step on from the entry that lut names.
+// Fitted levels sit on bin edges: then tau at the lower edge is tau.  (At u = 1 the walk ends on the entry of the last
+// level, xi = 0; without it tau = S-2 and xi = 1 - 2^-23 at least, above every 16-bit draw: the same code.)
+// inv, norm, pnorm: one value (layer norms), or per block (bucket norms; entry bb).
+template <int C1, bool PREV, bool WALK, bool BUCKET, class Hist, class Done>
+__device__ __forceinline__ void quantize_regs(float (&x)[32], unsigned int c0, unsigned int l, unsigned int round,
+                                               unsigned int k, unsigned int k0, unsigned int k1, const float *inv,
+                                               const float *norm, const float *pnorm, const unsigned char *lut,
+                                               const float4 *tab, const float *tprev, unsigned int (&D)[C1],
+                                               const unsigned int (&Dp)[C1], Hist &&hist, Done &&done) {
+#pragma unroll
+  for (int pp = 0; pp < 4; ++pp) {   // pairs of blocks: one generator call serves 8 coordinates of a lane
+    asm volatile("" : "+v"(c0));
+    unsigned int o[4];
+    philox4x32_10(c0, l, round, k, k0, k1, o);
+    c0 += 64u;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int bb = 2 * pp + half;
+      float *xb = &x[4 * bb];
+      pin_block(xb);
+      const float bi = inv[BUCKET ? bb : 0];
+      float u[4], mag[4];
+      unsigned int h[4];
+      int tau[4];
+      float4 lv[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        // min(|v| * inv, 1): the product is never negative or NaN for finite input, so the [0, 1] clamp of the
+        // multiply instruction is the same thing
+        u[j] = __builtin_amdgcn_fmed3f(fabsf(xb[j]) * bi, 0.0f, 1.0f);
+        tau[j] = lut[f2u(u[j]) >> 20];
+      }
+      hist(xb, u, bb);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) lv[j] = tab[tau[j]];
+      if (WALK) {
+        if (__ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            while (lv[j].z <= u[j]) { ++tau[j]; lv[j] = tab[tau[j]]; }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const unsigned int w16 = half ? (o[j] >> 16) : (o[j] & 0xFFFFu);
+        const float xi = (u[j] - lv[j].x) * lv[j].y;
+        // (w16 + 0.5) < xi * 65536  <=>  w16 < xi * 65536 - 0.5 : the scaling by 2^16 is exact, and the subtraction
+        // is exact whenever its result is not negative, so one fused operation decides the same.
+        const bool up = (float)w16 < __builtin_fmaf(xi, 65536.0f, -0.5f);
+        h[j] = (unsigned int)tau[j] + (up ? 1u : 0u);
+        // norm * l_h, the value the decoder will rebuild (the last entry's upper neighbour is never selected: xi = 0)
+        if (WALK || BUCKET) mag[j] = norm[BUCKET ? bb : 0] * (up ? lv[j].z : lv[j].x);
+        else mag[j] = up ? lv[j].w : lv[j].z;
+      }
+      insert_block<C1>(D, h, xb, bb);
+      if (PREV) {
+        // +-mag - prev = +-(mag -+ prev): the value's sign, now in the record, is folded into the previous code's sign
+        // (one operation per word), so that the table gives the previous value relative to it
+        unsigned int E[C1];
+#pragma unroll
+        for (int r = 0; r < C1; ++r) E[r] = __builtin_amdgcn_bitop3_b32(Dp[r], D[r], sign_bits<C1>(r), 0x78);   // a ^ (b & c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float pl = lds_float_at(tprev, extract_off<C1>(E, 4 * bb + j));   // table all zero without a message
+          mag[j] = mag[j] - (BUCKET ? pnorm[bb] * pl : pl);
+        }
+      }
+      done(bb, mag);
+#pragma unroll
+      for (int r = 0; r < C1; ++r) asm volatile("" : "+v"(D[r]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+struct NoHist {
+  __device__ __forceinline__ void operator()(const float *, const float (&)[4], int) const {}
+};
+
+// The lane's 32 coordinates of octet O of a layer of d entries (zeros past the end).
+__device__ __forceinline__ void load_octet(const float *__restrict__ v, long long O, long long d, int i, float (&x)[32]) {
+  const long long e0 = O * 2048 + 4 * i;
+  if ((O + 1) * 2048 <= d) {
+    v4f q[8];
+#pragma unroll
+    for (int bb = 0; bb < 8; ++bb)
+      q[bb] = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) v4f *>(as_global(v) + e0 + bb * kBlockCoords));
+#pragma unroll
+    for (int bb = 0; bb < 8; ++bb) { x[4 * bb] = q[bb].x; x[4 * bb + 1] = q[bb].y; x[4 * bb + 2] = q[bb].z; x[4 * bb + 3] = q[bb].w; }
+  } else {
+#pragma unroll
+    for (int bb = 0; bb < 8; ++bb) {
+      float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (e0 + bb * kBlockCoords < d) load4(v, e0 + bb * kBlockCoords, d, y);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * bb + j] = y[j];
+    }
+  }
+}
+
+// Block bb of an octet that lies inside its layer; vo: the octet's first coordinate (the same for the wave).
+__device__ __forceinline__ void load_block(const float *vo, int bb, unsigned int i, float *x) {
+  const auto *g = reinterpret_cast<const __attribute__((address_space(1))) char *>(as_global(vo));
+  const v4f q = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) v4f *>(g + (16u * i + 1024u * bb)));
+  x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+}
+
+// The tile sums of a run from its slots' fp32 chains: a wave takes every fourth tile, widens the 256 slots and combines
+// them by the halving tree.
+__device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, const LayerMeta &m, int4 st, int kr, int w, int i) {
+  for (int cc = w; cc < st.z; cc += kThreads / 64) {
+    const float *ch = chain + cc * kThreads;
+    double r = ((double)ch[i] + (double)ch[i + 128]) + ((double)ch[i + 64] + (double)ch[i + 192]);
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) r = r + __shfl_down(r, h, 64);
+    if (i == 0) a.dpartial[(size_t)kr * a.G + m.first_chunk + st.y + cc] = r;
+  }
+}
+
 // ------------------------------------------------------------------------------------------------ bucket scope
 // One norm per 128 consecutive coordinates (the experiments' setting, Sec. 7): the norms are computed by the wave
-// that quantizes, so the gradient is read from memory once (the second touch of an octet, a few microseconds after
-// the first, is served by the cache).
+// that quantizes, from the registers that it then quantizes from, so the gradient is read once.
 //
 // Per-wave shared memory of the bucket-scope quantizer.
 constexpr double kBucketRescueBelow = 7.888609052210118e-31;   // 2^-100
@@ -607,24 +773,24 @@ struct __attribute__((aligned(8))) BucketWave {
 // 2^-100 or not finite.  The 8 x 64 lane sums go through the wave's shared memory four blocks at a time (as doubles they
 // fill the area the single-precision pass used).  Every lane of the wave must call this; the result is the sum of
 // the lane's own bucket.
-template <bool FAST>
-__device__ __forceinline__ double bucket_sums_exact(const LayerMeta &m, long long O, const float *__restrict__ v,
-                                                 float *psum, int i) {
+__device__ __forceinline__ double bucket_sums_exact(const float (&x)[32], float *psum, int i) {
   double *dsum = reinterpret_cast<double *>(psum);
   const int q = i >> 2, r = i & 3;
   const int bb = q >> 1, hf = q & 1;
   double s = 0.0;
+#pragma unroll
   for (int half = 0; half < 2; ++half) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
     for (int b4 = 0; b4 < 4; ++b4) {
-      const long long e = (O * 8 + 4 * half + b4) * kBlockCoords + 4 * i;
-      float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (FAST || e < m.d) load4(v, e, FAST ? e + 4 : m.d, x);
       double acc = 0.0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_fma((double)x[j], (double)x[j], acc);
+      for (int j = 0; j < 4; ++j) {
+        const double xd = (double)x[16 * half + 4 * b4 + j];
+        acc = __builtin_fma(xd, xd, acc);
+      }
       dsum[72 * b4 + i + (i >> 3)] = acc;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -640,39 +806,41 @@ __device__ __forceinline__ double bucket_sums_exact(const LayerMeta &m, long lon
   return s;
 }
 
-// Sums of squares of the 16 buckets of one octet -> norm, inv (shared memory) and the octet's norm trailer.
+// The fit's weighted grid histogram of a run, in shared memory: 32-bit adds, the weights (at most 2^30) cut into their
+// low kHistLowBits bits and the rest, which is zero for most buckets of heavy-tailed vectors and then not added at all.
+// A run has at most 8 * 16384 coordinates and a copy takes every kHistCopies-th lane's, so no cell overflows:
+// 2^17 / 16 * (2^19 - 1) < 2^32 and 2^17 / 4 * 2^11 < 2^32.  Copies of a bin lie side by side: lanes that meet in a bin
+// collide rarely.  An add of 64 lanes keeps the CU's shared memory busy for 6 cycles here, against 13 for the 64-bit adds
+// of four copies that this replaces (10 for eight copies).
+constexpr int kHistLowBits = 19;
+constexpr int kHistCopies = 16, kHistHighCopies = 4;   // powers of two
+static_assert((long long)kSuperTile * kChunkCoords / kHistCopies * ((1 << kHistLowBits) - 1) < (1ll << 32), "low cells");
+
+// Statistics of the 16 buckets of one octet (the lane's 32 values in x) -> norm, inv (shared memory) and the octet's
+// norm trailer.
 // A lane's four squares are an fp32 fused chain; lane L then finishes bucket q = L/4 (block q/2, half q%2): it adds 8
 // consecutive lane sums, widened to fp64, by the in-order binary tree, then the four lanes of the quad combine
 // (neighbour, then pair), which continues the same tree.
 // A single-precision result below 2^-100 (squares may have vanished) or not finite (squares may have overflowed) is
 // replaced by the exact one (bucket_sums_exact).
 // ex: weight scale of the layer's type for the fit statistics (kTypeSkip: none); best: running maximum of the bit
-// patterns of the lane's bucket sums.
-template <bool FAST, int KIND>
-__device__ __forceinline__ void bucket_norms(const Dev &a, const LayerMeta &m, long long O, const float *__restrict__ v,
-                                             float *trailer, const float *prev_trailer, BucketWave &bw, int i, int ex,
-                                             unsigned long long &best) {
+// patterns of the lane's bucket sums.  Returns whether some weight of the octet has bits above kHistLowBits.
+template <int KIND>
+__device__ __forceinline__ bool bucket_norms(const Dev &a, const float (&x)[32], float *trailer, float prev_norm,
+                                             BucketWave &bw, int i, int ex, unsigned long long &best) {
 #pragma unroll
   for (int bb = 0; bb < 8; ++bb) {
-    const long long e = (O * 8 + bb) * kBlockCoords + 4 * i;
-    float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (FAST) {
-      const v4f q = *reinterpret_cast<const __attribute__((address_space(1))) v4f *>(as_global(v) + e);
-      x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
-    } else if (e < m.d) {
-      load4(v, e, m.d, x);
-    }
     float acc = 0.0f;
     if (KIND == kNormL2) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_fmaf(x[j], x[j], acc);
+      for (int j = 0; j < 4; ++j) acc = __builtin_fmaf(x[4 * bb + j], x[4 * bb + j], acc);
     } else if (KIND == kNormL1) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = acc + fabsf(x[j]);
+      for (int j = 0; j < 4; ++j) acc = acc + fabsf(x[4 * bb + j]);
     } else {
       unsigned int mb = 0u;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) mb = max(mb, f2u(x[j]) & 0x7FFFFFFFu);
+      for (int j = 0; j < 4; ++j) mb = max(mb, f2u(x[4 * bb + j]) & 0x7FFFFFFFu);
       acc = magnitude_from_bits(mb);
     }
     bw.psum[72 * bb + i + (i >> 3)] = acc;
@@ -698,7 +866,7 @@ __device__ __forceinline__ void bucket_norms(const Dev &a, const LayerMeta &m, l
   if (KIND == kNormL2) {
     const bool redo = !(s >= kBucketRescueBelow) || !(s <= 1.7976931348623157e308);
     if (__ballot(redo) != 0ull) {   // rare: all lanes of the wave take the exact path together
-      const double exact = bucket_sums_exact<FAST>(m, O, v, bw.psum, i);
+      const double exact = bucket_sums_exact(x, bw.psum, i);
       if (redo) s = exact;
     }
   }
@@ -727,134 +895,56 @@ __device__ __forceinline__ void bucket_norms(const Dev &a, const LayerMeta &m, l
     bw.wfix[8 * hf + bb] = wf;
     trailer[8 * hf + bb] = n;
   }
-  if (i < 16) bw.pnorm[i] = prev_trailer ? prev_trailer[i] : 0.0f;
+  if (i < 16) bw.pnorm[i] = prev_norm;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return __ballot(wf >> kHistLowBits) != 0ull;
 }
 
-// quantize_block with the block's own (bucket) norm, reciprocal and previous norm; the tables hold plain levels.
-constexpr int kBucketHistCopies = 4;   // power of two
-
-template <int C1, bool PREV>
-__device__ __forceinline__ void quantize_block_b(const float (&x)[4], const unsigned int (&o)[4], int half, float inv,
-                                                 float norm, float pnorm, const unsigned char *lut, const float4 *tab,
-                                                 const float *tprev, unsigned int (&D)[C1],
-                                                 const unsigned int (&Dp)[C1], float &acc, unsigned int wfix,
-                                                 unsigned long long *lh) {
-  float u[4];
-  int tau[4];
-  float4 lv[4];
+struct BucketHist {
+  const unsigned int *wfix;   // weights of the lane's eight buckets (its half's), shared memory
+  unsigned int *lo, *hi;      // the lane's copies
+  bool on;      // statistics are gathered (this and the next two: the same for the whole wave)
+  bool high;    // some weight of the octet has bits above kHistLowBits
+  bool plain;   // no such weight, and no coordinate of the octet is in raw magnitude bin 0
+  __device__ __forceinline__ void operator()(const float *x, const float (&u)[4], int bb) const {
+    if (!on) return;
+    const unsigned int w = wfix[bb];
+    if (plain) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    u[j] = __builtin_amdgcn_fmed3f(fabsf(x[j]) * inv, 0.0f, 1.0f);
-    tau[j] = lut[f2u(u[j]) >> 20];
-  }
-  if (wfix != 0u) {   // a bucket with weight: the fit's grid histogram (integer adds)
+      for (int j = 0; j < 4; ++j)
+        atomicAdd(&lo[__builtin_elementwise_sub_sat(f2u(u[j]) >> 20, (unsigned int)kGridBase) * kHistCopies], w);
+      return;
+    }
+    if (w == 0u) return;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if ((f2u(x[j]) & 0x7FF00000u) == 0u) continue;   // raw magnitude bin 0; also the +0 padding past the layer's end
+      if (fabsf(x[j]) < 0x1p-129f) continue;   // raw magnitude bin 0; also the +0 padding past the layer's end
       // u <= 1, so its bin never exceeds the last grid index: only the lower clamp is needed (saturating subtract)
       const unsigned int g = __builtin_elementwise_sub_sat(f2u(u[j]) >> 20, (unsigned int)kGridBase);
-      atomicAdd(&lh[g * kBucketHistCopies], (unsigned long long)wfix);
+      atomicAdd(&lo[g * kHistCopies], w & ((1u << kHistLowBits) - 1u));
+      if (high) atomicAdd(&hi[g * kHistHighCopies], w >> kHistLowBits);
     }
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) lv[j] = tab[tau[j]];
-  if (__ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      while (lv[j].z <= u[j]) { ++tau[j]; lv[j] = tab[tau[j]]; }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int jl = 4 * half + j;
-    const unsigned int w16 = half ? (o[j] >> 16) : (o[j] & 0xFFFFu);
-    const float xi = (u[j] - lv[j].x) * lv[j].y;
-    const bool up = (float)w16 < __builtin_fmaf(xi, 65536.0f, -0.5f);
-    const unsigned int h = (unsigned int)tau[j] + (up ? 1u : 0u);
-    const float mag = norm * (up ? lv[j].z : lv[j].x);
-    const float cur = __builtin_copysignf(mag, x[j]);
-    insert_code<C1>(D, (h << 1) | (f2u(x[j]) >> 31), 24 + jl);
-    float diff = cur;
-    if (PREV) {
-      const float pl = lds_float_at(tprev, extract_off<C1>(Dp, jl));   // +-level of the previous code
-      const float pv = pnorm * pl;
-      diff = cur - pv;
-    }
-    acc = __builtin_fmaf(diff, diff, acc);
-  }
-}
+};
 
-template <int C1, bool FAST, bool PREV, int KIND>
-__device__ __forceinline__ void quantize_octet_b(const Dev &a, const LayerMeta &m, int l, int k, long long O,
-                                                 const float *__restrict__ v, unsigned char *body,
-                                                 const unsigned char *prevbody, const unsigned char *lut,
-                                                 const float4 *tab, const float *tprev, BucketWave &bw, int i,
-                                                 float &acc, int ex, unsigned long long &best,
-                                                 unsigned long long *lh) {
-  constexpr long long OS = 256 * C1 + 64;   // bytes per octet: codes, then the 16 bucket norms
-  const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
-  unsigned char *oct = body + O * OS;
-  const unsigned char *poct = prevbody ? prevbody + O * OS : nullptr;
-  bucket_norms<FAST, KIND>(a, m, O, v, reinterpret_cast<float *>(oct + 256 * C1),
-                     poct ? reinterpret_cast<const float *>(poct + 256 * C1) : nullptr, bw, i, ex, best);
-  unsigned int D[C1], Dp[C1];
-#pragma unroll
-  for (int r = 0; r < C1; ++r) { D[r] = 0u; Dp[r] = 0u; }
-  if (PREV && poct != nullptr) load_record<C1>(poct, i, Dp);
-  float xa[4] = {0.0f, 0.0f, 0.0f, 0.0f}, xb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (FAST) {
-    load_block_fast(v, O * 8, i, xa);
-    load_block_fast(v, O * 8 + 1, i, xb);
-  }
-  const int hf8 = (i >> 5) * 8;
-#pragma unroll 1
-  for (int pp = 0; pp < 4; ++pp) {
-    const long long B0 = O * 8 + 2 * pp;
-    shift_out_pair<C1>(D);
-    if (FAST || B0 < m.nblk) {
-      float x0[4], x1[4];
-      if (FAST) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { x0[j] = xa[j]; x1[j] = xb[j]; }
-        if (pp < 3) {
-          load_block_fast(v, B0 + 2, i, xa);
-          load_block_fast(v, B0 + 3, i, xb);
-        }
-      } else {
-        load4(v, B0 * kBlockCoords + 4 * i, m.d, x0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x1[j] = 0.0f;
-        if (B0 + 1 < m.nblk) load4(v, (B0 + 1) * kBlockCoords + 4 * i, m.d, x1);
-      }
-      const float2 nn = *reinterpret_cast<const float2 *>(&bw.norm[hf8 + 2 * pp]);
-      const float2 ii = *reinterpret_cast<const float2 *>(&bw.inv[hf8 + 2 * pp]);
-      const float2 pn = *reinterpret_cast<const float2 *>(&bw.pnorm[hf8 + 2 * pp]);
-      unsigned int o[4];
-      philox4x32_10((unsigned int)((B0 >> 1) * 64 + i), (unsigned int)l, a.round, (unsigned int)k, k0, k1, o);
-      const uint2 wf = *reinterpret_cast<const uint2 *>(&bw.wfix[hf8 + 2 * pp]);   // fit statistics: the buckets' weights
-      quantize_block_b<C1, PREV>(x0, o, 0, ii.x, nn.x, pn.x, lut, tab, tprev, D, Dp, acc, wf.x, lh);
-      quantize_block_b<C1, PREV>(x1, o, 1, ii.y, nn.y, pn.y, lut, tab, tprev, D, Dp, acc, wf.y, lh);
-    }
-    if (PREV) shift_out_pair<C1>(Dp);
-  }
-  store_record<C1>(oct, i, D);
-}
-
+// Bound by the vector ALU (36 instructions per coordinate, 78 % of the cycles) and, next, by shared memory (46 %).  Four
+// waves a SIMD: 128 registers and 40 KiB of shared memory a workgroup.  Measured with statistics gathered, K = 8: 151 M
+// coordinates, 8 levels 1.51 -> 1.35 ms against the version that read every octet twice, in pairs of blocks, and added
+// 64-bit weights in four copies; 6.3 M coordinates, 16 levels 128 -> 80 us (most of it by shorter runs).
 template <int C1, bool PREV, int KIND>
-__global__ void __launch_bounds__(kThreads) k_quantize_b(Dev a) {
+__global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   __shared__ unsigned char lut[kLutSize];
-  __shared__ float4 tab[kMaxPoints];
-  __shared__ float tprev[2 * kMaxPoints];   // +-level of the previous message, indexed by code = sign | h << 1
-  __shared__ double red[kThreads];
+  __shared__ float4 tab[1 << (C1 - 1)];
+  __shared__ float tprev[1 << C1];   // +-level of the previous message, indexed by code = sign | h << 1
+  __shared__ float chain[kSuperTile * kThreads];   // the slots' squared distances, tile by tile
   __shared__ BucketWave bws[kThreads / 64];
-  // fit statistics of this run: weighted grid histogram, one copy per lane residue (a wave's lanes that meet in a
-  // bin then collide a quarter as often), copies of a bin side by side
-  __shared__ unsigned long long lh[kGridPoints * kBucketHistCopies];
+  __shared__ unsigned int lo[kGridPoints * kHistCopies], hi[kGridPoints * kHistHighCopies];
   __shared__ unsigned long long wmax[kThreads / 64];
-  // a workgroup takes a run of up to kSuperTile consecutive tiles of one layer: the tables are set up and the
-  // statistics flushed once per run
+  constexpr long long OS = 256 * C1 + 64;   // bytes per octet: codes, then the 16 bucket norms
+  // a workgroup takes a run of consecutive tiles of one layer: the tables are set up and the statistics flushed once
+  // per run
   const int4 st = a.stiles[blockIdx.x];
   const int l = st.x;
   const int k = a.node0 + blockIdx.y;
@@ -867,16 +957,16 @@ __global__ void __launch_bounds__(kThreads) k_quantize_b(Dev a) {
   const int kr = k - a.row0;   // row in the pointer tables and in the per-tile scratch; the fit statistics use k
   const unsigned char *prevmsg = (a.prev != nullptr) ? a.prev[kr] : nullptr;
   const int ex = a.type_exp[m.type];
+  const int walk = a.walk[m.type];
   if (t < m.S) {
-    const float lj = lev[t];
-    const float ln = (t + 1 < m.S) ? lev[t + 1] : __builtin_inff();
-    tab[t] = make_float4(lj, (t + 1 < m.S) ? rg[t] : 0.0f, ln, 0.0f);
+    const bool last = t + 1 == m.S;
+    tab[t] = make_float4(lev[t], last ? 0.0f : rg[t], last ? __builtin_inff() : lev[t + 1], 0.0f);
   }
   if (st.y == 0) {   // header of this layer: the norm entry is unused under bucket scope
     float *h = reinterpret_cast<float *>(a.msg[kr] + m.hdr_off);
     for (int j = t; j <= m.S; j += kThreads) h[j] = (j == 0) ? 0.0f : lev[j - 1];
   }
-  for (int c = t; c < (1 << m.planes); c += kThreads) {
+  for (int c = t; c < (1 << C1); c += kThreads) {
     float pl = 0.0f;
     if (prevmsg) {
       const float *hp = reinterpret_cast<const float *>(prevmsg + m.hdr_off);
@@ -885,30 +975,82 @@ __global__ void __launch_bounds__(kThreads) k_quantize_b(Dev a) {
     }
     tprev[c] = pl;
   }
-  for (int j = t; j < kGridPoints * kBucketHistCopies; j += kThreads) lh[j] = 0ull;
+  if (ex != kTypeSkip) {
+    for (int j = t; j < kGridPoints * kHistCopies; j += kThreads) lo[j] = 0u;
+    for (int j = t; j < kGridPoints * kHistHighCopies; j += kThreads) hi[j] = 0u;
+  }
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int i = t & 63;
-  unsigned long long *lhc = lh + (i & (kBucketHistCopies - 1));   // this lane's copy
+  const int hf8 = (i >> 5) * 8;
+  BucketWave &bw = bws[w];
   const float *__restrict__ v = a.grad[(size_t)kr * a.L + l];
   unsigned char *body = a.msg[kr] + m.body_off;
   const unsigned char *prevbody = prevmsg ? prevmsg + m.body_off : nullptr;
+  const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
   const long long noct = (m.nblk + 7) >> 3;
   unsigned long long best = 0ull;
-  for (int cc = 0; cc < st.z; ++cc) {
-    const int chunk = st.y + cc;
-    float acc = 0.0f;
-    for (int oo = 0; oo < 2; ++oo) {
-      const long long O = (long long)chunk * 8 + w * 2 + oo;
-      if (O >= noct) break;
-      if ((O + 1) * 2048 <= m.d)
-        quantize_octet_b<C1, true, PREV, KIND>(a, m, l, k, O, v, body, prevbody, lut, tab, tprev, bws[w], i, acc, ex, best, lhc);
-      else
-        quantize_octet_b<C1, false, PREV, KIND>(a, m, l, k, O, v, body, prevbody, lut, tab, tprev, bws[w], i, acc, ex, best, lhc);
+  // The wave's octets of the run, one after the other: two of each tile.  The next octet's values are requested block by
+  // block as the current one's are done with, into the same registers.
+  const int n = 2 * st.z;
+  float x[32], acc = 0.0f;
+  unsigned int Dp[C1];
+  float pn = 0.0f;
+#pragma unroll
+  for (int r = 0; r < C1; ++r) Dp[r] = 0u;
+  const long long O0 = (long long)st.y * 8 + w * 2;
+  if (O0 < noct) {
+    load_octet(v, O0, m.d, i, x);
+    if (PREV && prevbody != nullptr) {
+      load_record<C1>(prevbody + O0 * OS, i, Dp);
+      if (i < 16) pn = reinterpret_cast<const float *>(prevbody + O0 * OS + 256 * C1)[i];
     }
-    const double total = block_tree((double)acc, red);
-    if (t == 0) a.dpartial[(size_t)kr * a.G + m.first_chunk + chunk] = total;
   }
+#pragma unroll 1
+  for (int q = 0; q < n; ++q) {
+    const long long O = O0 + 8 * (q >> 1) + (q & 1), On = O0 + 8 * ((q + 1) >> 1) + ((q + 1) & 1);
+    if (O < noct) {
+      unsigned int D[C1], Dn[C1];
+#pragma unroll
+      for (int r = 0; r < C1; ++r) { D[r] = 0u; Dn[r] = 0u; }
+      int i = t & 63;   // kept opaque: addresses derived from it are cheaper to form again than to hold through the loop
+      asm volatile("" : "+v"(i));
+      const bool high = bucket_norms<KIND>(a, x, reinterpret_cast<float *>(body + O * OS + 256 * C1), pn, bw, i, ex, best);
+      const bool more = q + 1 < n && On < noct;
+      if (PREV && prevbody != nullptr && more) {
+        load_record<C1>(prevbody + On * OS, i, Dn);
+        if (i < 16) pn = reinterpret_cast<const float *>(prevbody + On * OS + 256 * C1)[i];
+      }
+      const bool full = more && (On + 1) * 2048 <= m.d;
+      const float *vn = v + On * 2048;
+      const auto done = [&](int bb, float (&diff)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __builtin_fmaf(diff[j], diff[j], acc);
+        asm volatile("" : "+v"(acc));
+        if (full) load_block(vn, bb, i, &x[4 * bb]);
+      };
+      float least = 3.402823466e+38f;
+#pragma unroll
+      for (int j = 0; j < 32; ++j) least = fminf(least, fabsf(x[j]));
+      const bool plain = !high && __ballot(least < 0x1p-129f) == 0ull;
+      const BucketHist hist = {bw.wfix + hf8, lo + (i & (kHistCopies - 1)), hi + (i & (kHistHighCopies - 1)), ex != kTypeSkip, high, plain};
+      const unsigned int c0 = (unsigned int)(O * 256 + i);
+      if (walk)
+        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
+      else
+        quantize_regs<C1, PREV, false, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
+      store_record<C1>(body + O * OS, i, D);
+      if (more && !full) load_octet(v, On, m.d, i, x);   // the layer's ragged last octet
+#pragma unroll
+      for (int r = 0; r < C1; ++r) Dp[r] = Dn[r];
+    }
+    if (q & 1) {
+      chain[(q >> 1) * kThreads + t] = acc;
+      acc = 0.0f;
+    }
+  }
+  __syncthreads();
+  sum_tiles(a, chain, m, st, kr, w, i);
   // statistics of the run: largest bucket sum (bit pattern of a non-negative double) and the histogram
 #pragma unroll
   for (int sh = 1; sh < 64; sh *= 2) {
@@ -925,9 +1067,12 @@ __global__ void __launch_bounds__(kThreads) k_quantize_b(Dev a) {
   if (ex != kTypeSkip) {
     unsigned long long *gh = reinterpret_cast<unsigned long long *>(a.hist + idx * kHistBins);
     for (int j = t; j < kGridPoints; j += kThreads) {
-      unsigned long long c = 0ull;
+      unsigned long long c = 0ull, ch = 0ull;
 #pragma unroll
-      for (int q = 0; q < kBucketHistCopies; ++q) c += lh[j * kBucketHistCopies + q];
+      for (int q = 0; q < kHistCopies; ++q) c += lo[j * kHistCopies + ((q + j) & (kHistCopies - 1))];
+#pragma unroll
+      for (int q = 0; q < kHistHighCopies; ++q) ch += hi[j * kHistHighCopies + q];
+      c += ch << kHistLowBits;
       if (c) atomicAdd(&gh[j], c);
     }
   }
@@ -1404,6 +1549,12 @@ __device__ void build_tables(const Dev &a, int mtype, int S, const float *slev) 
         if (slev[j] <= lo) tau = j;
     }
     lut[q] = (unsigned char)tau;
+  }
+  // does some interior level lie inside a bin?  (0 and 1 are edges; then a lane may have to step on from lut's entry)
+  if (threadIdx.x == 0) {
+    int walk = 0;
+    for (int j = 1; j <= S - 2; ++j) walk |= (f2u(slev[j]) & 0xFFFFFu) != 0u;
+    a.walk[mtype] = walk;
   }
 }
 
