@@ -71,6 +71,10 @@ struct qoda_ctx {
     bool valid() const { return slots[cur].valid; }
   };
   Table t_grad, t_msg, t_prev, t_in, t_x1, t_y, t_xh, t_xn, t_mean;
+  bool small = false;   // the model's size and code widths allow k_quantize_small
+  unsigned long long *d_exch = nullptr;   // its exchange area, zero between calls
+  unsigned int *d_finished = nullptr;
+  unsigned int *d_readers = nullptr;   // of the decode pass with its own step size; zero between calls
   void **d_node_tab = nullptr;   // per-node calls: L layer pointers, then the message and the previous message
   // norms kept by qoda_fit_levels_keep_norms for the quantize calls of the same round on the same vectors
   bool norms_valid = false;
@@ -243,6 +247,8 @@ Dev base_args(const qoda_ctx *c) {
   a.kind = c->kind;
   a.type_points = c->d_type_points;
   a.partial = c->d_partial; a.dpartial = c->d_dpartial; a.sumsq = c->d_sumsq;
+  a.readers = c->d_readers;
+  a.exch = c->d_exch; a.finished = c->d_finished;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.walk = c->d_walk;
   a.hist = c->d_hist; a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
@@ -283,7 +289,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_stiles, c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
-                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk};
+                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   qoda_ctx::Table *tabs[] = {&c->t_grad, &c->t_msg, &c->t_prev, &c->t_in, &c->t_x1, &c->t_y, &c->t_xh, &c->t_xn, &c->t_mean};
@@ -292,6 +298,18 @@ void free_all(qoda_ctx *c) {
       if (sl.dev) (void)hipFree(sl.dev);
   for (auto &r : c->prof_recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (hipEvent_t e : c->prof_pool) (void)hipEventDestroy(e);
+}
+
+// Whether a call that computes the norms of `nnodes` nodes itself runs them, the quantizer and delta in one launch: when
+// all its tiles are on the device at once (two workgroups of eight waves on each of 256 CUs).  Beyond that the tiles that
+// wait for their group keep others from loading, and the separate passes, with more waves in flight, are faster.  us per
+// round, separate / one launch: 2 x 512 entries, K = 4 (8 tiles) 28.8 / 21.7; 1.8 M entries, K = 4 (448 tiles, largest layer 48)
+// 52.7 / 38.5, one norm per vector 55.6 / 43.4; K = 1, 432 tiles in 193 layers 58.6 / 45.1; but 1544 tiles of a handful of
+// entries 47 / 69, 5.5 M entries, K = 4 (1.6 k tiles) 92 / 98, one norm per vector 95 / 122.
+// A caller who asks for the times of the kernels that this launch stands for gets those kernels.
+bool use_small(const qoda_ctx *c, int nnodes) {
+  const unsigned int parts = 1u << kIdSumsq | 1u << kIdNormFinalize | 1u << kIdNormVector | 1u << kIdDeltaFinalize;
+  return c->small && (long long)nnodes * c->G <= kSmallTiles && (c->prof_mask & parts) == 0u;
 }
 
 // norms of nodes [node0, node0+n) from the gradient table already on the device
@@ -324,6 +342,11 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
     const size_t n0 = (size_t)node0 * c->L, nn = (size_t)nnodes * c->L;
     LAUNCH(c, kIdZero, s, launch_zero_u32(c->d_hist + n0 * kHistBins, nn * kHistBins, s));
     LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_sumsq + n0), 2 * nn, s));
+  }
+  if (!cached && use_small(c, nnodes)) {
+    c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
+    LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
+    return QODA_OK;
   }
   if (!cached) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
@@ -450,10 +473,25 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_pooled, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_type_exp, (size_t)c->M));
   A(dev_alloc(&c->d_walk, (size_t)c->M));
+  A(dev_alloc(&c->d_readers, (size_t)1));
+  if (e == hipSuccess) A(hipMemset(c->d_readers, 0, sizeof(unsigned int)));
   if (c->scope == kScopeBucket) {   // the quantize pass gathers the fit's statistics itself
     A(dev_alloc(&c->d_type_exp_next, (size_t)c->M));
     A(dev_alloc(&c->d_type_skip, (size_t)c->M));
     A(dev_alloc(&c->d_hist, KL * kHistBins));
+  }
+  {
+    const bool one_width = (c->planes_mask & (c->planes_mask - 1u)) == 0u;
+    // under vector scope every workgroup combines all the layers' sums, 0.1 us each: from 64 layers on the separate
+    // kernels win (432 tiles in 193 layers, K = 1: 61 us per round against 66)
+    c->small = one_width && c->G > 0 && c->G <= kSmallTiles && c->scope != kScopeBucket &&
+               (c->scope != kScopeVector || c->L <= 64);
+    if (c->small) {
+      A(dev_alloc(&c->d_exch, 2 * KG));
+      A(dev_alloc(&c->d_finished, (size_t)c->K));
+      if (e == hipSuccess) A(hipMemset(c->d_exch, 0, 2 * KG * sizeof(unsigned long long)));
+      if (e == hipSuccess) A(hipMemset(c->d_finished, 0, (size_t)c->K * sizeof(unsigned int)));
+    }
   }
   A(dev_alloc(&c->d_dp_arg, (size_t)arg_total));
   A(dev_alloc(&c->d_dp_arg_off, (size_t)c->M));
@@ -712,6 +750,12 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     a.inv = nb.inv;
     bool kept = of_context && c->norms_valid && c->norms_round == round;
     for (int l = 0; l < c->L && kept; ++l) kept = c->norms_grad[(size_t)node * c->L + l] == grad_dev[l];
+    if (!kept && of_context && use_small(c, 1)) {
+      c->norms_valid = false;   // this node's kept norms are about to be overwritten
+      a.exch = c->d_exch + (size_t)node * 2 * c->G;   // the node's row
+      LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
+      return QODA_OK;
+    }
     if (!kept) {
       if (of_context) c->norms_valid = false;   // this node's kept norms are about to be overwritten
       LAUNCH_IF(c, of_context, kIdSumsq, s, launch_sumsq(a, false, s));
@@ -809,6 +853,14 @@ static int step_common(qoda_ctx *c, const void *const *msgs_dev, const float *co
   return QODA_OK;
 }
 
+// Whether the decode pass computes the step size itself: a launch less, but every workgroup repeats the sum over the K
+// distances and is counted (one atomic on one address).  us per round with the launch / without: 2 x 512 entries
+// 21.5 / 20.3, 152 k entries (20 tiles) 46.0 / 42.0, 6.3 M entries (387 tiles) 189 / 193.  One code width: the update is one launch.
+static bool fuse_scalars(const qoda_ctx *c) {
+  return c->G > 0 && c->G <= 64 && c->K <= 64 && (c->planes_mask & (c->planes_mask - 1u)) == 0u &&
+         (c->prof_mask & (1u << kIdStepScalars)) == 0u;
+}
+
 int qoda_step(qoda_ctx *c, const void *const *msgs_dev, const qoda_state *st, void *stream) {
   if (!c) return QODA_EINVAL;
   return guarded(c, [&]() -> int {
@@ -820,6 +872,10 @@ int qoda_step(qoda_ctx *c, const void *const *msgs_dev, const qoda_state *st, vo
     if (rc) return rc;
     a.acc = st->acc_dev;
     a.eta_out = st->eta_dev;
+    if (fuse_scalars(c)) {
+      LAUNCH(c, kIdDecodeUpdate, s, launch_decode(a, kDecodeUpdateScalars, c->planes_mask, s));
+      return QODA_OK;
+    }
     LAUNCH(c, kIdStepScalars, s, launch_step_scalars(a, s));
     LAUNCH(c, kIdDecodeUpdate, s, launch_decode(a, kDecodeUpdate, c->planes_mask, s));
     return QODA_OK;

@@ -12,6 +12,8 @@ constexpr int kSuperTile = 8;        // tiles per workgroup in the norm pass
 constexpr int kTaperWorkgroups = 2048;   // workgroups of 256 threads the device holds at once (256 CUs x 8)
 constexpr int kDecodeWaves = 2;       // waves (= octets) per workgroup in the decode pass: 1, 2 or 4
 constexpr int kThreads = 256;        // workgroup size everywhere: 4 waves, 256 reduction slots
+constexpr int kSmallThreads = 512;   // k_quantize_small: a wave per octet of a tile
+constexpr int kSmallTiles = 512;     // the most tiles of a group whose statistics k_quantize_small combines
 constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
 constexpr int kGridPoints = 257;     // normalised grid g_0 = 2^-32 ... g_256 = 1
@@ -56,6 +58,8 @@ struct Dev {
   const unsigned char *const *msgs_in;  // [K] messages to decode
   double *partial;    // [K*G] per-tile statistics (sums of squares, sums of magnitudes or largest magnitudes)
   double *dpartial;   // [K*G] per-tile squared differences
+  unsigned long long *exch;   // k_quantize_small: [K][2][G] statistics and squared distances in exchange; 0 between calls
+  unsigned int *finished;     // k_quantize_small: [K] workgroups that are done; 0 between calls
   double *sumsq;      // [K*L] the statistic of (node, layer); bucket scope: its largest bucket statistic
   float *norm;        // [K*L]
   float *inv;         // [K*L]
@@ -79,6 +83,7 @@ struct Dev {
   float *const *mean_out;
   double *acc;
   float *eta_out;  // may be nullptr
+  unsigned int *readers;     // kDecodeUpdateScalars: workgroups that have read acc; 0 between calls
   const float *gamma_in;   // extrapolate mode: device scalar
   unsigned long long *index_counts;   // [M*256] occurrences of every level index per type (code-length accounting)
   double *alt_sums;        // eq. (Alt): [2] lambda, mu (caller's)
@@ -96,8 +101,10 @@ struct Dev {
 
 // What the decode kernel does after the K-way mean: store it, apply eq. (ODA), apply eq. (ODA) with the two
 // rates of eq. (Alt) and accumulate ||X_t - X_{t+1}||^2, or take one plain step out = x - gamma * mean (the leg an
-// extra-gradient method repeats twice per round, Sec. 4).
-enum DecodeMode { kDecodeMean = 0, kDecodeUpdate = 1, kDecodeUpdateAlt = 2, kDecodeExtrapolate = 3 };
+// extra-gradient method repeats twice per round, Sec. 4).  kDecodeUpdateScalars: kDecodeUpdate that computes the step size
+// from the distances itself, without k_step_scalars before it.
+enum DecodeMode { kDecodeMean = 0, kDecodeUpdate = 1, kDecodeUpdateAlt = 2, kDecodeExtrapolate = 3,
+                  kDecodeUpdateScalars = 4 };
 
 // Kernel classes, for the optional per-kernel event timing of the host API.
 enum KernelId {
@@ -112,6 +119,8 @@ hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t s);
 hipError_t launch_norm_finalize(const Dev &a, hipStream_t s);
 hipError_t launch_norm_vector(const Dev &a, hipStream_t s);
 hipError_t launch_quantize(const Dev &a, unsigned int planes_mask, hipStream_t s);
+// norms, quantize and delta in one launch (layer and vector scope, one code width, groups of at most kSmallTiles tiles)
+hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStream_t s);
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s);
 hipError_t launch_step_scalars(const Dev &a, hipStream_t s);
 hipError_t launch_decode(const Dev &a, int mode, unsigned int planes_mask, hipStream_t s);   // mode: DecodeMode

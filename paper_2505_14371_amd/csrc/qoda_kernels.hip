@@ -625,7 +625,8 @@ __device__ __forceinline__ void pin_block(float *x) {
 
 // One octet from registers.  x: the lane's 32 values in order (zeros past the end of the layer: they give code 0 and
 // distance 0).  A block's four differences to the previous message (up to a sign that their square does not see) are
-// given to done(bb, diff) as soon as they are known; it may put new values into the block's place in x.
+// given to done(bb, diff) as soon as they are known; it may put new values into the block's place in x.  pairs: how many
+// of the four pairs of blocks to work on (the same for the wave).
 // Tables: lut as in build_tables; tprev[code] = value the previous message's code stands for.
 //   WALK = false, layer norms    tab[tau] = {l_tau, 1/gap, norm * l_tau, norm * l_tau+1}: the decoder's product, taken once
 //                                per table entry
@@ -639,9 +640,10 @@ __device__ __forceinline__ void quantize_regs(float (&x)[32], unsigned int c0, u
                                                unsigned int k, unsigned int k0, unsigned int k1, const float *inv,
                                                const float *norm, const float *pnorm, const unsigned char *lut,
                                                const float4 *tab, const float *tprev, unsigned int (&D)[C1],
-                                               const unsigned int (&Dp)[C1], Hist &&hist, Done &&done) {
+                                               const unsigned int (&Dp)[C1], Hist &&hist, Done &&done, int pairs = 4) {
 #pragma unroll
   for (int pp = 0; pp < 4; ++pp) {   // pairs of blocks: one generator call serves 8 coordinates of a lane
+    if (pp >= pairs) break;
     asm volatile("" : "+v"(c0));
     unsigned int o[4];
     philox4x32_10(c0, l, round, k, k0, k1, o);
@@ -747,6 +749,312 @@ __device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, cons
 #pragma unroll
     for (int h = 32; h >= 1; h >>= 1) r = r + __shfl_down(r, h, 64);
     if (i == 0) a.dpartial[(size_t)kr * a.G + m.first_chunk + st.y + cc] = r;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------ small models
+// Norms, quantization and the node's delta in one launch, for layer and vector scope.  A small model's pass is a chain of
+// short kernels (norm pass, its combination, for vector scope a second combination, quantize, delta), each a few
+// microseconds of launch and dependent loads around almost no work.  Here a workgroup of eight waves holds one tile in
+// registers (an octet a wave), reduces its statistic, publishes it, waits for those of its group (the tiles of its layer;
+// under vector scope all tiles of its node), combines them in the order that k_norm_finalize and k_norm_vector use, and
+// quantizes what it holds: one read of the vectors.  The node's last workgroup to finish sums the squared distances.
+//
+// What the workgroups exchange are the values themselves: a statistic is stored as the complement of its bit pattern, so
+// that the zeros left by the call before mean "not there yet" (no double that these sums produce has all bits set).  All
+// accesses to them are device-scope atomics, so no cache keeps an old value and no fence is needed.
+// Waiting cannot hang: after kSpins tries a workgroup computes the missing statistics itself, from the vectors, with the
+// same operations in the same order.
+// Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  Kernel time
+// for 2 x 512 entries, K = 4: 8.5 us against 13.8 for the four kernels it replaces and 10 for the gaps between them.
+constexpr int kSpins = 1024;
+
+__device__ __forceinline__ void publish(unsigned long long *p, double v) {
+  __hip_atomic_store(p, ~(unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The tree's steps for one wave, from 256 slots in shared memory; the total is valid in lane 0.  SUM false: the maximum.
+template <bool SUM>
+__device__ __forceinline__ double wave_tree(const double *slot, int i) {
+  double r = SUM ? (slot[i] + slot[i + 128]) + (slot[i + 64] + slot[i + 192])
+                 : fmax(fmax(slot[i], slot[i + 128]), fmax(slot[i + 64], slot[i + 192]));
+#pragma unroll
+  for (int h = 32; h >= 1; h >>= 1) {
+    const double o = __shfl_down(r, h, 64);
+    r = SUM ? r + o : fmax(r, o);
+  }
+  return r;
+}
+
+// A slot's statistic goes on through N more values.
+template <int N>
+__device__ __forceinline__ double add_terms(double acc, const float *x, int kind) {
+  if (kind == kNormL2) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc = __builtin_fma((double)x[j], (double)x[j], acc);
+  } else if (kind == kNormL1) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc = acc + fabs((double)x[j]);
+  } else {
+    unsigned int mb = 0u;
+#pragma unroll
+    for (int j = 0; j < N; ++j) mb = max(mb, f2u(x[j]) & 0x7FFFFFFFu);
+    acc = fmax(acc, (double)magnitude_from_bits(mb));
+  }
+  return acc;
+}
+
+// The statistic of any tile, from memory: what its own workgroup publishes.  All 512 threads call this (256 slots work).
+__device__ double tile_statistic(const float *__restrict__ v, long long d, int chunk, int kind, double *slot, int t) {
+  __syncthreads();
+  if (t < kThreads) {
+    double acc = 0.0;
+    const long long base = (long long)chunk * kChunkCoords + (long long)(t >> 6) * 16 * kBlockCoords + 4 * (t & 63);
+#pragma unroll 1
+    for (int s = 0; s < 16; ++s) {
+      float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (base + s * kBlockCoords < d) load4(v, base + s * kBlockCoords, d, x);
+      acc = add_terms<4>(acc, x, kind);
+    }
+    slot[t] = acc;
+  }
+  __syncthreads();
+  return kind == kNormLinf ? wave_tree<false>(slot, t & 63) : wave_tree<true>(slot, t & 63);
+}
+
+template <int C1, bool PREV>
+__global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
+  __shared__ unsigned char lut[kLutSize];
+  __shared__ float4 tab[1 << (C1 - 1)];
+  __shared__ float tprev[1 << C1];      // previous message's decode table indexed by code = sign | h << 1
+  __shared__ double slot[kThreads];
+  __shared__ float chain[kThreads];
+  __shared__ double group[kSmallTiles];   // the group's tile statistics
+  __shared__ double layer[kSmallTiles];   // vector scope: the layers' sums
+  __shared__ float scale[2];
+  __shared__ int missing[1];
+  const int2 tile = a.tiles[blockIdx.x];
+  const int l = tile.x;
+  const int k = a.node0 + blockIdx.y;
+  const LayerMeta m = a.meta[l];
+  const int t = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i = t & 63;
+  const int kr = k - a.row0;   // row of this node in the per-node scratch and pointer tables
+  const long long O = (long long)tile.y * 8 + w;   // octet index inside the layer
+  const bool live = O < ((m.nblk + 7) >> 3);
+  const unsigned char *prevmsg = (a.prev != nullptr) ? a.prev[kr] : nullptr;
+  const float *__restrict__ v = a.grad[(size_t)kr * a.L + l];
+  unsigned char *msg = a.msg[kr];
+  float x[32];
+  unsigned int D[C1], Dp[C1];
+#pragma unroll
+  for (int r = 0; r < C1; ++r) { D[r] = 0u; Dp[r] = 0u; }
+  if (live) {
+    load_octet(v, O, m.d, i, x);
+    if (PREV && prevmsg != nullptr) load_record<C1>(prevmsg + m.body_off + O * 256 * C1, i, Dp);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) x[j] = 0.0f;
+  }
+  // tables that do not depend on the norm
+  const float *lev = a.lev + (size_t)m.type * kMaxPoints;
+  const float *rg = a.rgap + (size_t)m.type * kMaxPoints;
+  const int walk = a.walk[m.type];
+  float lj = 0.0f, ln = 0.0f, gj = 0.0f;
+  if (t < m.S) {
+    lj = lev[t];
+    if (t + 1 < m.S) { ln = lev[t + 1]; gj = rg[t]; }
+  }
+  if (t < kLutSize / 4)
+    reinterpret_cast<unsigned int *>(lut)[t] = reinterpret_cast<const unsigned int *>(a.lut + (size_t)m.type * kLutSize)[t];
+  if (t < (1 << C1)) {   // codes past S-1 decode as the last level
+    float pv = 0.0f;
+    if (prevmsg) {
+      const float *hp = reinterpret_cast<const float *>(prevmsg + m.hdr_off);
+      const float mag = hp[0] * hp[1 + min(t >> 1, m.S - 1)];
+      pv = (t & 1) ? -mag : mag;
+    }
+    tprev[t] = pv;
+  }
+  // the tile's statistic; a slot runs through the octets of a pair of waves, the odd one goes on from the even one's sum
+  const int kind = a.kind;
+  const int sl = (w >> 1) * 64 + i;
+  double acc = 0.0;
+  if (!(w & 1)) {
+    if (live) acc = add_terms<32>(acc, x, kind);
+    slot[sl] = acc;
+  }
+  __syncthreads();
+  if ((w & 1) && live) slot[sl] = add_terms<32>(slot[sl], x, kind);
+  __syncthreads();
+  unsigned long long *stat = a.exch + (size_t)kr * 2 * a.G;   // the node's statistics, then its squared distances
+  unsigned long long *dist = stat + a.G;
+  const bool vec = a.scope == kScopeVector;
+  const int first = vec ? 0 : m.first_chunk, n = vec ? a.G : m.nchunks;   // the group
+  if (w == 0) {
+    const double own = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
+    if (i == 0) publish(&stat[m.first_chunk + tile.y], own);
+  }
+  // the group's statistics; n <= kSmallTiles, one thread each
+  int tries = 0;
+  for (;;) {
+    bool have = true;
+    if (t < n) {
+      const unsigned long long b = __hip_atomic_load(&stat[first + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      have = b != 0ull;
+      if (have) group[t] = __longlong_as_double((long long)~b);
+    }
+    if (__syncthreads_and(have)) break;
+    if (++tries < kSpins) continue;
+    // some workgroup of the group is not running: its statistic is computed here, one tile at a time
+    if (t == 0) missing[0] = 0x7FFFFFFF;
+    __syncthreads();
+    if (!have) atomicMin(&missing[0], t);
+    __syncthreads();
+    const int g = first + missing[0];
+    const int2 mt = a.tiles[g];
+    const double s = tile_statistic(a.grad[(size_t)kr * a.L + mt.x], a.meta[mt.x].d, mt.y, kind, slot, t);
+    if (t == 0) publish(&stat[g], s);   // the same value that its own workgroup stores
+    __syncthreads();
+  }
+  // combine: slot j takes items j, j + 256, ... in increasing order, then the tree
+  if (!vec) {
+    if (t < kThreads) {
+      double s = t < n ? group[t] : 0.0;
+      if (t + kThreads < n) s = kind == kNormLinf ? fmax(s, group[t + kThreads]) : s + group[t + kThreads];
+      slot[t] = s;
+    }
+  } else {
+    for (int q = w; q < a.L; q += kSmallThreads / 64) {   // layer sums, a wave each
+      const int f = a.meta[q].first_chunk, c = a.meta[q].nchunks;
+      double p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j = i + 64 * r;
+        p[r] = j < c ? group[f + j] : 0.0;
+        if (j + kThreads < c) p[r] = kind == kNormLinf ? fmax(p[r], group[f + j + kThreads]) : p[r] + group[f + j + kThreads];
+      }
+      double s = kind == kNormLinf ? fmax(fmax(p[0], p[2]), fmax(p[1], p[3])) : (p[0] + p[2]) + (p[1] + p[3]);
+#pragma unroll
+      for (int h = 32; h >= 1; h >>= 1) {
+        const double o = __shfl_down(s, h, 64);
+        s = kind == kNormLinf ? fmax(s, o) : s + o;
+      }
+      if (i == 0) {
+        layer[q] = s;
+        if (blockIdx.x == 0 && stat_finite(s, kind)) {   // a layer's own norm raises this flag under vector scope too
+          const float nl = norm_of(s, kind);
+          if (nl > 0.0f && nl < kFltMin) atomicOr(a.status, kStatusTinyNorm);
+        }
+      }
+    }
+    __syncthreads();
+    if (t < kThreads) {
+      double s = t < a.L ? layer[t] : 0.0;
+      if (t + kThreads < a.L) s = kind == kNormLinf ? fmax(s, layer[t + kThreads]) : s + layer[t + kThreads];
+      slot[t] = s;
+    }
+  }
+  __syncthreads();
+  if (w == 0) {
+    const double s = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
+    if (i == 0) {
+      const bool finite = stat_finite(s, kind);
+      const float nn = finite ? norm_of(s, kind) : 0.0f;
+      const float rr = rcp_floor(nn);
+      scale[0] = nn;
+      scale[1] = rr;
+      if (tile.y == 0) {   // one workgroup of the layer
+        const size_t idx = (size_t)kr * a.L + l;
+        a.sumsq[idx] = s;
+        a.norm[idx] = nn;
+        a.inv[idx] = rr;
+        if (!finite) atomicOr(a.status, kStatusNonFinite);
+        if (nn > 0.0f && nn < kFltMin) atomicOr(a.status, kStatusTinyNorm);
+      }
+      if (vec && m.first_chunk + tile.y == 0)   // layers without coordinates carry the node's norm too
+        for (int q = 0; q < a.n_empty; ++q) {
+          const size_t idx = (size_t)kr * a.L + a.empty_layers[q];
+          a.sumsq[idx] = s;
+          a.norm[idx] = nn;
+          a.inv[idx] = rr;
+        }
+    }
+  }
+  __syncthreads();
+  const float norm = scale[0], inv = scale[1];
+  if (t < m.S) {
+    const bool last = t + 1 == m.S;
+    tab[t] = walk ? make_float4(lj, gj, last ? __builtin_inff() : ln, 0.0f) : make_float4(lj, gj, norm * lj, last ? 0.0f : norm * ln);
+  }
+  if (tile.y == 0) {   // message header of this layer: {norm, levels[S]} (Sec. 3.2: the norm in C_q = 32 bits)
+    float *h = reinterpret_cast<float *>(msg + m.hdr_off);
+    if (t < m.S) h[1 + t] = lj;
+    if (t == 0) h[0] = norm;
+  }
+  __syncthreads();
+  float dacc = 0.0f;   // this slot's squared differences: an fp32 fused multiply-add chain in increasing coordinate
+  if (live) {
+    const unsigned int c0 = (unsigned int)(O * 256 + i);   // counter of the octet's first pair: 64 per 512 coordinates
+    const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
+    const int pairs = (int)min(4ll, (m.nblk + 1 - O * 8) >> 1);   // the layer's; the others stay code 0, distance 0
+    const auto keep = [&](int bb, float (&diff)[4]) {
+      pin_block(diff);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * bb + j] = diff[j];
+    };
+    if (walk) quantize_regs<C1, PREV, true, false>(x, c0, l, a.round, k, k0, k1, &inv, &norm, nullptr, lut, tab, tprev, D, Dp, NoHist(), keep, pairs);
+    else quantize_regs<C1, PREV, false, false>(x, c0, l, a.round, k, k0, k1, &inv, &norm, nullptr, lut, tab, tprev, D, Dp, NoHist(), keep, pairs);
+    store_record<C1>(msg + m.body_off + O * 256 * C1, i, D);
+    if (!(w & 1)) {
+#pragma unroll
+      for (int j = 0; j < 32; ++j) dacc = __builtin_fmaf(x[j], x[j], dacc);
+    }
+  }
+  if (!(w & 1)) chain[sl] = dacc;
+  __syncthreads();
+  if (w & 1) {
+    dacc = chain[sl];
+    if (live) {
+#pragma unroll
+      for (int j = 0; j < 32; ++j) dacc = __builtin_fmaf(x[j], x[j], dacc);
+    }
+    slot[sl] = (double)dacc;
+  }
+  __syncthreads();
+  if (w != 0) return;
+  // the node's last workgroup sums the squared distances (slot j: tiles j, j + 256, ... of the node), in one wave
+  const double total = wave_tree<true>(slot, i);
+  unsigned int done = 0u;
+  if (i == 0) {
+    publish(&dist[m.first_chunk + tile.y], total);
+    done = __hip_atomic_fetch_add(&a.finished[k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (__builtin_amdgcn_readfirstlane(done) != (unsigned int)a.G - 1u) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    double s = 0.0;
+    for (int g = i + 64 * r; g < a.G; g += kThreads) {
+      unsigned long long b;   // stored before its workgroup was counted: on its way at most
+      while ((b = __hip_atomic_load(&dist[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {}
+      s = s + __longlong_as_double((long long)~b);
+    }
+    slot[i + 64 * r] = s;
+  }
+  const double delta = wave_tree<true>(slot, i);
+  if (i == 0) {
+    a.delta[k] = delta;
+    a.finished[k] = 0u;
+  }
+  for (int g = i; g < 2 * a.G; g += 64) stat[g] = 0ull;   // everybody has read them
+  for (int q = 0; q < a.n_empty; ++q) {   // layers without coordinates: statistics (layer scope) and header entries
+    const int e = a.empty_layers[q];
+    const LayerMeta me = a.meta[e];
+    const size_t idx = (size_t)kr * a.L + e;
+    if (!vec && i == 0) { a.sumsq[idx] = 0.0; a.norm[idx] = 0.0f; a.inv[idx] = 0.0f; }
+    float *h = reinterpret_cast<float *>(msg + me.hdr_off);
+    for (int j = i; j <= me.S; j += 64) h[j] = (j == 0) ? (vec ? norm : 0.0f) : a.lev[(size_t)me.type * kMaxPoints + j - 1];
   }
 }
 
@@ -1110,16 +1418,21 @@ __global__ void __launch_bounds__(kThreads) k_delta_finalize(Dev a) {
 // ------------------------------------------------------------------------------------------------ step
 // eq. (general_stepsize): acc += (sum_k delta_k) / K^2 ; eta = gamma = (1 + acc)^(-1/2), taken as
 // rcp_floor(sqrt_floor(1 + acc)).
-__global__ void k_step_scalars(Dev a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ __forceinline__ double sum_distances(const Dev &a) {
   double sum = a.delta[0];
   for (int k = 1; k < a.K; ++k) sum = sum + a.delta[k];
-  const double acc = *a.acc + sum * a.invK2;
+  return *a.acc + sum * a.invK2;
+}
+__device__ __forceinline__ void store_scalars(const Dev &a, double acc, float eta) {
   *a.acc = acc;
-  const float eta = rcp_floor(sqrt_floor(1.0 + acc));
   a.eta[0] = eta;
   a.eta[1] = eta;
   if (a.eta_out) { a.eta_out[0] = eta; a.eta_out[1] = eta; }
+}
+__global__ void k_step_scalars(Dev a) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  const double acc = sum_distances(a);
+  store_scalars(a, acc, rcp_floor(sqrt_floor(1.0 + acc)));
 }
 
 // eq. (Alt), Sec. 6: the rates for the update of this round from the sums over the rounds before it,
@@ -1289,6 +1602,14 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
   const int i = t & 63;
   float eta = 0.0f, gamma = 0.0f, eta_prev = 0.0f, accx = 0.0f;
   if (MODE == kDecodeUpdate || MODE == kDecodeUpdateAlt) { eta = a.eta[0]; gamma = a.eta[1]; }
+  unsigned int readers = 0u;
+  double new_acc = 0.0;
+  if (MODE == kDecodeUpdateScalars) {   // every workgroup computes what k_step_scalars computes
+    new_acc = sum_distances(a);
+    asm volatile("" : "+v"(new_acc) : : "memory");   // *a.acc has been read before this workgroup is counted
+    if (t == 0) readers = __hip_atomic_fetch_add(a.readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    eta = gamma = rcp_floor(sqrt_floor(1.0 + new_acc));
+  }
   if (MODE == kDecodeUpdateAlt) eta_prev = a.eta[2];
   if (MODE == kDecodeExtrapolate) gamma = a.gamma_in[0];
   const long long noct = (m.nblk + 7) >> 3;
@@ -1301,6 +1622,10 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
   if (MODE == kDecodeUpdateAlt) {
     const double total = block_tree((double)accx, red);
     if (t == 0) a.dpartial[g] = total;
+  }
+  if (MODE == kDecodeUpdateScalars && t == 0 && readers == gridDim.x - 1u) {   // all workgroups have read *a.acc
+    store_scalars(a, new_acc, eta);
+    *a.readers = 0u;
   }
 }
 
@@ -1894,6 +2219,28 @@ hipError_t launch_quantize(const Dev &a, unsigned int planes_mask, hipStream_t s
   return hipGetLastError();
 }
 
+template <int C1>
+static void launch_small_width(const Dev &a, hipStream_t s) {
+  const dim3 grid(a.G, a.nnodes), block(kSmallThreads);
+  if (a.prev != nullptr) hipLaunchKernelGGL((k_quantize_small<C1, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_quantize_small<C1, false>), grid, block, 0, s, a);
+}
+
+hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStream_t s) {
+  switch (planes_mask) {   // one code width in the model
+    case 1u << 2: launch_small_width<2>(a, s); break;
+    case 1u << 3: launch_small_width<3>(a, s); break;
+    case 1u << 4: launch_small_width<4>(a, s); break;
+    case 1u << 5: launch_small_width<5>(a, s); break;
+    case 1u << 6: launch_small_width<6>(a, s); break;
+    case 1u << 7: launch_small_width<7>(a, s); break;
+    case 1u << 8: launch_small_width<8>(a, s); break;
+    case 1u << 9: launch_small_width<9>(a, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s) {
   hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes), dim3(kThreads), 0, s, a);
   return hipGetLastError();
@@ -1918,6 +2265,7 @@ static void launch_decode_scope(const Dev &a, int mode, size_t lds_bytes, hipStr
   if (mode == kDecodeExtrapolate) hipLaunchKernelGGL((k_decode<C1, kDecodeExtrapolate, BUCKET>), parts, small, lds_bytes, s, a);
   else if (mode == kDecodeUpdateAlt) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdateAlt, BUCKET>), whole, block, lds_bytes, s, a);
   else if (mode == kDecodeUpdate) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdate, BUCKET>), parts, small, lds_bytes, s, a);
+  else if (mode == kDecodeUpdateScalars) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdateScalars, BUCKET>), parts, small, lds_bytes, s, a);
   else hipLaunchKernelGGL((k_decode<C1, kDecodeMean, BUCKET>), parts, small, lds_bytes, s, a);
 }
 

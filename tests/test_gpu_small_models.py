@@ -1,0 +1,154 @@
+"""The one-launch quantize call of small models (norms, quantizer and delta together) and the update that computes its own
+step size, against the separate kernels -- which a call runs when their times are asked for -- and against the oracle.
+Everything bit for bit: messages, statistics, norms, reciprocals, distances, step sizes, iterates."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import helpers  # noqa: E402
+from paper_2505_14371_amd import qoda  # noqa: E402
+
+LAYER, VECTOR = qoda.SCOPE_LAYER, qoda.SCOPE_VECTOR
+ALL = ["k_sumsq<false>", "k_norm_finalize", "k_norm_vector", "k_delta_finalize", "k_step_scalars"]
+
+
+def gm(*a, **k):
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU test was selected but no GPU is visible")
+    import gpu_harness
+
+    return gpu_harness.GpuModel(*a, **k)
+
+
+SIZES = {
+    "ragged": [1, 0, 255, 257, 511, 513, 2047, 2049, 16383, 16385, 0, 40001],
+    "edge of a wave pair": [2048 * 3, 2048 * 3 + 1, 16384 - 2048, 4096],
+    "one tile": [16384],
+    "groups beyond 256 tiles": [16384 * 300 + 11, 5],
+    "all 512 tiles": [16384 * 511 + 2, 1000],     # the last size that one launch takes (K = 1)
+    "513 tiles": [16384 * 512 + 2],
+}
+
+
+def rounds(m, grads, each=False):
+    """Two rounds (without and with a previous message) and their updates; everything the calls leave behind."""
+    out = []
+    for t, g in enumerate(grads, 1):
+        m.set_grads(g)
+        (m.quantize_each if each else m.quantize_all)(t)
+        out += [m.messages(), m.ctx.read_buffer(qoda.BUF_DELTA)]
+        out += [m.ctx.read_buffer(b) for b in (qoda.BUF_SUMSQ, qoda.BUF_NORM, qoda.BUF_INV)]
+        m.step()
+        out += [m.y.cpu().numpy(), m.x_half.cpu().numpy(), m.x_next.cpu().numpy(), m.acc.cpu().numpy(), m.eta.cpu().numpy()]
+    return out, m.ctx.status()
+
+
+def same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a[0], b[0])) and a[1] == b[1]
+
+
+@pytest.mark.parametrize("scope", [LAYER, VECTOR])
+@pytest.mark.parametrize("kind", [qoda.NORM_L2, qoda.NORM_L1, qoda.NORM_LINF])
+@pytest.mark.parametrize("shape", SIZES)
+def test_one_launch_equals_the_separate_kernels(shape, kind, scope):
+    sizes = SIZES[shape]
+    K = 1 if "512" in shape or "513" in shape else 3
+    S = {qoda.NORM_L2: 16, qoda.NORM_L1: 5, qoda.NORM_LINF: 200}[kind]
+    rng = np.random.default_rng([kind, scope, len(sizes)])
+    grads = [[[(rng.standard_t(3, s) * 10.0 ** rng.uniform(-6, 3)).astype(np.float32) for s in sizes] for _ in range(K)]
+             for _ in range(2)]
+    grads[0][0][0][:] = 0.0
+    got = []
+    for mode in ("one", "separate", "node by node"):
+        m = gm(sizes, [0] * len(sizes), [S], K, seed=9, norm_scope=scope, norm_kind=kind)
+        if mode == "separate":
+            m.ctx.profile_enable(ALL)
+        got.append(rounds(m, grads, each=mode == "node by node"))
+        if mode == "separate":
+            times = m.ctx.profile_read()
+            assert times["k_sumsq<false>"][1] == 2 and times["k_step_scalars"][1] == 2
+        m.ctx.close()
+    assert same(got[0], got[1]) and same(got[2], got[1])
+
+
+@pytest.mark.parametrize("scope", [LAYER, VECTOR])
+def test_against_the_oracle(oracle, scope):
+    sizes, K, S = SIZES["ragged"], 3, 16
+    L = len(sizes)
+    lev = helpers.uniform_levels(S)
+    rng = np.random.default_rng(4)
+    m = gm(sizes, [0] * L, [S], K, seed=77, norm_scope=scope)
+    prev, acc = [None] * K, 0.0
+    for t in (1, 2, 3):
+        g = [[rng.standard_t(3, s).astype(np.float32) for s in sizes] for _ in range(K)]
+        m.set_grads(g)
+        m.quantize_all(t)
+        msgs, delta, want = m.messages(), m.ctx.read_buffer(qoda.BUF_DELTA), []
+        for k in range(K):
+            out = oracle.quantize(sizes, [S] * L, [lev] * L, g[k], 77, t, k, msg_prev=prev[k], scope=scope)
+            assert np.array_equal(msgs[k], out[0]) and delta[k] == out[2], (t, k)
+            prev[k] = out[0]
+            want.append(out[2])
+        m.step()
+        acc, eta = oracle.step_size(want, acc)
+        assert m.acc.cpu().numpy()[0] == acc and m.eta.cpu().numpy()[0] == eta
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 1e-45])
+@pytest.mark.parametrize("scope", [LAYER, VECTOR])
+def test_flags(scope, bad):
+    """Non-finite values and norms below the normal range raise the same flag on both paths; the next call is clean."""
+    sizes, K = [5000, 300, 20000], 2
+    rng = np.random.default_rng(1)
+    good = [[rng.standard_normal(s).astype(np.float32) for s in sizes] for _ in range(K)]
+    worse = [[v.copy() for v in g] for g in good]
+    if bad == 1e-45:
+        worse[1][1][:] = np.float32(bad)
+    else:
+        worse[1][1][7] = bad
+    seen = []
+    for names in (False, ALL):
+        m = gm(sizes, [0] * 3, [8], K, seed=2, norm_scope=scope)
+        m.ctx.profile_enable(names)
+        for g in (worse, good):
+            m.set_grads(g)
+            m.quantize_all(1)
+            seen.append(m.ctx.status())
+        seen.append(m.messages())
+    assert seen[0] == seen[3] and seen[0] != qoda.OK and seen[1] == seen[4] == qoda.OK
+    assert all(np.array_equal(a, b) for a, b in zip(seen[2], seen[5]))
+
+
+def test_replays_of_a_captured_round():
+    """A captured round leaves its exchange areas ready for the next replay, with eager rounds between."""
+    sizes, K = [4000, 30000, 257], 2
+    rng = np.random.default_rng(6)
+    grads = [[rng.standard_normal(s).astype(np.float32) for s in sizes] for _ in range(K)]
+    ms = [gm(sizes, [0] * 3, [8], K, seed=3) for _ in range(2)]
+
+    def one(m):
+        m.ctx.quantize_all(m.gp, 5, m.msg[0], m.msg[1])
+        m.ctx.step(m.msg[0], m.xp[0], m.xp[1], m.xp[2], m.acc, None, m.eta)
+
+    for m in ms:
+        m.set_grads(grads)
+        m.gp = qoda.pointer_array(m.grad_ptrs())
+        m.xp = [qoda.pointer_array(m.layer_ptrs(f)) for f in (m.x1, m.y, m.x_half)]
+        one(m)                      # fills the pointer tables
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        one(ms[0])
+    for step in range(6):
+        if step % 3 == 2:
+            one(ms[0])
+        else:
+            graph.replay()
+        one(ms[1])
+        torch.cuda.synchronize()
+        for a, b in ((ms[0].msg[0][0], ms[1].msg[0][0]), (ms[0].msg[0][1], ms[1].msg[0][1]), (ms[0].y, ms[1].y),
+                     (ms[0].x_half, ms[1].x_half), (ms[0].acc, ms[1].acc), (ms[0].eta, ms[1].eta)):
+            assert torch.equal(a, b), step
