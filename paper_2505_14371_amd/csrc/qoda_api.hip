@@ -41,7 +41,10 @@ struct qoda_ctx {
   double *d_partial = nullptr, *d_dpartial = nullptr, *d_sumsq = nullptr, *d_delta = nullptr;
   float *d_norm = nullptr, *d_inv = nullptr, *d_lev = nullptr, *d_rgap = nullptr, *d_eta = nullptr;
   unsigned char *d_lut = nullptr;
-  unsigned int *d_hist = nullptr, *d_status = nullptr;
+  unsigned int *d_hist = nullptr, *d_hist_last = nullptr, *d_status = nullptr;
+  int *d_type_first = nullptr;   // the layers of every type
+  int3 *d_type_layers = nullptr;
+  bool fit_one = false;   // k_fit_dp does the work of the kernels before it
   unsigned long long *d_pooled = nullptr;
   int *d_type_exp = nullptr, *d_walk = nullptr;
   short *d_dp_arg = nullptr;
@@ -251,6 +254,7 @@ Dev base_args(const qoda_ctx *c) {
   a.exch = c->d_exch; a.finished = c->d_finished;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.walk = c->d_walk;
+  a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
   a.hist = c->d_hist; a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
   a.dp_arg = c->d_dp_arg; a.dp_arg_off = c->d_dp_arg_off;
   a.status = c->d_status; a.eta = c->d_eta;
@@ -289,7 +293,8 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_stiles, c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
-                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers};
+                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
+                  c->d_type_first, c->d_type_layers};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   qoda_ctx::Table *tabs[] = {&c->t_grad, &c->t_msg, &c->t_prev, &c->t_in, &c->t_x1, &c->t_y, &c->t_xh, &c->t_xn, &c->t_mean};
@@ -310,6 +315,12 @@ void free_all(qoda_ctx *c) {
 bool use_small(const qoda_ctx *c, int nnodes) {
   const unsigned int parts = 1u << kIdSumsq | 1u << kIdNormFinalize | 1u << kIdNormVector | 1u << kIdDeltaFinalize;
   return c->small && (long long)nnodes * c->G <= kSmallTiles && (c->prof_mask & parts) == 0u;
+}
+
+// Whether k_fit_dp does the work of the kernels before it; a caller who asks for their times gets them.
+bool fit_in_one(const qoda_ctx *c) {
+  const unsigned int parts = 1u << kIdNormFinalize | 1u << kIdFitTypemax | 1u << kIdFitPool;
+  return c->fit_one && (c->prof_mask & parts) == 0u;
 }
 
 // norms of nodes [node0, node0+n) from the gradient table already on the device
@@ -340,8 +351,7 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
     cached = true;   // the bucket norms are computed by the quantize kernel itself, which also gathers the fit's
                      // statistics of these nodes: their histograms and running maxima start from zero
     const size_t n0 = (size_t)node0 * c->L, nn = (size_t)nnodes * c->L;
-    LAUNCH(c, kIdZero, s, launch_zero_u32(c->d_hist + n0 * kHistBins, nn * kHistBins, s));
-    LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_sumsq + n0), 2 * nn, s));
+    LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
   }
   if (!cached && use_small(c, nnodes)) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
@@ -451,6 +461,28 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   long long arg_total = 0;
   for (int m = 0; m < c->M; ++m) { arg_off[m] = arg_total; arg_total += (long long)c->type_points[m] * kGridPoints; }
 
+  std::vector<int> type_first((size_t)c->M + 1, 0);
+  std::vector<int3> type_layers((size_t)c->L);
+  for (int l = 0; l < c->L; ++l) ++type_first[(size_t)c->meta[l].type + 1];
+  int most_layers = 0;
+  for (int m = 0; m < c->M; ++m) {
+    most_layers = std::max(most_layers, type_first[(size_t)m + 1]);
+    type_first[(size_t)m + 1] += type_first[(size_t)m];
+  }
+  {
+    std::vector<int> at(type_first.begin(), type_first.end() - 1);
+    for (int l = 0; l < c->L; ++l) {
+      const LayerMeta &m = c->meta[l];
+      type_layers[(size_t)at[(size_t)m.type]++] = make_int3(l, m.first_chunk, m.nchunks);
+    }
+  }
+  int most_chunks = 0;
+  for (const LayerMeta &m : c->meta) most_chunks = std::max(most_chunks, m.nchunks);
+  // One workgroup per type goes through the type's pairs: worth it while these are few (eight pairs of up to 128 tiles
+  // cost it 8 us; the four launches that it saves 3 to 5 us each).
+  c->fit_one = c->scope != kScopeVector && (long long)c->K * most_layers <= kFitPairs &&
+               (long long)c->K * most_layers * most_chunks <= (1ll << 18);
+
   const size_t KL = (size_t)c->K * c->L, KG = (size_t)c->K * c->G;
   hipError_t e = hipSuccess;
   auto A = [&](hipError_t r) { if (e == hipSuccess) e = r; };
@@ -473,12 +505,17 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_pooled, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_type_exp, (size_t)c->M));
   A(dev_alloc(&c->d_walk, (size_t)c->M));
+  A(dev_alloc(&c->d_type_first, type_first.size()));
+  A(dev_alloc(&c->d_type_layers, type_layers.size()));
+  if (e == hipSuccess) A(hipMemcpy(c->d_type_first, type_first.data(), type_first.size() * sizeof(int), hipMemcpyHostToDevice));
+  if (e == hipSuccess) A(hipMemcpy(c->d_type_layers, type_layers.data(), type_layers.size() * sizeof(int3), hipMemcpyHostToDevice));
   A(dev_alloc(&c->d_readers, (size_t)1));
   if (e == hipSuccess) A(hipMemset(c->d_readers, 0, sizeof(unsigned int)));
   if (c->scope == kScopeBucket) {   // the quantize pass gathers the fit's statistics itself
     A(dev_alloc(&c->d_type_exp_next, (size_t)c->M));
     A(dev_alloc(&c->d_type_skip, (size_t)c->M));
     A(dev_alloc(&c->d_hist, KL * kHistBins));
+    if (e == hipSuccess) A(hipMemset(c->d_hist, 0, KL * kHistBins * sizeof(unsigned int)));
   }
   {
     const bool one_width = (c->planes_mask & (c->planes_mask - 1u)) == 0u;
@@ -616,39 +653,56 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
       hipStream_t s = static_cast<hipStream_t>(stream);
       Dev a = base_args(c);
       a.round = round;
+      if (fit_in_one(c)) {
+        LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitBuckets, s));
+        return QODA_OK;
+      }
       Dev nx = a;
       nx.type_exp = c->d_type_exp_next;
       LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(nx, s));   // also clears the pooled weights
       LAUNCH(c, kIdFitPool, s, launch_fit_pool_b(a, s));
-      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, s));
+      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitPooled, s));
       HIP_TRY(c, hipMemcpyAsync(c->d_type_exp, c->d_type_exp_next, c->M * sizeof(int), hipMemcpyDeviceToDevice, s));
       return QODA_OK;
     }
     int rc = check_layer_ptrs(c, reinterpret_cast<const void *const *>(grad_dev), KL, "qoda_fit_levels: grad_dev", true);
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!c->d_hist) HIP_TRY(c, dev_alloc(&c->d_hist, KL * kHistBins));
+    if (c->scope != kScopeBucket && !c->d_hist_last) {
+      if (!c->d_hist) {
+        unsigned int *h = nullptr;
+        HIP_TRY(c, dev_alloc(&h, KL * kHistBins));
+        const hipError_t e = launch_zero_u32(h, KL * kHistBins, s);
+        if (e != hipSuccess) { (void)hipFree(h); HIP_TRY(c, e); }
+        c->d_hist = h;
+      }
+      HIP_TRY(c, dev_alloc(&c->d_hist_last, KL * kHistBins));
+    }
     rc = sync_table(c, c->t_grad, reinterpret_cast<const void *const *>(grad_dev), KL, s);
     if (rc) return rc;
     c->norms_valid = false;
     Dev a = base_args(c);
     a.grad = reinterpret_cast<const float *const *>(c->t_grad.dev());
     a.round = round;
-    LAUNCH(c, kIdZero, s, launch_zero_u32(c->d_hist, KL * kHistBins, s));
     if (c->scope == kScopeBucket) {
       // two passes over the gradient: the scale of the weights, then the weighted histogram
-      LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_sumsq), 2 * KL, s));
+      LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist, c->d_sumsq, KL, s));
       LAUNCH(c, kIdBucketMax, s, launch_bucket_max(a, s));
       LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(a, s));
       LAUNCH(c, kIdBucketHist, s, launch_bucket_hist(a, s));
-      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, s));
+      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitPooled, s));
       return QODA_OK;
     }
-    rc = run_norm_pass(c, a, true, s);
-    if (rc) return rc;
-    LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(a, s));
-    LAUNCH(c, kIdFitPool, s, launch_fit_pool(a, s));
-    LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, s));
+    if (fit_in_one(c)) {
+      LAUNCH(c, kIdSumsqHist, s, launch_sumsq(a, true, s));
+      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitLayers, s));
+    } else {
+      rc = run_norm_pass(c, a, true, s);
+      if (rc) return rc;
+      LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(a, s));
+      LAUNCH(c, kIdFitPool, s, launch_fit_pool(a, s));
+      LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitPooled, s));
+    }
     if (keep_norms) {   // the caller has declared that these are the vectors the round's quantize calls will be given
       c->norms_grad.assign(grad_dev, grad_dev + KL);
       c->norms_round = round;
@@ -742,8 +796,7 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     // the bucket norms are computed by the quantize kernel, which also gathers this node's fit statistics into the
     // context (state of the next fit, not scratch): their histograms and running maxima start from zero
     const size_t n0 = (size_t)node * c->L, nn = (size_t)c->L;
-    LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_u32(c->d_hist + n0 * kHistBins, nn * kHistBins, s));
-    LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_sumsq + n0), 2 * nn, s));
+    LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
   } else {
     a.sumsq = nb.sumsq;
     a.norm = nb.norm;
@@ -1063,7 +1116,10 @@ int qoda_read_buffer(qoda_ctx *c, int32_t which, void *dst, size_t bytes, void *
       case QODA_BUF_NORM: src = c->d_norm; have = KL * sizeof(float); break;
       case QODA_BUF_INV: src = c->d_inv; have = KL * sizeof(float); break;
       case QODA_BUF_DELTA: src = c->d_delta; have = c->K * sizeof(double); break;
-      case QODA_BUF_HIST: src = c->d_hist; have = c->d_hist ? KL * kHistBins * sizeof(unsigned int) : 0; break;
+      case QODA_BUF_HIST:
+        src = c->scope == kScopeBucket ? c->d_hist : c->d_hist_last;
+        have = src ? KL * kHistBins * sizeof(unsigned int) : 0;
+        break;
       case QODA_BUF_POOLED: src = c->d_pooled; have = (size_t)c->M * kGridPoints * sizeof(unsigned long long); break;
       default: return fail(c, QODA_EINVAL, "qoda_read_buffer: unknown buffer %d", which);
     }

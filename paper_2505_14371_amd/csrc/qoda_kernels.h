@@ -68,7 +68,10 @@ struct Dev {
   float *rgap;        // [M*256]
   unsigned char *lut;  // [M*1024] level-search table: tau at the lower edge of the bin bits(u) >> 20
   int *walk;          // [M] some interior level of the type lies inside a bin of lut
-  unsigned int *hist;          // [K*L*2048]
+  unsigned int *hist;          // [K*L*2048] layer and vector scope: zero between fits
+  unsigned int *hist_last;     // [K*L*2048] layer and vector scope: the histogram of the last fit
+  const int *type_first;       // [M+1] the layers of type m are type_layers[type_first[m] .. type_first[m+1]-1]
+  const int3 *type_layers;     // [L] (layer, its first tile, its tiles)
   unsigned long long *pooled;  // [M*257]
   int *type_exp;               // [M]
   short *dp_arg;               // DP back-pointers, type m at dp_arg_off[m]
@@ -106,6 +109,11 @@ struct Dev {
 enum DecodeMode { kDecodeMean = 0, kDecodeUpdate = 1, kDecodeUpdateAlt = 2, kDecodeExtrapolate = 3,
                   kDecodeUpdateScalars = 4 };
 
+// Where k_fit_dp takes a type's pooled weights from: the pooling kernels, or its own pass over at most kFitPairs (node, layer)
+// pairs (layer scope; statistics gathered under bucket scope).
+enum FitSource { kFitPooled = 0, kFitLayers = 1, kFitBuckets = 2 };
+constexpr int kFitPairs = 32;
+
 // Kernel classes, for the optional per-kernel event timing of the host API.
 enum KernelId {
   kIdZero = 0, kIdSumsq, kIdSumsqHist, kIdNormFinalize, kIdReserved4 /* no kernel: keeps the class numbers of the others stable */, kIdQuantize, kIdDeltaFinalize, kIdStepScalars,
@@ -132,7 +140,8 @@ hipError_t launch_bucket_hist(const Dev &a, hipStream_t s);   // bucket scope: g
 hipError_t launch_fit_pool_b(const Dev &a, hipStream_t s);    // bucket scope: pooling of gathered grid histograms
 hipError_t launch_fit_typemax(const Dev &a, hipStream_t s);
 hipError_t launch_fit_pool(const Dev &a, hipStream_t s);
-hipError_t launch_fit_dp(const Dev &a, hipStream_t s);
+hipError_t launch_fit_dp(const Dev &a, int source, hipStream_t s);   // source: FitSource
+hipError_t launch_zero_stats(unsigned int *hist, double *stat, size_t n, hipStream_t s);   // bucket scope: n (node, layer) pairs
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 // nontemporal streaming over whole 64 KiB tiles of `bytes`: 16 loads and `stores` (0, 1, 2, 4, 8 or 16) stores per thread
 hipError_t launch_stream(const void *src, void *dst, size_t bytes, int stores, void *sink, hipStream_t s);

@@ -273,6 +273,13 @@ __global__ void k_zero_u32(unsigned int *p, size_t n) {
   for (; i < n; i += stride) p[i] = 0u;
 }
 
+// Bucket scope: the fit statistics of n (node, layer) pairs start from zero.
+__global__ void __launch_bounds__(kThreads) k_zero_stats(unsigned int *hist, double *stat) {
+  unsigned long long *h = reinterpret_cast<unsigned long long *>(hist + (size_t)blockIdx.x * kHistBins);
+  for (int j = threadIdx.x; j < kGridPoints; j += kThreads) h[j] = 0ull;
+  if (threadIdx.x == 0) stat[blockIdx.x] = 0.0;
+}
+
 // ------------------------------------------------------------------------------------------------ pass 1
 // Sum of squares of one tile in fp64 (Sec. 2.2, L2 norm before the root), optionally with the histogram of the
 // top 11 magnitude bits of every coordinate (the distribution estimate of Alg. 1 line 4).
@@ -1697,27 +1704,35 @@ __global__ void __launch_bounds__(kThreads) k_fit_typemax(Dev a) {
   }
 }
 
+// The weight of a vector in fixed point, exponent ex of its type.
+__device__ __forceinline__ unsigned long long fit_weight(double stat, int kind, int ex) {
+  return (unsigned long long)floor(ldexp(weight_of(stat, kind), 23 - ex));
+}
+// Grid index of the midpoint of a raw magnitude bin under the vector's normalisation.
+__device__ __forceinline__ int raw_bin_to_grid(int b, float inv) {
+  const float mid = u2f(((unsigned int)b << 20) | (1u << 19));
+  const int j = (int)(f2u(fminf(mid * inv, 1.0f)) >> 20) - kGridBase;
+  return max(0, min(j, kGridPoints - 1));
+}
+// A count of the accumulating histogram; it moves to the histogram of the last fit, and its cell is zero for the next one.
+__device__ __forceinline__ void move_count(const Dev &a, size_t idx, int b, unsigned int c) {
+  a.hist_last[idx * kHistBins + b] = c;
+  if (c != 0u) a.hist[idx * kHistBins + b] = 0u;
+}
+
 // Re-bin one (node, layer) histogram onto the normalised grid with weight floor(||v||_q^2 * 2^(23 - exponent)).
 __global__ void __launch_bounds__(kThreads) k_fit_pool(Dev a) {
   const int l = blockIdx.x, k = blockIdx.y;
   const LayerMeta m = a.meta[l];
-  const int ex = a.type_exp[m.type];
-  if (ex == kTypeSkip) return;
   const size_t idx = (size_t)k * a.L + l;
-  const unsigned long long wfix = (unsigned long long)floor(ldexp(weight_of(a.sumsq[idx], a.kind), 23 - ex));
-  const float inv = a.inv[idx];
-  if (wfix == 0ull || inv == 0.0f) return;
-  const unsigned int *cnt = a.hist + idx * kHistBins;
   unsigned long long *W = a.pooled + (size_t)m.type * kGridPoints;
+  const int ex = a.type_exp[m.type];
+  const unsigned long long wfix = ex == kTypeSkip ? 0ull : fit_weight(a.sumsq[idx], a.kind, ex);
+  const float inv = a.inv[idx];
   for (int b = threadIdx.x; b < kHistBins; b += kThreads) {
-    if (b == 0) continue;
-    const unsigned int c = cnt[b];
-    if (c == 0u) continue;
-    const float mid = u2f(((unsigned int)b << 20) | (1u << 19));
-    const float uc = fminf(mid * inv, 1.0f);
-    int j = (int)(f2u(uc) >> 20) - kGridBase;
-    j = max(0, min(j, kGridPoints - 1));
-    atomicAdd(&W[j], wfix * (unsigned long long)c);
+    const unsigned int c = a.hist[idx * kHistBins + b];
+    move_count(a, idx, b, c);
+    if (wfix != 0ull && inv != 0.0f && b != 0 && c != 0u) atomicAdd(&W[raw_bin_to_grid(b, inv)], wfix * (unsigned long long)c);
   }
 }
 
@@ -1901,6 +1916,8 @@ __device__ __forceinline__ double fit_cost(const FitRow &ra, const FitRow &rb) {
 }
 
 constexpr int kFitThreads = 1024;
+constexpr int kFitBatch = 8;        // pairs whose histograms are requested together
+static_assert(kHistBins == 2 * kFitThreads, "two raw bins a thread");
 constexpr int kFitLdsPoints = 128;  // up to this many level points the back-pointers stay in shared memory
 // The cost of a pair (a, b) does not depend on the stage, so every thread computes the costs of its pairs once and
 // keeps them in registers: grid index b (1..255, the only places an interior level can sit) has its b candidates
@@ -1908,8 +1925,18 @@ constexpr int kFitLdsPoints = 128;  // up to this many level points the back-poi
 // is then one shared-memory read, one addition and one comparison per pair, and a second step in which the first
 // thread of every b combines its segments in increasing a.
 constexpr int kFitSeg = 40;
+constexpr int kFitSegs = 7;         // segments of the largest grid index
 constexpr int kFitPad = 320;        // D rows are padded with +infinity: a segment may reach index 240 + 39
 
+// SRC: where the pooled weights come from.
+//   kFitPooled   k_fit_typemax and k_fit_pool have run
+//   kFitLayers   layer scope, at most kFitPairs (node, layer) pairs a type: the workgroup does for its type what
+//                k_norm_finalize, k_fit_typemax and k_fit_pool do, and clears the histogram for the next fit.  Four launches
+//                of 3 to 5 us less, 8 us more here: 6.3 M entries in 10 tensors, K = 8, 16 levels 184 -> 179 us per round.
+//                Of this kernel's 51 us there: norms 4, pooling 4, the three running sums 6, pair costs 8, thirteen stages
+//                24, last stage, backtrack and tables 4.
+//   kFitBuckets  bucket scope, as many pairs: pools what the last quantize passes gathered and derives the next scale
+template <int SRC>
 __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   __shared__ FitRow row[kGridPoints + 1];
   __shared__ double D[2][kFitPad];
@@ -1921,11 +1948,123 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   double (*wd)[kGridPoints] = reinterpret_cast<double (*)[kGridPoints]>(pbest);   // W, W*mid, (W*mid)*mid per bin
   double *rv = pbest;   // the last stage's candidates: after the stage loop
   int *ri = pa;
+  __shared__ unsigned long long Ws[SRC == kFitPooled ? 1 : kGridPoints];
+  __shared__ double stat[SRC == kFitPooled ? 1 : kFitPairs];
+  __shared__ float sinv[SRC == kFitLayers ? kFitPairs : 1];
+  __shared__ unsigned long long swgt[SRC == kFitLayers ? kFitPairs : 1];
   const int mtype = blockIdx.x;
-  if (a.type_exp[mtype] == kTypeSkip) return;   // all-zero or non-finite vectors: the type keeps its levels
   const int S = a.type_points[mtype];
   const int t = threadIdx.x;
-  const unsigned long long *W = a.pooled + (size_t)mtype * kGridPoints;
+  if (SRC == kFitPooled) {
+    if (a.type_exp[mtype] == kTypeSkip) return;   // all-zero or non-finite vectors: the type keeps its levels
+  } else {
+    const int f0 = a.type_first[mtype], nl = a.type_first[mtype + 1] - f0, P = a.K * nl;   // pair p: node p / nl
+    const auto at = [&](int p) { return (size_t)(p / nl) * a.L + a.type_layers[f0 + p % nl].x; };
+    unsigned int count[kFitBatch][2];   // raw bins t and t + 1024 of a batch of pairs: requested before the norms are worked out
+    if (SRC == kFitLayers) {
+#pragma unroll
+      for (int q = 0; q < kFitBatch; ++q) {
+        const size_t idx = q < P ? at(q) : 0;
+        count[q][0] = q < P ? a.hist[idx * kHistBins + t] : 0u;
+        count[q][1] = q < P ? a.hist[idx * kHistBins + kFitThreads + t] : 0u;
+      }
+      // norms, a wave per pair: slot j takes a layer's tiles j, j + 256, ... in increasing order, then the tree; lane i has
+      // the slots i, i + 64, i + 128, i + 192
+      const int i = t & 63;
+      for (int p = t >> 6; p < P; p += kFitThreads / 64) {
+        const int3 lay = a.type_layers[f0 + p % nl];   // layer, first tile, tiles
+        const int tiles = lay.z;
+        const double *part = a.partial + (size_t)(p / nl) * a.G + lay.y;
+        const bool sum = a.kind != kNormLinf;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        int c = i;
+        for (; c + 15 * 64 < tiles; c += 16 * 64) {   // loads 16 at a time, sums in the slots' order
+          double v[16];
+#pragma unroll
+          for (int q = 0; q < 16; ++q) v[q] = part[c + 64 * q];
+#pragma unroll
+          for (int q = 0; q < 16; ++q) acc[q & 3] = sum ? acc[q & 3] + v[q] : fmax(acc[q & 3], v[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          if (c + 64 * q < tiles) acc[q & 3] = sum ? acc[q & 3] + part[c + 64 * q] : fmax(acc[q & 3], part[c + 64 * q]);
+        double s = sum ? (acc[0] + acc[2]) + (acc[1] + acc[3]) : fmax(fmax(acc[0], acc[2]), fmax(acc[1], acc[3]));
+#pragma unroll
+        for (int h = 32; h >= 1; h >>= 1) {
+          const double o = __shfl_down(s, h, 64);
+          s = sum ? s + o : fmax(s, o);
+        }
+        if (i == 0) {
+          const bool finite = stat_finite(s, a.kind);
+          const float n = finite ? norm_of(s, a.kind) : 0.0f;
+          const float r = rcp_floor(n);
+          const size_t idx = (size_t)(p / nl) * a.L + lay.x;
+          a.sumsq[idx] = s;
+          a.norm[idx] = n;
+          a.inv[idx] = r;
+          if (!finite) atomicOr(a.status, kStatusNonFinite);
+          if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
+          stat[p] = s;
+          sinv[p] = r;
+        }
+      }
+    } else {
+      for (int p = t; p < P; p += kFitThreads) stat[p] = a.sumsq[at(p)];
+    }
+    for (int j = t; j < kGridPoints; j += kFitThreads) Ws[j] = 0ull;
+    const int was = SRC == kFitBuckets ? a.type_exp[mtype] : 0;   // the scale that the statistics were gathered under
+    __syncthreads();
+    // exponent of the type's largest weight
+    double mx = 0.0;
+    bool bad = false;
+    for (int p = 0; p < P; ++p) {
+      if (!stat_finite(stat[p], a.kind)) bad = true;
+      else mx = fmax(mx, weight_of(stat[p], a.kind));
+    }
+    const int found = (!bad && mx > 0.0) ? (int)((__double_as_longlong(mx) >> 52) & 0x7FF) - 1023 : kTypeSkip;
+    const int ex = SRC == kFitBuckets ? was : found;
+    if (SRC == kFitLayers) {
+      if (t < P) swgt[t] = ex == kTypeSkip || sinv[t] == 0.0f ? 0ull : fit_weight(stat[t], a.kind, ex);
+      __syncthreads();
+      for (int p0 = 0; p0 < P; p0 += kFitBatch) {
+        if (p0 > 0) {
+#pragma unroll
+          for (int q = 0; q < kFitBatch; ++q) {
+            const size_t idx = p0 + q < P ? at(p0 + q) : 0;
+            count[q][0] = p0 + q < P ? a.hist[idx * kHistBins + t] : 0u;
+            count[q][1] = p0 + q < P ? a.hist[idx * kHistBins + kFitThreads + t] : 0u;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < kFitBatch; ++q) {
+          const int p = p0 + q;
+          if (p >= P) break;
+          const size_t idx = at(p);
+          const unsigned long long wfix = swgt[p];
+          const float inv = sinv[p];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int b = t + h * kFitThreads;
+            const unsigned int c = count[q][h];
+            move_count(a, idx, b, c);
+            if (wfix != 0ull && b != 0 && c != 0u) atomicAdd(&Ws[raw_bin_to_grid(b, inv)], wfix * (unsigned long long)c);
+          }
+        }
+      }
+    } else if (ex != kTypeSkip) {
+      for (int e = t; e < P * kGridPoints; e += kFitThreads) {
+        const int p = e / kGridPoints, j = e - p * kGridPoints;
+        const size_t idx = at(p);
+        const unsigned long long c = reinterpret_cast<const unsigned long long *>(a.hist + idx * kHistBins)[j];
+        if (c) atomicAdd(&Ws[j], c);
+      }
+    }
+    __syncthreads();
+    if (t == 0) a.type_exp[mtype] = found;
+    for (int j = t; j < kGridPoints; j += kFitThreads) a.pooled[(size_t)mtype * kGridPoints + j] = Ws[j];
+    if (ex == kTypeSkip) return;   // all-zero or non-finite vectors: the type keeps its levels
+  }
+  const unsigned long long *W = SRC == kFitPooled ? a.pooled + (size_t)mtype * kGridPoints : Ws;
   const int last = kGridPoints - 1;
   const double inf = __longlong_as_double(0x7FF0000000000000ll);
   for (int j = t; j < kGridPoints; j += kFitThreads) {
@@ -1944,13 +2083,26 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
     const int f = t >> 6;
     const double *src = wd[f];
     double *dst = &row[0].p0 + f;   // p0, p1, p2 are the first three doubles of a row
-    double p = 0.0;
+    // a chain of 257 dependent additions: their operands are read 16 at a time, one batch ahead
+    constexpr int N = 16;
+    double p = 0.0, cur[N], nxt[N];
     dst[0] = 0.0;
-#pragma unroll 8
-    for (int j = 0; j < kGridPoints; ++j) {
-      p = p + src[j];
-      dst[4 * (j + 1)] = p;
+#pragma unroll
+    for (int q = 0; q < N; ++q) cur[q] = src[q];
+#pragma unroll 1
+    for (int j = 0; j < 256; j += N) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) nxt[q] = src[min(j + N + q, last)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        p = p + cur[q];
+        dst[4 * (j + q + 1)] = p;
+      }
+#pragma unroll
+      for (int q = 0; q < N; ++q) cur[q] = nxt[q];
     }
+    dst[4 * kGridPoints] = p + cur[0];
     if (f == 0) row[kGridPoints].g = 0.0;
   }
   __syncthreads();
@@ -1987,7 +2139,7 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
         const int aa = a0 + j;
         const FitRow ra = row[min(aa, last)];
         cost[j] = (aa <= b - 1) ? fit_cost(ra, rb) : inf;   // +infinity never wins a comparison below
-        __builtin_amdgcn_sched_barrier(0);   // one pair at a time: 40 rows in flight would not fit the registers
+        if ((j & 1) == 1) __builtin_amdgcn_sched_barrier(0);   // two pairs at a time: 40 rows in flight would not fit the registers
       }
     }
     __syncthreads();
@@ -2008,11 +2160,14 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
       pa[t] = a0 + bj;
       __syncthreads();
       if (b != 0 && seg == 0) {
-        int besta = pa[t];
-        for (int q = 1; q < nseg; ++q) {   // later segments hold larger a: they win only with a smaller cost
-          const double ov = pbest[t + q];
-          if (ov < best) { best = ov; besta = pa[t + q]; }
-        }
+        double ov[kFitSegs];
+#pragma unroll
+        for (int q = 1; q < kFitSegs; ++q) ov[q] = q < nseg ? pbest[t + q] : inf;
+        int won = t;
+#pragma unroll
+        for (int q = 1; q < kFitSegs; ++q)   // later segments hold larger a: they win only with a smaller cost
+          if (ov[q] < best) { best = ov[q]; won = t + q; }
+        const int besta = pa[won];
         if (!(b >= s && b <= last - (S - 1 - s))) best = inf;   // level s cannot sit here
         Dc[b] = best;
         if (lds_arg) sarg[s * 256 + b] = (unsigned char)(best < inf ? besta : 255);
@@ -2152,6 +2307,12 @@ hipError_t launch_stream(const void *src, void *dst, size_t bytes, int stores, v
     case 16: hipLaunchKernelGGL((k_stream<16>), grid, block, 0, s, a, b, tiles, k); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_zero_stats(unsigned int *hist, double *stat, size_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_zero_stats, dim3((unsigned int)n), dim3(kThreads), 0, s, hist, stat);
   return hipGetLastError();
 }
 
@@ -2347,8 +2508,11 @@ hipError_t launch_fit_pool(const Dev &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fit_dp(const Dev &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_fit_dp, dim3(a.M), dim3(kFitThreads), 0, s, a);
+hipError_t launch_fit_dp(const Dev &a, int source, hipStream_t s) {
+  const dim3 grid(a.M), block(kFitThreads);
+  if (source == kFitLayers) hipLaunchKernelGGL((k_fit_dp<kFitLayers>), grid, block, 0, s, a);
+  else if (source == kFitBuckets) hipLaunchKernelGGL((k_fit_dp<kFitBuckets>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_fit_dp<kFitPooled>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
