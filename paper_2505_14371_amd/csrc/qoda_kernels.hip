@@ -287,9 +287,16 @@ template <bool HIST, int KIND>
 __global__ void __launch_bounds__(kThreads) k_sumsq(Dev a) {
   __shared__ double red[kThreads];
   __shared__ unsigned int lh[HIST ? kHistBins : 1];
-  // a workgroup takes up to kSuperTile consecutive tiles of one layer, so that the histogram is flushed to
-  // global memory (integer atomics on a few hot addresses) once per run instead of once per tile
-  const int4 st = a.stiles[blockIdx.x];   // (layer, first chunk inside the layer, chunks)
+  // a workgroup takes up to kSuperTile consecutive tiles of one layer, so that the histogram is flushed to global
+  // memory (integer atomics on a few hot addresses) once per run instead of once per tile; without a histogram a small
+  // launch takes them one by one (see launch_sumsq_kind)
+  int4 st;   // (layer, first chunk inside the layer, chunks)
+  if (HIST || a.stiles != nullptr) {
+    st = a.stiles[blockIdx.x];
+  } else {
+    const int2 tile = a.tiles[blockIdx.x];
+    st = make_int4(tile.x, tile.y, 1, 0);
+  }
   const int l = st.x;
   const int k = a.node0 + blockIdx.y;
   const int kr = k - a.row0;   // row of this node in the per-node scratch and pointer tables
@@ -367,7 +374,15 @@ __global__ void __launch_bounds__(kThreads) k_norm_finalize(Dev a) {
     for (int c = threadIdx.x; c < m.nchunks; c += kThreads) acc = fmax(acc, p[c]);
     s = block_max(acc, red);
   } else {
-    for (int c = threadIdx.x; c < m.nchunks; c += kThreads) acc = acc + p[c];
+    int c = threadIdx.x;
+    for (; c + 7 * kThreads < m.nchunks; c += 8 * kThreads) {   // loads 8 at a time, sums in the slot's order
+      double v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = p[c + q * kThreads];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc = acc + v[q];
+    }
+    for (; c < m.nchunks; c += kThreads) acc = acc + p[c];
     s = block_tree(acc, red);
   }
   if (threadIdx.x == 0) {
@@ -2325,9 +2340,19 @@ hipError_t launch_zero_u32(unsigned int *p, size_t n, hipStream_t s) {
 
 template <int KIND>
 static void launch_sumsq_kind(const Dev &a, bool with_hist, hipStream_t s) {
-  const dim3 grid(a.GS, a.nnodes), block(kThreads);
-  if (with_hist) hipLaunchKernelGGL((k_sumsq<true, KIND>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_sumsq<false, KIND>), grid, block, 0, s, a);
+  const dim3 runs(a.GS, a.nnodes), tiles(a.G, a.nnodes), block(kThreads);
+  if (with_hist) {
+    hipLaunchKernelGGL((k_sumsq<true, KIND>), runs, block, 0, s, a);
+  } else if ((long long)a.G * a.nnodes <= kTaperWorkgroups || (long long)a.G * a.nnodes > 4 * kTaperWorkgroups) {
+    // Up to one device-fill, runs would leave most of the device idle: one vector of 1024 tiles, K = 1, compress and
+    // decompress 59.4 us with runs, 51.0 with single tiles.  From four fills on, single tiles drain more evenly: 9342 tiles
+    // 253.7 / 250.5, 11248 tiles 473.1 / 469.3.  Between, the runs' fewer workgroups win: 3096 tiles 111.1 / 113.4.
+    Dev b = a;
+    b.stiles = nullptr;
+    hipLaunchKernelGGL((k_sumsq<false, KIND>), tiles, block, 0, s, b);
+  } else {
+    hipLaunchKernelGGL((k_sumsq<false, KIND>), runs, block, 0, s, a);
+  }
 }
 
 hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t s) {
