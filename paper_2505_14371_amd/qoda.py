@@ -127,10 +127,17 @@ def pointer_array(xs: Sequence) -> C.Array:
     return _ptrs(list(xs))
 
 
+def address_array(addresses: Sequence[int]) -> C.Array:
+    """pointer_array() for a list of integer addresses, filled in one call."""
+    return (C.c_void_p * len(addresses))(*addresses)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
 
+        if torch.cuda.is_initialized():   # the current stream's handle without a Stream object: 0.4 us instead of 2.9
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

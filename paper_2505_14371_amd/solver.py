@@ -38,6 +38,7 @@ class QODA:
             if p.data_ptr() % 16 != 0:
                 raise ValueError("QODA: parameter storage must be 16-byte aligned")
         self.K = int(num_nodes)
+        self._sizes = [p.numel() for p in self.params]
         if layer_types is None:
             layer_types = [0 if p.dim() >= 2 else 1 for p in self.params]
             if 1 not in layer_types:
@@ -69,22 +70,23 @@ class QODA:
         self._p_xn = None if self._xn is None else qoda.pointer_array(self._xn)
         self.t = 0
 
-    def _check_grads(self, node_grads) -> List[int]:
+    def _check_grads(self, node_grads):
+        """The pointer array of the K x L gradients, every tensor looked at: this loop is most of a small model's host time."""
         if len(node_grads) != self.K:
             raise ValueError(f"QODA.step: {len(node_grads)} gradient lists for {self.K} nodes")
-        ptrs = []
+        sizes, f32, ptrs = self._sizes, torch.float32, []
         for g in node_grads:
-            if len(g) != len(self.params):
+            if len(g) != len(sizes):
                 raise ValueError("QODA.step: a node's gradient list does not match the parameters")
-            for t, p in zip(g, self.params):
-                if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and t.numel() == p.numel()):
+            for t, n in zip(g, sizes):
+                if not (t.is_cuda and t.dtype is f32 and t.is_contiguous() and t.numel() == n):
                     raise ValueError("QODA.step: gradients must be contiguous fp32 CUDA tensors shaped like the parameters")
-                ptrs.append(t.data_ptr())
-        return ptrs
+            ptrs += [t.data_ptr() for t in g]
+        return qoda.address_array(ptrs)
 
     def step(self, node_grads: Sequence[Sequence[torch.Tensor]], stream=None) -> None:
         """One round of Alg. 1 given the K nodes' dual vectors at the current query point (the parameters)."""
-        gp = qoda.pointer_array(self._check_grads(node_grads))
+        gp = self._check_grads(node_grads)
         self.t += 1
         t, cur = self.t, self.t & 1
         if self.fit_every > 0 and (t - 1) % self.fit_every == 0:
