@@ -1611,6 +1611,8 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
   const LayerMeta m = a.meta[l];
   if (m.planes != C1) return;
   const int TS = 1 << C1;
+  double new_acc = 0.0;
+  if (MODE == kDecodeUpdateScalars) new_acc = sum_distances(a);   // every wave computes what k_step_scalars computes
   for (int idx = threadIdx.x; idx < a.K * TS; idx += blockDim.x) {
     const int k = idx / TS, c = idx - k * TS;
     const float *hp = reinterpret_cast<const float *>(a.msgs_in[k] + m.hdr_off);
@@ -1618,6 +1620,10 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
     const float mag = BUCKET ? lvl : hp[0] * lvl;
     T[idx] = (c & 1) ? -mag : mag;
   }
+  // The workgroup counted last in a.readers overwrites *a.acc (below).  So a workgroup may be counted only after each of
+  // its waves has the old value in a register: the sum is complete here (the empty statement needs it), before the barrier,
+  // and the count comes after the barrier.
+  if (MODE == kDecodeUpdateScalars) asm volatile("" : "+v"(new_acc) : : "memory");
   __syncthreads();
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -1625,10 +1631,7 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
   float eta = 0.0f, gamma = 0.0f, eta_prev = 0.0f, accx = 0.0f;
   if (MODE == kDecodeUpdate || MODE == kDecodeUpdateAlt) { eta = a.eta[0]; gamma = a.eta[1]; }
   unsigned int readers = 0u;
-  double new_acc = 0.0;
-  if (MODE == kDecodeUpdateScalars) {   // every workgroup computes what k_step_scalars computes
-    new_acc = sum_distances(a);
-    asm volatile("" : "+v"(new_acc) : : "memory");   // *a.acc has been read before this workgroup is counted
+  if (MODE == kDecodeUpdateScalars) {
     if (t == 0) readers = __hip_atomic_fetch_add(a.readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     eta = gamma = rcp_floor(sqrt_floor(1.0 + new_acc));
   }
@@ -1645,7 +1648,7 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
     const double total = block_tree((double)accx, red);
     if (t == 0) a.dpartial[g] = total;
   }
-  if (MODE == kDecodeUpdateScalars && t == 0 && readers == gridDim.x - 1u) {   // all workgroups have read *a.acc
+  if (MODE == kDecodeUpdateScalars && t == 0 && readers == gridDim.x - 1u) {   // all waves of all workgroups have read *a.acc
     store_scalars(a, new_acc, eta);
     *a.readers = 0u;
   }

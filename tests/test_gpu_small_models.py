@@ -152,3 +152,28 @@ def test_replays_of_a_captured_round():
         for a, b in ((ms[0].msg[0][0], ms[1].msg[0][0]), (ms[0].msg[0][1], ms[1].msg[0][1]), (ms[0].y, ms[1].y),
                      (ms[0].x_half, ms[1].x_half), (ms[0].acc, ms[1].acc), (ms[0].eta, ms[1].eta)):
             assert torch.equal(a, b), step
+
+
+@pytest.mark.parametrize("S", [8, 256])      # two waves a workgroup; four, where the decode tables are large
+def test_every_wave_updates_with_the_same_step_size(S):
+    """The workgroup that is counted last stores the new accumulator, at once where its part of a tile lies past the layer's
+    end; no wave may read it after that.  Layers of a few octets (workgroups with and without work, waves of one workgroup
+    among them), distances that change the step size in every round, many rounds; bit for bit the separate kernels."""
+    sizes, K = [1, 2049, 3 * 2048, 2048, 5, 7 * 2048 + 9] * 8, 8
+    ms = [gm(sizes, [0] * len(sizes), [S], K, seed=4) for _ in range(2)]
+    ms[0].ctx.profile_enable(["k_sumsq<false>"])      # the quantize call's separate kernels in both: the update is compared
+    ms[1].ctx.profile_enable(["k_sumsq<false>", "k_step_scalars"])
+    for m in ms:
+        m.set_grads([[np.random.default_rng([S, k, l]).standard_normal(s).astype(np.float32) for l, s in enumerate(sizes)]
+                     for k in range(K)])
+    for t in range(1, 101):
+        for m in ms:
+            for k, f in enumerate(m.grad_flat):
+                f.mul_(-1.5 if (t + k) % 3 else 0.4)
+            m.quantize_all(t)
+            m.step()
+        a, b = ms
+        assert torch.equal(a.acc, b.acc) and torch.equal(a.eta, b.eta), t
+        for x, y in ((a.y, b.y), (a.x_half, b.x_half), (a.x_next, b.x_next)):
+            assert torch.equal(x, y), t
+    assert ms[1].ctx.profile_read()["k_step_scalars"][1] == 100
