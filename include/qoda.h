@@ -294,8 +294,13 @@ int qoda_status(qoda_ctx *ctx, void *stream);
  *   64 KiB tiles): reads `bytes` (multiple of 65536) from src_dev and writes bytes * stores_per_16_loads / 16 to the
  *   head of each tile of dst_dev.  0 stores: the read-only ceiling; 16: a copy; 2 and 8: about the read/write mix of
  *   the quantize pass and of the decode + update pass.  The measured ceilings that bench.py prints beside the nominal
- *   HBM peak come from this kernel. */
+ *   HBM peak come from this kernel.
+ * qoda_exchange_tries: in the one launch of small models the workgroups exchange their tiles' statistics; how often a
+ *   workgroup looks for the others' before it computes the missing ones itself, with the same results (default 1024, about
+ *   a millisecond, so that a group's workgroups that are not on the device together cannot stop it).  0: it does not look
+ *   and computes all of them, which a test uses to run that path.  QODA_EINVAL for tries < 0. */
 #define QODA_NUM_KERNELS 24
+int qoda_exchange_tries(qoda_ctx *ctx, int32_t tries);
 int qoda_profile_enable(qoda_ctx *ctx, uint32_t class_mask);
 int qoda_profile_read(qoda_ctx *ctx, double *ms, int64_t *launches, void *stream);
 const char *qoda_kernel_name(int32_t id);

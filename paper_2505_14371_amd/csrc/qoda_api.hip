@@ -77,6 +77,7 @@ struct qoda_ctx {
   bool small = false;   // the model's size and code widths allow k_quantize_small
   unsigned long long *d_exch = nullptr;   // its exchange area, zero between calls
   unsigned int *d_finished = nullptr;
+  int tries = kSmallTries;   // qoda_exchange_tries
   unsigned int *d_readers = nullptr;   // of the decode pass with its own step size; zero between calls
   void **d_node_tab = nullptr;   // per-node calls: L layer pointers, then the message and the previous message
   // norms kept by qoda_fit_levels_keep_norms for the quantize calls of the same round on the same vectors
@@ -251,7 +252,7 @@ Dev base_args(const qoda_ctx *c) {
   a.type_points = c->d_type_points;
   a.partial = c->d_partial; a.dpartial = c->d_dpartial; a.sumsq = c->d_sumsq;
   a.readers = c->d_readers;
-  a.exch = c->d_exch; a.finished = c->d_finished;
+  a.exch = c->d_exch; a.finished = c->d_finished; a.tries = c->tries;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
@@ -1151,6 +1152,13 @@ int qoda_status(qoda_ctx *c, void *stream) {
 int qoda_gather_statistics(qoda_ctx *c, int32_t enable) {
   if (!c) return QODA_EINVAL;
   c->gather = enable != 0;
+  return QODA_OK;
+}
+
+int qoda_exchange_tries(qoda_ctx *c, int32_t tries) {
+  if (!c) return QODA_EINVAL;
+  if (tries < 0) return fail(c, QODA_EINVAL, "qoda_exchange_tries: %d tries", tries);
+  c->tries = tries;
   return QODA_OK;
 }
 

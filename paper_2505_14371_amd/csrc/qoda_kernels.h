@@ -14,6 +14,7 @@ constexpr int kDecodeWaves = 2;       // waves (= octets) per workgroup in the d
 constexpr int kThreads = 256;        // workgroup size everywhere: 4 waves, 256 reduction slots
 constexpr int kSmallThreads = 512;   // k_quantize_small: a wave per octet of a tile
 constexpr int kSmallTiles = 512;     // the most tiles of a group whose statistics k_quantize_small combines
+constexpr int kSmallTries = 1024;    // looks for the statistics of a group before missing ones are computed (about 1 ms)
 constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
 constexpr int kGridPoints = 257;     // normalised grid g_0 = 2^-32 ... g_256 = 1
@@ -60,6 +61,7 @@ struct Dev {
   double *dpartial;   // [K*G] per-tile squared differences
   unsigned long long *exch;   // k_quantize_small: [K][2][G] statistics and squared distances in exchange; 0 between calls
   unsigned int *finished;     // k_quantize_small: [K] workgroups that are done; 0 between calls
+  int tries;                  // k_quantize_small: looks for the others' statistics; 0: it computes all of them
   double *sumsq;      // [K*L] the statistic of (node, layer); bucket scope: its largest bucket statistic
   float *norm;        // [K*L]
   float *inv;         // [K*L]

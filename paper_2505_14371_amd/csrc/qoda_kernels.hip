@@ -783,14 +783,15 @@ __device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, cons
 // quantizes what it holds: one read of the vectors.  The node's last workgroup to finish sums the squared distances.
 //
 // What the workgroups exchange are the values themselves: a statistic is stored as the complement of its bit pattern, so
-// that the zeros left by the call before mean "not there yet" (no double that these sums produce has all bits set).  All
-// accesses to them are device-scope atomics, so no cache keeps an old value and no fence is needed.
-// Waiting cannot hang: after kSpins tries a workgroup computes the missing statistics itself, from the vectors, with the
-// same operations in the same order.
+// that the zeros left by the call before mean "not there yet" (no double that these sums produce has all bits set).  Every
+// access to them is a device-scope atomic, so no cache keeps an old value; a value is all that a reader needs, so no fence
+// goes with it.  Only one order matters, that of a workgroup's stores and its count in `finished`: thread 0 makes both
+// stores and the count, and waits for the stores before it counts.  So who finds that all workgroups of a node have been
+// counted also finds all their values, and nothing but its own zeros is written there after that, in this call.
+// Waiting ends: after `tries` looks a workgroup computes the missing statistics itself, one per turn, from the vectors, with
+// the same operations in the same order, and keeps them to itself.
 // Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  Kernel time
 // for 2 x 512 entries, K = 4: 8.5 us against 13.8 for the four kernels it replaces and 10 for the gaps between them.
-constexpr int kSpins = 1024;
-
 __device__ __forceinline__ void publish(unsigned long long *p, double v) {
   __hip_atomic_store(p, ~(unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -919,26 +920,25 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
     if (i == 0) publish(&stat[m.first_chunk + tile.y], own);
   }
   // the group's statistics; n <= kSmallTiles, one thread each
-  int tries = 0;
-  for (;;) {
-    bool have = true;
-    if (t < n) {
+  bool have = t >= n;
+  for (int tries = 0;; ++tries) {
+    if (!have && a.tries > 0) {
       const unsigned long long b = __hip_atomic_load(&stat[first + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       have = b != 0ull;
       if (have) group[t] = __longlong_as_double((long long)~b);
     }
     if (__syncthreads_and(have)) break;
-    if (++tries < kSpins) continue;
-    // some workgroup of the group is not running: its statistic is computed here, one tile at a time
+    if (tries < a.tries) continue;
+    // some workgroup of the group is not running: its statistic is computed here, one tile per turn
     if (t == 0) missing[0] = 0x7FFFFFFF;
     __syncthreads();
     if (!have) atomicMin(&missing[0], t);
     __syncthreads();
-    const int g = first + missing[0];
-    const int2 mt = a.tiles[g];
+    const int q = missing[0];
+    const int2 mt = a.tiles[first + q];
     const double s = tile_statistic(a.grad[(size_t)kr * a.L + mt.x], a.meta[mt.x].d, mt.y, kind, slot, t);
-    if (t == 0) publish(&stat[g], s);   // the same value that its own workgroup stores
-    __syncthreads();
+    if (t == 0) group[q] = s;   // the same value that its own workgroup stores
+    if (t == q) have = true;
   }
   // combine: slot j takes items j, j + 256, ... in increasing order, then the tree
   if (!vec) {
@@ -1051,15 +1051,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   unsigned int done = 0u;
   if (i == 0) {
     publish(&dist[m.first_chunk + tile.y], total);
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // both of this thread's stores are done before the count
     done = __hip_atomic_fetch_add(&a.finished[k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (__builtin_amdgcn_readfirstlane(done) != (unsigned int)a.G - 1u) return;
+  asm volatile("" : : : "memory");   // the distances are read after the count
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     double s = 0.0;
     for (int g = i + 64 * r; g < a.G; g += kThreads) {
-      unsigned long long b;   // stored before its workgroup was counted: on its way at most
-      while ((b = __hip_atomic_load(&dist[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {}
+      const unsigned long long b = __hip_atomic_load(&dist[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       s = s + __longlong_as_double((long long)~b);
     }
     slot[i + 64 * r] = s;
@@ -1067,9 +1068,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   const double delta = wave_tree<true>(slot, i);
   if (i == 0) {
     a.delta[k] = delta;
-    a.finished[k] = 0u;
+    __hip_atomic_store(&a.finished[k], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  for (int g = i; g < 2 * a.G; g += 64) stat[g] = 0ull;   // everybody has read them
+  for (int g = i; g < 2 * a.G; g += 64)   // for the next call; everybody has read them
+    __hip_atomic_store(&stat[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int q = 0; q < a.n_empty; ++q) {   // layers without coordinates: statistics (layer scope) and header entries
     const int e = a.empty_layers[q];
     const LayerMeta me = a.meta[e];

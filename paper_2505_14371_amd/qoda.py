@@ -86,6 +86,7 @@ def load():
     L.qoda_code_length.argtypes = [vp, C.POINTER(C.c_uint64), C.c_uint32, C.POINTER(_CodeLength)]
     L.qoda_read_buffer.argtypes = [vp, C.c_int32, vp, C.c_size_t, vp]
     L.qoda_status.argtypes = [vp, vp]
+    L.qoda_exchange_tries.argtypes = [vp, C.c_int32]
     L.qoda_profile_enable.argtypes = [vp, C.c_uint32]
     L.qoda_profile_read.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_int64), vp]
     L.qoda_kernel_name.argtypes = [C.c_int32]
@@ -97,7 +98,7 @@ def load():
     for name in ("qoda_create", "qoda_destroy", "qoda_message_layout", "qoda_set_levels", "qoda_get_levels",
                  "qoda_fit_levels", "qoda_fit_levels_keep_norms", "qoda_gather_statistics", "qoda_quantize", "qoda_quantize_noalloc", "qoda_quantize_all", "qoda_dequant_aggregate", "qoda_step", "qoda_step_alt",
                  "qoda_step_rates", "qoda_extrapolate", "qoda_index_counts", "qoda_code_length",
-                 "qoda_read_buffer", "qoda_status", "qoda_profile_enable", "qoda_profile_read", "qoda_copy_calibration",
+                 "qoda_read_buffer", "qoda_status", "qoda_exchange_tries", "qoda_profile_enable", "qoda_profile_read", "qoda_copy_calibration",
                  "qoda_stream_calibration"):
         getattr(L, name).restype = C.c_int
     _lib = L
@@ -297,6 +298,10 @@ class Context:
         return int(self._lib.qoda_status(self._h, _stream(stream)))
 
     # -- measurement aids
+    def exchange_tries(self, tries: int):
+        """How often a workgroup of a small model's one launch looks for the others' statistics before it computes them."""
+        self._check(self._lib.qoda_exchange_tries(self._h, tries))
+
     def profile_enable(self, classes=True):
         """classes: True (all kernel classes), False (off), or an iterable of kernel names to time."""
         if classes is True:

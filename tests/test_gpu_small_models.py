@@ -75,6 +75,24 @@ def test_one_launch_equals_the_separate_kernels(shape, kind, scope):
 
 
 @pytest.mark.parametrize("scope", [LAYER, VECTOR])
+@pytest.mark.parametrize("kind", [qoda.NORM_L2, qoda.NORM_L1, qoda.NORM_LINF])
+@pytest.mark.parametrize("shape, K", [("ragged", 3), ("edge of a wave pair", 3), ("groups beyond 256 tiles", 1)])
+def test_workgroups_that_compute_the_statistics_of_others(shape, K, kind, scope):
+    """No looks at all (every workgroup computes all statistics of its group), one look, and the usual number, call by call
+    in turn and with other vectors each time: what one call leaves behind must not reach the next."""
+    sizes = SIZES[shape]
+    rng = np.random.default_rng([K, kind, scope])
+    ms = [gm(sizes, [0] * len(sizes), [16], K, seed=9, norm_scope=scope, norm_kind=kind) for _ in range(2)]
+    ms[1].ctx.profile_enable(ALL)
+    for tries in (0, 1024, 1, 0, 1, 1024):
+        grads = [[[(rng.standard_t(3, s) * 10.0 ** rng.uniform(-6, 3)).astype(np.float32) for s in sizes] for _ in range(K)]]
+        ms[0].ctx.exchange_tries(tries)
+        assert same(*[rounds(m, grads) for m in ms]), tries
+    with pytest.raises(qoda.QodaError):
+        ms[0].ctx.exchange_tries(-1)
+
+
+@pytest.mark.parametrize("scope", [LAYER, VECTOR])
 def test_against_the_oracle(oracle, scope):
     sizes, K, S = SIZES["ragged"], 3, 16
     L = len(sizes)
