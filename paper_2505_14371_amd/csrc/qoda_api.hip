@@ -45,6 +45,7 @@ struct qoda_ctx {
   int *d_type_first = nullptr;   // the layers of every type
   int3 *d_type_layers = nullptr;
   bool fit_one = false;   // k_fit_dp does the work of the kernels before it
+  bool hist_zero = false;   // layer and vector scope: the last fit was enqueued whole, so that it leaves d_hist zero
   unsigned long long *d_pooled = nullptr;
   int *d_type_exp = nullptr, *d_walk = nullptr;
   short *d_dp_arg = nullptr;
@@ -322,6 +323,15 @@ bool use_small(const qoda_ctx *c, int nnodes) {
 bool fit_in_one(const qoda_ctx *c) {
   const unsigned int parts = 1u << kIdNormFinalize | 1u << kIdFitTypemax | 1u << kIdFitPool;
   return c->fit_one && (c->prof_mask & parts) == 0u;
+}
+
+// Whether what is enqueued on this stream goes into a graph.  No answer counts as yes: the caller then takes nothing for
+// granted.
+bool is_captured(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // not the error of the launches that follow
+  return true;
 }
 
 // norms of nodes [node0, node0+n) from the gradient table already on the device
@@ -670,13 +680,7 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (c->scope != kScopeBucket && !c->d_hist_last) {
-      if (!c->d_hist) {
-        unsigned int *h = nullptr;
-        HIP_TRY(c, dev_alloc(&h, KL * kHistBins));
-        const hipError_t e = launch_zero_u32(h, KL * kHistBins, s);
-        if (e != hipSuccess) { (void)hipFree(h); HIP_TRY(c, e); }
-        c->d_hist = h;
-      }
+      if (!c->d_hist) HIP_TRY(c, dev_alloc(&c->d_hist, KL * kHistBins));
       HIP_TRY(c, dev_alloc(&c->d_hist_last, KL * kHistBins));
     }
     rc = sync_table(c, c->t_grad, reinterpret_cast<const void *const *>(grad_dev), KL, s);
@@ -694,6 +698,12 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
       LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitPooled, s));
       return QODA_OK;
     }
+    // The norm pass adds to a histogram that the fit before it left at zero (the consumer clears what it has taken).  That
+    // is not so for the first fit, nor after one that failed between its launches; and a captured fit can be replayed at
+    // any time, so it clears for itself and says nothing about the state now.
+    const bool captured = is_captured(s);
+    if (captured || !c->hist_zero) LAUNCH(c, kIdZero, s, launch_zero_u32(c->d_hist, KL * kHistBins, s));
+    if (!captured) c->hist_zero = false;
     if (fit_in_one(c)) {
       LAUNCH(c, kIdSumsqHist, s, launch_sumsq(a, true, s));
       LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitLayers, s));
@@ -704,6 +714,7 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
       LAUNCH(c, kIdFitPool, s, launch_fit_pool(a, s));
       LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitPooled, s));
     }
+    if (!captured) c->hist_zero = true;
     if (keep_norms) {   // the caller has declared that these are the vectors the round's quantize calls will be given
       c->norms_grad.assign(grad_dev, grad_dev + KL);
       c->norms_round = round;

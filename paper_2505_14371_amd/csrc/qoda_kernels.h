@@ -70,7 +70,7 @@ struct Dev {
   float *rgap;        // [M*256]
   unsigned char *lut;  // [M*1024] level-search table: tau at the lower edge of the bin bits(u) >> 20
   int *walk;          // [M] some interior level of the type lies inside a bin of lut
-  unsigned int *hist;          // [K*L*2048] layer and vector scope: zero between fits
+  unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit
   unsigned int *hist_last;     // [K*L*2048] layer and vector scope: the histogram of the last fit
   const int *type_first;       // [M+1] the layers of type m are type_layers[type_first[m] .. type_first[m+1]-1]
   const int3 *type_layers;     // [L] (layer, its first tile, its tiles)

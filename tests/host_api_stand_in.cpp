@@ -1,0 +1,103 @@
+// The host side of the library (csrc/qoda_api.hip) compiled for the CPU over stand-ins for the HIP runtime and for the kernel
+// launches, so that a test without a GPU can see which launches a call makes, let one of them fail, and capture and replay
+// them.  "Device" memory is host memory, filled with a pattern when it is allocated.  Launches are recorded by name; the only
+// effect they model is that of the level fit on its histogram: the norm pass adds to it, its consumer moves it away.
+#include "../paper_2505_14371_amd/csrc/qoda_api.hip"
+
+#include <cstdlib>
+#include <functional>
+
+namespace {
+std::string g_log;
+int g_fail_at = -1;           // launches until one fails; -1: none
+bool g_capturing = false;
+std::vector<std::function<void()>> g_graph;
+
+hipError_t record(const std::string &name, std::function<void()> effect = nullptr) {
+  if (g_fail_at == 0) { g_fail_at = -1; return hipErrorLaunchFailure; }
+  if (g_fail_at > 0) --g_fail_at;
+  g_log += name + "\n";
+  if (g_capturing) { if (effect) g_graph.push_back(effect); }
+  else if (effect) effect();
+  return hipSuccess;
+}
+}  // namespace
+
+extern "C" {
+void stand_in_reset() { g_log.clear(); g_fail_at = -1; }
+const char *stand_in_log() { return g_log.c_str(); }
+void stand_in_fail_at(int n) { g_fail_at = n; }
+void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); }
+void stand_in_replay() { for (auto &f : g_graph) f(); }
+
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) {
+  *p = std::malloc(n);
+  if (!*p) return hipErrorOutOfMemory;
+  std::memset(*p, 0xCD, n);
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
+  *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { *e = reinterpret_cast<hipEvent_t>(std::malloc(1)); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *t, hipEvent_t, hipEvent_t) { *t = 1.0f; return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "stand-in failure"; }
+}
+
+namespace qoda {
+
+static void move_histograms(const Dev &a) {   // what the consumer of the histogram does with it
+  const size_t n = (size_t)a.K * a.L * kHistBins;
+  std::memcpy(a.hist_last, a.hist, n * sizeof(unsigned int));
+  std::memset(a.hist, 0, n * sizeof(unsigned int));
+}
+
+hipError_t launch_zero_u32(unsigned int *p, size_t n, hipStream_t) { return record("zero", [=] { std::memset(p, 0, 4 * n); }); }
+hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t) {
+  if (!with_hist) return record("norms");
+  return record("norms+hist", [=] { for (size_t i = 0; i < (size_t)a.K * a.L; ++i) a.hist[i * kHistBins + 1] += 1; });
+}
+hipError_t launch_norm_finalize(const Dev &, hipStream_t) { return record("norm_finalize"); }
+hipError_t launch_norm_vector(const Dev &, hipStream_t) { return record("norm_vector"); }
+hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) { return record(a.scope == kScopeBucket ? "quantize_b" : "quantize"); }
+hipError_t launch_quantize_small(const Dev &, unsigned int, hipStream_t) { return record("quantize_small"); }
+hipError_t launch_delta_finalize(const Dev &, hipStream_t) { return record("delta"); }
+hipError_t launch_step_scalars(const Dev &, hipStream_t) { return record("step_scalars"); }
+hipError_t launch_decode(const Dev &, int mode, unsigned int, hipStream_t) { return record("decode:" + std::to_string(mode)); }
+hipError_t launch_alt_scalars(const Dev &, hipStream_t) { return record("alt_scalars"); }
+hipError_t launch_alt_finalize(const Dev &, hipStream_t) { return record("alt_finalize"); }
+hipError_t launch_index_hist(const Dev &a, unsigned int, hipStream_t) { return record("index_hist:" + std::to_string(a.GS)); }
+hipError_t launch_bucket_max(const Dev &a, hipStream_t) { return record("bucket_max:" + std::to_string(a.GS)); }
+hipError_t launch_bucket_hist(const Dev &a, hipStream_t) { return record("bucket_hist:" + std::to_string(a.GS)); }
+hipError_t launch_fit_pool_b(const Dev &, hipStream_t) { return record("fit_pool_b"); }
+hipError_t launch_fit_typemax(const Dev &, hipStream_t) { return record("fit_typemax"); }
+hipError_t launch_fit_pool(const Dev &a, hipStream_t) { return record("fit_pool", [=] { move_histograms(a); }); }
+hipError_t launch_fit_dp(const Dev &a, int source, hipStream_t) {
+  if (source == kFitLayers) return record("fit_dp:layers", [=] { move_histograms(a); });
+  return record(source == kFitBuckets ? "fit_dp:buckets" : "fit_dp:pooled");
+}
+hipError_t launch_zero_stats(unsigned int *, double *, size_t, hipStream_t) { return record("zero_stats"); }
+hipError_t launch_copy(const void *, void *, size_t, hipStream_t) { return record("copy"); }
+hipError_t launch_stream(const void *, void *, size_t, int, void *, hipStream_t) { return record("stream"); }
+hipError_t launch_build_tables(const Dev &, int, hipStream_t) { return record("build_tables"); }
+// small uploads through kernel arguments: done, not recorded
+hipError_t launch_stage_words(void *dst, const void *src, size_t n, hipStream_t) { std::memcpy(dst, src, 4 * n); return hipSuccess; }
+hipError_t launch_stage_pointers(void **dst, const void *const *src, size_t n, hipStream_t) {
+  std::memcpy(dst, src, n * sizeof(void *));
+  return hipSuccess;
+}
+
+}  // namespace qoda

@@ -1,0 +1,110 @@
+"""Which launches a call makes, seen on the CPU: the library's host side over stand-ins for HIP and the kernels
+(tests/host_api_stand_in.cpp), driven through the ordinary binding."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM_INCLUDE = "/opt/rocm/include"
+
+
+@pytest.fixture(scope="session")
+def stand_in(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None or not os.path.isdir(ROCM_INCLUDE):
+        pytest.skip("no g++ or no HIP headers")
+    lib = str(tmp_path_factory.mktemp("routes") / "libqoda_routes.so")
+    cmd = [gxx, "-O1", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+           "-Wl,-Bsymbolic",       # its own hip functions, also where another library of the process has some
+           "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=(&x)", "-I" + ROCM_INCLUDE, "-x", "c++",
+           os.path.join(HERE, "host_api_stand_in.cpp"), "-o", lib]
+    done = subprocess.run(cmd, capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr[-4000:]
+    return lib
+
+
+@pytest.fixture()
+def routes(stand_in, monkeypatch):
+    """make(sizes, ...) -> (context, launches(call) -> names of the launches the call makes)."""
+    from paper_2505_14371_amd import qoda
+
+    monkeypatch.setattr(qoda, "_lib", None)
+    monkeypatch.setattr(qoda, "LIB_PATH", stand_in)
+    lib = qoda.load()
+    lib.stand_in_log.restype = ctypes.c_char_p
+
+    class Model:
+        def __init__(self, sizes, types=None, points=(8,), K=1, **kw):
+            types = [0] * len(sizes) if types is None else types
+            self.ctx = qoda.Context(sizes, types, list(points), K, 1, **kw)
+            self.K, self.L = K, len(sizes)
+            self.grads = [4096] * (K * len(sizes))       # never read: any aligned address will do
+            self.msgs, self.prev = [[4096 + 256 * (2 * k + h) for k in range(K)] for h in (0, 1)]
+            self.lib = lib
+            self.t = 0
+
+        def launches(self, call):
+            lib.stand_in_reset()
+            call()
+            return lib.stand_in_log().decode().split()
+
+        def fit(self, keep=False):
+            self.t += 1
+            f = self.ctx.fit_levels_keep_norms if keep else self.ctx.fit_levels
+            return self.launches(lambda: f(self.grads, self.t, stream=0))
+
+        def histogram(self):
+            return self.ctx.read_buffer(qoda.BUF_HIST, stream=0)
+
+    yield Model
+    qoda._lib = None
+
+
+@pytest.mark.parametrize("K, layers, scope", [(2, 3, 0), (3, 11, 0), (2, 3, 1)])   # one kernel after the norm pass; several; vector
+class TestHistogramOfTheFit:
+    """Every fit counts its own vectors once, whatever happened to the calls before it."""
+
+    def counted_once(self, m):
+        h = m.histogram()
+        return np.array_equal(h[:, :, 1], np.ones((m.K, m.L), np.uint32)) and h.sum() == m.K * m.L
+
+    def test_repeated(self, routes, K, layers, scope):
+        m = routes([100] * layers, K=K, norm_scope=scope)
+        assert m.fit().count("zero") == 1            # the first one clears what was allocated
+        for _ in range(3):
+            assert self.counted_once(m)
+            assert "zero" not in m.fit()
+
+    def test_after_a_launch_that_failed(self, routes, K, layers, scope):
+        from paper_2505_14371_amd import qoda
+
+        m = routes([100] * layers, K=K, norm_scope=scope)
+        n = len(m.fit()) - 1                         # launches of a fit that need not clear
+        for at in range(n):
+            with pytest.raises(qoda.QodaError):
+                m.launches(lambda: (m.lib.stand_in_fail_at(at), m.ctx.fit_levels(m.grads, 50, stream=0)))
+            m.fit()
+            assert self.counted_once(m), at
+
+    def test_captured(self, routes, K, layers, scope):
+        for first_is_captured in (True, False):
+            m = routes([100] * layers, K=K, norm_scope=scope)
+            if not first_is_captured:
+                m.fit()
+            m.lib.stand_in_capture(1)
+            m.fit()
+            m.lib.stand_in_capture(0)
+            m.fit()                                  # an eager fit before the first replay
+            assert self.counted_once(m)
+            m.lib.stand_in_replay()
+            assert self.counted_once(m)
+            with pytest.raises(Exception):
+                m.launches(lambda: (m.lib.stand_in_fail_at(1), m.ctx.fit_levels(m.grads, 50, stream=0)))
+            m.lib.stand_in_replay()                  # a replay after a call that failed
+            assert self.counted_once(m)
+            m.fit()
+            assert self.counted_once(m)
