@@ -137,8 +137,10 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
 
-        if torch.cuda.is_initialized():   # the current stream's handle without a Stream object: 0.4 us instead of 2.9
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+        # the current stream's handle without a Stream object: 0.4 us instead of 2.9; not a public function of torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch.cuda.current_device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

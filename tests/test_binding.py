@@ -1,0 +1,22 @@
+"""The binding's and the solver's handling of arguments, without a GPU."""
+import types
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2505_14371_amd import qoda  # noqa: E402
+
+
+@pytest.mark.parametrize("has_raw", [True, False])
+def test_current_stream_with_and_without_torchs_private_function(monkeypatch, has_raw):
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    if has_raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert qoda._stream(None) == (73 if has_raw else 77)
+    assert qoda._stream(5) == 5 and qoda._stream(0) is None
+    assert qoda._stream(types.SimpleNamespace(cuda_stream=9)) == 9
