@@ -38,7 +38,6 @@ class QODA:
             if p.data_ptr() % 16 != 0:
                 raise ValueError("QODA: parameter storage must be 16-byte aligned")
         self.K = int(num_nodes)
-        self._sizes = [p.numel() for p in self.params]
         if layer_types is None:
             layer_types = [0 if p.dim() >= 2 else 1 for p in self.params]
             if 1 not in layer_types:
@@ -74,7 +73,7 @@ class QODA:
         """The pointer array of the K x L gradients, every tensor looked at: this loop is most of a small model's host time."""
         if len(node_grads) != self.K:
             raise ValueError(f"QODA.step: {len(node_grads)} gradient lists for {self.K} nodes")
-        sizes, f32, ptrs = self._sizes, torch.float32, []
+        sizes, f32, ptrs = [p.numel() for p in self.params], torch.float32, []
         for g in node_grads:
             if len(g) != len(sizes):
                 raise ValueError("QODA.step: a node's gradient list does not match the parameters")

@@ -20,3 +20,19 @@ def test_current_stream_with_and_without_torchs_private_function(monkeypatch, ha
     assert qoda._stream(None) == (73 if has_raw else 77)
     assert qoda._stream(5) == 5 and qoda._stream(0) is None
     assert qoda._stream(types.SimpleNamespace(cuda_stream=9)) == 9
+
+
+def test_gradients_are_compared_with_the_parameters_as_they_are():
+    """A parameter that was given another size since the solver was made: gradients of the old size are refused."""
+    from paper_2505_14371_amd.solver import QODA
+
+    class Grad(torch.Tensor):
+        is_cuda = True
+
+    opt = object.__new__(QODA)
+    opt.params, opt.K = [torch.zeros(6), torch.zeros(3)], 2
+    grads = [[torch.zeros(n).as_subclass(Grad) for n in (6, 3)] for _ in range(2)]
+    assert list(opt._check_grads(grads)) == [g.data_ptr() for node in grads for g in node]
+    opt.params[1].data = torch.zeros(5)
+    with pytest.raises(ValueError):
+        opt._check_grads(grads)
