@@ -1940,17 +1940,13 @@ constexpr int kFitBatch = 8;        // pairs whose histograms are requested toge
 static_assert(kHistBins == 2 * kFitThreads, "two raw bins a thread");
 constexpr int kFitLdsPoints = 128;  // up to this many level points the back-pointers stay in shared memory
 // The cost of a pair (a, b) does not depend on the stage, so every thread computes the costs of its pairs once and
-// keeps them in registers: grid index b (1..255, the only places an interior level can sit) has its candidates
-// a = b-1, b-2, ... 0 cut into segments of kFitSeg by their distance from b, one thread per segment -- 1008 threads, at most
-// kFitSeg costs each, ordered by segment so that the threads of a wave hold pairs of about the same distance.
-// A stage first takes every b's nearest segment (four waves); that gives an upper bound of the minimum.  A wave of farther
-// segments then works only if some lane's smallest cost, added to a lower bound of the previous stage, does not exceed that
-// bound: no other candidate can win or tie.  (fl(D + cost) is monotone in both, so the bounds hold to the bit: the previous
-// stage's values are at least fl(.. fl(min D_1 + min cost) .. + min cost).)  A third step combines the segments.  The costs
-// grow with the distance and the minimum falls with every stage, so most stages do the first step only.
-constexpr int kFitSeg = 37;
+// keeps them in registers: grid index b (1..255, the only places an interior level can sit) has its b candidates
+// a = 0..b-1 cut into segments of kFitSeg, one thread per segment -- 945 threads, at most kFitSeg costs each.  A stage
+// is then one shared-memory read, one addition and one comparison per pair, and a second step in which the first
+// thread of every b combines its segments in increasing a.
+constexpr int kFitSeg = 40;
 constexpr int kFitSegs = 7;         // segments of the largest grid index
-constexpr int kFitPad = 304;        // D rows: kFitSeg entries of +infinity, then the grid indices
+constexpr int kFitPad = 320;        // D rows are padded with +infinity: a segment may reach index 240 + 39
 
 // SRC: where the pooled weights come from.
 //   kFitPooled   k_fit_typemax and k_fit_pool have run
@@ -2135,93 +2131,64 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   const bool lds_arg = S <= kFitLdsPoints;   // candidates a are at most 254: a byte each, 255 for "none"
   if (S > 2) {
     // level 1 at grid index b: cost of the bins below g_b against the levels 0 and g_b
-    double low = inf;   // smallest value of the previous stage, or a bound below it
-    for (int b = t; b < kGridPoints; b += kFitThreads) {
-      const double d1 = (b >= 1 && b <= last - (S - 2)) ? (row[b].g * row[b].p1 - row[b].p2) : inf;
-      D[1][kFitSeg + b] = d1;
-      low = d1;
-    }
-    // this thread's grid index b (0: no work) and segment: segment d has the indices 37d + 1 .. 255
-    int b = 0, d = 0;
+    for (int b = t; b < kGridPoints; b += kFitThreads)
+      D[1][b] = (b >= 1 && b <= last - (S - 2)) ? (row[b].g * row[b].p1 - row[b].p2) : inf;
+    // this thread's grid index b, segment and number of segments of b (b = 0: no work): the indices
+    // 40(g-1)+1 .. 40g have g segments each
+    int b = 0, seg = 0, nseg = 0;
     {
       int base = 0;
-#pragma unroll
-      for (int q = 0; q < kFitSegs; ++q) {
-        const int cnt = last - 1 - kFitSeg * q;
+      for (int g = 1; (g - 1) * kFitSeg + 1 <= last - 1; ++g) {
+        const int r0 = (g - 1) * kFitSeg + 1, r1 = min(g * kFitSeg, last - 1);
+        const int cnt = (r1 - r0 + 1) * g;
         if (t >= base && t < base + cnt) {
-          d = q;
-          b = kFitSeg * q + 1 + t - base;
+          const int o = t - base;
+          b = r0 + o / g;
+          seg = o - (o / g) * g;
+          nseg = g;
         }
         base += cnt;
       }
     }
-    const int a0 = b - kFitSeg * (d + 1);   // its first candidate; below 0 there is none
+    const int a0 = seg * kFitSeg;
     double cost[kFitSeg];
-    double least = inf;
     {
       const FitRow rb = row[b];
 #pragma unroll
       for (int j = 0; j < kFitSeg; ++j) {
         const int aa = a0 + j;
-        const FitRow ra = row[max(aa, 0)];
-        cost[j] = (b != 0 && aa >= 0) ? fit_cost(ra, rb) : inf;   // +infinity never wins a comparison below
-        least = fmin(least, cost[j]);
-        __builtin_amdgcn_sched_barrier(0);   // one pair at a time: 37 rows in flight would not fit the registers
+        const FitRow ra = row[min(aa, last)];
+        cost[j] = (aa <= b - 1) ? fit_cost(ra, rb) : inf;   // +infinity never wins a comparison below
+        if ((j & 1) == 1) __builtin_amdgcn_sched_barrier(0);   // two pairs at a time: 40 rows in flight would not fit the registers
       }
     }
-    // the smallest level-1 value and the smallest cost of all pairs
-    double step = least;
-#pragma unroll
-    for (int h = 1; h < 64; h *= 2) {
-      low = fmin(low, __shfl_xor(low, h, 64));
-      step = fmin(step, __shfl_xor(step, h, 64));
-    }
-    __syncthreads();   // pbest still holds the terms of the prefix sums until here
-    if ((t & 63) == 0) { pbest[t >> 6] = low; pbest[64 + (t >> 6)] = step; }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kFitThreads / 64; ++q) { low = fmin(low, pbest[q]); step = fmin(step, pbest[64 + q]); }
     __syncthreads();
     for (int s = 2; s <= S - 2; ++s) {
       // D of the previous stage is +infinity wherever level s-1 cannot sit (in particular below index s-1), so the
       // candidates need no range test: min over a of D[a] + cost(a, b), the smallest a on equal cost
-      const double *Dp = D[(s - 1) & 1] + kFitSeg + a0;
-      double *Dc = D[s & 1] + kFitSeg;
-      const bool sits = b >= s && b <= last - (S - 1 - s);   // level s can sit at b
-#pragma unroll 1
-      for (int far = 0; far < 2; ++far) {   // the nearest segments, then the others
-        const bool turn = (t >= 256) == (far != 0);
-        if (turn && __ballot(sits && (far == 0 || !(low + least > pbest[max(b, 1) - 1]))) != 0ull) {
-          double best = inf;
-          int bj = 0;
+      const double *Dp = D[(s - 1) & 1] + a0;
+      double *Dc = D[s & 1];
+      double best = inf;
+      int bj = 0;
 #pragma unroll
-          for (int j = 0; j < kFitSeg; ++j) {
-            const double c = Dp[j] + cost[j];   // never a NaN: costs and D are finite or +infinity
-            bj = (c < best) ? j : bj;
-            best = fmin(best, c);
-            if ((j & 7) == 7) __builtin_amdgcn_sched_barrier(0);   // reads eight at a time: more would spill the costs
-          }
-          pbest[t] = best;
-          pa[t] = a0 + bj;
-        } else if (turn) {
-          pbest[t] = inf;
-        }
-        if (far == 0) __syncthreads();
+      for (int j = 0; j < kFitSeg; ++j) {
+        const double c = Dp[j] + cost[j];   // never a NaN: costs and D are finite or +infinity
+        bj = (c < best) ? j : bj;
+        best = fmin(best, c);
       }
-      low = low + step;
+      pbest[t] = best;
+      pa[t] = a0 + bj;
       __syncthreads();
-      if (t < last - 1) {   // b = t + 1: its segments in increasing a, i.e. from the farthest to the nearest
-        double best = inf;
+      if (b != 0 && seg == 0) {
+        double ov[kFitSegs];
+#pragma unroll
+        for (int q = 1; q < kFitSegs; ++q) ov[q] = q < nseg ? pbest[t + q] : inf;
         int won = t;
 #pragma unroll
-        for (int q = kFitSegs - 1; q >= 0; --q) {
-          // segment q starts at thread sum over r < q of (255 - 37 r)
-          const int at = q * (last - 1) - kFitSeg * (q * (q - 1) / 2) + t - kFitSeg * q;
-          const double ov = t >= kFitSeg * q ? pbest[at] : inf;
-          if (ov < best) { best = ov; won = at; }   // larger a wins only with a smaller cost
-        }
+        for (int q = 1; q < kFitSegs; ++q)   // later segments hold larger a: they win only with a smaller cost
+          if (ov[q] < best) { best = ov[q]; won = t + q; }
         const int besta = pa[won];
-        if (!sits) best = inf;
+        if (!(b >= s && b <= last - (S - 1 - s))) best = inf;   // level s cannot sit here
         Dc[b] = best;
         if (lds_arg) sarg[s * 256 + b] = (unsigned char)(best < inf ? besta : 255);
         else arg[(size_t)s * kGridPoints + b] = (short)(best < inf ? besta : -1);
@@ -2230,7 +2197,7 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
     }
     // last level (1.0) at grid index `last`: one candidate per thread, then the smallest cost (ties: smallest index)
     {
-      const double *Dp = D[(S - 2) & 1] + kFitSeg;
+      const double *Dp = D[(S - 2) & 1];
       double c = inf;
       if (t < kThreads && t >= S - 2 && t <= last - 1) {
         const FitRow ra = row[t], rb = row[last];
