@@ -918,11 +918,14 @@ static int step_common(qoda_ctx *c, const void *const *msgs_dev, const float *co
   return QODA_OK;
 }
 
-// Whether the decode pass computes the step size itself: a launch less, but every workgroup repeats the sum over the K
-// distances and is counted (one atomic on one address).  us per round with the launch / without: 2 x 512 entries
-// 21.5 / 20.3, 152 k entries (20 tiles) 46.0 / 42.0, 6.3 M entries (387 tiles) 189 / 193.  One code width: the update is one launch.
+// Whether the decode pass computes the step size itself: a launch less, but every wave repeats the sum over the K distances,
+// a chain of dependent loads and additions, and every workgroup is counted, one atomic on one address.  So it is for few
+// nodes and few tiles.  us per step with the launch / without: 1 tile, K = 1 8.8 / 6.3, K = 16 16.1 / 15.3, K = 64 40.0 /
+// 40.8; 8 tiles, K = 16 17.0 / 16.4, K = 32 26.9 / 28.6; 16 tiles, K = 8 14.0 / 12.5, K = 16 19.3 / 19.7, K = 64 45.5 / 63.9;
+// 32 tiles, K = 4 12.9 / 12.1, K = 6 12.9 / 13.2; 40 tiles, K = 1 11.2 / 10.6, K = 3 11.7 / 11.7; 64 tiles, K = 1 11.8 / 13.0.
+// One code width: the update is one launch.
 static bool fuse_scalars(const qoda_ctx *c) {
-  return c->G > 0 && c->G <= 64 && c->K <= 64 && (c->planes_mask & (c->planes_mask - 1u)) == 0u &&
+  return c->G > 0 && c->G <= 40 && c->K <= 16 && c->G * c->K <= 128 && (c->planes_mask & (c->planes_mask - 1u)) == 0u &&
          (c->prof_mask & (1u << kIdStepScalars)) == 0u;
 }
 

@@ -177,7 +177,7 @@ def test_every_wave_updates_with_the_same_step_size(S):
     """The workgroup that is counted last stores the new accumulator, at once where its part of a tile lies past the layer's
     end; no wave may read it after that.  Layers of a few octets (workgroups with and without work, waves of one workgroup
     among them), distances that change the step size in every round, many rounds; bit for bit the separate kernels."""
-    sizes, K = [1, 2049, 3 * 2048, 2048, 5, 7 * 2048 + 9] * 8, 8
+    sizes, K = [1, 2049, 3 * 2048, 2048, 5, 7 * 2048 + 9] * 4, 5      # 24 tiles; wide codes: 5 tables of 2 KB, four waves
     ms = [gm(sizes, [0] * len(sizes), [S], K, seed=4) for _ in range(2)]
     ms[0].ctx.profile_enable(["k_sumsq<false>"])      # the quantize call's separate kernels in both: the update is compared
     ms[1].ctx.profile_enable(["k_sumsq<false>", "k_step_scalars"])

@@ -108,3 +108,21 @@ class TestHistogramOfTheFit:
             assert self.counted_once(m)
             m.fit()
             assert self.counted_once(m)
+
+
+@pytest.mark.parametrize("tiles, K, fused", [
+    (1, 16, True), (1, 17, False), (8, 16, True), (9, 16, False), (16, 8, True), (17, 8, False), (32, 4, True),
+    (40, 1, True), (41, 1, False), (40, 3, True), (64, 64, False), (2, 64, False)])
+def test_update_that_computes_its_own_step_size(routes, tiles, K, fused):
+    m = routes([16384] * tiles, K=K)
+    names = m.launches(lambda: m.ctx.step(m.msgs, m.grads[:tiles], m.grads[:tiles], m.grads[:tiles], 4096, None, 4096, stream=0))
+    assert names == (["decode:4"] if fused else ["step_scalars", "decode:1"])
+    m.ctx.profile_enable(["k_step_scalars"])
+    names = m.launches(lambda: m.ctx.step(m.msgs, m.grads[:tiles], m.grads[:tiles], m.grads[:tiles], 4096, None, 4096, stream=0))
+    assert names == ["step_scalars", "decode:1"]
+
+
+def test_update_of_several_code_widths(routes):
+    m = routes([100, 100], types=[0, 1], points=(8, 32))
+    names = m.launches(lambda: m.ctx.step(m.msgs, m.grads, m.grads, m.grads, 4096, None, 4096, stream=0))
+    assert names == ["step_scalars", "decode:1"]
