@@ -489,10 +489,14 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   }
   int most_chunks = 0;
   for (const LayerMeta &m : c->meta) most_chunks = std::max(most_chunks, m.nchunks);
-  // One workgroup per type goes through the type's pairs: worth it while these are few (eight pairs of up to 128 tiles
-  // cost it 8 us; the four launches that it saves 3 to 5 us each).
-  c->fit_one = c->scope != kScopeVector && (long long)c->K * most_layers <= kFitPairs &&
-               (long long)c->K * most_layers * most_chunks <= (1ll << 18);
+  // One workgroup per type goes through the type's pairs: worth it while these are few.  us per fit with the kernels before
+  // it / in one.  Layer scope: 1 pair of 1 tile 44.6 / 39.2, of 100 tiles 58.4 / 53.3, of 4000 tiles 92.1 / 88.2; 8 pairs of 1
+  // tile 47.5 / 45.0, of 100 tiles 62.0 / 60.2, of 500 86.1 / 85.0, of 1000 130.8 / 132.2; 12 pairs of 100 tiles 63.3 / 65.2;
+  // 32 pairs of 100 tiles 78.0 / 100.3.  Bucket scope (from gathered statistics): 1 pair 35.6 / 30.3, 8 pairs 36.4 / 31.3, 32
+  // pairs 36.7 / 35.4.
+  const long long pairs = (long long)c->K * most_layers;
+  c->fit_one = c->scope == kScopeBucket ? pairs <= kFitBucketPairs
+                                        : c->scope == kScopeLayer && pairs <= kFitLayerPairs && pairs * most_chunks <= 4096;
 
   const size_t KL = (size_t)c->K * c->L, KG = (size_t)c->K * c->G;
   hipError_t e = hipSuccess;

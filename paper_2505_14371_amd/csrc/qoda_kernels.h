@@ -111,10 +111,11 @@ struct Dev {
 enum DecodeMode { kDecodeMean = 0, kDecodeUpdate = 1, kDecodeUpdateAlt = 2, kDecodeExtrapolate = 3,
                   kDecodeUpdateScalars = 4 };
 
-// Where k_fit_dp takes a type's pooled weights from: the pooling kernels, or its own pass over at most kFitPairs (node, layer)
-// pairs (layer scope; statistics gathered under bucket scope).
+// Where k_fit_dp takes a type's pooled weights from: the pooling kernels, or its own pass over the type's (node, layer) pairs
+// (layer scope; statistics gathered under bucket scope), at most as many as stated here.
 enum FitSource { kFitPooled = 0, kFitLayers = 1, kFitBuckets = 2 };
-constexpr int kFitPairs = 32;
+constexpr int kFitLayerPairs = 8;    // their histograms are requested together
+constexpr int kFitBucketPairs = 32;
 
 // Kernel classes, for the optional per-kernel event timing of the host API.
 enum KernelId {

@@ -1936,7 +1936,6 @@ __device__ __forceinline__ double fit_cost(const FitRow &ra, const FitRow &rb) {
 }
 
 constexpr int kFitThreads = 1024;
-constexpr int kFitBatch = 8;        // pairs whose histograms are requested together
 static_assert(kHistBins == 2 * kFitThreads, "two raw bins a thread");
 constexpr int kFitLdsPoints = 128;  // up to this many level points the back-pointers stay in shared memory
 // The cost of a pair (a, b) does not depend on the stage, so every thread computes the costs of its pairs once and
@@ -1950,12 +1949,12 @@ constexpr int kFitPad = 320;        // D rows are padded with +infinity: a segme
 
 // SRC: where the pooled weights come from.
 //   kFitPooled   k_fit_typemax and k_fit_pool have run
-//   kFitLayers   layer scope, at most kFitPairs (node, layer) pairs a type: the workgroup does for its type what
+//   kFitLayers   layer scope, at most kFitLayerPairs (node, layer) pairs a type: the workgroup does for its type what
 //                k_norm_finalize, k_fit_typemax and k_fit_pool do, and clears the histogram for the next fit.  Four launches
 //                of 3 to 5 us less, 8 us more here: 6.3 M entries in 10 tensors, K = 8, 16 levels 184 -> 179 us per round.
 //                Of this kernel's 51 us there: norms 4, pooling 4, the three running sums 6, pair costs 8, thirteen stages
 //                24, last stage, backtrack and tables 4.
-//   kFitBuckets  bucket scope, as many pairs: pools what the last quantize passes gathered and derives the next scale
+//   kFitBuckets  bucket scope, at most kFitBucketPairs: pools what the last quantize passes gathered and derives the next scale
 template <int SRC>
 __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   __shared__ FitRow row[kGridPoints + 1];
@@ -1969,9 +1968,9 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   double *rv = pbest;   // the last stage's candidates: after the stage loop
   int *ri = pa;
   __shared__ unsigned long long Ws[SRC == kFitPooled ? 1 : kGridPoints];
-  __shared__ double stat[SRC == kFitPooled ? 1 : kFitPairs];
-  __shared__ float sinv[SRC == kFitLayers ? kFitPairs : 1];
-  __shared__ unsigned long long swgt[SRC == kFitLayers ? kFitPairs : 1];
+  __shared__ double stat[SRC == kFitPooled ? 1 : SRC == kFitLayers ? kFitLayerPairs : kFitBucketPairs];
+  __shared__ float sinv[SRC == kFitLayers ? kFitLayerPairs : 1];
+  __shared__ unsigned long long swgt[SRC == kFitLayers ? kFitLayerPairs : 1];
   const int mtype = blockIdx.x;
   const int S = a.type_points[mtype];
   const int t = threadIdx.x;
@@ -1980,10 +1979,10 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   } else {
     const int f0 = a.type_first[mtype], nl = a.type_first[mtype + 1] - f0, P = a.K * nl;   // pair p: node p / nl
     const auto at = [&](int p) { return (size_t)(p / nl) * a.L + a.type_layers[f0 + p % nl].x; };
-    unsigned int count[kFitBatch][2];   // raw bins t and t + 1024 of a batch of pairs: requested before the norms are worked out
+    unsigned int count[kFitLayerPairs][2];   // raw bins t and t + 1024 of the pairs: requested before the norms are worked out
     if (SRC == kFitLayers) {
 #pragma unroll
-      for (int q = 0; q < kFitBatch; ++q) {
+      for (int q = 0; q < kFitLayerPairs; ++q) {
         const size_t idx = q < P ? at(q) : 0;
         count[q][0] = q < P ? a.hist[idx * kHistBins + t] : 0u;
         count[q][1] = q < P ? a.hist[idx * kHistBins + kFitThreads + t] : 0u;
@@ -2046,29 +2045,18 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
     if (SRC == kFitLayers) {
       if (t < P) swgt[t] = ex == kTypeSkip || sinv[t] == 0.0f ? 0ull : fit_weight(stat[t], a.kind, ex);
       __syncthreads();
-      for (int p0 = 0; p0 < P; p0 += kFitBatch) {
-        if (p0 > 0) {
 #pragma unroll
-          for (int q = 0; q < kFitBatch; ++q) {
-            const size_t idx = p0 + q < P ? at(p0 + q) : 0;
-            count[q][0] = p0 + q < P ? a.hist[idx * kHistBins + t] : 0u;
-            count[q][1] = p0 + q < P ? a.hist[idx * kHistBins + kFitThreads + t] : 0u;
-          }
-        }
+      for (int p = 0; p < kFitLayerPairs; ++p) {
+        if (p >= P) break;
+        const size_t idx = at(p);
+        const unsigned long long wfix = swgt[p];
+        const float inv = sinv[p];
 #pragma unroll
-        for (int q = 0; q < kFitBatch; ++q) {
-          const int p = p0 + q;
-          if (p >= P) break;
-          const size_t idx = at(p);
-          const unsigned long long wfix = swgt[p];
-          const float inv = sinv[p];
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int b = t + h * kFitThreads;
-            const unsigned int c = count[q][h];
-            move_count(a, idx, b, c);
-            if (wfix != 0ull && b != 0 && c != 0u) atomicAdd(&Ws[raw_bin_to_grid(b, inv)], wfix * (unsigned long long)c);
-          }
+        for (int h = 0; h < 2; ++h) {
+          const int b = t + h * kFitThreads;
+          const unsigned int c = count[p][h];
+          move_count(a, idx, b, c);
+          if (wfix != 0ull && b != 0 && c != 0u) atomicAdd(&Ws[raw_bin_to_grid(b, inv)], wfix * (unsigned long long)c);
         }
       }
     } else if (ex != kTypeSkip) {

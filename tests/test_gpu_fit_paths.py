@@ -29,7 +29,7 @@ def state(m, M, scope):
 
 @pytest.mark.parametrize("scope", [qoda.SCOPE_LAYER, qoda.SCOPE_BUCKET])
 @pytest.mark.parametrize("kind", [qoda.NORM_L2, qoda.NORM_L1, qoda.NORM_LINF])
-@pytest.mark.parametrize("K, layers", [(1, 1), (4, 8), (3, 11), (16, 2)])     # 1, 32, 33 (separate kernels), 32 pairs
+@pytest.mark.parametrize("K, layers", [(1, 1), (2, 4), (8, 1), (3, 3), (4, 8), (3, 11), (16, 2)])     # pairs: 8 and 32 are limits
 def test_one_kernel_equals_the_separate_ones(K, layers, kind, scope):
     rng = np.random.default_rng([K, layers, kind])
     sizes = [int(s) for s in rng.integers(1, 30000, layers)] + [0, 16384 * 9 + 5]

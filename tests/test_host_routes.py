@@ -126,3 +126,30 @@ def test_update_of_several_code_widths(routes):
     m = routes([100, 100], types=[0, 1], points=(8, 32))
     names = m.launches(lambda: m.ctx.step(m.msgs, m.grads, m.grads, m.grads, 4096, None, 4096, stream=0))
     assert names == ["step_scalars", "decode:1"]
+
+
+ONE, SEVERAL = ["norms+hist", "fit_dp:layers"], ["norms+hist", "norm_finalize", "fit_typemax", "fit_pool", "fit_dp:pooled"]
+
+
+@pytest.mark.parametrize("K, layers, tiles, names", [
+    (1, 1, 1, ONE), (1, 8, 1, ONE), (8, 1, 1, ONE), (4, 2, 512, ONE), (1, 1, 4096, ONE),        # up to 8 pairs a type, 4096 tiles
+    (1, 9, 1, SEVERAL), (3, 3, 1, SEVERAL), (8, 4, 1, SEVERAL), (4, 2, 513, SEVERAL), (1, 1, 4097, SEVERAL)])
+def test_fit_from_vectors(routes, K, layers, tiles, names):
+    m = routes([16384 * tiles] + [100] * (layers - 1), K=K)
+    m.fit()
+    assert m.fit() == names
+    m.ctx.profile_enable(["k_fit_pool"])
+    assert m.fit() == SEVERAL
+
+
+@pytest.mark.parametrize("K, layers, one", [(1, 1, True), (4, 8, True), (3, 11, False)])      # 32 pairs, 33
+def test_fit_from_gathered_statistics(routes, K, layers, one):
+    m = routes([16384 * 3000] + [100] * (layers - 1), K=K, norm_scope=2)
+    names = m.launches(lambda: m.ctx.fit_levels(None, 3, stream=0))
+    assert names == (["fit_dp:buckets"] if one else ["fit_typemax", "fit_pool_b", "fit_dp:pooled"])
+
+
+def test_pairs_are_counted_per_type(routes):
+    m = routes([100] * 12, types=[l % 2 for l in range(12)], points=(8, 8), K=1)
+    m.fit()
+    assert m.fit() == ONE
