@@ -33,10 +33,10 @@ struct qoda_ctx {
   // device memory owned by the context
   LayerMeta *d_meta = nullptr;
   int2 *d_tiles = nullptr;
-  int4 *d_stiles = nullptr;
+  int4 *d_runs[4] = {};   // runs of at most 1, 2, 4 and kSuperTile tiles (the first three under bucket scope only)
   int *d_empty = nullptr;
   int n_empty = 0;
-  int GS = 0;
+  int n_runs[4] = {};
   int *d_type_points = nullptr;
   double *d_partial = nullptr, *d_dpartial = nullptr, *d_sumsq = nullptr, *d_delta = nullptr;
   float *d_norm = nullptr, *d_inv = nullptr, *d_lev = nullptr, *d_rgap = nullptr, *d_eta = nullptr;
@@ -243,10 +243,10 @@ Dev base_args(const qoda_ctx *c) {
   std::memset(&a, 0, sizeof a);
   a.meta = c->d_meta;
   a.tiles = c->d_tiles;
-  a.stiles = c->d_stiles;
+  a.stiles = c->d_runs[3];
   a.empty_layers = c->d_empty;
   a.n_empty = c->n_empty;
-  a.GS = c->GS;
+  a.GS = c->n_runs[3];
   a.L = c->L; a.G = c->G; a.K = c->K; a.M = c->M;
   a.scope = c->scope;
   a.kind = c->kind;
@@ -293,7 +293,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 }
 
 void free_all(qoda_ctx *c) {
-  void *ptrs[] = {c->d_meta, c->d_tiles, c->d_stiles, c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
+  void *ptrs[] = {c->d_meta, c->d_tiles, c->d_runs[0], c->d_runs[1], c->d_runs[2], c->d_runs[3], c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
                   c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
                   c->d_type_first, c->d_type_layers};
@@ -305,6 +305,28 @@ void free_all(qoda_ctx *c) {
       if (sl.dev) (void)hipFree(sl.dev);
   for (auto &r : c->prof_recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (hipEvent_t e : c->prof_pool) (void)hipEventDestroy(e);
+}
+
+// Which runs of tiles a launch over `nnodes` nodes takes under bucket scope.  A run's workgroup sets up its tables and, where
+// it gathers statistics, clears and flushes them, for about a quarter to a half of what a tile costs it; against that stands
+// a device that is not full, or is full of workgroups of unequal length.
+//   kRunsQuantize  us of the quantize pass with runs of 1 / 2 / 4 / 8, S = 16: 256 tiles 24 / 32 / 53 / 92; 1024 tiles 37 / 40 /
+//                  59 / 99; 1280 53 / 42 / 60 / 99; 3096 87 / 85 / 81 / 115; 8192 200 / 181 / 195 / 205; 10000 240 / 215 / 215 / 258;
+//                  12288 290 / 261 / 254 / 274; 24 k 551 / 493 / 486 / 489; 49 k 1092 / 1001 / 976 / 973; 90 k 1995 / 1824 / 1769 / 1760
+//   kRunsFit       us of the fit from vectors (two passes over them): 512 tiles 85 / 117 / 185 / 323; 2048 138 / 143 / 212 / 365;
+//                  3096 167 / 166 / - / 369; 10000 403 / 380 / - / 449; 40 k 1423 / 1273 / 1280 / 1362; 75 k 2607 / 2335 / 2315 / 2320
+//   kRunsCount     us of qoda_index_counts, S = 8 (128), with 1 / 2 / 8: 512 tiles 34 (41) / 32 (36) / 40 (43); 1024 40 (55) / 35 (42)
+//                  / 40 (43); 1536 47 (65) / 39 (48) / 40 (45); 3096 66 (99) / 49 (67) / 43 (50)
+enum RunUse { kRunsQuantize, kRunsFit, kRunsCount };
+void use_runs(const qoda_ctx *c, Dev &a, RunUse use, int nnodes) {
+  if (c->scope != kScopeBucket) return;   // the long runs
+  const long long n = (long long)nnodes * c->G;
+  int i = 3;
+  if (use == kRunsQuantize) i = n <= 1024 ? 0 : n <= 10000 ? 1 : n <= 65536 ? 2 : 3;
+  if (use == kRunsFit) i = n <= 2048 ? 0 : n <= 65536 ? 1 : 3;
+  if (use == kRunsCount) i = n <= 1024 ? 1 : 3;
+  a.stiles = c->d_runs[i];
+  a.GS = c->n_runs[i];
 }
 
 // Whether a call that computes the norms of `nnodes` nodes itself runs them, the quantizer and delta in one launch: when
@@ -363,6 +385,7 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
                      // statistics of these nodes: their histograms and running maxima start from zero
     const size_t n0 = (size_t)node0 * c->L, nn = (size_t)nnodes * c->L;
     LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
+    use_runs(c, a, kRunsQuantize, nnodes);
   }
   if (!cached && use_small(c, nnodes)) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
@@ -430,7 +453,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   std::vector<int2> tiles((size_t)c->G);
   for (int l = 0; l < c->L; ++l)
     for (int ch = 0; ch < c->meta[l].nchunks; ++ch) tiles[(size_t)c->meta[l].first_chunk + ch] = make_int2(l, ch);
-  // Runs of tiles for the kernels that keep per-run state (histograms, tables): kSuperTile tiles each, except that in
+  // Runs of tiles for the kernels that keep per-run state (histograms, tables): up to kSuperTile tiles each, except that in
   // large models the runs shorten towards the end of the table (4, 2, then 1 tile), so that the last workgroups of a
   // launch are short ones and it drains evenly instead of waiting for a last wave of full-length runs.  The table is
   // the same for every node and a launch goes through it node after node, so every node pays the extra flushes of its
@@ -438,17 +461,10 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   // (workgroups the device holds) / K tiles per node, twice and four times that for the pairs and fours.  A launch of fewer than
   // four device-fills of full-length workgroups keeps full runs throughout: there the extra flushes of the short runs
   // cost more than the tail (measured on 0.4 k tiles per node: +20 % on the norm pass).
-  // Under bucket scope the table serves the quantize pass, which is bound by the vector ALU: what counts there is that
-  // every CU gets the same work, and a workgroup's tables and flush cost about a quarter of a tile.  Few tiles: single
-  // ones, then pairs (3096 tiles, K = 8: 167 us per round with runs of 8, 133 with 3, 119 with 1, 2 or 4; single ones also
-  // leave the most workgroups to a call for one node).  From 16 k tiles on, full runs that shorten at the end: 75 k tiles,
-  // K = 8: 1.93 ms with runs of 8, 1.96 with 4, 1.99 with 2, 2.17 with 1.
-  std::vector<int4> stiles;
-  {
-    const bool bucket = c->scope == kScopeBucket;
-    const long long total = chunks * c->K;
-    const int longest = !bucket || total > 16384 ? kSuperTile : total > 4096 ? 2 : 1;
-    const bool large = total >= (bucket ? 16384 : 4ll * kSuperTile * kTaperWorkgroups);
+  // Bucket scope has tables of shorter runs too; use_runs says which launch takes which.
+  auto list_runs = [&](int longest) {
+    std::vector<int4> runs;
+    const bool large = longest == kSuperTile && chunks * c->K >= 4ll * kSuperTile * kTaperWorkgroups;
     const long long T = large ? (kTaperWorkgroups + c->K - 1) / c->K : 0;
     long long before = 0;   // tiles of the layers already listed
     for (int l = 0; l < c->L; ++l) {
@@ -457,13 +473,20 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
         const long long left = chunks - (before + ch);   // tiles from here to the end of the table
         const int want = left <= T ? 1 : left <= 3 * T ? 2 : left <= 7 * T ? 4 : kSuperTile;
         const int len = std::min(std::min(want, longest), n - ch);
-        stiles.push_back(make_int4(l, ch, len, 0));
+        runs.push_back(make_int4(l, ch, len, 0));
         ch += len;
       }
       before += n;
     }
+    return runs;
+  };
+  std::vector<int4> runs[4];   // longest 1, 2, 4 and kSuperTile: those that a launch of one node or of all can take
+  if (c->scope == kScopeBucket) {
+    if (chunks <= 2048) runs[0] = list_runs(1);
+    runs[1] = list_runs(2);
+    if (chunks <= 65536) runs[2] = list_runs(4);
   }
-  c->GS = (int)stiles.size();
+  runs[3] = list_runs(kSuperTile);
   std::vector<int> empty;
   for (int l = 0; l < c->L; ++l)
     if (c->meta[l].d == 0) empty.push_back(l);
@@ -503,7 +526,12 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   auto A = [&](hipError_t r) { if (e == hipSuccess) e = r; };
   A(dev_alloc(&c->d_meta, (size_t)c->L));
   A(dev_alloc(&c->d_tiles, (size_t)c->G));
-  A(dev_alloc(&c->d_stiles, (size_t)c->GS));
+  for (int i = 0; i < 4; ++i) {
+    c->n_runs[i] = (int)runs[i].size();
+    if (c->n_runs[i] == 0) continue;
+    A(dev_alloc(&c->d_runs[i], runs[i].size()));
+    if (e == hipSuccess) A(hipMemcpy(c->d_runs[i], runs[i].data(), runs[i].size() * sizeof(int4), hipMemcpyHostToDevice));
+  }
   A(dev_alloc(&c->d_empty, (size_t)c->n_empty));
   A(dev_alloc(&c->d_type_points, (size_t)c->M));
   A(dev_alloc(&c->d_partial, KG));
@@ -554,7 +582,6 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_node_tab, (size_t)c->L + 64));
   if (e == hipSuccess) A(hipMemcpy(c->d_meta, c->meta.data(), c->L * sizeof(LayerMeta), hipMemcpyHostToDevice));
   if (e == hipSuccess && c->G) A(hipMemcpy(c->d_tiles, tiles.data(), c->G * sizeof(int2), hipMemcpyHostToDevice));
-  if (e == hipSuccess && c->GS) A(hipMemcpy(c->d_stiles, stiles.data(), c->GS * sizeof(int4), hipMemcpyHostToDevice));
   if (e == hipSuccess && c->n_empty) A(hipMemcpy(c->d_empty, empty.data(), c->n_empty * sizeof(int), hipMemcpyHostToDevice));
   if (e == hipSuccess) A(hipMemcpy(c->d_type_points, c->type_points.data(), c->M * sizeof(int), hipMemcpyHostToDevice));
   if (e == hipSuccess) A(hipMemcpy(c->d_dp_arg_off, arg_off.data(), c->M * sizeof(long long), hipMemcpyHostToDevice));
@@ -696,6 +723,7 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
     if (c->scope == kScopeBucket) {
       // two passes over the gradient: the scale of the weights, then the weighted histogram
       LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist, c->d_sumsq, KL, s));
+      use_runs(c, a, kRunsFit, c->K);
       LAUNCH(c, kIdBucketMax, s, launch_bucket_max(a, s));
       LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(a, s));
       LAUNCH(c, kIdBucketHist, s, launch_bucket_hist(a, s));
@@ -813,6 +841,7 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     // context (state of the next fit, not scratch): their histograms and running maxima start from zero
     const size_t n0 = (size_t)node * c->L, nn = (size_t)c->L;
     LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
+    use_runs(c, a, kRunsQuantize, 1);
   } else {
     a.sumsq = nb.sumsq;
     a.norm = nb.norm;
@@ -981,6 +1010,7 @@ int qoda_index_counts(qoda_ctx *c, const void *const *msgs_dev, uint64_t *counts
     int rc = decode_common(c, msgs_dev, a, s, "qoda_index_counts: msgs_dev");
     if (rc) return rc;
     a.index_counts = c->d_index_counts;
+    use_runs(c, a, kRunsCount, c->K);
     LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_index_counts), 2 * n, s));
     LAUNCH(c, kIdIndexHist, s, launch_index_hist(a, c->planes_mask, s));
     static_assert(sizeof(uint64_t) == sizeof(unsigned long long), "64-bit counters");

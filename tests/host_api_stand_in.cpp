@@ -72,7 +72,7 @@ hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t) {
 }
 hipError_t launch_norm_finalize(const Dev &, hipStream_t) { return record("norm_finalize"); }
 hipError_t launch_norm_vector(const Dev &, hipStream_t) { return record("norm_vector"); }
-hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) { return record(a.scope == kScopeBucket ? "quantize_b" : "quantize"); }
+hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) { return record(a.scope == kScopeBucket ? "quantize_b:" + std::to_string(a.GS) : "quantize"); }
 hipError_t launch_quantize_small(const Dev &, unsigned int, hipStream_t) { return record("quantize_small"); }
 hipError_t launch_delta_finalize(const Dev &, hipStream_t) { return record("delta"); }
 hipError_t launch_step_scalars(const Dev &, hipStream_t) { return record("step_scalars"); }

@@ -87,3 +87,28 @@ def test_runs_of_two_tiles(oracle):
     base = [values("spiky", s, rng) for s in sizes]
     grads = [[np.roll(b, 77 * k) for b in base] for k in range(K)]
     check(oracle, gm(sizes, [0] * 3, [S], K, seed=31, norm_scope=BUCKET), sizes, S, K, grads, (0, 15), False)
+
+
+def test_runs_of_four_tiles_equal_single_ones():
+    """10 k tiles over all nodes in one call (runs of four, some cut short by the end of a layer) against a call for every
+    node (single tiles): messages, distances and gathered statistics."""
+    sizes, K = [16384 * 638 + 5, 2049, 16384], 16
+    a, b = [gm(sizes, [0] * 3, [16], K, seed=3, norm_scope=BUCKET) for _ in range(2)]
+    g = torch.Generator(device="cuda")
+    for k in range(K):
+        g.manual_seed(k)
+        z = torch.randn(a.flat_len, device="cuda", generator=g)
+        for m in (a, b):
+            m.grad_flat[k].copy_(z ** 3)
+    for m in (a, b):
+        m.fit(1)
+    for t in (1, 2):
+        a.quantize_all(t)
+        b.quantize_each(t)
+        assert np.array_equal(a.ctx.read_buffer(qoda.BUF_DELTA), b.ctx.read_buffer(qoda.BUF_DELTA))
+        assert np.array_equal(a.ctx.read_buffer(qoda.BUF_SUMSQ), b.ctx.read_buffer(qoda.BUF_SUMSQ))
+        assert np.array_equal(a.ctx.read_buffer(qoda.BUF_HIST), b.ctx.read_buffer(qoda.BUF_HIST))
+        for x, y in zip(a.msg[a.cur], b.msg[b.cur]):
+            assert torch.equal(x, y)
+        for m in (a, b):
+            m.cur, m.have_prev = 1 - m.cur, True

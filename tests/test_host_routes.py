@@ -20,7 +20,7 @@ def stand_in(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("routes") / "libqoda_routes.so")
     cmd = [gxx, "-O1", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
            "-Wl,-Bsymbolic",       # its own hip functions, also where another library of the process has some
-           "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=(&x)", "-I" + ROCM_INCLUDE, "-x", "c++",
+           "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=static_cast<const void*>(&x)", "-I" + ROCM_INCLUDE, "-x", "c++",
            os.path.join(HERE, "host_api_stand_in.cpp"), "-o", lib]
     done = subprocess.run(cmd, capture_output=True, text=True)
     assert done.returncode == 0, done.stderr[-4000:]
@@ -153,3 +153,36 @@ def test_pairs_are_counted_per_type(routes):
     m = routes([100] * 12, types=[l % 2 for l in range(12)], points=(8, 8), K=1)
     m.fit()
     assert m.fit() == ONE
+
+
+class TestRunsUnderBucketScope:
+    """The number of workgroups a node (the length of the table of runs) of the passes that work on runs of tiles."""
+
+    def runs(self, names):
+        return {n.split(":")[0]: int(n.split(":")[1]) for n in names if n.split(":")[-1].isdigit()}
+
+    # tiles of a node, K; runs of the quantize pass (all nodes, one node), of the fit from vectors, of the index counts
+    @pytest.mark.parametrize("tiles, K, all_nodes, one_node, fit, count", [
+        (128, 8, 128, 128, 128, 64), (129, 8, 65, 129, 129, 17), (256, 8, 128, 256, 256, 32), (257, 8, 129, 257, 129, 33),
+        (1025, 1, 513, 513, 1025, 129), (1250, 8, 625, 625, 625, 157), (1251, 8, 313, 626, 626, 157), (8192, 8, 2048, 4096, 4096, None)])
+    def test_lengths(self, routes, tiles, K, all_nodes, one_node, fit, count):
+        m = routes([16384 * tiles - 5], K=K, norm_scope=2)
+        assert self.runs(m.launches(lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))["quantize_b"] == all_nodes
+        for call in (m.ctx.quantize, m.ctx.quantize_noalloc):
+            assert self.runs(m.launches(lambda: call(0, m.grads[:1], 1, m.msgs[0], m.prev[0], stream=0)))["quantize_b"] == one_node
+        got = self.runs(m.fit())
+        assert got["bucket_max"] == got["bucket_hist"] == fit
+        got = self.runs(m.launches(lambda: m.ctx.index_counts(m.msgs, stream=0)))["index_hist"]
+        if count is None:       # full runs, with shorter ones at the end of a large table
+            T = 2048 // K
+            assert got == T + T + T + -(-(tiles - 7 * T) // 8)
+        else:
+            assert got == count
+
+    def test_runs_end_with_their_layer(self, routes):
+        m = routes([16384 * 3, 1, 0, 16384 * 1100], K=1, norm_scope=2)
+        assert self.runs(m.launches(lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, None, stream=0)))["quantize_b"] == 2 + 1 + 550
+
+    def test_other_scopes_keep_full_runs(self, routes):
+        m = routes([16384 * 100], K=1)
+        assert m.launches(lambda: m.ctx.index_counts(m.msgs, stream=0)) == ["zero", "index_hist:13"]
