@@ -288,8 +288,8 @@ __global__ void __launch_bounds__(kThreads) k_sumsq(Dev a) {
   __shared__ double red[kThreads];
   __shared__ unsigned int lh[HIST ? kHistBins : 1];
   // a workgroup takes up to kSuperTile consecutive tiles of one layer, so that the histogram is flushed to global
-  // memory (integer atomics on a few hot addresses) once per run instead of once per tile; without a histogram a small
-  // launch takes them one by one (see launch_sumsq_kind)
+  // memory (integer atomics on a few hot addresses) once per run instead of once per tile; without a histogram most
+  // launches take them one by one (see launch_sumsq_kind)
   int4 st;   // (layer, first chunk inside the layer, chunks)
   if (HIST || a.stiles != nullptr) {
     st = a.stiles[blockIdx.x];
@@ -2334,17 +2334,21 @@ hipError_t launch_zero_u32(unsigned int *p, size_t n, hipStream_t s) {
 template <int KIND>
 static void launch_sumsq_kind(const Dev &a, bool with_hist, hipStream_t s) {
   const dim3 runs(a.GS, a.nnodes), tiles(a.G, a.nnodes), block(kThreads);
+  // Without a histogram nothing is kept per run, and single tiles are the most even load.  Only where they would fill the
+  // device one and a half to two times (the second fill's waves come and go with too few loads in flight) fewer, longer
+  // workgroups are a little faster.  us of the pass with runs / single tiles, K = 1 and K = 8: 512 tiles 20 / 10 and - ; 2048
+  // 31 / 27; 2560 38 / 32 and 38 / 32; 2800 39 / 35 and 34 / 35; 3096 39 / 37 and 36 / 38; 3300 38 / 40 and 39 / 40; 3600 45 / 43
+  // and 41 / 44; 3900 44 / 44 and 45 / 45; 4600 57 / 52 and 58 / 52; 8192 90 / 88 and 87 / 87; 32768 323 / 322.
+  const long long n = (long long)a.G * a.nnodes;
+  const bool long_runs = n > 4 * kTaperWorkgroups / 3 && n < 15 * kTaperWorkgroups / 8;
   if (with_hist) {
     hipLaunchKernelGGL((k_sumsq<true, KIND>), runs, block, 0, s, a);
-  } else if ((long long)a.G * a.nnodes <= kTaperWorkgroups || (long long)a.G * a.nnodes > 4 * kTaperWorkgroups) {
-    // Up to one device-fill, runs would leave most of the device idle: one vector of 1024 tiles, K = 1, compress and
-    // decompress 59.4 us with runs, 51.0 with single tiles.  From four fills on, single tiles drain more evenly: 9342 tiles
-    // 253.7 / 250.5, 11248 tiles 473.1 / 469.3.  Between, the runs' fewer workgroups win: 3096 tiles 111.1 / 113.4.
+  } else if (long_runs) {
+    hipLaunchKernelGGL((k_sumsq<false, KIND>), runs, block, 0, s, a);
+  } else {
     Dev b = a;
     b.stiles = nullptr;
     hipLaunchKernelGGL((k_sumsq<false, KIND>), tiles, block, 0, s, b);
-  } else {
-    hipLaunchKernelGGL((k_sumsq<false, KIND>), runs, block, 0, s, a);
   }
 }
 
