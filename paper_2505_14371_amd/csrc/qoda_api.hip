@@ -331,10 +331,12 @@ void use_runs(const qoda_ctx *c, Dev &a, RunUse use, int nnodes) {
 
 // Whether a call that computes the norms of `nnodes` nodes itself runs them, the quantizer and delta in one launch: when
 // all its tiles are on the device at once (two workgroups of eight waves on each of 256 CUs).  Beyond that the tiles that
-// wait for their group keep others from loading, and the separate passes, with more waves in flight, are faster.  us per
-// round, separate / one launch: 2 x 512 entries, K = 4 (8 tiles) 28.8 / 21.7; 1.8 M entries, K = 4 (448 tiles, largest layer 48)
-// 52.7 / 38.5, one norm per vector 55.6 / 43.4; K = 1, 432 tiles in 193 layers 58.6 / 45.1; but 1544 tiles of a handful of
-// entries 47 / 69, 5.5 M entries, K = 4 (1.6 k tiles) 92 / 98, one norm per vector 95 / 122.
+// wait for their group keep others from loading, and the separate passes, with more waves in flight, are faster; a single
+// group comes to that point earlier, as all wait for the slowest.  us per quantize call, separate / one launch, S = 4:
+// one layer of 128 tiles 24.7 / 15.6, 256 25.0 / 18.2, 384 22.6 / 22.1, 416 22.5 / 22.8 (S = 64 28.1 / 24.8), 448 at S = 64 23.4 /
+// 24.3, 512 23.9 / 25.8; four nodes of 128 tiles 28.7 / 21.9; 512 tiles in 64 layers 27.9 / 22.3; one norm per vector, 416
+// tiles 29.6 / 25.1, 480 25.0 / 26.1.  Rounds beyond 512 tiles: 1544 tiles of a handful of entries 47 / 69, 5.5 M entries, K = 4
+// (1.6 k tiles) 92 / 98, one norm per vector 95 / 122.
 // A caller who asks for the times of the kernels that this launch stands for gets those kernels.
 bool use_small(const qoda_ctx *c, int nnodes) {
   const unsigned int parts = 1u << kIdSumsq | 1u << kIdNormFinalize | 1u << kIdNormVector | 1u << kIdDeltaFinalize;
@@ -564,8 +566,9 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
     const bool one_width = (c->planes_mask & (c->planes_mask - 1u)) == 0u;
     // under vector scope every workgroup combines all the layers' sums, 0.1 us each: from 64 layers on the separate
     // kernels win (432 tiles in 193 layers, K = 1: 61 us per round against 66)
-    c->small = one_width && c->G > 0 && c->G <= kSmallTiles && c->scope != kScopeBucket &&
-               (c->scope != kScopeVector || c->L <= 64);
+    c->small = one_width && c->G > 0 && c->G <= kSmallTiles &&
+               (c->scope == kScopeLayer ? most_chunks <= kSmallGroup
+                                        : c->scope == kScopeVector && c->G <= kSmallGroup && c->L <= kSmallLayers);
     if (c->small) {
       A(dev_alloc(&c->d_exch, 2 * KG));
       A(dev_alloc(&c->d_finished, (size_t)c->K));

@@ -13,7 +13,9 @@ constexpr int kTaperWorkgroups = 2048;   // workgroups of 256 threads the device
 constexpr int kDecodeWaves = 2;       // waves (= octets) per workgroup in the decode pass: 1, 2 or 4
 constexpr int kThreads = 256;        // workgroup size everywhere: 4 waves, 256 reduction slots
 constexpr int kSmallThreads = 512;   // k_quantize_small: a wave per octet of a tile
-constexpr int kSmallTiles = 512;     // the most tiles of a group whose statistics k_quantize_small combines
+constexpr int kSmallTiles = 512;     // the most tiles of a launch of k_quantize_small,
+constexpr int kSmallGroup = 416;     // of a group whose statistics it combines,
+constexpr int kSmallLayers = 64;     // and the most layers under vector scope
 constexpr int kSmallTries = 1024;    // looks for the statistics of a group before missing ones are computed (about 1 ms)
 constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
@@ -130,7 +132,7 @@ hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t s);
 hipError_t launch_norm_finalize(const Dev &a, hipStream_t s);
 hipError_t launch_norm_vector(const Dev &a, hipStream_t s);
 hipError_t launch_quantize(const Dev &a, unsigned int planes_mask, hipStream_t s);
-// norms, quantize and delta in one launch (layer and vector scope, one code width, groups of at most kSmallTiles tiles)
+// norms, quantize and delta in one launch (layer and vector scope, one code width, groups of at most kSmallGroup tiles)
 hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStream_t s);
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s);
 hipError_t launch_step_scalars(const Dev &a, hipStream_t s);

@@ -852,8 +852,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   __shared__ float tprev[1 << C1];      // previous message's decode table indexed by code = sign | h << 1
   __shared__ double slot[kThreads];
   __shared__ float chain[kThreads];
-  __shared__ double group[kSmallTiles];   // the group's tile statistics
-  __shared__ double layer[kSmallTiles];   // vector scope: the layers' sums
+  __shared__ double group[kSmallGroup];   // the group's tile statistics
+  __shared__ double layer[kSmallLayers];   // vector scope: the layers' sums
+  __shared__ double total_stat[1];
   __shared__ float scale[2];
   __shared__ int missing[1];
   const int2 tile = a.tiles[blockIdx.x];
@@ -919,7 +920,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
     const double own = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
     if (i == 0) publish(&stat[m.first_chunk + tile.y], own);
   }
-  // the group's statistics; n <= kSmallTiles, one thread each
+  // the group's statistics; n <= kSmallGroup, one thread each
   bool have = t >= n;
   for (int tries = 0;; ++tries) {
     if (!have && a.tries > 0) {
@@ -987,6 +988,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
       const float rr = rcp_floor(nn);
       scale[0] = nn;
       scale[1] = rr;
+      total_stat[0] = s;
       if (tile.y == 0) {   // one workgroup of the layer
         const size_t idx = (size_t)kr * a.L + l;
         a.sumsq[idx] = s;
@@ -995,13 +997,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
         if (!finite) atomicOr(a.status, kStatusNonFinite);
         if (nn > 0.0f && nn < kFltMin) atomicOr(a.status, kStatusTinyNorm);
       }
-      if (vec && m.first_chunk + tile.y == 0)   // layers without coordinates carry the node's norm too
-        for (int q = 0; q < a.n_empty; ++q) {
-          const size_t idx = (size_t)kr * a.L + a.empty_layers[q];
-          a.sumsq[idx] = s;
-          a.norm[idx] = nn;
-          a.inv[idx] = rr;
-        }
     }
   }
   __syncthreads();
@@ -1014,6 +1009,19 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
     float *h = reinterpret_cast<float *>(msg + m.hdr_off);
     if (t < m.S) h[1 + t] = lj;
     if (t == 0) h[0] = norm;
+  }
+  // layers without coordinates: statistics (under vector scope the node's) and header entries, a wave each
+  for (int q = blockIdx.x * (kSmallThreads / 64) + w; q < a.n_empty; q += gridDim.x * (kSmallThreads / 64)) {
+    const int e = a.empty_layers[q];
+    const LayerMeta me = a.meta[e];
+    const size_t idx = (size_t)kr * a.L + e;
+    if (i == 0) {
+      a.sumsq[idx] = vec ? total_stat[0] : 0.0;
+      a.norm[idx] = vec ? norm : 0.0f;
+      a.inv[idx] = vec ? inv : 0.0f;
+    }
+    float *h = reinterpret_cast<float *>(msg + me.hdr_off);
+    for (int j = i; j <= me.S; j += 64) h[j] = (j == 0) ? (vec ? norm : 0.0f) : a.lev[(size_t)me.type * kMaxPoints + j - 1];
   }
   __syncthreads();
   float dacc = 0.0f;   // this slot's squared differences: an fp32 fused multiply-add chain in increasing coordinate
@@ -1072,14 +1080,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   }
   for (int g = i; g < 2 * a.G; g += 64)   // for the next call; everybody has read them
     __hip_atomic_store(&stat[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int q = 0; q < a.n_empty; ++q) {   // layers without coordinates: statistics (layer scope) and header entries
-    const int e = a.empty_layers[q];
-    const LayerMeta me = a.meta[e];
-    const size_t idx = (size_t)kr * a.L + e;
-    if (!vec && i == 0) { a.sumsq[idx] = 0.0; a.norm[idx] = 0.0f; a.inv[idx] = 0.0f; }
-    float *h = reinterpret_cast<float *>(msg + me.hdr_off);
-    for (int j = i; j <= me.S; j += 64) h[j] = (j == 0) ? (vec ? norm : 0.0f) : a.lev[(size_t)me.type * kMaxPoints + j - 1];
-  }
 }
 
 // ------------------------------------------------------------------------------------------------ bucket scope

@@ -30,6 +30,9 @@ SIZES = {
     "groups beyond 256 tiles": [16384 * 300 + 11, 5],
     "all 512 tiles": [16384 * 511 + 2, 1000],     # the last size that one launch takes (K = 1)
     "513 tiles": [16384 * 512 + 2],
+    "a group of 416 tiles": [16384 * 415 + 7, 16384 * 96],      # 512 in all
+    "many empty layers": [3000, 0, 16384 * 2 + 5, 1] + [0] * 57,
+    "still more empty layers": [0] * 400 + [20, 16384 + 3] + [0] * 3,
 }
 
 
@@ -55,7 +58,7 @@ def same(a, b):
 @pytest.mark.parametrize("shape", SIZES)
 def test_one_launch_equals_the_separate_kernels(shape, kind, scope):
     sizes = SIZES[shape]
-    K = 1 if "512" in shape or "513" in shape else 3
+    K = 1 if "512" in shape or "513" in shape or "416" in shape else 3
     S = {qoda.NORM_L2: 16, qoda.NORM_L1: 5, qoda.NORM_LINF: 200}[kind]
     rng = np.random.default_rng([kind, scope, len(sizes)])
     grads = [[[(rng.standard_t(3, s) * 10.0 ** rng.uniform(-6, 3)).astype(np.float32) for s in sizes] for _ in range(K)]

@@ -186,3 +186,35 @@ class TestRunsUnderBucketScope:
     def test_other_scopes_keep_full_runs(self, routes):
         m = routes([16384 * 100], K=1)
         assert m.launches(lambda: m.ctx.index_counts(m.msgs, stream=0)) == ["zero", "index_hist:13"]
+
+
+SMALL, LAYERS, VECTOR = ["quantize_small"], ["norms", "norm_finalize", "quantize", "delta"], ["norms", "norm_finalize", "norm_vector", "quantize", "delta"]
+
+
+@pytest.mark.parametrize("tiles, layers, K, scope, all_nodes, one_node", [
+    (1, 1, 1, 0, SMALL, SMALL), (64, 8, 1, 0, SMALL, SMALL), (65, 8, 1, 0, LAYERS, LAYERS), (128, 1, 4, 0, SMALL, SMALL),
+    (129, 1, 4, 0, LAYERS, SMALL), (416, 1, 1, 0, SMALL, SMALL), (417, 1, 1, 0, LAYERS, LAYERS), (1, 512, 1, 0, SMALL, SMALL),
+    (416, 1, 1, 1, SMALL, SMALL), (417, 1, 1, 1, VECTOR, VECTOR), (6, 64, 1, 1, SMALL, SMALL), (1, 65, 1, 1, VECTOR, VECTOR),
+    (200, 2, 2, 1, VECTOR, SMALL)])
+def test_one_launch_of_small_models(routes, tiles, layers, K, scope, all_nodes, one_node):
+    m = routes([16384 * tiles] * layers, K=K, norm_scope=scope)
+    every = lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)
+    one = lambda: m.ctx.quantize(0, m.grads[:layers], 1, m.msgs[0], m.prev[0], stream=0)
+    static = lambda: m.ctx.quantize_noalloc(0, m.grads[:layers], 1, m.msgs[0], None, stream=0)
+    separate = VECTOR if scope else LAYERS
+    assert m.launches(every) == all_nodes and m.launches(one) == one_node
+    assert m.launches(static) == separate                # never: the exchange area is the context's
+    m.ctx.profile_enable(["k_quantize", "k_decode<true>"])
+    assert m.launches(every) == all_nodes
+    m.ctx.profile_enable(["k_delta_finalize"])
+    assert m.launches(every) == separate and m.launches(one) == separate
+
+
+def test_one_launch_is_for_one_code_width_and_computes_norms(routes):
+    m = routes([100, 100], types=[0, 1], points=(8, 32))
+    call = lambda t=1: m.ctx.quantize_all(m.grads, t, m.msgs, None, stream=0)
+    assert m.launches(call) == LAYERS
+    m = routes([100, 100])
+    m.fit(keep=True)                                     # round 1: the norms are there
+    assert m.launches(call) == ["quantize", "delta"]
+    assert m.launches(lambda: call(2)) == SMALL and m.launches(call) == SMALL
