@@ -36,21 +36,37 @@ def _one(pattern: str) -> str:
 
 
 def _short(name: str) -> str:
-    """Kernel symbol -> the library's kernel class name (qoda_kernel_name): qoda::k_decode<4, 1, false>(qoda::Dev) ->
-    k_decode<true>; qoda::k_quantize<4>(...) and qoda::k_quantize_b<4>(...) -> k_quantize; k_sumsq<true> stays."""
+    """Kernel symbol -> the library's kernel class name (qoda_kernel_name): qoda::k_decode<4, 1, false>(qoda::Dev) and
+    mode 4, the update that computes its own step size -> k_decode<true>; qoda::k_quantize<4>(...), qoda::k_quantize_b<4>(...)
+    and qoda::k_quantize_small<4, true>(...) -> k_quantize; k_sumsq<true> stays."""
     m = re.search(r"(k_[a-z0-9_]+)(<[^>]*>)?", name)
     if not m:
         return name[:60]
     base = m.group(1)
     raw = [a.strip() for a in (m.group(2) or "<>")[1:-1].split(",") if a.strip()]
     if base == "k_decode" and len(raw) >= 2:
-        return "k_decode<" + {"0": "false", "1": "true", "2": "alt", "3": "extrapolate"}.get(raw[1], raw[1]) + ">"
-    if base in ("k_quantize", "k_quantize_b"):   # whatever the code width, with or without a previous message
+        return "k_decode<" + {"0": "false", "1": "true", "2": "alt", "3": "extrapolate", "4": "true"}.get(raw[1], raw[1]) + ">"
+    if base in ("k_quantize", "k_quantize_b", "k_quantize_small"):   # whatever the code width, with or without a previous message
         return "k_quantize"
     if base == "k_index_hist":
         return base
     args = [a for a in raw if not a.isdigit()]
     return base + ("<" + ", ".join(args) + ">" if args else "")
+
+
+def _label(name: str) -> str:
+    """The class name, and which of its kernels where a class has several."""
+    label = _short(name)
+    if label == "k_quantize" and re.search(r"k_quantize(_b|_small)?<\d+, false", name):
+        label = "k_quantize (no prev)"   # the round-1 variant that reads no previous message
+    if "k_quantize_small" in name:
+        label += " [with norms and delta]"
+    if re.search(r"k_decode<\d+, 4", name):
+        label += " [with step size]"
+    m = re.search(r"k_fit_dp<([12])>", name)
+    if m:
+        label += " [with norms and pooling]" if m.group(1) == "1" else " [with pooling]"
+    return label
 
 
 def _counters(directory: str):
@@ -72,9 +88,7 @@ def _sq_summary(a):
                 name = r["Kernel_Name"]
                 if "qoda::" not in name:
                     continue
-                label = _short(name)
-                if label == "k_quantize" and re.search(r"k_quantize(_b)?<\d+, false", name):
-                    label = "k_quantize (no prev)"
+                label = _label(name)
                 agg[label][r["Counter_Name"]].append(float(r["Counter_Value"]))
     lines = [f"# rocprofv3 --pmc summary (SQ / GRBM counters): {a.name}", "# command:", "#   " + a.command, "#",
              "# probe output:"] + ["#   " + l for l in log.strip().splitlines()]
@@ -158,17 +172,15 @@ def main():
                   f"#   workload={b['config']['workload']} ms_per_step={b['ms_per_step']:.4f} value={b['value']:.1f} {b['unit']} "
                   f"hbm_peak_fraction_algorithmic={b['hbm_peak_fraction_algorithmic']:.4f}",
                   f"#   roofline: kernel={r['kernel']} avg_ms={r['avg_ms']:.4f} achieved={r['achieved']:.1f} GB/s frac={r['frac']:.4f}"]
-    lines += ["", "kernel-trace --stats (ours only):", f"{'kernel':<36}{'calls':>7}{'avg_us':>12}{'min_us':>12}{'max_us':>12}{'pct':>8}"]
+    lines += ["", "kernel-trace --stats (ours only):", f"{'kernel':<42}{'calls':>7}{'avg_us':>12}{'min_us':>12}{'max_us':>12}{'pct':>8}"]
     for r in csv.DictReader(open(_one(os.path.join(a.stats, "**", "*_kernel_stats.csv")))):
         if "qoda::" not in r["Name"]:
             continue
-        label = _short(r["Name"])
-        if label == "k_quantize" and re.search(r"k_quantize(_b)?<\d+, false", r["Name"]):
-            label = "k_quantize (no prev)"   # the round-1 variant that reads no previous message
-        width = re.search(r"k_(quantize|quantize_b|decode)<(\d+)", r["Name"])
+        label = _label(r["Name"])
+        width = re.search(r"k_(quantize|quantize_b|quantize_small|decode)<(\d+)", r["Name"])
         if width and a.bench_json:             # a run with two workloads: tell their code widths apart
             label += f" [{width.group(2)}-bit codes]"
-        lines.append(f"{label:<36}{r['Calls']:>7}{float(r['AverageNs']) / 1e3:>12.1f}"
+        lines.append(f"{label:<42}{r['Calls']:>7}{float(r['AverageNs']) / 1e3:>12.1f}"
                      f"{float(r['MinNs']) / 1e3:>12.1f}{float(r['MaxNs']) / 1e3:>12.1f}{float(r['Percentage']):>8.2f}")
     traffic = {}
     if a.fetch and a.write:

@@ -36,3 +36,19 @@ def test_gradients_are_compared_with_the_parameters_as_they_are():
     opt.params[1].data = torch.zeros(5)
     with pytest.raises(ValueError):
         opt._check_grads(grads)
+
+
+@pytest.mark.parametrize("symbol, cls, label", [
+    ("void qoda::k_quantize<4, true>(qoda::Dev)", "k_quantize", "k_quantize"),
+    ("void qoda::k_quantize_b<4, false, 2>(qoda::Dev)", "k_quantize", "k_quantize (no prev)"),
+    ("void qoda::k_quantize_small<4, true>(qoda::Dev)", "k_quantize", "k_quantize [with norms and delta]"),
+    ("void qoda::k_decode<4, 1, false>(qoda::Dev)", "k_decode<true>", "k_decode<true>"),
+    ("void qoda::k_decode<4, 4, false>(qoda::Dev)", "k_decode<true>", "k_decode<true> [with step size]"),
+    ("void qoda::k_fit_dp<1>(qoda::Dev)", "k_fit_dp", "k_fit_dp [with norms and pooling]"),
+    ("void qoda::k_sumsq<true, 2>(qoda::Dev)", "k_sumsq<true>", "k_sumsq<true>")])
+def test_profile_summary_knows_the_kernels(symbol, cls, label):
+    from paper_2505_14371_amd.harness import profile_summary
+
+    names = [qoda.kernel_name(i) for i in range(qoda.NUM_KERNELS)]
+    assert profile_summary._short(symbol) == cls and cls in names
+    assert profile_summary._label(symbol) == label
