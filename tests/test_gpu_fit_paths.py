@@ -1,6 +1,7 @@
 """The level fit that runs in the norm pass and one more kernel (few (node, layer) pairs per type) against the fit that goes
 through the separate kernels, which a call takes when their times are asked for or when a type has more pairs.  Histograms,
-pooled weights, norms, levels and the messages made with them, bit for bit, over repeated fits."""
+pooled weights, norms, levels and the messages made with them, bit for bit, over repeated fits.  Which of these sizes take
+which route is checked in test_host_routes.py."""
 import numpy as np
 import pytest
 

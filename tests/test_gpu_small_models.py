@@ -1,6 +1,7 @@
 """The one-launch quantize call of small models (norms, quantizer and delta together) and the update that computes its own
 step size, against the separate kernels -- which a call runs when their times are asked for -- and against the oracle.
-Everything bit for bit: messages, statistics, norms, reciprocals, distances, step sizes, iterates."""
+Everything bit for bit: messages, statistics, norms, reciprocals, distances, step sizes, iterates.  That the calls take the
+route named here at these sizes, and at which sizes they do not, is checked in test_host_routes.py."""
 import numpy as np
 import pytest
 

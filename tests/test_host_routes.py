@@ -218,3 +218,45 @@ def test_one_launch_is_for_one_code_width_and_computes_norms(routes):
     m.fit(keep=True)                                     # round 1: the norms are there
     assert m.launches(call) == ["quantize", "delta"]
     assert m.launches(lambda: call(2)) == SMALL and m.launches(call) == SMALL
+
+
+def test_routes_of_the_sizes_that_the_gpu_tests_compare(routes):
+    """tests/test_gpu_small_models.py and tests/test_gpu_fit_paths.py compare a route with the separate kernels.  Here: at their
+    sizes it is that route which is taken, or, on the other side of a limit, is not."""
+    from test_gpu_small_models import SIZES
+
+    def quantize(m):
+        return (m.launches(lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)),
+                m.launches(lambda: m.ctx.quantize(0, m.grads[:m.L], 1, m.msgs[0], m.prev[0], stream=0)))
+
+    def update(m):
+        x = m.grads[:m.L]
+        return m.launches(lambda: m.ctx.step(m.msgs, x, x, x, 4096, None, 4096, stream=0))
+
+    # shape: nodes; one launch for all nodes and for one node, under layer and under vector scope; step size in the update
+    want = {"ragged": (3, True, True, True, True, True), "edge of a wave pair": (3, True, True, True, True, True),
+            "one tile": (3, True, True, True, True, True), "groups beyond 256 tiles": (3, False, True, False, True, False),
+            "all 512 tiles": (1, False, False, False, False, False), "513 tiles": (1, False, False, False, False, False),
+            "a group of 416 tiles": (1, True, True, False, False, False), "many empty layers": (3, True, True, True, True, True),
+            "still more empty layers": (3, True, True, False, False, True)}
+    assert set(want) == set(SIZES)
+    for shape, (K, *small, fused) in want.items():
+        for scope in (0, 1):
+            m = routes(SIZES[shape], points=(16,), K=K, norm_scope=scope)
+            assert [names == SMALL for names in quantize(m)] == small[2 * scope:2 * scope + 2], (shape, scope)
+            assert (update(m) == ["decode:4"]) == fused, shape
+    m = routes([1, 2049, 3 * 2048, 2048, 5, 7 * 2048 + 9] * 4, points=(256,), K=5)     # the step sizes of a hundred rounds
+    assert update(m) == ["decode:4"]
+    for K, layers, layer_scope, bucket_scope in ((1, 1, True, True), (2, 4, True, True), (8, 1, False, True), (3, 3, False, True),
+                                                 (4, 8, False, True), (3, 11, False, False), (16, 2, False, True)):
+        sizes = [20000] * layers + [0, 16384 * 9 + 5]
+        if K == 1:
+            sizes[0] = 16384 * 257 + 3
+        types = [0] * layers + [0 if layers == 1 else 2, 1]
+        points = [8] * (max(types) + 2)
+        m = routes(sizes, types=types, points=points, K=K)
+        m.fit()
+        assert (m.fit() == ONE) == layer_scope, (K, layers)
+        m = routes(sizes, types=types, points=points, K=K, norm_scope=2)
+        names = m.launches(lambda: m.ctx.fit_levels(None, 3, stream=0))
+        assert (names == ["fit_dp:buckets"]) == bucket_scope, (K, layers)
