@@ -19,7 +19,8 @@
  *   - Host arrays (pointer tables, levels) are consumed before a call returns: they reach the device as kernel
  *     arguments, so no call copies from host memory later or waits for an earlier upload.  The library keeps a few
  *     device copies of every K-wide pointer array it is given and recognises a set it has seen; the calls of a round
- *     enqueue kernels (and, for the statistics-based fit, one device-to-device copy) only.  Such a round can be
+ *     enqueue kernels (and, for the statistics-based fit of a type with more than 32 (node, layer) pairs, one
+ *     device-to-device copy) only.  Such a round can be
  *     captured into a HIP graph; pointers and the round number are then fixed in the captured launches.  The calls
  *     that wait (see above) cannot be captured.
  *   - Non-finite input (a vector -- layer, whole dual vector or bucket, by scope -- whose sum of squares is not a
@@ -104,9 +105,10 @@ typedef struct {
   int32_t norm_scope;         /* QODA_SCOPE_*: what one norm covers */
 } qoda_config;
 
-/* Create / destroy.  qoda_create allocates all device scratch (a few MB plus 8 bytes per 16384 coordinates per
- * node; the fit's histogram, 8 KB per (node, layer), is allocated on the first qoda_fit_levels, under bucket scope
- * at once).  Levels start
+/* Create / destroy.  qoda_create allocates all device scratch (a few MB plus 16 bytes per 16384 coordinates per
+ * node, under bucket scope up to 28 more per 16384 coordinates of the model, in small models 16 more per node; the fit's
+ * histograms, two of 8 KB per (node, layer), are allocated on the first qoda_fit_levels, under bucket scope one of
+ * them, at once).  Levels start
  * uniform: l_j = j/(S-1).  On failure *out is NULL. */
 int qoda_create(const qoda_config *cfg, qoda_ctx **out);
 int qoda_destroy(qoda_ctx *ctx);
@@ -138,7 +140,7 @@ int qoda_get_levels(qoda_ctx *ctx, int32_t type, float *levels_host, void *strea
 int qoda_fit_levels(qoda_ctx *ctx, const float *const *grad_dev, uint32_t round, void *stream);
 
 /* Bucket scope only (no effect otherwise): whether the quantize passes that follow gather the histogram for the next
- * statistics-based fit (default: yes).  Gathering costs the quantize pass 11-13 %; a caller who updates the levels
+ * statistics-based fit (default: yes).  Gathering costs the quantize pass 7-12 %; a caller who updates the levels
  * every few thousand rounds, as the paper's experiments do, switches it on for the round before an update step only.
  * A pass that does not gather still records the largest bucket sum per (node, layer), from which the next
  * qoda_fit_levels(NULL) derives the weight scale; its pooled histogram is empty then and the levels stay. */

@@ -790,8 +790,9 @@ __device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, cons
 // counted also finds all their values, and nothing but its own zeros is written there after that, in this call.
 // Waiting ends: after `tries` looks a workgroup computes the missing statistics itself, one per turn, from the vectors, with
 // the same operations in the same order, and keeps them to itself.
-// Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  Kernel time
-// for 2 x 512 entries, K = 4: 8.5 us against 13.8 for the four kernels it replaces and 10 for the gaps between them.
+// Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  A quantize
+// call, with the separate kernels / in one launch: 2 x 512 entries, K = 4 17.2 / 8.6 us, one tile, K = 1 17.0 / 10.1, 100 tiles,
+// K = 5 33.7 / 21.1 (more where the rule stands, use_small).
 __device__ __forceinline__ void publish(unsigned long long *p, double v) {
   __hip_atomic_store(p, ~(unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1261,10 +1262,13 @@ struct BucketHist {
   }
 };
 
-// Bound by the vector ALU (36 instructions per coordinate, 78 % of the cycles) and, next, by shared memory (46 %).  Four
-// waves a SIMD: 128 registers and 40 KiB of shared memory a workgroup.  Measured with statistics gathered, K = 8: 151 M
-// coordinates, 8 levels 1.51 -> 1.35 ms against the version that read every octet twice, in pairs of blocks, and added
-// 64-bit weights in four copies; 6.3 M coordinates, 16 levels 128 -> 80 us (most of it by shorter runs).
+// Bound by the vector ALU (35.6 instructions per coordinate, 87 % of the cycles) and, next, by shared memory (52 %).  Up to
+// 32 levels (codes of 6 bits) four waves a SIMD: 128 registers (up to 60 bytes a lane of them in scratch memory) and 39.2 to 39.9 KiB
+// of shared memory a workgroup.  Wider codes have larger tables (40.6, 42.1 and 45.1 KiB for 7, 8 and 9 bits): three workgroups a
+// CU, and the compiler takes 159 to 165 registers.  Measured against the version that read every octet twice, in pairs of
+// blocks, and added 64-bit weights in four copies, with statistics gathered, K = 8: 151 M coordinates, 8 levels 1.51 -> 1.36 ms;
+// a whole quantize call on 10 k tiles (164 M coordinates over all nodes), us: 4 levels 283 -> 205, 16 295 -> 213, 27 299 -> 240,
+// 64 323 -> 258, 256 330 -> 268; 3096 tiles, 16 levels 124 -> 89 (much of it by shorter runs, see use_runs).
 template <int C1, bool PREV, int KIND>
 __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   __shared__ unsigned char lut[kLutSize];
@@ -1951,8 +1955,8 @@ constexpr int kFitPad = 320;        // D rows are padded with +infinity: a segme
 //   kFitPooled   k_fit_typemax and k_fit_pool have run
 //   kFitLayers   layer scope, at most kFitLayerPairs (node, layer) pairs a type: the workgroup does for its type what
 //                k_norm_finalize, k_fit_typemax and k_fit_pool do, and clears the histogram for the next fit.  Four launches
-//                of 3 to 5 us less, 8 us more here: 6.3 M entries in 10 tensors, K = 8, 16 levels 184 -> 179 us per round.
-//                Of this kernel's 51 us there: norms 4, pooling 4, the three running sums 6, pair costs 8, thirteen stages
+//                of 3 to 5 us less, 8 us more here: 6.3 M entries in 10 tensors, K = 8, 16 levels 183 -> 177.5 us per round.
+//                Of this kernel's 52 us there: norms 4, pooling 4, the three running sums 6, pair costs 8, thirteen stages
 //                24, last stage, backtrack and tables 4.
 //   kFitBuckets  bucket scope, at most kFitBucketPairs: pools what the last quantize passes gathered and derives the next scale
 template <int SRC>
