@@ -140,7 +140,7 @@ int qoda_get_levels(qoda_ctx *ctx, int32_t type, float *levels_host, void *strea
 int qoda_fit_levels(qoda_ctx *ctx, const float *const *grad_dev, uint32_t round, void *stream);
 
 /* Bucket scope only (no effect otherwise): whether the quantize passes that follow gather the histogram for the next
- * statistics-based fit (default: yes).  Gathering costs the quantize pass 7-12 %; a caller who updates the levels
+ * statistics-based fit (default: yes).  Gathering costs the quantize pass 6-12 %; a caller who updates the levels
  * every few thousand rounds, as the paper's experiments do, switches it on for the round before an update step only.
  * A pass that does not gather still records the largest bucket sum per (node, layer), from which the next
  * qoda_fit_levels(NULL) derives the weight scale; its pooled histogram is empty then and the levels stay. */

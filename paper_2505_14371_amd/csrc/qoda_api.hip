@@ -310,9 +310,9 @@ void free_all(qoda_ctx *c) {
 // Which runs of tiles a launch over `nnodes` nodes takes under bucket scope.  A run's workgroup sets up its tables and, where
 // it gathers statistics, clears and flushes them, for about a quarter to a half of what a tile costs it; against that stands
 // a device that is not full, or is full of workgroups of unequal length.
-//   kRunsQuantize  us of the quantize pass with runs of 1 / 2 / 4 / 8, S = 16: 256 tiles 24 / 32 / 53 / 92; 1024 tiles 37 / 40 /
-//                  59 / 99; 1280 53 / 42 / 60 / 99; 3096 87 / 85 / 81 / 115; 8192 200 / 181 / 195 / 205; 10000 240 / 215 / 215 / 258;
-//                  12288 290 / 261 / 254 / 274; 24 k 551 / 493 / 486 / 489; 49 k 1092 / 1001 / 976 / 973; 90 k 1995 / 1824 / 1769 / 1760
+//   kRunsQuantize  us of the quantize pass with runs of 1 / 2 / 4 / 8, S = 16: 768 tiles 35 / 37 / 56 / 98; 1024 36 / 40 / 59 / 98;
+//                  1280 55 / 44 / 61 / 98; 3096 87 / 81 / 79 / 112; 8192 194 / 176 / 189 / 201; 10000 239 / 210 / 208 / 251;
+//                  12288 287 / 255 / 245 / 269; 24 k 541 / 469 / 461 / 461; 65 k 1441 / 1255 / 1222 / 1205; 90 k 1964 / 1725 / 1679 / 1665
 //   kRunsFit       us of the fit from vectors (two passes over them): 512 tiles 85 / 117 / 185 / 323; 2048 138 / 143 / 212 / 365;
 //                  3096 167 / 166 / - / 369; 10000 403 / 380 / - / 449; 40 k 1423 / 1273 / 1280 / 1362; 75 k 2607 / 2335 / 2315 / 2320
 //   kRunsCount     us of qoda_index_counts, S = 8 (128), with 1 / 2 / 8: 512 tiles 34 (41) / 32 (36) / 40 (43); 1024 40 (55) / 35 (42)

@@ -1147,6 +1147,7 @@ __device__ __forceinline__ double bucket_sums_exact(const float (&x)[32], float 
 // of four copies that this replaces (10 for eight copies).
 constexpr int kHistLowBits = 19;
 constexpr int kHistCopies = 16, kHistHighCopies = 4;   // powers of two
+constexpr int kHistFewCopies = 2;    // of the low cells, where a run is a single octet: 2^11 / 2 * (2^19 - 1) < 2^32
 static_assert((long long)kSuperTile * kChunkCoords / kHistCopies * ((1 << kHistLowBits) - 1) < (1ll << 32), "low cells");
 
 // Statistics of the 16 buckets of one octet (the lane's 32 values in x) -> norm, inv (shared memory) and the octet's
@@ -1262,13 +1263,15 @@ struct BucketHist {
   }
 };
 
-// Bound by the vector ALU (35.6 instructions per coordinate, 87 % of the cycles) and, next, by shared memory (52 %).  Up to
-// 32 levels (codes of 6 bits) four waves a SIMD: 128 registers (up to 60 bytes a lane of them in scratch memory) and 39.2 to 39.9 KiB
+// Bound by the vector ALU (36.5 instructions per coordinate, 89 % of the cycles) and, next, by shared memory (52 %).  Up to
+// 32 levels (codes of 6 bits) four waves a SIMD: 128 registers (up to 32 bytes a lane of them in scratch memory) and 39.2 to 39.9 KiB
 // of shared memory a workgroup.  Wider codes have larger tables (40.6, 42.1 and 45.1 KiB for 7, 8 and 9 bits): three workgroups a
-// CU, and the compiler takes 159 to 165 registers.  Measured against the version that read every octet twice, in pairs of
-// blocks, and added 64-bit weights in four copies, with statistics gathered, K = 8: 151 M coordinates, 8 levels 1.51 -> 1.36 ms;
-// a whole quantize call on 10 k tiles (164 M coordinates over all nodes), us: 4 levels 283 -> 205, 16 295 -> 213, 27 299 -> 240,
-// 64 323 -> 258, 256 330 -> 268; 3096 tiles, 16 levels 124 -> 89 (much of it by shorter runs, see use_runs).
+// CU, and the compiler takes 160 to 166 registers.  Measured against the version that read every octet twice, in pairs of
+// blocks, and added 64-bit weights in four copies, with statistics gathered, K = 8: 151 M coordinates, 8 levels 1.51 -> 1.35 ms;
+// a whole quantize call on 10 k tiles (164 M coordinates over all nodes), us: 4 levels 283 -> 200, 16 295 -> 211, 27 299 -> 217,
+// 64 323 -> 262, 256 330 -> 270; 3096 tiles, 16 levels 124 -> 81 (much of it by shorter runs, see use_runs).
+// Layers of a block or two have a form of one pair of blocks, and runs of one octet fewer copies of the histogram: 200 layers of
+// 50 entries, K = 8, 16 levels, gathering 24.6 us before, 27.7 without these two, 22.5 now.
 template <int C1, bool PREV, int KIND>
 __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   __shared__ unsigned char lut[kLutSize];
@@ -1311,8 +1314,15 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
     }
     tprev[c] = pl;
   }
+  // a run of one octet (a small layer) has so few adds that fewer copies, and less to clear and to flush, serve better
+  const bool few = m.nblk - (long long)st.y * (kChunkCoords / kBlockCoords) <= 8;
+  const int copies = few ? kHistFewCopies : kHistCopies;
   if (ex != kTypeSkip) {
-    for (int j = t; j < kGridPoints * kHistCopies; j += kThreads) lo[j] = 0u;
+    if (few) {
+      for (int j = t; j < kGridPoints * kHistFewCopies; j += kThreads) lo[(j / kHistFewCopies) * kHistCopies + j % kHistFewCopies] = 0u;
+    } else {
+      for (int j = t; j < kGridPoints * kHistCopies; j += kThreads) lo[j] = 0u;
+    }
     for (int j = t; j < kGridPoints * kHistHighCopies; j += kThreads) hi[j] = 0u;
   }
   __syncthreads();
@@ -1369,9 +1379,11 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
 #pragma unroll
       for (int j = 0; j < 32; ++j) least = fminf(least, fabsf(x[j]));
       const bool plain = !high && __ballot(least < 0x1p-129f) == 0ull;
-      const BucketHist hist = {bw.wfix + hf8, lo + (i & (kHistCopies - 1)), hi + (i & (kHistHighCopies - 1)), ex != kTypeSkip, high, plain};
+      const BucketHist hist = {bw.wfix + hf8, lo + (i & (copies - 1)), hi + (i & (kHistHighCopies - 1)), ex != kTypeSkip, high, plain};
       const unsigned int c0 = (unsigned int)(O * 256 + i);
-      if (walk)
+      if (m.nblk - O * 8 <= 2)   // one pair of blocks is all there is: the others would be worked on for nothing
+        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done, 1);
+      else if (walk)
         quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
       else
         quantize_regs<C1, PREV, false, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
@@ -1404,8 +1416,13 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
     unsigned long long *gh = reinterpret_cast<unsigned long long *>(a.hist + idx * kHistBins);
     for (int j = t; j < kGridPoints; j += kThreads) {
       unsigned long long c = 0ull, ch = 0ull;
+      if (few) {
 #pragma unroll
-      for (int q = 0; q < kHistCopies; ++q) c += lo[j * kHistCopies + ((q + j) & (kHistCopies - 1))];
+        for (int q = 0; q < kHistFewCopies; ++q) c += lo[j * kHistCopies + q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < kHistCopies; ++q) c += lo[j * kHistCopies + ((q + j) & (kHistCopies - 1))];
+      }
 #pragma unroll
       for (int q = 0; q < kHistHighCopies; ++q) ch += hi[j * kHistHighCopies + q];
       c += ch << kHistLowBits;

@@ -112,3 +112,14 @@ def test_runs_of_four_tiles_equal_single_ones():
             assert torch.equal(x, y)
         for m in (a, b):
             m.cur, m.have_prev = 1 - m.cur, True
+
+
+@pytest.mark.parametrize("irregular", [False, True])
+@pytest.mark.parametrize("kind", ["equal", "spiky", "sparse"])
+@pytest.mark.parametrize("S", [4, 16, 129])
+def test_small_layers_and_short_last_octets(oracle, S, kind, irregular):
+    """Octets of one pair of blocks and of two, layers of one octet (fewer copies of the histogram) and of one octet more."""
+    sizes, K = [50, 256, 257, 511, 512, 513, 1024, 2048, 2048 + 1, 2048 + 512, 2048 + 513, 4096, 16384 + 300], 2
+    rng = np.random.default_rng([S, len(kind), 1])
+    grads = [[values(kind, s, rng) for s in sizes] for _ in range(K)]
+    check(oracle, gm(sizes, [0] * len(sizes), [S], K, seed=31, norm_scope=BUCKET), sizes, S, K, grads, range(K), irregular)
