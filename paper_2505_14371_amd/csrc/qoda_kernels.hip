@@ -1919,24 +1919,27 @@ __device__ void build_tables(const Dev &a, int mtype, int S, const float *slev) 
   float *rg = a.rgap + (size_t)mtype * kMaxPoints;
   unsigned char *lut = a.lut + (size_t)mtype * kLutSize;
   for (int j = threadIdx.x; j < kMaxPoints; j += (int)blockDim.x) rg[j] = (j < S - 1) ? rcp_floor(slev[j + 1] - slev[j]) : 0.0f;
-  // entry q serves the values whose bit pattern >> 20 is q: tau at the lower edge of that bin.
+  // entry q serves the values whose bit pattern >> 20 is q: tau at the lower edge of that bin, the largest j <= S-2 with
+  // slev[j] <= edge (the levels increase, so that j is found by halving).
   for (int q = threadIdx.x; q < kLutSize; q += (int)blockDim.x) {
     const float lo = u2f((unsigned int)q << 20);
     int tau = 0;
     if (q > 1016) {
       tau = S - 2;
     } else {
-      for (int j = 1; j <= S - 2; ++j)
-        if (slev[j] <= lo) tau = j;
+      for (int n = S - 2; n > 0;) {   // the answer lies in tau .. tau + n
+        const int h = (n + 1) >> 1;
+        if (slev[tau + h] <= lo) { tau += h; n -= h; }
+        else n = h - 1;
+      }
     }
     lut[q] = (unsigned char)tau;
   }
   // does some interior level lie inside a bin?  (0 and 1 are edges; then a lane may have to step on from lut's entry)
-  if (threadIdx.x == 0) {
-    int walk = 0;
-    for (int j = 1; j <= S - 2; ++j) walk |= (f2u(slev[j]) & 0xFFFFFu) != 0u;
-    a.walk[mtype] = walk;
-  }
+  int inside = 0;
+  for (int j = threadIdx.x; j < S; j += (int)blockDim.x) inside |= (f2u(slev[j]) & 0xFFFFFu) != 0u;
+  const int walk = __syncthreads_or(inside);
+  if (threadIdx.x == 0) a.walk[mtype] = walk;
 }
 
 __global__ void __launch_bounds__(kThreads) k_build_tables(Dev a, int mtype) {
@@ -1950,7 +1953,7 @@ __global__ void __launch_bounds__(kThreads) k_build_tables(Dev a, int mtype) {
 // Exact minimisation of eq. (Qada2) over interior levels on the grid by dynamic programming; one workgroup per type.
 // cost(a, b) = sum over bins i in [a, b) of W_i (g_b - mid_i)(mid_i - g_a), from prefix sums P0, P1, P2 of W, W*mid,
 // W*mid^2 taken sequentially in increasing bin (fp64; the same operation order as the CPU checker).
-struct __attribute__((aligned(32))) FitRow { double p0, p1, p2, g; };
+struct FitRow { double p0, p1, p2, g; };
 
 __device__ __forceinline__ double fit_cost(const FitRow &ra, const FitRow &rb) {
   return ((ra.g + rb.g) * (rb.p1 - ra.p1) - (rb.p2 - ra.p2)) - (ra.g * rb.g) * (rb.p0 - ra.p0);
@@ -1960,35 +1963,49 @@ constexpr int kFitThreads = 1024;
 static_assert(kHistBins == 2 * kFitThreads, "two raw bins a thread");
 constexpr int kFitLdsPoints = 128;  // up to this many level points the back-pointers stay in shared memory
 // The cost of a pair (a, b) does not depend on the stage, so every thread computes the costs of its pairs once and
-// keeps them in registers: grid index b (1..255, the only places an interior level can sit) has its b candidates
-// a = 0..b-1 cut into segments of kFitSeg, one thread per segment -- 945 threads, at most kFitSeg costs each.  A stage
-// is then one shared-memory read, one addition and one comparison per pair, and a second step in which the first
-// thread of every b combines its segments in increasing a.
-constexpr int kFitSeg = 40;
-constexpr int kFitSegs = 7;         // segments of the largest grid index
-constexpr int kFitPad = 320;        // D rows are padded with +infinity: a segment may reach index 240 + 39
+// keeps them in registers.  Grid indices b (1..255, the only places an interior level can sit) go two by two: couple q has
+// b = 2q-1 and 2q, whose candidates a = 0..2q-1 are cut into segments of kFitSeg, one thread per segment for both b -- 975
+// threads, 2 * kFitSeg costs each.  A stage is then, per pair, half a shared-memory read, one addition, one comparison, one
+// minimum and one select, and a second step in which four threads per b combine its segments in increasing a.
+// Bound by one CU: a stage takes 1.6 us, of which 1.0 is the issue of 4 fp64 instructions per pair and, beside them, 16 cycles
+// of shared memory per 128-bit read of a wave; the rest is the chain of the second step.  Segments are 144 bytes apart, so
+// that the 15 of them start on different banks.  With one b a thread (40 candidates, twice the reads; segments 320 bytes apart,
+// rows of the prefix sums 1280, which met on banks) the kernel took, with layers / gathered statistics: 4 levels 28.3 / 27.7
+// us, now 19.5 / 18.0; 8 35.9 / 34.0, 27 / 24; 16 51.4 / 49.7, 39.8 / 37.2; 64 139 / 137, 119 / 114; 256 508 / 509, 447 / 433.
+constexpr int kFitSeg = 18;
+constexpr int kFitSegs = 15;        // segments of the last couple
+constexpr int kFitGroup = kFitSeg / 2;   // couples kFitGroup*(g-1)+1 .. kFitGroup*g have g segments each
+constexpr int kFitPad = 272;        // rows are read up to index 14 * 18 + 17
+static_assert(kFitGroup * kFitSegs * (kFitSegs - 1) / 2 + 2 * kFitSegs <= kFitThreads - 32, "two b of 14 groups and the last two couples");
+
+// A neighbour's value inside a group of four lanes (quad permutation CTRL).
+template <int CTRL>
+__device__ __forceinline__ double quad_swap(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo));
+}
 
 // SRC: where the pooled weights come from.
 //   kFitPooled   k_fit_typemax and k_fit_pool have run
 //   kFitLayers   layer scope, at most kFitLayerPairs (node, layer) pairs a type: the workgroup does for its type what
 //                k_norm_finalize, k_fit_typemax and k_fit_pool do, and clears the histogram for the next fit.  Four launches
 //                of 3 to 5 us less, 8 us more here: 6.3 M entries in 10 tensors, K = 8, 16 levels 183 -> 177.5 us per round.
-//                Of this kernel's 52 us there: norms 4, pooling 4, the three running sums 6, pair costs 8, thirteen stages
-//                24, last stage, backtrack and tables 4.
+//                Of this kernel's 40 us there: norms 4, pooling 4, the three running sums 3, pair costs 5, thirteen stages
+//                20, last stage, backtrack and tables 4.
 //   kFitBuckets  bucket scope, at most kFitBucketPairs: pools what the last quantize passes gathered and derives the next scale
 template <int SRC>
 __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
-  __shared__ FitRow row[kGridPoints + 1];
-  __shared__ double D[2][kFitPad];
-  __shared__ double pbest[kFitThreads];   // first the per-bin terms of the prefix sums, then the segments' minima
-  __shared__ int pa[kFitThreads];         // ... and where they are taken
+  __shared__ __attribute__((aligned(16))) double D[2][kFitPad];
+  __shared__ __attribute__((aligned(16))) double P[3][kFitPad], gv[kFitPad];   // by grid index: sums over the bins below it, its value
+  __shared__ __attribute__((aligned(16))) double pbest[2 * kFitThreads - 64];   // the segments' minima for both b of their couple
+  __shared__ unsigned char pj[2 * kFitThreads];   // ... and where in the segment they are taken
   __shared__ float slev[kMaxPoints];
-  __shared__ unsigned char sarg[kFitLdsPoints * 256];   // back-pointers of the stages, when S is small enough
-  static_assert(3 * kGridPoints <= kFitThreads, "the per-bin terms share the segments' array");
-  double (*wd)[kGridPoints] = reinterpret_cast<double (*)[kGridPoints]>(pbest);   // W, W*mid, (W*mid)*mid per bin
-  double *rv = pbest;   // the last stage's candidates: after the stage loop
-  int *ri = pa;
-  __shared__ unsigned long long Ws[SRC == kFitPooled ? 1 : kGridPoints];
+  // back-pointers of the stages 2, 3, ..., when S is small enough; before the stages the pooled weights and the per-bin terms
+  __shared__ __attribute__((aligned(16))) unsigned char sarg[(kFitLdsPoints - 2) * 256];
+  unsigned long long *Ws = reinterpret_cast<unsigned long long *>(sarg);
+  double (*wd)[kFitPad + 16] = reinterpret_cast<double (*)[kFitPad + 16]>(sarg + 8 * kFitPad);   // W, W*mid, (W*mid)*mid per bin
+  static_assert(sizeof(sarg) >= 8 * kFitPad + 3 * 8 * (kFitPad + 16), "weights and terms share the back-pointers' space");
   __shared__ double stat[SRC == kFitPooled ? 1 : SRC == kFitLayers ? kFitLayerPairs : kFitBucketPairs];
   __shared__ float sinv[SRC == kFitLayers ? kFitLayerPairs : 1];
   __shared__ unsigned long long swgt[SRC == kFitLayers ? kFitLayerPairs : 1];
@@ -2103,144 +2120,180 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
     wd[0][j] = wj;
     wd[1][j] = wm;
     wd[2][j] = wm * mid;
-    row[j].g = (double)grid_value(j);
+    gv[j] = (double)grid_value(j);
   }
   for (int j = t; j < 2 * kFitPad; j += kFitThreads) D[0][j] = inf;   // both rows: index 0, index `last`, the padding
   __syncthreads();
-  // the three running sums, each by one thread of its own wave, bin after bin
-  if ((t & 63) == 0 && t < 3 * 64) {
-    const int f = t >> 6;
-    const double *src = wd[f];
-    double *dst = &row[0].p0 + f;   // p0, p1, p2 are the first three doubles of a row
-    // a chain of 257 dependent additions: their operands are read 16 at a time, one batch ahead
+  // the three running sums, bin after bin: a chain of 257 dependent additions; their operands are read 16 at a time, a batch
+  // ahead, into two sets of registers by turns.  Three lanes of one wave: an access to shared memory takes its time however
+  // few lanes make it (in three waves the sums took 4.1 us, in one 2.7).
+  if (t < 3) {
+    const double *src = wd[t];
+    double *dst = P[t];
     constexpr int N = 16;
-    double p = 0.0, cur[N], nxt[N];
+    double p = 0.0, x[N], y[N];
     dst[0] = 0.0;
 #pragma unroll
-    for (int q = 0; q < N; ++q) cur[q] = src[q];
+    for (int q = 0; q < N; ++q) x[q] = src[q];
 #pragma unroll 1
-    for (int j = 0; j < 256; j += N) {
+    for (int j = 0; j < 256; j += 2 * N) {
 #pragma unroll
-      for (int q = 0; q < N; ++q) nxt[q] = src[min(j + N + q, last)];
+      for (int q = 0; q < N; ++q) y[q] = src[j + N + q];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 0; q < N; ++q) {
-        p = p + cur[q];
-        dst[4 * (j + q + 1)] = p;
-      }
+      for (int q = 0; q < N; ++q) { p = p + x[q]; dst[j + q + 1] = p; }
 #pragma unroll
-      for (int q = 0; q < N; ++q) cur[q] = nxt[q];
+      for (int q = 0; q < N; ++q) x[q] = src[j + 2 * N + q];   // the last time: bin 256, then padding
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < N; ++q) { p = p + y[q]; dst[j + N + q + 1] = p; }
     }
-    dst[4 * kGridPoints] = p + cur[0];
-    if (f == 0) row[kGridPoints].g = 0.0;
+    dst[kGridPoints] = p + x[0];
   }
   __syncthreads();
-  if (row[kGridPoints].p0 == 0.0) return;   // no mass on the grid at all: the type keeps its levels
+  if (P[0][kGridPoints] == 0.0) return;   // no mass on the grid at all: the type keeps its levels
+  const auto row_at = [&](int j) { return FitRow{P[0][j], P[1][j], P[2][j], gv[j]}; };
   short *arg = a.dp_arg + a.dp_arg_off[mtype];
   const bool lds_arg = S <= kFitLdsPoints;   // candidates a are at most 254: a byte each, 255 for "none"
   if (S > 2) {
     // level 1 at grid index b: cost of the bins below g_b against the levels 0 and g_b
     for (int b = t; b < kGridPoints; b += kFitThreads)
-      D[1][b] = (b >= 1 && b <= last - (S - 2)) ? (row[b].g * row[b].p1 - row[b].p2) : inf;
-    // this thread's grid index b, segment and number of segments of b (b = 0: no work): the indices
-    // 40(g-1)+1 .. 40g have g segments each
-    int b = 0, seg = 0, nseg = 0;
+      D[1][b] = (b >= 1 && b <= last - (S - 2)) ? (gv[b] * P[1][b] - P[2][b]) : inf;
+    // this thread's couple (0: no work) and segment
+    int couple = 0, seg = 0;
     {
-      int base = 0;
-      for (int g = 1; (g - 1) * kFitSeg + 1 <= last - 1; ++g) {
-        const int r0 = (g - 1) * kFitSeg + 1, r1 = min(g * kFitSeg, last - 1);
-        const int cnt = (r1 - r0 + 1) * g;
-        if (t >= base && t < base + cnt) {
-          const int o = t - base;
-          b = r0 + o / g;
-          seg = o - (o / g) * g;
-          nseg = g;
-        }
-        base += cnt;
-      }
+      int g = 1, base = 0;
+      while (base + kFitGroup * g <= t) { base += kFitGroup * g; ++g; }
+      const int o = t - base, w = (int)(((float)o + 0.5f) * (1.0f / (float)g));   // o / g: o < 9 * 15
+      const int q = kFitGroup * (g - 1) + 1 + w;
+      if (q <= 128) { couple = q; seg = o - w * g; }
     }
     const int a0 = seg * kFitSeg;
-    double cost[kFitSeg];
+    double cost[2][kFitSeg];
     {
-      const FitRow rb = row[b];
+      const int b1 = max(2 * couple, 1);
+      const FitRow r0 = row_at(b1 - 1), r1 = row_at(b1);
+      FitRow nx = row_at(a0);
 #pragma unroll
       for (int j = 0; j < kFitSeg; ++j) {
         const int aa = a0 + j;
-        const FitRow ra = row[min(aa, last)];
-        cost[j] = (aa <= b - 1) ? fit_cost(ra, rb) : inf;   // +infinity never wins a comparison below
-        if ((j & 1) == 1) __builtin_amdgcn_sched_barrier(0);   // two pairs at a time: 40 rows in flight would not fit the registers
+        const FitRow ra = nx;
+        if (j + 1 < kFitSeg) nx = row_at(aa + 1);   // a row ahead; up to index 269, beyond the grid: not used
+        asm volatile("" : : : "memory");            // all rows in flight would not fit the registers
+        cost[0][j] = fit_cost(ra, r0);
+        cost[1][j] = fit_cost(ra, r1);
+        if (!(aa < b1 - 1)) cost[0][j] = inf;       // +infinity never wins a comparison below
+        if (!(aa < b1 && b1 < last)) cost[1][j] = inf;   // (b = 256 is no place for an interior level)
+        asm volatile("" : "+v"(cost[0][j]), "+v"(cost[1][j]));
       }
     }
+    // the second step's index b, and which of its segments: four threads per b, four segments each
+    const int cb = 1 + (t >> 2), cq = (cb + 1) >> 1, cg = (cq + kFitGroup - 1) / kFitGroup;   // cb's couple, its segments
+    const int cs = 4 * (t & 3), cn = cb < last ? cg : 0;
+    const int cfirst = kFitGroup * (cg * (cg - 1) / 2) + (cq - 1 - kFitGroup * (cg - 1)) * cg + cs;   // the thread of this one's first
     __syncthreads();
     for (int s = 2; s <= S - 2; ++s) {
       // D of the previous stage is +infinity wherever level s-1 cannot sit (in particular below index s-1), so the
       // candidates need no range test: min over a of D[a] + cost(a, b), the smallest a on equal cost
       const double *Dp = D[(s - 1) & 1] + a0;
       double *Dc = D[s & 1];
-      double best = inf;
-      int bj = 0;
+      if (couple != 0) {
+        double best0 = inf, best1 = inf;
+        int j0 = 0, j1 = 0;
+        constexpr int N = 6;   // values of D that are read together, a batch ahead
+        double d[2][N];
 #pragma unroll
-      for (int j = 0; j < kFitSeg; ++j) {
-        const double c = Dp[j] + cost[j];   // never a NaN: costs and D are finite or +infinity
-        bj = (c < best) ? j : bj;
-        best = fmin(best, c);
-      }
-      pbest[t] = best;
-      pa[t] = a0 + bj;
-      __syncthreads();
-      if (b != 0 && seg == 0) {
-        double ov[kFitSegs];
+        for (int q = 0; q < N; ++q) d[0][q] = Dp[q];
 #pragma unroll
-        for (int q = 1; q < kFitSegs; ++q) ov[q] = q < nseg ? pbest[t + q] : inf;
-        int won = t;
+        for (int j = 0; j < kFitSeg; ++j) {
+          if (j % N == 0) {
+            asm volatile("" : : : "memory");
+            if (j + N < kFitSeg) {
 #pragma unroll
-        for (int q = 1; q < kFitSegs; ++q)   // later segments hold larger a: they win only with a smaller cost
-          if (ov[q] < best) { best = ov[q]; won = t + q; }
-        const int besta = pa[won];
-        if (!(b >= s && b <= last - (S - 1 - s))) best = inf;   // level s cannot sit here
-        Dc[b] = best;
-        if (lds_arg) sarg[s * 256 + b] = (unsigned char)(best < inf ? besta : 255);
-        else arg[(size_t)s * kGridPoints + b] = (short)(best < inf ? besta : -1);
-      }
-      __syncthreads();
-    }
-    // last level (1.0) at grid index `last`: one candidate per thread, then the smallest cost (ties: smallest index)
-    {
-      const double *Dp = D[(S - 2) & 1];
-      double c = inf;
-      if (t < kThreads && t >= S - 2 && t <= last - 1) {
-        const FitRow ra = row[t], rb = row[last];
-        c = Dp[t] + fit_cost(ra, rb);
-      }
-      if (t < kThreads) {
-        rv[t] = c;
-        ri[t] = (c < inf) ? t : 0x7FFFFFFF;
-      }
-      __syncthreads();
-      for (int h = kThreads / 2; h >= 1; h >>= 1) {
-        if (t < h) {
-          const double ov = rv[t + h];
-          const int oi = ri[t + h];
-          if (ov < rv[t] || (ov == rv[t] && oi < ri[t])) { rv[t] = ov; ri[t] = oi; }
+              for (int q = 0; q < N; ++q) d[(j / N + 1) & 1][q] = Dp[j + N + q];
+            }
+            asm volatile("" : : : "memory");
+          }
+          const double c0 = d[(j / N) & 1][j % N] + cost[0][j], c1 = d[(j / N) & 1][j % N] + cost[1][j];
+          // never a NaN: costs and D are finite or +infinity
+          j0 = (c0 < best0) ? j : j0;
+          best0 = fmin(best0, c0);
+          j1 = (c1 < best1) ? j : j1;
+          best1 = fmin(best1, c1);
+          asm volatile("" : "+v"(j0), "+v"(j1));   // left to itself the compiler keeps all comparisons for later
         }
-        __syncthreads();
+        pbest[2 * t] = best0;
+        pbest[2 * t + 1] = best1;
+        *reinterpret_cast<unsigned short *>(&pj[2 * t]) = (unsigned short)(j0 | j1 << 8);
       }
+      __syncthreads();
+      {
+        // a chain of dependent instructions: short rather than few
+        double ov[4];
+        int oa[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const bool have = cs + q < cn;
+          const int e = have ? 2 * (cfirst + q) + 1 - (cb & 1) : 0;
+          ov[q] = pbest[e];
+          oa[q] = (cs + q) * kFitSeg + pj[e];
+          if (!have) ov[q] = inf;
+        }
+        // later segments hold larger a: they win only with a smaller cost
+        if (ov[1] < ov[0]) { ov[0] = ov[1]; oa[0] = oa[1]; }
+        if (ov[3] < ov[2]) { ov[2] = ov[3]; oa[2] = oa[3]; }
+        if (ov[2] < ov[0]) { ov[0] = ov[2]; oa[0] = oa[2]; }
+        double best = ov[0], o = quad_swap<0xB1>(best);   // and so between the four threads
+        int at = oa[0], ob = __builtin_amdgcn_mov_dpp(at, 0xB1, 0xF, 0xF, true);
+        if (o < best) { best = o; at = ob; }
+        o = quad_swap<0x4E>(best);
+        ob = __builtin_amdgcn_mov_dpp(at, 0x4E, 0xF, 0xF, true);
+        if (o < best) { best = o; at = ob; }
+        if ((t & 3) == 0 && cb < last) {
+          if (!(cb >= s && cb <= last - (S - 1 - s))) best = inf;   // level s cannot sit here
+          Dc[cb] = best;
+          if (lds_arg) sarg[(s - 2) * 256 + cb] = (unsigned char)(best < inf ? at : 255);
+          else arg[(size_t)s * kGridPoints + cb] = (short)(best < inf ? at : -1);
+        }
+      }
+      __syncthreads();
     }
   }
-  if (t == 0) {
-    slev[0] = 0.0f;
-    slev[S - 1] = 1.0f;
+  if (t < 64) {   // one wave: the last level (1.0) sits at grid index `last`
+    int b = 0;
     if (S > 2) {
-      int b = ri[0];
+      // the smallest cost over its candidates (ties: smallest index), four neighbours a lane
+      const double *Dp = D[(S - 2) & 1];
+      const FitRow rb = row_at(last);
+      double best = inf;
+      b = 0x7FFFFFFF;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int aa = 4 * t + q;
+        if (aa >= S - 2 && aa <= last - 1) {
+          const double c = Dp[aa] + fit_cost(row_at(aa), rb);
+          if (c < best) { best = c; b = aa; }
+        }
+      }
+#pragma unroll
+      for (int h = 1; h < 64; h *= 2) {
+        const double o = __shfl_xor(best, h, 64);
+        const int oi = __shfl_xor(b, h, 64);
+        if (o < best || (o == best && oi < b)) { best = o; b = oi; }
+      }
+    }
+    if (t == 0) {
+      slev[0] = 0.0f;
+      slev[S - 1] = 1.0f;
       for (int s = S - 2; s >= 1; --s) {
         b = max(1, min(b, last - 1));   // cannot trigger for finite costs; keeps a corrupted table in bounds
         slev[s] = grid_value(b);
-        if (s >= 2) b = lds_arg ? (int)sarg[s * 256 + b] : (int)arg[(size_t)s * kGridPoints + b];
+        if (s >= 2) b = lds_arg ? (int)sarg[(s - 2) * 256 + b] : (int)arg[(size_t)s * kGridPoints + b];
       }
     }
-    for (int j = 0; j < S; ++j) a.lev[(size_t)mtype * kMaxPoints + j] = slev[j];
   }
   __syncthreads();
+  for (int j = t; j < S; j += kFitThreads) a.lev[(size_t)mtype * kMaxPoints + j] = slev[j];
   build_tables(a, mtype, S, slev);
 }
 
