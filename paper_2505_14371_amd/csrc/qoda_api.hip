@@ -40,7 +40,7 @@ struct qoda_ctx {
   int *d_type_points = nullptr;
   double *d_partial = nullptr, *d_dpartial = nullptr, *d_sumsq = nullptr, *d_delta = nullptr;
   float *d_norm = nullptr, *d_inv = nullptr, *d_lev = nullptr, *d_rgap = nullptr, *d_eta = nullptr;
-  unsigned char *d_lut = nullptr;
+  float4 *d_bins = nullptr;
   unsigned int *d_hist = nullptr, *d_hist_last = nullptr, *d_status = nullptr;
   int *d_type_first = nullptr;   // the layers of every type
   int3 *d_type_layers = nullptr;
@@ -255,7 +255,7 @@ Dev base_args(const qoda_ctx *c) {
   a.readers = c->d_readers;
   a.exch = c->d_exch; a.finished = c->d_finished; a.tries = c->tries;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
-  a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.walk = c->d_walk;
+  a.lev = c->d_lev; a.rgap = c->d_rgap; a.bins = c->d_bins; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
   a.hist = c->d_hist; a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
   a.dp_arg = c->d_dp_arg; a.dp_arg_off = c->d_dp_arg_off;
@@ -294,7 +294,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_runs[0], c->d_runs[1], c->d_runs[2], c->d_runs[3], c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
-                  c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
+                  c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_bins, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
                   c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
                   c->d_type_first, c->d_type_layers};
   for (void *p : ptrs)
@@ -310,9 +310,10 @@ void free_all(qoda_ctx *c) {
 // Which runs of tiles a launch over `nnodes` nodes takes under bucket scope.  A run's workgroup sets up its tables and, where
 // it gathers statistics, clears and flushes them, for about a quarter to a half of what a tile costs it; against that stands
 // a device that is not full, or is full of workgroups of unequal length.
-//   kRunsQuantize  us of the quantize pass with runs of 1 / 2 / 4 / 8, S = 16: 768 tiles 35 / 37 / 56 / 98; 1024 36 / 40 / 59 / 98;
-//                  1280 55 / 44 / 61 / 98; 3096 87 / 81 / 79 / 112; 8192 194 / 176 / 189 / 201; 10000 239 / 210 / 208 / 251;
-//                  12288 287 / 255 / 245 / 269; 24 k 541 / 469 / 461 / 461; 65 k 1441 / 1255 / 1222 / 1205; 90 k 1964 / 1725 / 1679 / 1665
+//   kRunsQuantize  us of a quantize call with runs of 1 / 2 / 4, S = 16, K = 8: 768 tiles 33 / 39 / 56; 1024 37 / 39 / 56; 1280 50 / 45 /
+//                  62; 2048 63 / 53 / 63; 3096 92 / 81 / 82; 8192 220 / 179 / 170; 10000 252 / 213 / 207; 12288 315 / 255 / 247; 24 k 596 / 502
+//                  / 485; 65 k 1518 / 1241 / 1197; 90 k 2011 / 1764 / 1701 (runs of 8 would be 1 % faster at 90 k, and keep 4 KiB more
+//                  of shared memory, which the pass does not have: see k_quantize_b)
 //   kRunsFit       us of the fit from vectors (two passes over them): 512 tiles 85 / 117 / 185 / 323; 2048 138 / 143 / 212 / 365;
 //                  3096 167 / 166 / - / 369; 10000 403 / 380 / - / 449; 40 k 1423 / 1273 / 1280 / 1362; 75 k 2607 / 2335 / 2315 / 2320
 //   kRunsCount     us of qoda_index_counts, S = 8 (128), with 1 / 2 / 8: 512 tiles 34 (41) / 32 (36) / 40 (43); 1024 40 (55) / 35 (42)
@@ -322,7 +323,7 @@ void use_runs(const qoda_ctx *c, Dev &a, RunUse use, int nnodes) {
   if (c->scope != kScopeBucket) return;   // the long runs
   const long long n = (long long)nnodes * c->G;
   int i = 3;
-  if (use == kRunsQuantize) i = n <= 1024 ? 0 : n <= 10000 ? 1 : n <= 65536 ? 2 : 3;
+  if (use == kRunsQuantize) i = n <= 1024 ? 0 : n <= 10000 ? 1 : 2;   // at most kQuantRun tiles
   if (use == kRunsFit) i = n <= 2048 ? 0 : n <= 65536 ? 1 : 3;
   if (use == kRunsCount) i = n <= 1024 ? 1 : 3;
   a.stiles = c->d_runs[i];
@@ -486,7 +487,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   if (c->scope == kScopeBucket) {
     if (chunks <= 2048) runs[0] = list_runs(1);
     runs[1] = list_runs(2);
-    if (chunks <= 65536) runs[2] = list_runs(4);
+    runs[2] = list_runs(kQuantRun);
   }
   runs[3] = list_runs(kSuperTile);
   std::vector<int> empty;
@@ -545,7 +546,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_lev, (size_t)c->M * kMaxPoints));
   A(dev_alloc(&c->d_rgap, (size_t)c->M * kMaxPoints));
   A(dev_alloc(&c->d_eta, 3));
-  A(dev_alloc(&c->d_lut, (size_t)c->M * kLutSize));
+  A(dev_alloc(&c->d_bins, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_status, 2));   // the status word, and a word no kernel result depends on
   A(dev_alloc(&c->d_pooled, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_type_exp, (size_t)c->M));

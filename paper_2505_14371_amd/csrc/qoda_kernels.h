@@ -9,6 +9,7 @@ namespace qoda {
 constexpr int kBlockCoords = 256;    // coordinates per packed block (one wave64 step of 128-bit loads)
 constexpr int kChunkCoords = 16384;  // coordinates per workgroup tile (64 blocks) = one reduction chunk
 constexpr int kSuperTile = 8;        // the most tiles of a run (passes that keep histograms or tables per run)
+constexpr int kQuantRun = 4;         // ... of the quantize pass under bucket scope
 constexpr int kTaperWorkgroups = 2048;   // workgroups of 256 threads the device holds at once (256 CUs x 8)
 constexpr int kDecodeWaves = 2;       // waves (= octets) per workgroup in the decode pass: 1, 2 or 4
 constexpr int kThreads = 256;        // workgroup size everywhere: 4 waves, 256 reduction slots
@@ -21,7 +22,6 @@ constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
 constexpr int kGridPoints = 257;     // normalised grid g_0 = 2^-32 ... g_256 = 1
 constexpr int kMaxPoints = 256;
-constexpr int kLutSize = 1024;       // level-search table indexed by bits(u) >> 20 (u in [0,1] -> 0..1016)
 constexpr int kTypeSkip = 0x7fffffff;
 constexpr int kBucketCoords = 128;   // coordinates per bucket when every bucket carries its own norm
 
@@ -70,8 +70,8 @@ struct Dev {
   double *delta;      // [K]
   float *lev;         // [M*256]
   float *rgap;        // [M*256]
-  unsigned char *lut;  // [M*1024] level-search table: tau at the lower edge of the bin bits(u) >> 20
-  int *walk;          // [M] some interior level of the type lies inside a bin of lut
+  float4 *bins;       // [M*257] level-search table by grid bin: {l_tau, 1/gap, l_tau+1, tau} at the bin's lower edge
+  int *walk;          // [M] some interior level of the type lies inside a bin, or not above the first one
   unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit
   unsigned int *hist_last;     // [K*L*2048] layer and vector scope: the histogram of the last fit
   const int *type_first;       // [M+1] the layers of type m are type_layers[type_first[m] .. type_first[m+1]-1]

@@ -60,10 +60,14 @@ __device__ float rcp_floor(float x) {
   return r;
 }
 
+// x minus one unit of the last place where m is negative.
+__device__ __forceinline__ float step_down(float x, int m) { return u2f(f2u(x) + (unsigned int)(m >> 31)); }
+
 // The same two functions for the per-bucket norms, where they run once per 128 coordinates and their cost shows:
 // straight-line code for arguments in a comfortable range (sums of squares in [2^-200, 2^200]), the general
-// routines otherwise.  Both return exactly what sqrt_floor / rcp_floor return (the definitions are by exact
-// comparisons, so any way of finding the largest float that passes them gives the same bits).
+// routines otherwise.  Both return exactly what sqrt_floor / rcp_floor return: the definitions are by exact
+// comparisons, and a value less than one unit of the last place off needs only one of them.  (Candidates from two units
+// above, stepped down by three comparisons in fp64 each, and a correctly rounded root before them, took twice as long.)
 __device__ __forceinline__ void norm_and_inverse(double s, float &n_out, float &r_out) {
   const long long bits = __double_as_longlong(s);
   const int e = (int)((bits >> 52) & 0x7FF) - 1023;
@@ -72,27 +76,19 @@ __device__ __forceinline__ void norm_and_inverse(double s, float &n_out, float &
     r_out = rcp_floor(n_out);
     return;
   }
-  // s = sp * 4^k with sp in [1, 4): root in single precision, then the candidates around it are tested exactly
+  // s = sp * 4^k with sp in [1, 4)
   const int k = e >> 1;
   const double sp = __longlong_as_double(bits - ((long long)(2 * k) << 52));
-  const float r0 = __builtin_sqrtf((float)sp);   // within one unit of the last place of the true root of sp
-  float n = u2f(f2u(r0) + 1u);
-#pragma unroll
-  for (int it = 0; it < 3; ++it) {
-    const double nd = (double)n;
-    if (nd * nd > sp) n = u2f(f2u(n) - 1u);
-  }
-  n = u2f(f2u(n) + ((unsigned int)k << 23));   // times 2^k: exact, the result is a normal number
-  // reciprocal: hardware estimate, then the same exact test on the candidates around it
-  const float q0 = __builtin_amdgcn_rcpf(n);
-  float r = u2f(f2u(q0) + 1u);
+  const float sf = (float)sp;                       // 1/4 unit of the root
+  const float y = __builtin_amdgcn_rsqf(sf);        // 1/sqrt(sp) to a few units: one Newton step leaves rounding only
+  const float n0 = sf * y;
+  float n = __builtin_fmaf(__builtin_fmaf(-n0, n0, sf), 0.5f * y, n0);   // within 3/4 unit: it or the float below it
   const double nd = (double)n;
-#pragma unroll
-  for (int it = 0; it < 3; ++it) {
-    if (nd * (double)r > 1.0) r = u2f(f2u(r) - 1u);
-  }
-  n_out = n;
-  r_out = r;
+  n = step_down(n, (int)(__double_as_longlong(__builtin_fma(-nd, nd, sp)) >> 32));   // the fused operation has the exact sign
+  const float q = __builtin_fmaf(__builtin_fmaf(-n, y, 1.0f), y, y);     // y is within a few units of 1/n too: 1/2 unit
+  const float r = step_down(q, (int)f2u(__builtin_fmaf(-n, q, 1.0f)));
+  n_out = u2f(f2u(n) + ((unsigned int)k << 23));    // times 2^k, 2^-k: exact, the results are normal numbers
+  r_out = u2f(f2u(r) - ((unsigned int)k << 23));
 }
 
 // Fixed halving tree over the 256 slots: p[i] += p[i+h], h = 128 .. 1.  The two cross-wave steps are one pass
@@ -139,18 +135,14 @@ __device__ __forceinline__ double weight_of(double s, int kind) { return kind ==
 // largest magnitude from the running maximum of magnitude bit patterns: an infinity or a NaN pattern gives +infinity
 __device__ __forceinline__ float magnitude_from_bits(unsigned int mb) { return u2f(mb > 0x7F7FFFFFu ? 0x7F800000u : mb); }
 
-// rcp_floor for a norm in a comfortable range by straight-line code (estimate, then the exact test on the
-// candidates around it), the general routine otherwise: the same bits either way.
+// rcp_floor for a norm in a comfortable range by straight-line code (as in norm_and_inverse), the general routine
+// otherwise: the same bits either way.
 __device__ __forceinline__ float inverse_of(float n) {
   const int e = (int)((f2u(n) >> 23) & 0xFF) - 127;
   if (e < -100 || e > 100) return rcp_floor(n);
-  float r = u2f(f2u(__builtin_amdgcn_rcpf(n)) + 1u);
-  const double nd = (double)n;
-#pragma unroll
-  for (int it = 0; it < 3; ++it) {
-    if (nd * (double)r > 1.0) r = u2f(f2u(r) - 1u);
-  }
-  return r;
+  const float y = __builtin_amdgcn_rcpf(n);
+  const float q = __builtin_fmaf(__builtin_fmaf(-n, y, 1.0f), y, y);   // within 1/2 unit
+  return step_down(q, (int)f2u(__builtin_fmaf(-n, q, 1.0f)));
 }
 
 // Philox4x32-10 (Salmon et al., SC'11).
@@ -170,6 +162,51 @@ __device__ __forceinline__ void philox4x32_10(unsigned int c0, unsigned int c1, 
     c0 = n0; c1 = n1; c2 = n2; c3 = n3;
   }
   out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
+}
+
+// Table entry of a value u in [0, 1], by its grid bin (bins: kGridPoints entries in shared memory, see build_tables): one
+// 128-bit read gives {l_tau, 1/gap, l_tau+1, tau}, tau being that of the bin's lower edge.  (A table of tau by bin and one of
+// {l_tau, 1/gap, l_tau+1} by tau were two reads one after the other.)
+__device__ __forceinline__ float4 bin_entry(const float4 *bins, float u) {
+  return bins[__builtin_elementwise_sub_sat(f2u(u) >> 20, (unsigned int)kGridBase)];
+}
+
+// The grid bins' entries of a type into shared memory; where a lane may have to walk on from the entry of its bin (walk), also
+// the entries by tau, the last one with the upper neighbour +infinity, which stops every walk.
+__device__ __forceinline__ void load_tables(const Dev &a, int type, int S, int walk, float4 *bins, float4 *tab) {
+  const float4 *src = a.bins + (size_t)type * kGridPoints;
+  for (int j = threadIdx.x; j < kGridPoints; j += (int)blockDim.x) bins[j] = src[j];
+  if (walk) {
+    const float *lev = a.lev + (size_t)type * kMaxPoints, *rg = a.rgap + (size_t)type * kMaxPoints;
+    for (int j = threadIdx.x; j < S; j += (int)blockDim.x)
+      tab[j] = make_float4(lev[j], j + 1 < S ? rg[j] : 0.0f, j + 1 < S ? lev[j + 1] : __builtin_inff(), u2f((unsigned int)j));
+  }
+}
+
+// A value of lane bb of the lane's row of 16 lanes.
+template <int BB>
+__device__ __forceinline__ unsigned int row_lane(unsigned int v) {
+  return (unsigned int)__builtin_amdgcn_mov_dpp((int)v, 0x150 + BB, 0xF, 0xF, true);   // row_newbcast
+}
+__device__ __forceinline__ unsigned int row_value(unsigned int v, int bb) {   // bb in 0..7, known where this is unrolled
+  switch (bb) {
+    case 0: return row_lane<0>(v);
+    case 1: return row_lane<1>(v);
+    case 2: return row_lane<2>(v);
+    case 3: return row_lane<3>(v);
+    case 4: return row_lane<4>(v);
+    case 5: return row_lane<5>(v);
+    case 6: return row_lane<6>(v);
+    default: return row_lane<7>(v);
+  }
+}
+
+// A neighbour's value inside a group of four lanes (quad permutation CTRL).
+template <int CTRL>
+__device__ __forceinline__ double quad_swap(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo));
 }
 
 // Loads through pointers read from device tables: tell the compiler they point to global memory.
@@ -437,28 +474,25 @@ __global__ void __launch_bounds__(kThreads) k_norm_vector(Dev a) {
 // the block inside its pair.
 template <int C1, bool PREV>
 __device__ __forceinline__ void quantize_block(const float (&x)[4], const unsigned int (&o)[4], int half, float inv,
-                                               float norm, const unsigned char *lut, const float4 *tab,
+                                               float norm, const float4 *bins, const float4 *tab, bool walk,
                                                const float *tprev, unsigned int (&D)[C1], const unsigned int (&Dp)[C1],
                                                float &acc) {
   float u[4];
-  int tau[4];
-  float4 lv[4];                    // {l_tau, 1/gap, l_tau+1, -}; entry S-1 = {1, 0, +inf, -}
+  float4 lv[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     // min(|v| * inv, 1): the product is never negative or NaN for finite input, so the [0, 1] clamp of the
     // multiply instruction is the same thing
     u[j] = __builtin_amdgcn_fmed3f(fabsf(x[j]) * inv, 0.0f, 1.0f);
-    tau[j] = lut[f2u(u[j]) >> 20];
+    lv[j] = bin_entry(bins, u[j]);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) lv[j] = tab[tau[j]];
-  // The table gave tau at the lower edge of u's bin; a level inside the bin (never the case for fitted levels,
-  // which sit on bin edges) makes some lanes walk on.  At u = 1 the walk ends on the entry of the last level
-  // itself (xi = 0, never rounds up), which yields the same code and value as tau = S-2 rounding up.
-  if (__ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
+  // A level inside a bin (walk; never the case for fitted levels, which sit on bin edges) makes some lanes walk on from the
+  // entry of its lower edge.  At u = 1 the walk ends on the entry of the last level itself (xi = 0, never rounds up), which
+  // yields the same code and value as tau = S-2 rounding up: there xi is 1 - 2^-23 at least, above every 16-bit draw.
+  if (walk && __ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      while (lv[j].z <= u[j]) { ++tau[j]; lv[j] = tab[tau[j]]; }
+      while (lv[j].z <= u[j]) lv[j] = tab[f2u(lv[j].w) + 1u];
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -468,7 +502,7 @@ __device__ __forceinline__ void quantize_block(const float (&x)[4], const unsign
     // (w16 + 0.5) < xi * 65536  <=>  w16 < xi * 65536 - 0.5 : the scaling by 2^16 is exact, and the subtraction
     // is exact whenever its result is not negative, so one fused operation decides the same.
     const bool up = (float)w16 < __builtin_fmaf(xi, 65536.0f, -0.5f);
-    const unsigned int h = (unsigned int)tau[j] + (up ? 1u : 0u);
+    const unsigned int h = f2u(lv[j].w) + (up ? 1u : 0u);
     // norm * l_h, the value the decoder will rebuild (the +inf of the last entry is never selected: there xi = 0)
     const float mag = norm * (up ? lv[j].z : lv[j].x);
     const float cur = __builtin_copysignf(mag, x[j]);
@@ -495,9 +529,8 @@ __device__ __forceinline__ void load_block_fast(const float *__restrict__ v, lon
 template <int C1, bool FAST, bool PREV>
 __device__ __forceinline__ void quantize_octet(const Dev &a, const LayerMeta &m, int l, int k, long long O,
                                                const float *__restrict__ v, unsigned char *body,
-                                               const unsigned char *prevbody, float inv, float norm,
-                                               const unsigned char *lut, const float4 *tab, const float *tprev, int i,
-                                               float &acc) {
+                                               const unsigned char *prevbody, float inv, float norm, const float4 *bins,
+                                               const float4 *tab, bool walk, const float *tprev, int i, float &acc) {
   const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
   unsigned int D[C1], Dp[C1];
 #pragma unroll
@@ -529,9 +562,9 @@ __device__ __forceinline__ void quantize_octet(const Dev &a, const LayerMeta &m,
       }
       unsigned int o[4];
       philox4x32_10((unsigned int)((B0 >> 1) * 64 + i), (unsigned int)l, a.round, (unsigned int)k, k0, k1, o);
-      quantize_block<C1, PREV>(x0, o, 0, inv, norm, lut, tab, tprev, D, Dp, acc);
+      quantize_block<C1, PREV>(x0, o, 0, inv, norm, bins, tab, walk, tprev, D, Dp, acc);
       // a block past the end of the layer is all padding: +0 inputs give code 0 and add nothing, as required
-      quantize_block<C1, PREV>(x1, o, 1, inv, norm, lut, tab, tprev, D, Dp, acc);
+      quantize_block<C1, PREV>(x1, o, 1, inv, norm, bins, tab, walk, tprev, D, Dp, acc);
     }
     if (PREV) shift_out_pair<C1>(Dp);
   }
@@ -540,7 +573,7 @@ __device__ __forceinline__ void quantize_octet(const Dev &a, const LayerMeta &m,
 
 template <int C1, bool PREV>
 __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, int l, int k, int chunk,
-                                              const unsigned char *lut, const float4 *tab, const float *tprev,
+                                              const float4 *bins, const float4 *tab, bool walk, const float *tprev,
                                               double *red) {
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -557,9 +590,9 @@ __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, 
     const long long O = (long long)chunk * 8 + w * 2 + oo;   // octet index inside the layer
     if (O >= noct) break;
     if ((O + 1) * 2048 <= m.d)
-      quantize_octet<C1, true, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, lut, tab, tprev, i, acc);
+      quantize_octet<C1, true, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, bins, tab, walk, tprev, i, acc);
     else
-      quantize_octet<C1, false, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, lut, tab, tprev, i, acc);
+      quantize_octet<C1, false, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, bins, tab, walk, tprev, i, acc);
   }
   const double total = block_tree((double)acc, red);
   if (t == 0) a.dpartial[(size_t)kr * a.G + blockIdx.x] = total;
@@ -567,9 +600,9 @@ __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, 
 
 template <int C1, bool PREV>
 __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
-  __shared__ unsigned char lut[kLutSize];
-  __shared__ float4 tab[kMaxPoints];
-  __shared__ float tprev[2 * kMaxPoints];   // previous message's decode table indexed by code = sign | h << 1
+  __shared__ float4 bins[kGridPoints];
+  __shared__ float4 tab[1 << (C1 - 1)];
+  __shared__ float tprev[1 << C1];   // previous message's decode table indexed by code = sign | h << 1
   __shared__ double red[kThreads];
   const int2 tile = a.tiles[blockIdx.x];
   const int l = tile.x;
@@ -578,16 +611,11 @@ __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
   if (m.planes != C1) return;   // layers of another code width are served by another instantiation
   const int t = threadIdx.x;
   const float *lev = a.lev + (size_t)m.type * kMaxPoints;
-  const float *rg = a.rgap + (size_t)m.type * kMaxPoints;
-  reinterpret_cast<unsigned int *>(lut)[t] = reinterpret_cast<const unsigned int *>(a.lut + (size_t)m.type * kLutSize)[t];
   const int kr = k - a.row0;
   const float norm = a.norm[(size_t)kr * a.L + l];
   const unsigned char *prevmsg = (a.prev != nullptr) ? a.prev[kr] : nullptr;
-  if (t < m.S) {
-    const float lj = lev[t];
-    const float ln = (t + 1 < m.S) ? lev[t + 1] : __builtin_inff();   // the last entry stops every walk
-    tab[t] = make_float4(lj, (t + 1 < m.S) ? rg[t] : 0.0f, ln, 0.0f);
-  }
+  const bool walk = a.walk[m.type] != 0;
+  load_tables(a, m.type, m.S, walk, bins, tab);
   if (tile.y == 0) {   // message header of this layer: {norm, levels[S]} (Sec. 3.2: the norm in C_q = 32 bits)
     float *h = reinterpret_cast<float *>(a.msg[kr] + m.hdr_off);
     for (int j = t; j <= m.S; j += kThreads) h[j] = (j == 0) ? norm : lev[j - 1];
@@ -602,7 +630,7 @@ __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
     tprev[c] = pv;
   }
   __syncthreads();
-  quantize_tile<C1, PREV>(a, m, l, k, tile.y, lut, tab, tprev, red);
+  quantize_tile<C1, PREV>(a, m, l, k, tile.y, bins, tab, walk, tprev, red);
 }
 
 // ------------------------------------------------------------------------------------------------ octets in registers
@@ -649,19 +677,17 @@ __device__ __forceinline__ void pin_block(float *x) {
 // distance 0).  A block's four differences to the previous message (up to a sign that their square does not see) are
 // given to done(bb, diff) as soon as they are known; it may put new values into the block's place in x.  pairs: how many
 // of the four pairs of blocks to work on (the same for the wave).
-// Tables: lut as in build_tables; tprev[code] = value the previous message's code stands for.
-//   WALK = false, layer norms    tab[tau] = {l_tau, 1/gap, norm * l_tau, norm * l_tau+1}: the decoder's product, taken once
-//                                per table entry
-//   WALK = true, or bucket norms tab[tau] = {l_tau, 1/gap, l_tau+1, -}
-// WALK: some level of the type lies inside a bin of lut, so a lane may have to step on from the entry that lut names.
+// Tables: bins and tab as in load_tables; tprev[code] = value the previous message's code stands for.
+// WALK: some level of the type lies inside a grid bin, so a lane may have to step on from the entry of its bin.
 // Fitted levels sit on bin edges: then tau at the lower edge is tau.  (At u = 1 the walk ends on the entry of the last
 // level, xi = 0; without it tau = S-2 and xi = 1 - 2^-23 at least, above every 16-bit draw: the same code.)
-// inv, norm, pnorm: one value (layer norms), or per block (bucket norms; entry bb).
+// sc: one set of scales (layer norms), or one per block (bucket norms; lane bb of the lane's row holds block bb's).
+struct Scales { float inv, norm, pnorm; };
+
 template <int C1, bool PREV, bool WALK, bool BUCKET, class Hist, class Done>
 __device__ __forceinline__ void quantize_regs(float (&x)[32], unsigned int c0, unsigned int l, unsigned int round,
-                                               unsigned int k, unsigned int k0, unsigned int k1, const float *inv,
-                                               const float *norm, const float *pnorm, const unsigned char *lut,
-                                               const float4 *tab, const float *tprev, unsigned int (&D)[C1],
+                                               unsigned int k, unsigned int k0, unsigned int k1, Scales sc,
+                                               const float4 *bins, const float4 *tab, const float *tprev, unsigned int (&D)[C1],
                                                const unsigned int (&Dp)[C1], Hist &&hist, Done &&done, int pairs = 4) {
 #pragma unroll
   for (int pp = 0; pp < 4; ++pp) {   // pairs of blocks: one generator call serves 8 coordinates of a lane
@@ -675,28 +701,26 @@ __device__ __forceinline__ void quantize_regs(float (&x)[32], unsigned int c0, u
       const int bb = 2 * pp + half;
       float *xb = &x[4 * bb];
       pin_block(xb);
-      const float bi = inv[BUCKET ? bb : 0];
+      const float bi = BUCKET ? u2f(row_value(f2u(sc.inv), bb)) : sc.inv;
       float u[4], mag[4];
       unsigned int h[4];
-      int tau[4];
       float4 lv[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         // min(|v| * inv, 1): the product is never negative or NaN for finite input, so the [0, 1] clamp of the
         // multiply instruction is the same thing
         u[j] = __builtin_amdgcn_fmed3f(fabsf(xb[j]) * bi, 0.0f, 1.0f);
-        tau[j] = lut[f2u(u[j]) >> 20];
+        lv[j] = bin_entry(bins, u[j]);
       }
       hist(xb, u, bb);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) lv[j] = tab[tau[j]];
       if (WALK) {
         if (__ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            while (lv[j].z <= u[j]) { ++tau[j]; lv[j] = tab[tau[j]]; }
+            while (lv[j].z <= u[j]) lv[j] = tab[f2u(lv[j].w) + 1u];
         }
       }
+      const float bn = BUCKET ? u2f(row_value(f2u(sc.norm), bb)) : sc.norm;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const unsigned int w16 = half ? (o[j] >> 16) : (o[j] & 0xFFFFu);
@@ -704,22 +728,22 @@ __device__ __forceinline__ void quantize_regs(float (&x)[32], unsigned int c0, u
         // (w16 + 0.5) < xi * 65536  <=>  w16 < xi * 65536 - 0.5 : the scaling by 2^16 is exact, and the subtraction
         // is exact whenever its result is not negative, so one fused operation decides the same.
         const bool up = (float)w16 < __builtin_fmaf(xi, 65536.0f, -0.5f);
-        h[j] = (unsigned int)tau[j] + (up ? 1u : 0u);
+        h[j] = f2u(lv[j].w) + (up ? 1u : 0u);
         // norm * l_h, the value the decoder will rebuild (the last entry's upper neighbour is never selected: xi = 0)
-        if (WALK || BUCKET) mag[j] = norm[BUCKET ? bb : 0] * (up ? lv[j].z : lv[j].x);
-        else mag[j] = up ? lv[j].w : lv[j].z;
+        mag[j] = bn * (up ? lv[j].z : lv[j].x);
       }
       insert_block<C1>(D, h, xb, bb);
       if (PREV) {
         // +-mag - prev = +-(mag -+ prev): the value's sign, now in the record, is folded into the previous code's sign
         // (one operation per word), so that the table gives the previous value relative to it
+        const float bp = BUCKET ? u2f(row_value(f2u(sc.pnorm), bb)) : 0.0f;
         unsigned int E[C1];
 #pragma unroll
         for (int r = 0; r < C1; ++r) E[r] = __builtin_amdgcn_bitop3_b32(Dp[r], D[r], sign_bits<C1>(r), 0x78);   // a ^ (b & c)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const float pl = lds_float_at(tprev, extract_off<C1>(E, 4 * bb + j));   // table all zero without a message
-          mag[j] = mag[j] - (BUCKET ? pnorm[bb] * pl : pl);
+          mag[j] = mag[j] - (BUCKET ? bp * pl : pl);
         }
       }
       done(bb, mag);
@@ -848,7 +872,7 @@ __device__ double tile_statistic(const float *__restrict__ v, long long d, int c
 
 template <int C1, bool PREV>
 __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
-  __shared__ unsigned char lut[kLutSize];
+  __shared__ float4 bins[kGridPoints];
   __shared__ float4 tab[1 << (C1 - 1)];
   __shared__ float tprev[1 << C1];      // previous message's decode table indexed by code = sign | h << 1
   __shared__ double slot[kThreads];
@@ -884,15 +908,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   }
   // tables that do not depend on the norm
   const float *lev = a.lev + (size_t)m.type * kMaxPoints;
-  const float *rg = a.rgap + (size_t)m.type * kMaxPoints;
   const int walk = a.walk[m.type];
-  float lj = 0.0f, ln = 0.0f, gj = 0.0f;
-  if (t < m.S) {
-    lj = lev[t];
-    if (t + 1 < m.S) { ln = lev[t + 1]; gj = rg[t]; }
-  }
-  if (t < kLutSize / 4)
-    reinterpret_cast<unsigned int *>(lut)[t] = reinterpret_cast<const unsigned int *>(a.lut + (size_t)m.type * kLutSize)[t];
+  const float lj = t < m.S ? lev[t] : 0.0f;
+  load_tables(a, m.type, m.S, walk, bins, tab);
   if (t < (1 << C1)) {   // codes past S-1 decode as the last level
     float pv = 0.0f;
     if (prevmsg) {
@@ -1002,10 +1020,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   }
   __syncthreads();
   const float norm = scale[0], inv = scale[1];
-  if (t < m.S) {
-    const bool last = t + 1 == m.S;
-    tab[t] = walk ? make_float4(lj, gj, last ? __builtin_inff() : ln, 0.0f) : make_float4(lj, gj, norm * lj, last ? 0.0f : norm * ln);
-  }
   if (tile.y == 0) {   // message header of this layer: {norm, levels[S]} (Sec. 3.2: the norm in C_q = 32 bits)
     float *h = reinterpret_cast<float *>(msg + m.hdr_off);
     if (t < m.S) h[1 + t] = lj;
@@ -1035,8 +1049,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) x[4 * bb + j] = diff[j];
     };
-    if (walk) quantize_regs<C1, PREV, true, false>(x, c0, l, a.round, k, k0, k1, &inv, &norm, nullptr, lut, tab, tprev, D, Dp, NoHist(), keep, pairs);
-    else quantize_regs<C1, PREV, false, false>(x, c0, l, a.round, k, k0, k1, &inv, &norm, nullptr, lut, tab, tprev, D, Dp, NoHist(), keep, pairs);
+    if (walk) quantize_regs<C1, PREV, true, false>(x, c0, l, a.round, k, k0, k1, Scales{inv, norm, 0.0f}, bins, tab, tprev, D, Dp, NoHist(), keep, pairs);
+    else quantize_regs<C1, PREV, false, false>(x, c0, l, a.round, k, k0, k1, Scales{inv, norm, 0.0f}, bins, tab, tprev, D, Dp, NoHist(), keep, pairs);
     store_record<C1>(msg + m.body_off + O * 256 * C1, i, D);
     if (!(w & 1)) {
 #pragma unroll
@@ -1097,7 +1111,6 @@ struct __attribute__((aligned(8))) BucketWave {
   float psum[8 * 72];
   float norm[16];       // [8*half + block] of the current octet
   float inv[16];
-  float pnorm[16];      // the previous message's norms of the same buckets
   unsigned int wfix[16];   // fit statistics: integer weight of the bucket (0: gathers nothing)
 };
 
@@ -1134,21 +1147,21 @@ __device__ __forceinline__ double bucket_sums_exact(const float (&x)[32], float 
       s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
     }
   }
-  s = s + __shfl_xor(s, 1, 64);
-  s = s + __shfl_xor(s, 2, 64);
+  s = s + quad_swap<0xB1>(s);
+  s = s + quad_swap<0x4E>(s);
   return s;
 }
 
 // The fit's weighted grid histogram of a run, in shared memory: 32-bit adds, the weights (at most 2^30) cut into their
 // low kHistLowBits bits and the rest, which is zero for most buckets of heavy-tailed vectors and then not added at all.
-// A run has at most 8 * 16384 coordinates and a copy takes every kHistCopies-th lane's, so no cell overflows:
-// 2^17 / 16 * (2^19 - 1) < 2^32 and 2^17 / 4 * 2^11 < 2^32.  Copies of a bin lie side by side: lanes that meet in a bin
+// A run has at most 4 * 16384 coordinates and a copy takes every kHistCopies-th lane's, so no cell overflows:
+// 2^16 / 16 * (2^19 - 1) < 2^32 and 2^16 / 4 * 2^11 < 2^32.  Copies of a bin lie side by side: lanes that meet in a bin
 // collide rarely.  An add of 64 lanes keeps the CU's shared memory busy for 6 cycles here, against 13 for the 64-bit adds
 // of four copies that this replaces (10 for eight copies).
 constexpr int kHistLowBits = 19;
 constexpr int kHistCopies = 16, kHistHighCopies = 4;   // powers of two
 constexpr int kHistFewCopies = 2;    // of the low cells, where a run is a single octet: 2^11 / 2 * (2^19 - 1) < 2^32
-static_assert((long long)kSuperTile * kChunkCoords / kHistCopies * ((1 << kHistLowBits) - 1) < (1ll << 32), "low cells");
+static_assert((long long)kQuantRun * kChunkCoords / kHistCopies * ((1 << kHistLowBits) - 1) < (1ll << 32), "low cells");
 
 // Statistics of the 16 buckets of one octet (the lane's 32 values in x) -> norm, inv (shared memory) and the octet's
 // norm trailer.
@@ -1159,9 +1172,10 @@ static_assert((long long)kSuperTile * kChunkCoords / kHistCopies * ((1 << kHistL
 // replaced by the exact one (bucket_sums_exact).
 // ex: weight scale of the layer's type for the fit statistics (kTypeSkip: none); best: running maximum of the bit
 // patterns of the lane's bucket sums.  Returns whether some weight of the octet has bits above kHistLowBits.
+// sc, wfix: norm, inv and weight of the half's buckets, as quantize_regs takes them.
 template <int KIND>
-__device__ __forceinline__ bool bucket_norms(const Dev &a, const float (&x)[32], float *trailer, float prev_norm,
-                                             BucketWave &bw, int i, int ex, unsigned long long &best) {
+__device__ __forceinline__ bool bucket_norms(const Dev &a, const float (&x)[32], float *trailer, BucketWave &bw, int i, int ex,
+                                             unsigned long long &best, Scales &sc, unsigned int &wfix) {
 #pragma unroll
   for (int bb = 0; bb < 8; ++bb) {
     float acc = 0.0f;
@@ -1189,13 +1203,13 @@ __device__ __forceinline__ bool bucket_norms(const Dev &a, const float (&x)[32],
   if (KIND == kNormLinf) {
     const float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
     s = (double)mx;
-    s = fmax(s, __shfl_xor(s, 1, 64));
-    s = fmax(s, __shfl_xor(s, 2, 64));
+    s = fmax(s, quad_swap<0xB1>(s));
+    s = fmax(s, quad_swap<0x4E>(s));
   } else {
     s = (((double)p[0] + (double)p[1]) + ((double)p[2] + (double)p[3])) +
         (((double)p[4] + (double)p[5]) + ((double)p[6] + (double)p[7]));
-    s = s + __shfl_xor(s, 1, 64);
-    s = s + __shfl_xor(s, 2, 64);
+    s = s + quad_swap<0xB1>(s);
+    s = s + quad_swap<0x4E>(s);
   }
   if (KIND == kNormL2) {
     const bool redo = !(s >= kBucketRescueBelow) || !(s <= 1.7976931348623157e308);
@@ -1229,22 +1243,25 @@ __device__ __forceinline__ bool bucket_norms(const Dev &a, const float (&x)[32],
     bw.wfix[8 * hf + bb] = wf;
     trailer[8 * hf + bb] = n;
   }
-  if (i < 16) bw.pnorm[i] = prev_norm;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int at = 8 * (i >> 5) + (i & 7);
+  sc.norm = bw.norm[at];
+  sc.inv = bw.inv[at];
+  wfix = bw.wfix[at];
   return __ballot(wf >> kHistLowBits) != 0ull;
 }
 
 struct BucketHist {
-  const unsigned int *wfix;   // weights of the lane's eight buckets (its half's), shared memory
+  unsigned int wfix;    // weights of the eight buckets of the lane's half: lane bb of a row holds block bb's
   unsigned int *lo, *hi;      // the lane's copies
   bool on;      // statistics are gathered (this and the next two: the same for the whole wave)
   bool high;    // some weight of the octet has bits above kHistLowBits
   bool plain;   // no such weight, and no coordinate of the octet is in raw magnitude bin 0
   __device__ __forceinline__ void operator()(const float *x, const float (&u)[4], int bb) const {
     if (!on) return;
-    const unsigned int w = wfix[bb];
+    const unsigned int w = row_value(wfix, bb);
     if (plain) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -1263,21 +1280,22 @@ struct BucketHist {
   }
 };
 
-// Bound by the vector ALU (36.5 instructions per coordinate, 89 % of the cycles) and, next, by shared memory (52 %).  Up to
-// 32 levels (codes of 6 bits) four waves a SIMD: 128 registers (up to 32 bytes a lane of them in scratch memory) and 39.2 to 39.9 KiB
-// of shared memory a workgroup.  Wider codes have larger tables (40.6, 42.1 and 45.1 KiB for 7, 8 and 9 bits): three workgroups a
-// CU, and the compiler takes 160 to 166 registers.  Measured against the version that read every octet twice, in pairs of
-// blocks, and added 64-bit weights in four copies, with statistics gathered, K = 8: 151 M coordinates, 8 levels 1.51 -> 1.35 ms;
-// a whole quantize call on 10 k tiles (164 M coordinates over all nodes), us: 4 levels 283 -> 200, 16 295 -> 211, 27 299 -> 217,
-// 64 323 -> 262, 256 330 -> 270; 3096 tiles, 16 levels 124 -> 81 (much of it by shorter runs, see use_runs).
-// Layers of a block or two have a form of one pair of blocks, and runs of one octet fewer copies of the histogram: 200 layers of
-// 50 entries, K = 8, 16 levels, gathering 24.6 us before, 27.7 without these two, 22.5 now.
+// Bound by the vector ALU (35.7 instructions per coordinate) together with what its waves wait for: shared memory is busy 45 % of
+// the time, and a wave spends 44 % of its own waiting for a value.  Up to 32 levels (codes of 6 bits) four waves a SIMD: 128
+// registers (none spilled up to 16 levels) and 38.4 to 39.6 KiB of shared memory a workgroup, of which the table by grid bin is 4
+// KiB; so a run has at most 4 tiles.  Wider codes have larger tables, three workgroups a CU, and the compiler takes 160 to 166
+// registers.  What made it 151 M coordinates, K = 8, 8 levels 1345 -> 1252 us and 3112 tiles, 16 levels 87 -> 79 us: one 128-bit
+// table read per coordinate instead of two reads one after the other; the buckets' scales in registers, broadcast along the rows
+// of 16 lanes, instead of four reads per block; root and reciprocal with one exact test each; the previous record requested at
+// the start of its octet instead of one ahead (128 registers without spills).  Entries requested a block ahead need 20 registers
+// more: 2144 us.
+// Layers of a block or two have a form of one pair of blocks, and runs of one octet fewer copies of the histogram.
 template <int C1, bool PREV, int KIND>
 __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
-  __shared__ unsigned char lut[kLutSize];
+  __shared__ float4 bins[kGridPoints];
   __shared__ float4 tab[1 << (C1 - 1)];
   __shared__ float tprev[1 << C1];   // +-level of the previous message, indexed by code = sign | h << 1
-  __shared__ float chain[kSuperTile * kThreads];   // the slots' squared distances, tile by tile
+  __shared__ float chain[kQuantRun * kThreads];   // the slots' squared distances, tile by tile
   __shared__ BucketWave bws[kThreads / 64];
   __shared__ unsigned int lo[kGridPoints * kHistCopies], hi[kGridPoints * kHistHighCopies];
   __shared__ unsigned long long wmax[kThreads / 64];
@@ -1291,16 +1309,11 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   if (m.planes != C1) return;
   const int t = threadIdx.x;
   const float *lev = a.lev + (size_t)m.type * kMaxPoints;
-  const float *rg = a.rgap + (size_t)m.type * kMaxPoints;
-  reinterpret_cast<unsigned int *>(lut)[t] = reinterpret_cast<const unsigned int *>(a.lut + (size_t)m.type * kLutSize)[t];
   const int kr = k - a.row0;   // row in the pointer tables and in the per-tile scratch; the fit statistics use k
   const unsigned char *prevmsg = (a.prev != nullptr) ? a.prev[kr] : nullptr;
   const int ex = a.type_exp[m.type];
   const int walk = a.walk[m.type];
-  if (t < m.S) {
-    const bool last = t + 1 == m.S;
-    tab[t] = make_float4(lev[t], last ? 0.0f : rg[t], last ? __builtin_inff() : lev[t + 1], 0.0f);
-  }
+  load_tables(a, m.type, m.S, 1, bins, tab);   // the form for one pair of blocks walks, whatever the type
   if (st.y == 0) {   // header of this layer: the norm entry is unused under bucket scope
     float *h = reinterpret_cast<float *>(a.msg[kr] + m.hdr_off);
     for (int j = t; j <= m.S; j += kThreads) h[j] = (j == 0) ? 0.0f : lev[j - 1];
@@ -1328,7 +1341,6 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   __syncthreads();
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int i = t & 63;
-  const int hf8 = (i >> 5) * 8;
   BucketWave &bw = bws[w];
   const float *__restrict__ v = a.grad[(size_t)kr * a.L + l];
   unsigned char *body = a.msg[kr] + m.body_off;
@@ -1347,26 +1359,25 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
   const long long O0 = (long long)st.y * 8 + w * 2;
   if (O0 < noct) {
     load_octet(v, O0, m.d, i, x);
-    if (PREV && prevbody != nullptr) {
-      load_record<C1>(prevbody + O0 * OS, i, Dp);
-      if (i < 16) pn = reinterpret_cast<const float *>(prevbody + O0 * OS + 256 * C1)[i];
-    }
   }
 #pragma unroll 1
   for (int q = 0; q < n; ++q) {
     const long long O = O0 + 8 * (q >> 1) + (q & 1), On = O0 + 8 * ((q + 1) >> 1) + ((q + 1) & 1);
     if (O < noct) {
-      unsigned int D[C1], Dn[C1];
+      unsigned int D[C1];
 #pragma unroll
-      for (int r = 0; r < C1; ++r) { D[r] = 0u; Dn[r] = 0u; }
+      for (int r = 0; r < C1; ++r) D[r] = 0u;
       int i = t & 63;   // kept opaque: addresses derived from it are cheaper to form again than to hold through the loop
       asm volatile("" : "+v"(i));
-      const bool high = bucket_norms<KIND>(a, x, reinterpret_cast<float *>(body + O * OS + 256 * C1), pn, bw, i, ex, best);
-      const bool more = q + 1 < n && On < noct;
-      if (PREV && prevbody != nullptr && more) {
-        load_record<C1>(prevbody + On * OS, i, Dn);
-        if (i < 16) pn = reinterpret_cast<const float *>(prevbody + On * OS + 256 * C1)[i];
+      if (PREV && prevbody != nullptr) {   // requested here, used after the norms: a record held ahead would cost C1 registers
+        load_record<C1>(prevbody + O * OS, i, Dp);
+        pn = reinterpret_cast<const float *>(prevbody + O * OS + 256 * C1)[8 * (i >> 5) + (i & 7)];
       }
+      Scales sc;
+      unsigned int wfix;
+      const bool high = bucket_norms<KIND>(a, x, reinterpret_cast<float *>(body + O * OS + 256 * C1), bw, i, ex, best, sc, wfix);
+      sc.pnorm = pn;
+      const bool more = q + 1 < n && On < noct;
       const bool full = more && (On + 1) * 2048 <= m.d;
       const float *vn = v + On * 2048;
       const auto done = [&](int bb, float (&diff)[4]) {
@@ -1375,22 +1386,23 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
         asm volatile("" : "+v"(acc));
         if (full) load_block(vn, bb, i, &x[4 * bb]);
       };
-      float least = 3.402823466e+38f;
+      bool plain = false;
+      if (ex != kTypeSkip) {
+        float least = 3.402823466e+38f;
 #pragma unroll
-      for (int j = 0; j < 32; ++j) least = fminf(least, fabsf(x[j]));
-      const bool plain = !high && __ballot(least < 0x1p-129f) == 0ull;
-      const BucketHist hist = {bw.wfix + hf8, lo + (i & (copies - 1)), hi + (i & (kHistHighCopies - 1)), ex != kTypeSkip, high, plain};
+        for (int j = 0; j < 32; ++j) least = fminf(least, fabsf(x[j]));
+        plain = !high && __ballot(least < 0x1p-129f) == 0ull;
+      }
+      const BucketHist hist = {wfix, lo + (i & (copies - 1)), hi + (i & (kHistHighCopies - 1)), ex != kTypeSkip, high, plain};
       const unsigned int c0 = (unsigned int)(O * 256 + i);
       if (m.nblk - O * 8 <= 2)   // one pair of blocks is all there is: the others would be worked on for nothing
-        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done, 1);
+        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, sc, bins, tab, tprev, D, Dp, hist, done, 1);
       else if (walk)
-        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
+        quantize_regs<C1, PREV, true, true>(x, c0, l, a.round, k, k0, k1, sc, bins, tab, tprev, D, Dp, hist, done);
       else
-        quantize_regs<C1, PREV, false, true>(x, c0, l, a.round, k, k0, k1, bw.inv + hf8, bw.norm + hf8, bw.pnorm + hf8, lut, tab, tprev, D, Dp, hist, done);
+        quantize_regs<C1, PREV, false, true>(x, c0, l, a.round, k, k0, k1, sc, bins, tab, tprev, D, Dp, hist, done);
       store_record<C1>(body + O * OS, i, D);
       if (more && !full) load_octet(v, On, m.d, i, x);   // the layer's ragged last octet
-#pragma unroll
-      for (int r = 0; r < C1; ++r) Dp[r] = Dn[r];
     }
     if (q & 1) {
       chain[(q >> 1) * kThreads + t] = acc;
@@ -1914,40 +1926,41 @@ __global__ void __launch_bounds__(kThreads) k_fit_pool_b(Dev a) {
 
 __device__ __forceinline__ float grid_value(int j) { return u2f((unsigned int)(j + kGridBase) << 20); }
 
-// Search tables of one type from its levels (in shared memory): reciprocal gaps and the bin -> index table.
-__device__ void build_tables(const Dev &a, int mtype, int S, const float *slev) {
+// Search tables of one type from its levels (in shared memory; sgap: room for kMaxPoints): reciprocal gaps, and for every
+// grid bin the entry {l_tau, 1/gap, l_tau+1, tau} of its lower edge, tau = the largest j <= S-2 with l_j <= edge (the levels
+// increase, so that j is found by halving).  Bin 0 also serves all values below it: its entry is that of tau = 0.
+__device__ void build_tables(const Dev &a, int mtype, int S, const float *slev, float *sgap) {
   float *rg = a.rgap + (size_t)mtype * kMaxPoints;
-  unsigned char *lut = a.lut + (size_t)mtype * kLutSize;
-  for (int j = threadIdx.x; j < kMaxPoints; j += (int)blockDim.x) rg[j] = (j < S - 1) ? rcp_floor(slev[j + 1] - slev[j]) : 0.0f;
-  // entry q serves the values whose bit pattern >> 20 is q: tau at the lower edge of that bin, the largest j <= S-2 with
-  // slev[j] <= edge (the levels increase, so that j is found by halving).
-  for (int q = threadIdx.x; q < kLutSize; q += (int)blockDim.x) {
-    const float lo = u2f((unsigned int)q << 20);
-    int tau = 0;
-    if (q > 1016) {
-      tau = S - 2;
-    } else {
-      for (int n = S - 2; n > 0;) {   // the answer lies in tau .. tau + n
-        const int h = (n + 1) >> 1;
-        if (slev[tau + h] <= lo) { tau += h; n -= h; }
-        else n = h - 1;
-      }
-    }
-    lut[q] = (unsigned char)tau;
+  for (int j = threadIdx.x; j < kMaxPoints; j += (int)blockDim.x) {
+    const float r = (j < S - 1) ? rcp_floor(slev[j + 1] - slev[j]) : 0.0f;
+    rg[j] = r;
+    sgap[j] = r;
   }
-  // does some interior level lie inside a bin?  (0 and 1 are edges; then a lane may have to step on from lut's entry)
+  // Does some interior level lie inside a bin, or not above the first one?  Then a lane may have to step on from the entry of
+  // its bin.  (0 and 1 are edges.)
   int inside = 0;
-  for (int j = threadIdx.x; j < S; j += (int)blockDim.x) inside |= (f2u(slev[j]) & 0xFFFFFu) != 0u;
+  for (int j = threadIdx.x + 1; j <= S - 2; j += (int)blockDim.x)
+    inside |= (f2u(slev[j]) & 0xFFFFFu) != 0u || f2u(slev[j]) <= (unsigned int)kGridBase << 20;
   const int walk = __syncthreads_or(inside);
   if (threadIdx.x == 0) a.walk[mtype] = walk;
+  for (int g = threadIdx.x; g < kGridPoints; g += (int)blockDim.x) {
+    const float lo = u2f((unsigned int)(g + kGridBase) << 20);
+    int tau = 0;
+    for (int n = g == 0 ? 0 : S - 2; n > 0;) {   // the answer lies in tau .. tau + n
+      const int h = (n + 1) >> 1;
+      if (slev[tau + h] <= lo) { tau += h; n -= h; }
+      else n = h - 1;
+    }
+    a.bins[(size_t)mtype * kGridPoints + g] = make_float4(slev[tau], sgap[tau], slev[tau + 1], u2f((unsigned int)tau));
+  }
 }
 
 __global__ void __launch_bounds__(kThreads) k_build_tables(Dev a, int mtype) {
-  __shared__ float slev[kMaxPoints];
+  __shared__ float slev[kMaxPoints], sgap[kMaxPoints];
   const int S = a.type_points[mtype];
   for (int j = threadIdx.x; j < S; j += kThreads) slev[j] = a.lev[(size_t)mtype * kMaxPoints + j];
   __syncthreads();
-  build_tables(a, mtype, S, slev);
+  build_tables(a, mtype, S, slev, sgap);
 }
 
 // Exact minimisation of eq. (Qada2) over interior levels on the grid by dynamic programming; one workgroup per type.
@@ -1977,14 +1990,6 @@ constexpr int kFitSegs = 15;        // segments of the last couple
 constexpr int kFitGroup = kFitSeg / 2;   // couples kFitGroup*(g-1)+1 .. kFitGroup*g have g segments each
 constexpr int kFitPad = 272;        // rows are read up to index 14 * 18 + 17
 static_assert(kFitGroup * kFitSegs * (kFitSegs - 1) / 2 + 2 * kFitSegs <= kFitThreads - 32, "two b of 14 groups and the last two couples");
-
-// A neighbour's value inside a group of four lanes (quad permutation CTRL).
-template <int CTRL>
-__device__ __forceinline__ double quad_swap(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo));
-}
 
 // SRC: where the pooled weights come from.
 //   kFitPooled   k_fit_typemax and k_fit_pool have run
@@ -2294,7 +2299,7 @@ __global__ void __launch_bounds__(kFitThreads) k_fit_dp(Dev a) {
   }
   __syncthreads();
   for (int j = t; j < S; j += kFitThreads) a.lev[(size_t)mtype * kMaxPoints + j] = slev[j];
-  build_tables(a, mtype, S, slev);
+  build_tables(a, mtype, S, slev, reinterpret_cast<float *>(pbest));   // the segments' minima are no longer needed
 }
 
 // ------------------------------------------------------------------------------------------------ calibration
