@@ -11,7 +11,7 @@ constexpr int kChunkCoords = 16384;  // coordinates per workgroup tile (64 block
 constexpr int kSuperTile = 8;        // the most tiles of a run (passes that keep histograms or tables per run)
 constexpr int kQuantRun = 4;         // ... of the quantize pass under bucket scope
 constexpr int kTaperWorkgroups = 2048;   // workgroups of 256 threads the device holds at once (256 CUs x 8)
-constexpr int kDecodeWaves = 2;       // waves (= octets) per workgroup in the decode pass: 1, 2 or 4
+constexpr int kDecodeOctets = 2;      // octets per workgroup in the decode pass: 1, 2, 4 or 8
 constexpr int kThreads = 256;        // workgroup size everywhere: 4 waves, 256 reduction slots
 constexpr int kSmallThreads = 512;   // k_quantize_small: a wave per octet of a tile
 constexpr int kSmallTiles = 512;     // the most tiles of a launch of k_quantize_small,

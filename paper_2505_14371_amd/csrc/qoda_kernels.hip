@@ -261,8 +261,8 @@ __device__ __forceinline__ unsigned int extract_code(const unsigned int (&D)[C1]
 }
 
 // Byte offset (code * 4) of code jj into a table of floats: two instructions (shift or funnel shift, mask).
-template <int C1>
-__device__ __forceinline__ unsigned int extract_off(const unsigned int (&D)[C1], int jj) {
+template <int C1, int N>
+__device__ __forceinline__ unsigned int extract_off(const unsigned int (&D)[N], int jj) {
   const int pos = C1 * jj, r = pos >> 5, sh = pos & 31;
   unsigned int v;
   if (sh + C1 <= 32) v = (sh >= 2) ? (D[r] >> (sh - 2)) : (D[r] << (2 - sh));
@@ -1537,51 +1537,90 @@ __global__ void __launch_bounds__(kThreads) k_alt_finalize(Dev a) {
 }
 
 // DECODE + K-way mean (+ eq. (ODA) update unless MODE is kDecodeMean): one pass over Y, X_1 and the K messages.
-// One octet per wave at a time: 32 running sums per lane, K records of C1 words, then 8 blocks of state.
-// Under kDecodeUpdateAlt the lane also rebuilds X_t = X_1 + eta_prev * Y_t and adds (X_t - X_{t+1})^2 to its
-// slot's fp32 fused chain (coordinates in increasing order, as in the quantizer's distance term).
-// The 8 bucket norms a lane needs from one octet's trailer (its half's, blocks 0..7): two 128-bit loads.
-__device__ __forceinline__ void load_bucket_norms(const unsigned char *trailer, int i, float (&n)[8]) {
-  const auto *g = reinterpret_cast<const __attribute__((address_space(1))) v4f *>(as_global(trailer)) + 2 * (i >> 5);
-  const v4f a = g[0], b = g[1];
-  n[0] = a.x; n[1] = a.y; n[2] = a.z; n[3] = a.w; n[4] = b.x; n[5] = b.y; n[6] = b.z; n[7] = b.w;
+// A wave takes NB = 8, 4 or 2 consecutive blocks of an octet: 4 * NB running sums per lane, the codes of K records, then the
+// blocks of state.
+// Under kDecodeUpdateAlt the lane also rebuilds X_t = X_1 + eta_prev * Y_t; its differences X_t - X_{t+1} are left in sum.
+
+// Words that hold 4*NB codes from any bit of a record where a part can start (a multiple of 4*NB*C1 bits).
+template <int C1, int NB>
+constexpr int part_words() {
+  int most = 0;
+  for (int part = 0; part < 8 / NB; ++part) {
+    const int first = 4 * NB * C1 * part, end = first + 4 * NB * C1;
+    const int words = (end + 31) / 32 - first / 32;
+    most = words > most ? words : most;
+  }
+  return most;
 }
 
-template <int C1, int MODE, bool FAST, bool BUCKET>
-__device__ __forceinline__ void decode_octet(const Dev &a, const LayerMeta &m, int l, long long O, const float *T, int i,
-                                             float eta, float gamma, float eta_prev, float &accx) {
+// The record words of a lane that hold the codes of blocks NB*part .. of one octet (the last word again where a part needs
+// fewer than the others).
+template <int C1, int NB>
+__device__ __forceinline__ void load_part(const unsigned char *octet, int part, int i, unsigned int (&D)[part_words<C1, NB>()]) {
+  const auto *g = reinterpret_cast<const __attribute__((address_space(1))) unsigned int *>(as_global(octet));
+  const int w0 = (4 * NB * C1 * part) >> 5;
+#pragma unroll
+  for (int r = 0; r < part_words<C1, NB>(); ++r) D[r] = __builtin_nontemporal_load(g + min(w0 + r, C1 - 1) * 64 + i);
+}
+
+// A part may start inside a word: its codes are moved to bit 0.
+template <int C1, int NB>
+__device__ __forceinline__ void align_part(unsigned int (&D)[part_words<C1, NB>()], int part) {
+  if constexpr (4 * NB * C1 % 32 != 0) {
+    constexpr int N = part_words<C1, NB>();
+    const int sh = (4 * NB * C1 * part) & 31;
+#pragma unroll
+    for (int r = 0; r < N; ++r) D[r] = __builtin_amdgcn_alignbit(r + 1 < N ? D[r + 1] : 0u, D[r], sh);
+  }
+}
+
+// The bucket norms a lane needs from one octet's trailer (its half's, blocks NB*part ..).
+template <int NB>
+__device__ __forceinline__ void load_bucket_norms(const unsigned char *trailer, int part, int i, float (&n)[NB]) {
+  typedef float vec __attribute__((ext_vector_type(NB == 2 ? 2 : 4)));
+  constexpr int V = NB == 2 ? 2 : 4;
+  const auto *g = reinterpret_cast<const __attribute__((address_space(1))) vec *>(as_global(trailer)) + (8 / V) * (i >> 5) + part * (NB / V);
+#pragma unroll
+  for (int q = 0; q < NB / V; ++q) {
+    const vec v = g[q];
+#pragma unroll
+    for (int j = 0; j < V; ++j) n[V * q + j] = v[j];
+  }
+}
+
+// What a wave needs of one node's message: codes and, under bucket scope, norms.
+template <int C1, int NB, bool BUCKET>
+struct Part {
+  unsigned int D[part_words<C1, NB>()];
+  float n[BUCKET ? NB : 1];
+  __device__ __forceinline__ void load(const unsigned char *octet, int part, int i) {
+    load_part<C1, NB>(octet, part, i, D);
+    if constexpr (BUCKET) load_bucket_norms<NB>(octet + 256 * C1, part, i, n);
+  }
+};
+
+template <int C1, int MODE, bool FAST, bool BUCKET, int NB>
+__device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, int l, long long O, int part, const float *T, int i,
+                                            float eta, float gamma, float eta_prev, Part<C1, NB, BUCKET> cur, float (&sum)[4 * NB]) {
   constexpr int TS = 1 << C1;   // table entries per node, indexed by code = sign | h << 1
   constexpr long long OS = 256 * C1 + (BUCKET ? 64 : 0);   // bytes per octet (bucket scope: codes + 16 norms)
   const long long boff = m.body_off + O * OS;
-  float sum[32];
-  unsigned int Dc[C1], Dn[C1];
-  float nc[8], nn[8];   // bucket scope: this node's and the next node's bucket norms for the lane's 8 blocks
-  load_record<C1>(a.msgs_in[0] + boff, i, Dc);
-  if (BUCKET) load_bucket_norms(a.msgs_in[0] + boff + 256 * C1, i, nc);
-  for (int k = 0; k < a.K; ++k) {
-#pragma unroll
-    for (int r = 0; r < C1; ++r) Dn[r] = 0u;
-    if (k + 1 < a.K) {
-      load_record<C1>(a.msgs_in[k + 1] + boff, i, Dn);
-      if (BUCKET) load_bucket_norms(a.msgs_in[k + 1] + boff + 256 * C1, i, nn);
-    }
+  for (int k = 0; k < a.K; ++k) {   // cur: node k's, requested before; the next node's are requested now
+    Part<C1, NB, BUCKET> nxt = {};
+    if (k + 1 < a.K) nxt.load(a.msgs_in[k + 1] + boff, part, i);
     const float *Tk = T + k * TS;
+    align_part<C1, NB>(cur.D, part);
 #pragma unroll
-    for (int jj = 0; jj < 32; ++jj) {
-      float val = lds_float_at(Tk, extract_off<C1>(Dc, jj));   // layer / vector scope: +-norm_k * level
-      if (BUCKET) val = nc[jj >> 2] * val;                     // bucket scope: the table holds +-level
+    for (int jj = 0; jj < 4 * NB; ++jj) {
+      float val = lds_float_at(Tk, extract_off<C1>(cur.D, jj));   // layer / vector scope: +-norm_k * level
+      if (BUCKET) val = cur.n[jj >> 2] * val;                     // bucket scope: the table holds +-level
       sum[jj] = (k == 0) ? val : sum[jj] + val;
     }
-#pragma unroll
-    for (int r = 0; r < C1; ++r) Dc[r] = Dn[r];
-    if (BUCKET) {
-#pragma unroll
-      for (int b = 0; b < 8; ++b) nc[b] = nn[b];
-    }
+    cur = nxt;
   }
 #pragma unroll
-  for (int bb = 0; bb < 8; ++bb) {
-    const long long B = O * 8 + bb;
+  for (int bb = 0; bb < NB; ++bb) {
+    const long long B = O * 8 + part * NB + bb;
     if (FAST || B < m.nblk) {
       const long long e = B * kBlockCoords + 4 * i;
       const long long dlim = FAST ? e + 4 : m.d;   // FAST: the whole block is inside the layer
@@ -1615,36 +1654,45 @@ __device__ __forceinline__ void decode_octet(const Dev &a, const LayerMeta &m, i
           xn[j] = x1[j] + ey;
           const float gm = gamma * mean[j];
           xh[j] = xn[j] - gm;
-          if (MODE == kDecodeUpdateAlt) {
-            const float diff = xt - xn[j];
-            accx = __builtin_fmaf(diff, diff, accx);
-          }
+          if (MODE == kDecodeUpdateAlt) sum[4 * bb + j] = xt - xn[j];
         }
         store4(a.y[l], e, dlim, y);
         store4(a.x_half[l], e, dlim, xh);
         if (a.x_next) store4(a.x_next[l], e, dlim, xn);
       }
+    } else if (MODE == kDecodeUpdateAlt) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum[4 * bb + j] = 0.0f;
     }
   }
 }
 
-// The decode pass runs best in short workgroups of one octet per wave (measured against one tile per workgroup of
-// four waves with two octets each: 6 % faster at K = 8, 4 % at K = 16): a workgroup has blockDim / 64 waves (1, 2 or 4)
-// and takes that many consecutive octets of a tile.  Only the (Alt) variant keeps one workgroup of four waves per
-// tile, two octets per wave: its squared-distance term is defined per slot and tile (a slot's chain runs through both
-// octets of its wave).
-template <int C1, int MODE, bool BUCKET>
-__global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
+// The decode pass runs best in short workgroups (measured against one tile per workgroup of four waves with two octets
+// each: 6 % faster at K = 8, 4 % at K = 16): a workgroup takes a few consecutive octets of a tile (kDecodeOctets), 8 / NB waves
+// an octet.  How many blocks a wave takes is chosen by decode_blocks.  Only the (Alt) variant keeps a workgroup to the tile
+// (eight waves): its squared-distance term is defined per slot and tile; a slot's chain runs through the two octets of a pair of
+// waves, the odd one goes on from the even one's sum.  (A tile in four waves, two octets each, one after the other: 184 M
+// coordinates, K = 4, 128 levels 185 us, now 172.)
+template <int C1, int MODE, bool BUCKET, int NB>
+__global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
   extern __shared__ float T[];   // [K][2^C1]: +-norm_k * level_h (bucket scope: +-level_h) from the K message headers
-  __shared__ double red[MODE == kDecodeUpdateAlt ? kThreads : 1];
-  constexpr bool WHOLE = MODE == kDecodeUpdateAlt;
-  const int nw = blockDim.x >> 6;
-  const int PARTS = WHOLE ? 1 : 8 / nw;   // workgroups per tile
-  const int g = blockIdx.x / PARTS, part = blockIdx.x - g * PARTS;
+  constexpr bool ALT = MODE == kDecodeUpdateAlt;
+  __shared__ double red[ALT ? kThreads : 1];
+  const int noct_wg = (int)(blockDim.x >> 6) * NB / 8;   // octets of a workgroup
+  const int parts = 8 / noct_wg;                         // workgroups per tile
+  const int g = blockIdx.x / parts, part = blockIdx.x - g * parts;
   const int2 tile = a.tiles[g];
   const int l = tile.x;
   const LayerMeta m = a.meta[l];
   if (m.planes != C1) return;
+  const int t = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i = t & 63;
+  const int piece = w % (8 / NB);
+  const long long O = (long long)tile.y * 8 + part * noct_wg + w / (8 / NB);
+  const bool live = O < ((m.nblk + 7) >> 3);
+  Part<C1, NB, BUCKET> first = {};
+  if (live) first.load(a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)), piece, i);   // before the tables are there
   const int TS = 1 << C1;
   double new_acc = 0.0;
   if (MODE == kDecodeUpdateScalars) new_acc = sum_distances(a);   // every wave computes what k_step_scalars computes
@@ -1660,28 +1708,47 @@ __global__ void __launch_bounds__(kThreads) k_decode(Dev a) {
   // and the count comes after the barrier.
   if (MODE == kDecodeUpdateScalars) asm volatile("" : "+v"(new_acc) : : "memory");
   __syncthreads();
-  const int t = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int i = t & 63;
-  float eta = 0.0f, gamma = 0.0f, eta_prev = 0.0f, accx = 0.0f;
-  if (MODE == kDecodeUpdate || MODE == kDecodeUpdateAlt) { eta = a.eta[0]; gamma = a.eta[1]; }
+  float eta = 0.0f, gamma = 0.0f, eta_prev = 0.0f;
+  if (MODE == kDecodeUpdate || ALT) { eta = a.eta[0]; gamma = a.eta[1]; }
   unsigned int readers = 0u;
   if (MODE == kDecodeUpdateScalars) {
     if (t == 0) readers = __hip_atomic_fetch_add(a.readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     eta = gamma = rcp_floor(sqrt_floor(1.0 + new_acc));
   }
-  if (MODE == kDecodeUpdateAlt) eta_prev = a.eta[2];
+  if (ALT) eta_prev = a.eta[2];
   if (MODE == kDecodeExtrapolate) gamma = a.gamma_in[0];
-  const long long noct = (m.nblk + 7) >> 3;
-  for (int oo = 0; oo < (WHOLE ? 2 : 1); ++oo) {
-    const long long O = (long long)tile.y * 8 + (WHOLE ? w * 2 + oo : part * nw + w);
-    if (O >= noct) break;
-    if ((O + 1) * 2048 <= m.d) decode_octet<C1, MODE, true, BUCKET>(a, m, l, O, T, i, eta, gamma, eta_prev, accx);
-    else decode_octet<C1, MODE, false, BUCKET>(a, m, l, O, T, i, eta, gamma, eta_prev, accx);
+  float sum[4 * NB];
+  if (live) {
+    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
+    else decode_part<C1, MODE, false, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
   }
-  if (MODE == kDecodeUpdateAlt) {
-    const double total = block_tree((double)accx, red);
-    if (t == 0) a.dpartial[g] = total;
+  if (ALT) {
+    // a slot's fp32 fused chain in increasing coordinate: even waves first
+    float *chain = reinterpret_cast<float *>(red);
+    const int sl = (w >> 1) * 64 + i;
+    float accx = 0.0f;
+    if (!(w & 1)) {
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) accx = __builtin_fmaf(sum[j], sum[j], accx);
+      }
+      chain[sl] = accx;
+    }
+    __syncthreads();
+    if (w & 1) {
+      accx = chain[sl];
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) accx = __builtin_fmaf(sum[j], sum[j], accx);
+      }
+    }
+    __syncthreads();   // the chains' room becomes that of the 256 slots
+    if (w & 1) red[sl] = (double)accx;
+    __syncthreads();
+    if (w == 0) {
+      const double total = wave_tree<true>(red, i);
+      if (i == 0) a.dpartial[g] = total;
+    }
   }
   if (MODE == kDecodeUpdateScalars && t == 0 && readers == gridDim.x - 1u) {   // all waves of all workgroups have read *a.acc
     store_scalars(a, new_acc, eta);
@@ -2518,17 +2585,52 @@ hipError_t launch_step_scalars(const Dev &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// How many blocks of an octet a wave of the decode pass takes, for G tiles.  While the waves do not fill the device the pass
+// is a chain of loads and table reads, K nodes one after the other: the shorter a wave's part the better.  Beyond about 300
+// tiles whole octets have the fewest loads; the passes that read and write iterates gain again from half octets in the
+// largest launches (more waves with loads in flight), under bucket scope from 700 tiles on.  us with 8 / 4 / 2 blocks, S = 16:
+//   update      K = 4: 4 tiles 9.4 / 7.1 / 5.8, 64 11.8 / 8.9 / 7.3, 160 18.2 / 14.1 / 12.6, 256 20.5 / 18.7 / 16.4, 400 27.5 / 26.8 / 24.9, 512
+//               31.7 / 32.1 / 29.8; K = 8: 64 16.6 / 12.7 / 10.5, 256 23.2 / 21.4 / 19.5, 320 27.7 / 26.0 / 26.6, 400 32.6 / 32.2 / 30.3, 512 36.1
+//               / 36.8 / 35.8, 600 40.4 / 45.0 / 41.3; K = 16: 256 30.8 / 28.8 / 26.8, 320 34.2 / 32.8 / 35.4, 400 39.3 / 39.9 / 40.0; with 8 / 4,
+//               K = 8: 800 48.4 / 50.5 (bucket norms 58.3 / 52.2), 1600 95 / 99 (99.5 / 98.7), 3200 186 / 182 (193 / 184), 6400 366 / 353
+//               (370 / 360); K = 4: 20000 1056 / 1024 (1050 / 1023)
+//   extrapolate K = 4: 64 8.8 / 6.3 / 5.5, 256 13.5 / 12.1 / 11.1, 400 17.7 / 15.5 / 16.5, 512 19.0 / 17.7 / 18.6, 600 20.6 / 22.8 / 21.6; K = 8, with
+//               8 / 4: 800 30.6 / 33.3 (39.1 / 34.7), 1600 58 / 62 (65.7 / 63.5), 3200 117 / 113 (125 / 117), 6400 222 / 215 (240 / 225)
+//   mean        K = 4: 64 6.1 / 5.1 / 4.7, 128 6.4 / 5.7 / 5.7, 160 6.5 / 6.0 / 6.1, 256 7.1 / 7.4 / 7.9; K = 8: 64 8.4 / 7.1 / 6.5, 128 8.8 / 8.0 / 7.8, 160
+//               8.8 / 8.6 / 9.2, 256 9.8 / 10.9 / 12.4; with 8 / 4, K = 8: 1600 41 / 45, 6400 154 / 157
+static int decode_blocks(int G, int K, int mode, bool bucket) {
+  if (mode == kDecodeMean) return G <= 128 ? 2 : G <= 160 ? 4 : 8;
+  if (G <= 256 || (mode == kDecodeUpdate && G <= 512 && K <= 8)) return 2;
+  if (G <= (mode == kDecodeUpdate ? 384 : 512)) return 4;
+  return G > (bucket ? 700 : 2400) ? 4 : 8;
+}
+
+template <int C1, int MODE, bool BUCKET, int NB>
+static void launch_decode_blocks(const Dev &a, size_t lds_bytes, hipStream_t s) {
+  // short workgroups: two octets, four where the K decode tables are large enough to limit the workgroups per CU
+  const int oct = MODE == kDecodeUpdateAlt ? 8 : (lds_bytes > 8192 && NB > 2) ? 4 : kDecodeOctets;
+  const dim3 grid((unsigned int)a.G * (8 / oct)), block(64 * oct * 8 / NB);
+  hipLaunchKernelGGL((k_decode<C1, MODE, BUCKET, NB>), grid, block, lds_bytes, s, a);
+}
+
+template <int C1, int MODE, bool BUCKET>
+static void launch_decode_mode(const Dev &a, size_t lds_bytes, hipStream_t s) {
+  if constexpr (MODE == kDecodeUpdateAlt) launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
+  else if constexpr (MODE == kDecodeUpdateScalars) launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s);   // few tiles
+  else switch (decode_blocks(a.G, a.K, MODE, BUCKET)) {
+    case 2: launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s); break;
+    case 4: launch_decode_blocks<C1, MODE, BUCKET, 4>(a, lds_bytes, s); break;
+    default: launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
+  }
+}
+
 template <int C1, bool BUCKET>
 static void launch_decode_scope(const Dev &a, int mode, size_t lds_bytes, hipStream_t s) {
-  const dim3 whole(a.G), block(kThreads);                                           // one workgroup per tile
-  // short workgroups: two waves, four where the K decode tables are large enough to limit the workgroups per CU
-  const int nw = lds_bytes > 8192 ? 4 : kDecodeWaves;
-  const dim3 parts((unsigned int)a.G * (8 / nw)), small(64 * nw);
-  if (mode == kDecodeExtrapolate) hipLaunchKernelGGL((k_decode<C1, kDecodeExtrapolate, BUCKET>), parts, small, lds_bytes, s, a);
-  else if (mode == kDecodeUpdateAlt) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdateAlt, BUCKET>), whole, block, lds_bytes, s, a);
-  else if (mode == kDecodeUpdate) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdate, BUCKET>), parts, small, lds_bytes, s, a);
-  else if (mode == kDecodeUpdateScalars) hipLaunchKernelGGL((k_decode<C1, kDecodeUpdateScalars, BUCKET>), parts, small, lds_bytes, s, a);
-  else hipLaunchKernelGGL((k_decode<C1, kDecodeMean, BUCKET>), parts, small, lds_bytes, s, a);
+  if (mode == kDecodeExtrapolate) launch_decode_mode<C1, kDecodeExtrapolate, BUCKET>(a, lds_bytes, s);
+  else if (mode == kDecodeUpdateAlt) launch_decode_mode<C1, kDecodeUpdateAlt, BUCKET>(a, lds_bytes, s);
+  else if (mode == kDecodeUpdate) launch_decode_mode<C1, kDecodeUpdate, BUCKET>(a, lds_bytes, s);
+  else if (mode == kDecodeUpdateScalars) launch_decode_mode<C1, kDecodeUpdateScalars, BUCKET>(a, lds_bytes, s);
+  else launch_decode_mode<C1, kDecodeMean, BUCKET>(a, lds_bytes, s);
 }
 
 template <int C1>

@@ -1,0 +1,120 @@
+"""The decode pass in parts of two, four and eight blocks a wave, for every code width, at sizes on both sides of each line of
+the choice: mean, update, plain step and the update of eq. (Alt) against the oracle's operations, equal to the bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2505_14371_amd import qoda  # noqa: E402
+
+
+def gm(*a, **k):
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU test was selected but no GPU is visible")
+    import gpu_harness
+
+    return gpu_harness.GpuModel(*a, **k)
+
+
+def passes(m, sizes):
+    """{pass: the layers it leaves}, from the same message and state."""
+    rng = np.random.default_rng(5)
+    x1, y = ([rng.standard_normal(s).astype(np.float32) for s in sizes] for _ in range(2))
+    rates = torch.tensor([0.37, 0.53], device="cuda")
+    out = {}
+    m.aggregate()
+    out["mean"] = m.layers(m.mean)
+    m.set_layers(m.x1, x1)
+    m.set_layers(m.y, y)
+    m.ctx.extrapolate(m.msg[m.cur], m.layer_ptrs(m.x1), m.layer_ptrs(m.x_half), rates[1:])
+    out["extrapolate"] = m.layers(m.x_half)
+    m.ctx.step_rates(m.msg[m.cur], m.layer_ptrs(m.x1), m.layer_ptrs(m.y), m.layer_ptrs(m.x_half), rates, m.layer_ptrs(m.x_next))
+    out["y"], out["x_half"], out["x_next"] = m.layers(m.y), m.layers(m.x_half), m.layers(m.x_next)
+    return x1, y, rates.cpu().numpy(), out
+
+
+def check(oracle, sizes, S, K, scope, some=None):
+    L = len(sizes)
+    m = gm(sizes, [0] * L, [S], K, seed=4, norm_scope=scope)
+    rng = np.random.default_rng(S)
+    grads = [[rng.standard_t(3, s).astype(np.float32) for s in sizes] for _ in range(K)]
+    m.set_grads(grads)
+    m.quantize_all(1)
+    x1, y, (eta, gamma), out = passes(m, sizes)
+    mean = oracle.dequant_aggregate(sizes, [S] * L, m.messages(), scope=scope)
+    for l in range(L):
+        assert np.array_equal(out["mean"][l], mean[l])
+        assert np.array_equal(out["extrapolate"][l], x1[l] - gamma * mean[l])
+        want = y[l].copy()
+        x_next, x_half = oracle.oda_update(mean[l], x1[l], want, eta, gamma, want_next=True)
+        assert np.array_equal(out["y"][l], want) and np.array_equal(out["x_half"][l], x_half) and np.array_equal(out["x_next"][l], x_next)
+
+
+RAGGED = [1, 255, 257, 1023, 1025, 1537, 2047, 2048, 2049, 0, 16384 + 513, 5 * 2048 + 3]
+
+
+@pytest.mark.parametrize("scope", [0, 2])
+@pytest.mark.parametrize("S", [2, 4, 8, 16, 32, 64, 128, 256])
+def test_parts_of_two_blocks(oracle, S, scope):
+    check(oracle, RAGGED, S, 3, scope)
+
+
+@pytest.mark.parametrize("scope", [0, 2])
+@pytest.mark.parametrize("tiles, K", [(127, 1), (129, 2), (161, 1), (257, 2), (385, 9), (513, 1)])
+def test_sizes_of_the_choice(oracle, tiles, K, scope):
+    """Up to 128 / 160 tiles the mean takes two / four blocks a wave, up to 256 / 384 or 512 the others."""
+    S = 16 if tiles % 2 else 8
+    check(oracle, [16384 * (tiles - len(RAGGED)) - 700] + RAGGED, S, K, scope)
+
+
+@pytest.mark.parametrize("scope", [0, 2])
+@pytest.mark.parametrize("S", [2, 4, 8, 16, 32, 64, 128, 256])
+def test_half_octets_equal_whole_ones(S, scope):
+    """Two models with the same tensor, in the second one repeated until the update takes half octets: the same bits."""
+    n, times = 2048 * 8 * 40 + 1700, 61          # 41 tiles, 2501
+    got = []
+    for reps in (1, times):
+        m = gm([n] * reps, [0] * reps, [S], 1, seed=4, norm_scope=scope)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(1)
+        x = torch.randn(n, device="cuda", generator=g)
+        for o in m.off[:1] if reps == 1 else m.off:
+            m.grad_flat[0][int(o): int(o) + n] = x
+        m.quantize_all(1)
+        rates = torch.tensor([0.37, 0.53], device="cuda")
+        m.ctx.step_rates(m.msg[0], m.layer_ptrs(m.x1), m.layer_ptrs(m.y), m.layer_ptrs(m.x_half), rates, None)
+        m.ctx.extrapolate(m.msg[0], m.layer_ptrs(m.x1), m.layer_ptrs(m.x_next), rates[1:])
+        m.aggregate()
+        got.append([t[:n].cpu().numpy().copy() for t in (m.y, m.x_half, m.x_next, m.mean)])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("scope", [0, 2])
+@pytest.mark.parametrize("S", [4, 32, 256])
+def test_distance_of_the_iterates(oracle, S, scope):
+    """eq. (Alt), two rounds, tiles whose octets end at every wave: the sum of squares over slots and tiles."""
+    K, L = 3, len(RAGGED)
+    m = gm(RAGGED, [0] * L, [S], K, seed=4, norm_scope=scope)
+    rng = np.random.default_rng(S)
+    x1 = [rng.standard_normal(s).astype(np.float32) for s in RAGGED]
+    m.set_layers(m.x1, x1)
+    y = [np.zeros(s, np.float32) for s in RAGGED]
+    lam = mu = 0.0
+    eta_prev = np.float32(1.0)
+    for t in (1, 2, 3):
+        m.set_grads([[rng.standard_t(3, s).astype(np.float32) for s in RAGGED] for _ in range(K)])
+        m.quantize_all_alt(t)
+        deltas = m.ctx.read_buffer(qoda.BUF_DELTA)
+        mean = oracle.dequant_aggregate(RAGGED, [S] * L, m.messages(), scope=scope)
+        m.step_alt(0.25)
+        eta, gamma = oracle.alt_step_size(lam, mu, 0.25)
+        _, x_half, dx2 = oracle.oda_update_alt(RAGGED, mean, x1, y, eta_prev, eta, gamma, want_next=False)
+        lam, mu = oracle.alt_advance(deltas, dx2, lam, mu)
+        eta_prev = eta
+        assert np.array_equal(m.alt_sums.cpu().numpy(), [lam, mu])
+        got_y, got_x = m.layers(m.y), m.layers(m.x_half)
+        for l in range(L):
+            assert np.array_equal(got_y[l], y[l]) and np.array_equal(got_x[l], x_half[l])
