@@ -172,15 +172,19 @@ __device__ __forceinline__ float4 bin_entry(const float4 *bins, float u) {
 }
 
 // The grid bins' entries of a type into shared memory; where a lane may have to walk on from the entry of its bin (walk), also
-// the entries by tau, the last one with the upper neighbour +infinity, which stops every walk.
+// the entries by tau, the last one with the upper neighbour +infinity, which stops every walk.  256 threads or more; all loads
+// are requested before the first is used (one after the other they cost a small launch 1 us).
 __device__ __forceinline__ void load_tables(const Dev &a, int type, int S, int walk, float4 *bins, float4 *tab) {
-  const float4 *src = a.bins + (size_t)type * kGridPoints;
-  for (int j = threadIdx.x; j < kGridPoints; j += (int)blockDim.x) bins[j] = src[j];
-  if (walk) {
-    const float *lev = a.lev + (size_t)type * kMaxPoints, *rg = a.rgap + (size_t)type * kMaxPoints;
-    for (int j = threadIdx.x; j < S; j += (int)blockDim.x)
-      tab[j] = make_float4(lev[j], j + 1 < S ? rg[j] : 0.0f, j + 1 < S ? lev[j + 1] : __builtin_inff(), u2f((unsigned int)j));
-  }
+  static_assert(kGridPoints == kThreads + 1 && kMaxPoints == kThreads, "one entry a thread, and one more");
+  const v4f *src = reinterpret_cast<const v4f *>(a.bins + (size_t)type * kGridPoints);
+  const float *lev = a.lev + (size_t)type * kMaxPoints, *rg = a.rgap + (size_t)type * kMaxPoints;
+  const int t = threadIdx.x, j = min(t, kThreads - 1);
+  const v4f v = src[j], last = src[kThreads];
+  const float lj = lev[j], ln = lev[min(j + 1, kMaxPoints - 1)], rj = rg[j];
+  if (t >= kThreads) return;
+  *reinterpret_cast<v4f *>(&bins[t]) = v;
+  if (t == 0) *reinterpret_cast<v4f *>(&bins[kThreads]) = last;
+  if (walk && t < S) tab[t] = make_float4(lj, rj, t + 1 < S ? ln : __builtin_inff(), u2f((unsigned int)t));   // rgap is 0 from S-1 on
 }
 
 // A value of lane bb of the lane's row of 16 lanes.
@@ -812,6 +816,7 @@ __device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, cons
 // goes with it.  Only one order matters, that of a workgroup's stores and its count in `finished`: thread 0 makes both
 // stores and the count, and waits for the stores before it counts.  So who finds that all workgroups of a node have been
 // counted also finds all their values, and nothing but its own zeros is written there after that, in this call.
+// A group of one tile has nothing to exchange and waits for nothing (2 x 512 entries, K = 4: 0.6 us less).
 // Waiting ends: after `tries` looks a workgroup computes the missing statistics itself, one per turn, from the vectors, with
 // the same operations in the same order, and keeps them to itself.
 // Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  A quantize
@@ -937,10 +942,13 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   const int first = vec ? 0 : m.first_chunk, n = vec ? a.G : m.nchunks;   // the group
   if (w == 0) {
     const double own = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
-    if (i == 0) publish(&stat[m.first_chunk + tile.y], own);
+    if (i == 0) {
+      if (n == 1) group[0] = own;   // nobody else needs it
+      else publish(&stat[m.first_chunk + tile.y], own);
+    }
   }
   // the group's statistics; n <= kSmallGroup, one thread each
-  bool have = t >= n;
+  bool have = t >= n || n == 1;
   for (int tries = 0;; ++tries) {
     if (!have && a.tries > 0) {
       const unsigned long long b = __hip_atomic_load(&stat[first + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
