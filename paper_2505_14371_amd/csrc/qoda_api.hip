@@ -53,6 +53,13 @@ struct qoda_ctx {
   int *d_type_exp_next = nullptr;   // bucket scope: the weight scales the next gathering pass will use
   int *d_type_skip = nullptr;       // bucket scope: "no scale" for every type (passes that gather no histogram)
   bool gather = true;               // bucket scope: quantize passes gather the fit's histogram
+  // Bucket scope: two sets of statistics (d_hist, d_sumsq hold both).  stat_set is that of the last pass; while stat_swap
+  // holds the other one is zero, so that a pass over all nodes gathers into it without a launch that clears, and has the
+  // old one cleared by its last kernel.  Captured work can be replayed at any time and must find its set where it left it: from
+  // the first captured call on (and after one that failed between its launches) the sets stay and every pass clears its own.
+  int stat_set = 0;
+  bool stat_swap = false;
+  static constexpr size_t kStatPairs = 8192;   // (node, layer) pairs up to which there are two sets (64 MiB each)
   unsigned long long *d_index_counts = nullptr;   // [M*256], allocated by the first qoda_index_counts
   // device pointer tables (uploaded when their host shadow changes)
   // A few device copies per table, each remembering the host array it was filled from: a caller that alternates
@@ -257,7 +264,9 @@ Dev base_args(const qoda_ctx *c) {
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.bins = c->d_bins; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
-  a.hist = c->d_hist; a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
+  a.hist = c->d_hist + (c->d_hist ? c->stat_set * (size_t)c->K * c->L * kHistBins : 0);
+  a.sumsq += c->stat_set * (size_t)c->K * c->L;
+  a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
   a.dp_arg = c->d_dp_arg; a.dp_arg_off = c->d_dp_arg_off;
   a.status = c->d_status; a.eta = c->d_eta;
   a.seed = c->seed;
@@ -386,8 +395,18 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
   if (c->scope == kScopeBucket) {
     cached = true;   // the bucket norms are computed by the quantize kernel itself, which also gathers the fit's
                      // statistics of these nodes: their histograms and running maxima start from zero
-    const size_t n0 = (size_t)node0 * c->L, nn = (size_t)nnodes * c->L;
-    LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
+    const size_t n0 = (size_t)node0 * c->L, nn = (size_t)nnodes * c->L, KL = (size_t)c->K * c->L;
+    if (c->stat_swap && is_captured(s)) c->stat_swap = false;
+    if (c->stat_swap && nnodes == c->K && (c->prof_mask & (1u << kIdZero)) == 0u) {
+      c->stat_swap = false;   // until all is enqueued
+      a.hist_old = a.hist;
+      a.sumsq_old = a.sumsq;
+      c->stat_set = 1 - c->stat_set;
+      a.hist = c->d_hist + c->stat_set * KL * kHistBins;
+      a.sumsq = c->d_sumsq + c->stat_set * KL;
+    } else {
+      LAUNCH(c, kIdZero, s, launch_zero_stats(a.hist + n0 * kHistBins, a.sumsq + n0, nn, s));
+    }
     use_runs(c, a, kRunsQuantize, nnodes);
   }
   if (!cached && use_small(c, nnodes)) {
@@ -402,6 +421,7 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
   }
   LAUNCH(c, kIdQuantize, s, launch_quantize(a, c->planes_mask, s));
   LAUNCH(c, kIdDeltaFinalize, s, launch_delta_finalize(a, s));
+  if (a.hist_old) c->stat_swap = true;
   return QODA_OK;
 }
 
@@ -539,7 +559,8 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_type_points, (size_t)c->M));
   A(dev_alloc(&c->d_partial, KG));
   A(dev_alloc(&c->d_dpartial, KG));
-  A(dev_alloc(&c->d_sumsq, KL));
+  const size_t sets = c->scope == kScopeBucket && KL <= qoda_ctx::kStatPairs && c->L < 65535 /* grid.y of k_delta_finalize */ ? 2 : 1;
+  A(dev_alloc(&c->d_sumsq, sets * KL));
   A(dev_alloc(&c->d_delta, (size_t)c->K));
   A(dev_alloc(&c->d_norm, KL));
   A(dev_alloc(&c->d_inv, KL));
@@ -560,8 +581,10 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   if (c->scope == kScopeBucket) {   // the quantize pass gathers the fit's statistics itself
     A(dev_alloc(&c->d_type_exp_next, (size_t)c->M));
     A(dev_alloc(&c->d_type_skip, (size_t)c->M));
-    A(dev_alloc(&c->d_hist, KL * kHistBins));
-    if (e == hipSuccess) A(hipMemset(c->d_hist, 0, KL * kHistBins * sizeof(unsigned int)));
+    A(dev_alloc(&c->d_hist, sets * KL * kHistBins));
+    if (e == hipSuccess) A(hipMemset(c->d_hist, 0, sets * KL * kHistBins * sizeof(unsigned int)));
+    if (e == hipSuccess) A(hipMemset(c->d_sumsq, 0, sets * KL * sizeof(double)));
+    c->stat_swap = sets == 2;
   }
   {
     const bool one_width = (c->planes_mask & (c->planes_mask - 1u)) == 0u;
@@ -697,6 +720,7 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
       // from the statistics the last quantize pass of every node gathered: pool, fit (with the scale they were gathered
       // under), then the scale for the next pass from the gathered maxima
       hipStream_t s = static_cast<hipStream_t>(stream);
+      if (c->stat_swap && is_captured(s)) c->stat_swap = false;
       Dev a = base_args(c);
       a.round = round;
       if (fit_in_one(c)) {
@@ -726,7 +750,8 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
     a.round = round;
     if (c->scope == kScopeBucket) {
       // two passes over the gradient: the scale of the weights, then the weighted histogram
-      LAUNCH(c, kIdZero, s, launch_zero_stats(c->d_hist, c->d_sumsq, KL, s));
+      if (c->stat_swap && is_captured(s)) c->stat_swap = false;
+      LAUNCH(c, kIdZero, s, launch_zero_stats(a.hist, a.sumsq, KL, s));
       use_runs(c, a, kRunsFit, c->K);
       LAUNCH(c, kIdBucketMax, s, launch_bucket_max(a, s));
       LAUNCH(c, kIdFitTypemax, s, launch_fit_typemax(a, s));
@@ -844,7 +869,8 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     // the bucket norms are computed by the quantize kernel, which also gathers this node's fit statistics into the
     // context (state of the next fit, not scratch): their histograms and running maxima start from zero
     const size_t n0 = (size_t)node * c->L, nn = (size_t)c->L;
-    LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_stats(c->d_hist + n0 * kHistBins, c->d_sumsq + n0, nn, s));
+    if (c->stat_swap && is_captured(s)) c->stat_swap = false;
+    LAUNCH_IF(c, of_context, kIdZero, s, launch_zero_stats(a.hist + n0 * kHistBins, a.sumsq + n0, nn, s));
     use_runs(c, a, kRunsQuantize, 1);
   } else {
     a.sumsq = nb.sumsq;
@@ -1165,12 +1191,12 @@ int qoda_read_buffer(qoda_ctx *c, int32_t which, void *dst, size_t bytes, void *
     const void *src = nullptr;
     size_t have = 0;
     switch (which) {
-      case QODA_BUF_SUMSQ: src = c->d_sumsq; have = KL * sizeof(double); break;
+      case QODA_BUF_SUMSQ: src = c->d_sumsq + c->stat_set * KL; have = KL * sizeof(double); break;
       case QODA_BUF_NORM: src = c->d_norm; have = KL * sizeof(float); break;
       case QODA_BUF_INV: src = c->d_inv; have = KL * sizeof(float); break;
       case QODA_BUF_DELTA: src = c->d_delta; have = c->K * sizeof(double); break;
       case QODA_BUF_HIST:
-        src = c->scope == kScopeBucket ? c->d_hist : c->d_hist_last;
+        src = c->scope == kScopeBucket ? c->d_hist + c->stat_set * KL * kHistBins : c->d_hist_last;
         have = src ? KL * kHistBins * sizeof(unsigned int) : 0;
         break;
       case QODA_BUF_POOLED: src = c->d_pooled; have = (size_t)c->M * kGridPoints * sizeof(unsigned long long); break;

@@ -74,6 +74,8 @@ struct Dev {
   int *walk;          // [M] some interior level of the type lies inside a bin, or not above the first one
   unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit
   unsigned int *hist_last;     // [K*L*2048] layer and vector scope: the histogram of the last fit
+  unsigned int *hist_old;      // bucket scope: statistics that k_delta_finalize clears (this and the next); or nullptr
+  double *sumsq_old;
   const int *type_first;       // [M+1] the layers of type m are type_layers[type_first[m] .. type_first[m+1]-1]
   const int3 *type_layers;     // [L] (layer, its first tile, its tiles)
   unsigned long long *pooled;  // [M*257]

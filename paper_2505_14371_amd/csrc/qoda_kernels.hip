@@ -315,11 +315,12 @@ __global__ void k_zero_u32(unsigned int *p, size_t n) {
 }
 
 // Bucket scope: the fit statistics of n (node, layer) pairs start from zero.
-__global__ void __launch_bounds__(kThreads) k_zero_stats(unsigned int *hist, double *stat) {
-  unsigned long long *h = reinterpret_cast<unsigned long long *>(hist + (size_t)blockIdx.x * kHistBins);
+__device__ __forceinline__ void zero_stats(unsigned int *hist, double *stat, size_t pair) {
+  unsigned long long *h = reinterpret_cast<unsigned long long *>(hist + pair * kHistBins);
   for (int j = threadIdx.x; j < kGridPoints; j += kThreads) h[j] = 0ull;
-  if (threadIdx.x == 0) stat[blockIdx.x] = 0.0;
+  if (threadIdx.x == 0) stat[pair] = 0.0;
 }
+__global__ void __launch_bounds__(kThreads) k_zero_stats(unsigned int *hist, double *stat) { zero_stats(hist, stat, blockIdx.x); }
 
 // ------------------------------------------------------------------------------------------------ pass 1
 // Sum of squares of one tile in fp64 (Sec. 2.2, L2 norm before the root), optionally with the histogram of the
@@ -1452,9 +1453,14 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
 }
 
 // delta_k: slot j takes the node's tiles j, j+256, ... (all layers, in order), then the halving tree.
+// Bucket scope, with a.hist_old: further workgroups clear the statistics of the pass before, for the next one.
 __global__ void __launch_bounds__(kThreads) k_delta_finalize(Dev a) {
   __shared__ double red[kThreads];
   const int k = a.node0 + blockIdx.x;
+  if (blockIdx.y != 0) {
+    zero_stats(a.hist_old, a.sumsq_old, (size_t)k * a.L + blockIdx.y - 1);
+    return;
+  }
   const int kr = k - a.row0;   // row in the per-node scratch and pointer tables
   const double *p = a.dpartial + (size_t)kr * a.G;
   double acc = 0.0;
@@ -2579,7 +2585,8 @@ hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStre
 }
 
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes), dim3(kThreads), 0, s, a);
+  // the layers go into grid.y: up to 65534 of them (the caller sees to it)
+  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes, a.hist_old ? 1 + a.L : 1), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
