@@ -1706,7 +1706,11 @@ __global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
   const long long O = (long long)tile.y * 8 + part * noct_wg + w / (8 / NB);
   const bool live = O < ((m.nblk + 7) >> 3);
   Part<C1, NB, BUCKET> first = {};
-  if (live) first.load(a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)), piece, i);   // before the tables are there
+  const unsigned char *octet = live ? a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)) : nullptr;
+  // before the tables are there; a whole octet of wide codes after it (C1 = 7, K = 6, 1095 tiles: mean 35.7 us early, 34.7 late;
+  // narrow ones: C1 = 5, K = 1, 1024 tiles, a quantize call and a mean 50.8 early, 51.6 late; C1 = 4, K = 8, 9207 tiles 198.1, 199.6)
+  constexpr bool EARLY = NB < 8 || C1 <= 6;
+  if (EARLY && live) first.load(octet, piece, i);
   const int TS = 1 << C1;
   double new_acc = 0.0;
   if (MODE == kDecodeUpdateScalars) new_acc = sum_distances(a);   // every wave computes what k_step_scalars computes
@@ -1733,6 +1737,7 @@ __global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
   if (MODE == kDecodeExtrapolate) gamma = a.gamma_in[0];
   float sum[4 * NB];
   if (live) {
+    if (!EARLY) first.load(octet, piece, i);
     if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
     else decode_part<C1, MODE, false, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
   }
