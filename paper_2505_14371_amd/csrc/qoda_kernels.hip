@@ -1290,8 +1290,8 @@ struct BucketHist {
 };
 
 // Bound by the vector ALU (35.7 instructions per coordinate) together with what its waves wait for: shared memory is busy 45 % of
-// the time, and a wave spends 44 % of its own waiting for a value.  Up to 32 levels (codes of 6 bits) four waves a SIMD: 128
-// registers (none spilled up to 16 levels) and 38.4 to 39.6 KiB of shared memory a workgroup, of which the table by grid bin is 4
+// the time, and a wave spends 44 % of its own waiting for a value.  Up to 64 levels (codes of 7 bits) four waves a SIMD: 128
+// registers (none spilled up to 16 levels) and 38.1 to 39.4 KiB of shared memory a workgroup, of which the table by grid bin is 4
 // KiB; so a run has at most 4 tiles.  Wider codes have larger tables, three workgroups a CU, and the compiler takes 160 to 166
 // registers.  What made it 151 M coordinates, K = 8, 8 levels 1345 -> 1252 us and 3112 tiles, 16 levels 87 -> 79 us: one 128-bit
 // table read per coordinate instead of two reads one after the other; the buckets' scales in registers, broadcast along the rows
