@@ -12,6 +12,7 @@
 // Arithmetic that feeds an integer decision (level index, rounding direction, packed bits, histogram bin) is
 // written as single IEEE operations with contraction off, so that it has one well-defined result.
 
+#include "qoda_choices.h"
 #include "qoda_kernels.h"
 
 namespace qoda {
@@ -186,6 +187,9 @@ __device__ __forceinline__ void load_tables(const Dev &a, int type, int S, int w
   if (t == 0) *reinterpret_cast<v4f *>(&bins[kThreads]) = last;
   if (walk && t < S) tab[t] = make_float4(lj, rj, t + 1 < S ? ln : __builtin_inff(), u2f((unsigned int)t));   // rgap is 0 from S-1 on
 }
+
+// The lane's number in its wave, from no register that would have to be kept for it.
+__device__ __forceinline__ int lane_id() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
 // A value of lane bb of the lane's row of 16 lanes.
 template <int BB>
@@ -1553,7 +1557,8 @@ __global__ void __launch_bounds__(kThreads) k_alt_finalize(Dev a) {
 // DECODE + K-way mean (+ eq. (ODA) update unless MODE is kDecodeMean): one pass over Y, X_1 and the K messages.
 // A wave takes NB = 8, 4 or 2 consecutive blocks of an octet: 4 * NB running sums per lane, the codes of K records, then the
 // blocks of state.
-// Under kDecodeUpdateAlt the lane also rebuilds X_t = X_1 + eta_prev * Y_t; its differences X_t - X_{t+1} are left in sum.
+// Under kDecodeUpdateAlt the lane also rebuilds X_t = X_1 + eta_prev * Y_t; its differences X_t - X_{t+1} go on the slot's chain
+// (CHAIN) or are left in diffs.
 
 // Words that hold 4*NB codes from any bit of a record where a part can start (a multiple of 4*NB*C1 bits).
 template <int C1, int NB>
@@ -1613,12 +1618,15 @@ struct Part {
   }
 };
 
-template <int C1, int MODE, bool FAST, bool BUCKET, int NB>
+template <int C1, int MODE, bool FAST, bool BUCKET, int NB, bool CHAIN>
 __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, int l, long long O, int part, const float *T, int i,
-                                            float eta, float gamma, float eta_prev, Part<C1, NB, BUCKET> cur, float (&sum)[4 * NB]) {
+                                            float eta, float gamma, float eta_prev, Part<C1, NB, BUCKET> cur,
+                                            float (&diffs)[MODE == kDecodeUpdateAlt ? 4 * NB : 1], float &chain) {
   constexpr int TS = 1 << C1;   // table entries per node, indexed by code = sign | h << 1
   constexpr long long OS = 256 * C1 + (BUCKET ? 64 : 0);   // bytes per octet (bucket scope: codes + 16 norms)
   const long long boff = m.body_off + O * OS;
+  float sum[4 * NB];
+  if (CHAIN) cur.load(a.msgs_in[0] + boff, part, i);   // (and the sums in here: with both outside the compiler takes 200 registers)
   for (int k = 0; k < a.K; ++k) {   // cur: node k's, requested before; the next node's are requested now
     Part<C1, NB, BUCKET> nxt = {};
     if (k + 1 < a.K) nxt.load(a.msgs_in[k + 1] + boff, part, i);
@@ -1632,11 +1640,12 @@ __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, in
     }
     cur = nxt;
   }
+  const int lane = CHAIN ? i : lane_id();   // i, which the loop above need not keep (with two octets a wave keeping it is cheaper)
 #pragma unroll
   for (int bb = 0; bb < NB; ++bb) {
     const long long B = O * 8 + part * NB + bb;
     if (FAST || B < m.nblk) {
-      const long long e = B * kBlockCoords + 4 * i;
+      const long long e = B * kBlockCoords + 4 * lane;
       const long long dlim = FAST ? e + 4 : m.d;   // FAST: the whole block is inside the layer
       float mean[4];
 #pragma unroll
@@ -1668,27 +1677,32 @@ __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, in
           xn[j] = x1[j] + ey;
           const float gm = gamma * mean[j];
           xh[j] = xn[j] - gm;
-          if (MODE == kDecodeUpdateAlt) sum[4 * bb + j] = xt - xn[j];
+          if (MODE == kDecodeUpdateAlt) {
+            const float diff = xt - xn[j];
+            if (CHAIN) chain = __builtin_fmaf(diff, diff, chain);
+            else diffs[4 * bb + j] = diff;
+          }
         }
         store4(a.y[l], e, dlim, y);
         store4(a.x_half[l], e, dlim, xh);
         if (a.x_next) store4(a.x_next[l], e, dlim, xn);
       }
-    } else if (MODE == kDecodeUpdateAlt) {
+    } else if (MODE == kDecodeUpdateAlt && !CHAIN) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) sum[4 * bb + j] = 0.0f;
+      for (int j = 0; j < 4; ++j) diffs[4 * bb + j] = 0.0f;
     }
   }
 }
 
 // The decode pass runs best in short workgroups (measured against one tile per workgroup of four waves with two octets
 // each: 6 % faster at K = 8, 4 % at K = 16): a workgroup takes a few consecutive octets of a tile (kDecodeOctets), 8 / NB waves
-// an octet.  How many blocks a wave takes is chosen by decode_blocks.  Only the (Alt) variant keeps a workgroup to the tile
-// (eight waves): its squared-distance term is defined per slot and tile; a slot's chain runs through the two octets of a pair of
-// waves, the odd one goes on from the even one's sum.  (A tile in four waves, two octets each, one after the other: 184 M
-// coordinates, K = 4, 128 levels 185 us, now 172.)
+// an octet.  How many blocks a wave takes is chosen by decode_blocks.  Only the (Alt) variant keeps a workgroup to the tile: its
+// squared-distance term is defined per slot and tile.  It has eight waves, where a slot's chain goes from the even wave of a pair to
+// the odd one, or (NB = 16) four, each with two octets, one after the other; alt_blocks chooses.  Four waves a SIMD (128
+// registers) are two tiles of eight waves on a CU: with one register more it is one, under bucket scope with 8 and 9 bits 11 k tiles,
+// K = 4 791 and 813 us, now 643 and 672.
 template <int C1, int MODE, bool BUCKET, int NB>
-__global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
+__global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDecodeUpdateAlt ? 1 : (BUCKET && NB > 8) ? 3 : 4) k_decode(Dev a) {
   extern __shared__ float T[];   // [K][2^C1]: +-norm_k * level_h (bucket scope: +-level_h) from the K message headers
   constexpr bool ALT = MODE == kDecodeUpdateAlt;
   __shared__ double red[ALT ? kThreads : 1];
@@ -1702,14 +1716,15 @@ __global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int i = t & 63;
-  const int piece = w % (8 / NB);
-  const long long O = (long long)tile.y * 8 + part * noct_wg + w / (8 / NB);
-  const bool live = O < ((m.nblk + 7) >> 3);
-  Part<C1, NB, BUCKET> first = {};
+  constexpr int PB = NB < 8 ? NB : 8;   // blocks of a wave's part
+  const int piece = w % (8 / PB);
+  const long long O = (long long)tile.y * 8 + part * noct_wg + w * NB / 8, noct = (m.nblk + 7) >> 3;
+  const bool live = O < noct;
+  Part<C1, PB, BUCKET> first = {};
   const unsigned char *octet = live ? a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)) : nullptr;
   // before the tables are there; a whole octet of wide codes after it (C1 = 7, K = 6, 1095 tiles: mean 35.7 us early, 34.7 late;
   // narrow ones: C1 = 5, K = 1, 1024 tiles, a quantize call and a mean 50.8 early, 51.6 late; C1 = 4, K = 8, 9207 tiles 198.1, 199.6)
-  constexpr bool EARLY = NB < 8 || C1 <= 6;
+  constexpr bool EARLY = NB < 8 || (NB == 8 && C1 <= 6);
   if (EARLY && live) first.load(octet, piece, i);
   const int TS = 1 << C1;
   double new_acc = 0.0;
@@ -1735,21 +1750,29 @@ __global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
   }
   if (ALT) eta_prev = a.eta[2];
   if (MODE == kDecodeExtrapolate) gamma = a.gamma_in[0];
-  float sum[4 * NB];
-  if (live) {
+  float diffs[ALT ? 4 * PB : 1], accx = 0.0f;
+  if constexpr (NB > 8) {
+    for (int oo = 0; oo < NB / 8; ++oo) {
+      const long long Oc = O + oo;
+      if (Oc >= noct) break;
+      if ((Oc + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
+      else decode_part<C1, MODE, false, BUCKET, PB, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
+    }
+    const double total = block_tree((double)accx, red);
+    if (t == 0) a.dpartial[g] = total;
+  } else if (live) {
     if (!EARLY) first.load(octet, piece, i);
-    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
-    else decode_part<C1, MODE, false, BUCKET, NB>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, sum);
+    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
+    else decode_part<C1, MODE, false, BUCKET, PB, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
   }
-  if (ALT) {
+  if (ALT && NB == 8) {
     // a slot's fp32 fused chain in increasing coordinate: even waves first
     float *chain = reinterpret_cast<float *>(red);
     const int sl = (w >> 1) * 64 + i;
-    float accx = 0.0f;
     if (!(w & 1)) {
       if (live) {
 #pragma unroll
-        for (int j = 0; j < 4 * NB; ++j) accx = __builtin_fmaf(sum[j], sum[j], accx);
+        for (int j = 0; j < 4 * PB; ++j) accx = __builtin_fmaf(diffs[j], diffs[j], accx);
       }
       chain[sl] = accx;
     }
@@ -1758,7 +1781,7 @@ __global__ void __launch_bounds__(2 * kThreads) k_decode(Dev a) {
       accx = chain[sl];
       if (live) {
 #pragma unroll
-        for (int j = 0; j < 4 * NB; ++j) accx = __builtin_fmaf(sum[j], sum[j], accx);
+        for (int j = 0; j < 4 * PB; ++j) accx = __builtin_fmaf(diffs[j], diffs[j], accx);
       }
     }
     __syncthreads();   // the chains' room becomes that of the 256 slots
@@ -2635,8 +2658,10 @@ static void launch_decode_blocks(const Dev &a, size_t lds_bytes, hipStream_t s) 
 
 template <int C1, int MODE, bool BUCKET>
 static void launch_decode_mode(const Dev &a, size_t lds_bytes, hipStream_t s) {
-  if constexpr (MODE == kDecodeUpdateAlt) launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
-  else if constexpr (MODE == kDecodeUpdateScalars) launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s);   // few tiles
+  if constexpr (MODE == kDecodeUpdateAlt) {
+    if (alt_blocks(a.G, a.K, BUCKET, C1) == 16) launch_decode_blocks<C1, MODE, BUCKET, 16>(a, lds_bytes, s);
+    else launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
+  } else if constexpr (MODE == kDecodeUpdateScalars) launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s);   // few tiles
   else switch (decode_blocks(a.G, a.K, MODE, BUCKET)) {
     case 2: launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s); break;
     case 4: launch_decode_blocks<C1, MODE, BUCKET, 4>(a, lds_bytes, s); break;

@@ -3,6 +3,7 @@
 // them.  "Device" memory is host memory, filled with a pattern when it is allocated.  Launches are recorded by name; the only
 // effect they model is that of the level fit on its histogram: the norm pass adds to it, its consumer moves it away.
 #include "../paper_2505_14371_amd/csrc/qoda_api.hip"
+#include "../paper_2505_14371_amd/csrc/qoda_choices.h"
 
 #include <cstdlib>
 #include <functional>
@@ -28,6 +29,7 @@ void stand_in_reset() { g_log.clear(); g_fail_at = -1; }
 const char *stand_in_log() { return g_log.c_str(); }
 void stand_in_fail_at(int n) { g_fail_at = n; }
 void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); }
+int stand_in_alt_blocks(int G, int K, int bucket, int bits) { return alt_blocks(G, K, bucket != 0, bits); }
 void stand_in_replay() { for (auto &f : g_graph) f(); }
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }

@@ -118,3 +118,29 @@ def test_distance_of_the_iterates(oracle, S, scope):
         got_y, got_x = m.layers(m.y), m.layers(m.x_half)
         for l in range(L):
             assert np.array_equal(got_y[l], y[l]) and np.array_equal(got_x[l], x_half[l])
+
+
+@pytest.mark.parametrize("scope, tiles, K", [(0, 513, 2), (0, 768, 4), (0, 1000, 2), (2, 530, 1), (2, 768, 3)])
+@pytest.mark.parametrize("S", [4, 16, 128, 256])
+def test_tiles_in_four_waves_equal_tiles_in_eight(S, scope, tiles, K):
+    """eq. (Alt): a model whose tiles are cut into four waves, and the same with an empty-handed tensor behind it (all zeros: its
+    tiles add 0 to their slots), which is cut into eight: iterates and the sum of their squared distances."""
+    sizes = [16384 * (tiles - len(RAGGED)) - 700] + RAGGED
+    got = []
+    for more in ([], [16384 * 600]):
+        m = gm(sizes + more, [0] * (len(sizes) + len(more)), [S], K, seed=4, norm_scope=scope)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(1)
+        n = int(m.off[len(sizes) - 1]) + sizes[-1]
+        rows = [torch.randn(n, device="cuda", generator=g) for _ in range(K + 1)]
+        for k in range(K):
+            m.grad_flat[k][:n] = rows[k]
+        m.x1[:n] = rows[K]
+        for t in (1, 2, 3):
+            m.quantize_all_alt(t)
+            m.step_alt(0.25)
+        used = torch.cat([torch.arange(int(o), int(o) + s) for o, s in zip(m.off, sizes)])
+        got.append([m.alt_sums.cpu().numpy()] + [t.cpu()[used].numpy() for t in (m.y, m.x_half, m.x_next)])
+    assert got[0][0][1] > 0
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
