@@ -6,6 +6,67 @@
 
 namespace qoda {
 
+// Blocks of an octet that a wave of the other decode passes takes, for G tiles: 2, 4 or 8.  While its waves do not fill the device a
+// pass is a chain of loads and table reads, K nodes one after the other: the shorter a wave's part the better (G up to 256, 128 for
+// the mean).  Then a wave's fixed work and its loads of part of a word weigh more, and whole octets are best, except: (1) with one
+// or two nodes there is no chain to speak of, and many short waves hide the loads and stores of the iterates; (2) wide codes, and bucket
+// norms, take more registers for whole octets (80 to 92 under bucket scope: five or six waves a SIMD), so that half octets win
+// from two thirds of a fill on; (3) where whole octets just fill the device (1100 to 1500 tiles, with bucket norms 513 to 640) they win;
+// (4) with decode tables above 8 KiB a part of two blocks serves half the octets that the others serve with one set of tables.
+// us of a call with 8 / 4 / 2 blocks:
+//   mean         5 bits, K = 4: 64 5.6 / 4.8 / 4.3, 128 5.8 / 5.9 / 5.8, 256 6.8 / 7.7 / 8.4; 9 bits, K = 2: 256
+//                7.2 / 6.7 / 7.3, 600 13.4 / 14.9 / 15.8, 1000 23.5 / 20.9 / 23.4; bucket norms, 8 bits, K = 8:
+//                600 26.2 / 29.0 / 30.1, 1000 46.0 / 42.8 / 47.0, 6400 279 / 250 / 275
+//   extrapolate  5 bits, K = 8: 200 16.6 / 14.2 / 14.2, 320 18.9 / 16.9 / 18.8, 512 22.1 / 21.8 / 24.3, 600 25.4
+//                / 27.9 / 28.9; K = 16: 384 26.3 / 25.8 / 30.2, 512 30.2 / 31.1 / 35.5; bucket norms, 8 bits, K
+//                = 4: 600 23.6 / 26.3 / 25.4, 700 33.0 / 28.2 / 28.4, 3200 128 / 114 / 113; 5 bits, K = 8: 700
+//                29.6 / 32.0 / 34.9, 800 38.6 / 34.5 / 40.6, 1300 51.1 / 51.6 / 60.5
+//   update       5 bits, K = 1: 600 33.5 / 35.9 / 29.4, 2400 119 / 120 / 108; K = 2: 600 34.2 / 37.2 / 31.5, 3200
+//                155 / 152 / 146; K = 8: 200 23.8 / 20.1 / 18.7, 320 27.4 / 26.0 / 26.9, 450 33.3 / 35.0 / 32.1,
+//                600 40.8 / 45.0 / 41.3, 3200 188 / 188 / 183; 9 bits, K = 8: 256 28.1 / 24.8 / 24.5, 512 41.2 /
+//                41.8 / 46.0, 1000 86.5 / 79.9 / 86.9; bucket norms, 8 bits, K = 4: 600 37.5 / 41.5 / 37.5, 800
+//                56.2 / 51.3 / 49.7, 3200 198 / 186 / 172; 5 bits, K = 8: 600 41.6 / 45.8 / 44.0, 800 60.0 /
+//                56.2 / 57.2, 1300 82.2 / 85.5 / 86.0
+inline int decode_blocks(int G, int K, int mode, bool bucket, int bits) {
+  const bool wide = bits >= 7, tables = (long long)K << bits > 2048;   // tables: 8 KiB
+  const int full = bucket && bits >= 6 ? 640 : 750;                   // where whole octets need a second fill
+  if (mode == kDecodeMean) {
+    if (G <= 128) return tables && G > 64 ? 4 : 2;
+    if (G <= 160) return bits >= 8 && K > 2 && !tables ? 2 : 4;
+    if (K == 1) return (G > 512 && G <= (!bucket ? 850 : wide ? 640 : 750)) || (bucket && !wide && bits != 5 && G > 1000) ? 8 : 4;
+    if (tables ? G <= (bits == 9 ? 320 : 200) : K == 2 && G <= (wide ? 512 : 256)) return 4;
+    if (bucket) return (wide ? G > (K <= 8 ? full : 900) : K == 2 && G > 850 && G <= 1100) ? 4 : 8;
+    return K == 2 && bits >= 8 && G > 900 ? 4 : 8;
+  }
+  const bool update = mode == kDecodeUpdate;
+  if (update) {
+    if (G <= 256 || K <= 2) return 2;
+    if (tables) { if (G <= 400) return 4; }
+    else if (wide && K <= (bits == 7 ? 4 : 8)) return K >= 4 && G > 512 && G <= (bucket ? full : 850) ? 8 : 2;
+    else if (K <= 4 ? G <= 512 || (G > 2000 && G <= 5600) : K <= 8 && G > 330 && G <= 450) return 2;
+    else if (K > 4 && G <= 384) return 4;
+  } else {
+    if (G <= (tables || K > 16 ? 160 : 256)) return 2;
+    if (G <= (wide || K <= 8 ? 512 : 384)) return 4;
+    if (K == 1) return G > (bucket ? full : 1100) ? 2 : 8;
+  }
+  // from about one fill on
+  if (tables && G > 1024 && G <= 1150) return 8;
+  if (bucket && bits >= 6) return G > full ? 4 : 8;
+  if (bucket) return (G > full && G <= 900) || (K <= (update ? 16 : 8) && G > full && (G <= 1100 || G > 1500)) ? 4 : 8;
+  if (tables) return (G > 900 && G <= 1024) || G > 1800 ? 4 : 8;
+  return K <= 8 && G > 2400 && (update || bits >= 5) ? 4 : 8;
+}
+
+// Whether the mean in whole octets requests node 0's record before it sets up its tables.  Codes of up to 6 bits, time with that
+// against without, mean over 200 to 6400 tiles: K = 1 and 2, 3 to 5 bits 0.96 to 0.98; K = 3 and 5, 4 to 6 bits 0.985 to 1.0 (from 1200
+// tiles on 0.93 to 0.99); K = 8 to 16 1.00 to 1.015; bucket norms, K = 1 0.97, K = 2 0.97 to 1.005, K = 3 to 16 1.01 to 1.045.  Other
+// passes: 1.005 to 1.03 for every K; wider codes: 1.0 to 1.01.  With 5 bits and bucket norms it costs the sixth wave of a SIMD (81
+// registers).
+constexpr bool mean_early(int G, int K, bool bucket, int bits) {
+  return bits <= 6 && (K <= 2 ? !bucket || bits != 5 : !bucket && K <= 6 && G > 900);
+}
+
 // Blocks of a tile's 64 that a wave of the (Alt) decode pass takes, one workgroup a tile: 8 (eight waves) or 16 (four waves, two
 // octets one after the other).  Two workgroups of eight waves fit a CU, four of four waves (three under bucket scope, and with codes
 // of 6 bits and more a few spilled registers): just beyond 512 tiles, where the second half of a launch in eight waves is mostly

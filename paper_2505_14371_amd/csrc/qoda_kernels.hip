@@ -1618,7 +1618,8 @@ struct Part {
   }
 };
 
-template <int C1, int MODE, bool FAST, bool BUCKET, int NB, bool CHAIN>
+// EARLY: cur is node 0's part already, requested before the tables were set up.
+template <int C1, int MODE, bool FAST, bool BUCKET, int NB, bool EARLY, bool CHAIN>
 __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, int l, long long O, int part, const float *T, int i,
                                             float eta, float gamma, float eta_prev, Part<C1, NB, BUCKET> cur,
                                             float (&diffs)[MODE == kDecodeUpdateAlt ? 4 * NB : 1], float &chain) {
@@ -1626,7 +1627,7 @@ __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, in
   constexpr long long OS = 256 * C1 + (BUCKET ? 64 : 0);   // bytes per octet (bucket scope: codes + 16 norms)
   const long long boff = m.body_off + O * OS;
   float sum[4 * NB];
-  if (CHAIN) cur.load(a.msgs_in[0] + boff, part, i);   // (and the sums in here: with both outside the compiler takes 200 registers)
+  if (!EARLY) cur.load(a.msgs_in[0] + boff, part, i);
   for (int k = 0; k < a.K; ++k) {   // cur: node k's, requested before; the next node's are requested now
     Part<C1, NB, BUCKET> nxt = {};
     if (k + 1 < a.K) nxt.load(a.msgs_in[k + 1] + boff, part, i);
@@ -1696,12 +1697,13 @@ __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, in
 
 // The decode pass runs best in short workgroups (measured against one tile per workgroup of four waves with two octets
 // each: 6 % faster at K = 8, 4 % at K = 16): a workgroup takes a few consecutive octets of a tile (kDecodeOctets), 8 / NB waves
-// an octet.  How many blocks a wave takes is chosen by decode_blocks.  Only the (Alt) variant keeps a workgroup to the tile: its
+// an octet.  How many blocks a wave takes is chosen by decode_blocks.  EARLY: node 0's part is requested before the tables are set
+// up (parts of octets always; whole ones where mean_early says so).  Only the (Alt) variant keeps a workgroup to the tile: its
 // squared-distance term is defined per slot and tile.  It has eight waves, where a slot's chain goes from the even wave of a pair to
 // the odd one, or (NB = 16) four, each with two octets, one after the other; alt_blocks chooses.  Four waves a SIMD (128
 // registers) are two tiles of eight waves on a CU: with one register more it is one, under bucket scope with 8 and 9 bits 11 k tiles,
 // K = 4 791 and 813 us, now 643 and 672.
-template <int C1, int MODE, bool BUCKET, int NB>
+template <int C1, int MODE, bool BUCKET, int NB, bool EARLY>
 __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDecodeUpdateAlt ? 1 : (BUCKET && NB > 8) ? 3 : 4) k_decode(Dev a) {
   extern __shared__ float T[];   // [K][2^C1]: +-norm_k * level_h (bucket scope: +-level_h) from the K message headers
   constexpr bool ALT = MODE == kDecodeUpdateAlt;
@@ -1721,11 +1723,7 @@ __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDec
   const long long O = (long long)tile.y * 8 + part * noct_wg + w * NB / 8, noct = (m.nblk + 7) >> 3;
   const bool live = O < noct;
   Part<C1, PB, BUCKET> first = {};
-  const unsigned char *octet = live ? a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)) : nullptr;
-  // before the tables are there; a whole octet of wide codes after it (C1 = 7, K = 6, 1095 tiles: mean 35.7 us early, 34.7 late;
-  // narrow ones: C1 = 5, K = 1, 1024 tiles, a quantize call and a mean 50.8 early, 51.6 late; C1 = 4, K = 8, 9207 tiles 198.1, 199.6)
-  constexpr bool EARLY = NB < 8 || (NB == 8 && C1 <= 6);
-  if (EARLY && live) first.load(octet, piece, i);
+  if (EARLY && live) first.load(a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)), piece, i);
   const int TS = 1 << C1;
   double new_acc = 0.0;
   if (MODE == kDecodeUpdateScalars) new_acc = sum_distances(a);   // every wave computes what k_step_scalars computes
@@ -1755,15 +1753,14 @@ __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDec
     for (int oo = 0; oo < NB / 8; ++oo) {
       const long long Oc = O + oo;
       if (Oc >= noct) break;
-      if ((Oc + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
-      else decode_part<C1, MODE, false, BUCKET, PB, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
+      if ((Oc + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
+      else decode_part<C1, MODE, false, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
     }
     const double total = block_tree((double)accx, red);
     if (t == 0) a.dpartial[g] = total;
   } else if (live) {
-    if (!EARLY) first.load(octet, piece, i);
-    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
-    else decode_part<C1, MODE, false, BUCKET, PB, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
+    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
+    else decode_part<C1, MODE, false, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
   }
   if (ALT && NB == 8) {
     // a slot's fp32 fused chain in increasing coordinate: even waves first
@@ -2628,44 +2625,30 @@ hipError_t launch_step_scalars(const Dev &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// How many blocks of an octet a wave of the decode pass takes, for G tiles.  While the waves do not fill the device the pass
-// is a chain of loads and table reads, K nodes one after the other: the shorter a wave's part the better.  Beyond about 300
-// tiles whole octets have the fewest loads; the passes that read and write iterates gain again from half octets in the
-// largest launches (more waves with loads in flight), under bucket scope from 700 tiles on.  us with 8 / 4 / 2 blocks, S = 16:
-//   update      K = 4: 4 tiles 9.4 / 7.1 / 5.8, 64 11.8 / 8.9 / 7.3, 160 18.2 / 14.1 / 12.6, 256 20.5 / 18.7 / 16.4, 400 27.5 / 26.8 / 24.9, 512
-//               31.7 / 32.1 / 29.8; K = 8: 64 16.6 / 12.7 / 10.5, 256 23.2 / 21.4 / 19.5, 320 27.7 / 26.0 / 26.6, 400 32.6 / 32.2 / 30.3, 512 36.1
-//               / 36.8 / 35.8, 600 40.4 / 45.0 / 41.3; K = 16: 256 30.8 / 28.8 / 26.8, 320 34.2 / 32.8 / 35.4, 400 39.3 / 39.9 / 40.0; with 8 / 4,
-//               K = 8: 800 48.4 / 50.5 (bucket norms 58.3 / 52.2), 1600 95 / 99 (99.5 / 98.7), 3200 186 / 182 (193 / 184), 6400 366 / 353
-//               (370 / 360); K = 4: 20000 1056 / 1024 (1050 / 1023)
-//   extrapolate K = 4: 64 8.8 / 6.3 / 5.5, 256 13.5 / 12.1 / 11.1, 400 17.7 / 15.5 / 16.5, 512 19.0 / 17.7 / 18.6, 600 20.6 / 22.8 / 21.6; K = 8, with
-//               8 / 4: 800 30.6 / 33.3 (39.1 / 34.7), 1600 58 / 62 (65.7 / 63.5), 3200 117 / 113 (125 / 117), 6400 222 / 215 (240 / 225)
-//   mean        K = 4: 64 6.1 / 5.1 / 4.7, 128 6.4 / 5.7 / 5.7, 160 6.5 / 6.0 / 6.1, 256 7.1 / 7.4 / 7.9; K = 8: 64 8.4 / 7.1 / 6.5, 128 8.8 / 8.0 / 7.8, 160
-//               8.8 / 8.6 / 9.2, 256 9.8 / 10.9 / 12.4; with 8 / 4, K = 8: 1600 41 / 45, 6400 154 / 157
-static int decode_blocks(int G, int K, int mode, bool bucket) {
-  if (mode == kDecodeMean) return G <= 128 ? 2 : G <= 160 ? 4 : 8;
-  if (G <= 256 || (mode == kDecodeUpdate && G <= 512 && K <= 8)) return 2;
-  if (G <= (mode == kDecodeUpdate ? 384 : 512)) return 4;
-  return G > (bucket ? 700 : 2400) ? 4 : 8;
-}
-
-template <int C1, int MODE, bool BUCKET, int NB>
+template <int C1, int MODE, bool BUCKET, int NB, bool EARLY>
 static void launch_decode_blocks(const Dev &a, size_t lds_bytes, hipStream_t s) {
   // short workgroups: two octets, four where the K decode tables are large enough to limit the workgroups per CU
   const int oct = MODE == kDecodeUpdateAlt ? 8 : (lds_bytes > 8192 && NB > 2) ? 4 : kDecodeOctets;
   const dim3 grid((unsigned int)a.G * (8 / oct)), block(64 * oct * 8 / NB);
-  hipLaunchKernelGGL((k_decode<C1, MODE, BUCKET, NB>), grid, block, lds_bytes, s, a);
+  hipLaunchKernelGGL((k_decode<C1, MODE, BUCKET, NB, EARLY>), grid, block, lds_bytes, s, a);
 }
 
 template <int C1, int MODE, bool BUCKET>
 static void launch_decode_mode(const Dev &a, size_t lds_bytes, hipStream_t s) {
   if constexpr (MODE == kDecodeUpdateAlt) {
-    if (alt_blocks(a.G, a.K, BUCKET, C1) == 16) launch_decode_blocks<C1, MODE, BUCKET, 16>(a, lds_bytes, s);
-    else launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
-  } else if constexpr (MODE == kDecodeUpdateScalars) launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s);   // few tiles
-  else switch (decode_blocks(a.G, a.K, MODE, BUCKET)) {
-    case 2: launch_decode_blocks<C1, MODE, BUCKET, 2>(a, lds_bytes, s); break;
-    case 4: launch_decode_blocks<C1, MODE, BUCKET, 4>(a, lds_bytes, s); break;
-    default: launch_decode_blocks<C1, MODE, BUCKET, 8>(a, lds_bytes, s);
+    if (alt_blocks(a.G, a.K, BUCKET, C1) == 16) launch_decode_blocks<C1, MODE, BUCKET, 16, false>(a, lds_bytes, s);
+    else launch_decode_blocks<C1, MODE, BUCKET, 8, C1 <= 6>(a, lds_bytes, s);
+  } else if constexpr (MODE == kDecodeUpdateScalars) {
+    launch_decode_blocks<C1, MODE, BUCKET, 2, true>(a, lds_bytes, s);   // few tiles
+  } else {
+    switch (decode_blocks(a.G, a.K, MODE, BUCKET, C1)) {
+      case 2: launch_decode_blocks<C1, MODE, BUCKET, 2, true>(a, lds_bytes, s); return;
+      case 4: launch_decode_blocks<C1, MODE, BUCKET, 4, true>(a, lds_bytes, s); return;
+    }
+    if constexpr (MODE == kDecodeMean && mean_early(1, 1, BUCKET, C1)) {
+      if (mean_early(a.G, a.K, BUCKET, C1)) { launch_decode_blocks<C1, MODE, BUCKET, 8, true>(a, lds_bytes, s); return; }
+    }
+    launch_decode_blocks<C1, MODE, BUCKET, 8, false>(a, lds_bytes, s);
   }
 }
 

@@ -35,7 +35,7 @@ def passes(m, sizes):
     return x1, y, rates.cpu().numpy(), out
 
 
-def check(oracle, sizes, S, K, scope, some=None):
+def check(oracle, sizes, S, K, scope):
     L = len(sizes)
     m = gm(sizes, [0] * L, [S], K, seed=4, norm_scope=scope)
     rng = np.random.default_rng(S)
@@ -62,40 +62,43 @@ def test_parts_of_two_blocks(oracle, S, scope):
 
 
 @pytest.mark.parametrize("scope", [0, 2])
-@pytest.mark.parametrize("tiles, K", [(127, 1), (129, 2), (161, 1), (257, 2), (385, 9), (513, 1)])
-def test_sizes_of_the_choice(oracle, tiles, K, scope):
-    """Up to 128 / 160 tiles the mean takes two / four blocks a wave, up to 256 / 384 or 512 the others."""
-    S = 16 if tiles % 2 else 8
+@pytest.mark.parametrize("tiles, K, S", [(127, 1, 16), (129, 2, 8), (161, 1, 128), (100, 8, 256), (257, 2, 4), (300, 9, 8), (300, 9, 64),
+                                         (320, 3, 256), (385, 9, 16), (513, 1, 64), (450, 3, 32), (650, 5, 128), (800, 3, 16)])
+def test_sizes_of_the_choice(oracle, tiles, K, S, scope):
+    """Parts of two, four and eight blocks in every pass with one node and more, codes of odd and even widths, decode tables on both
+    sides of 8 KiB (the sizes lie on both sides of the lines of decode_blocks)."""
     check(oracle, [16384 * (tiles - len(RAGGED)) - 700] + RAGGED, S, K, scope)
 
 
 @pytest.mark.parametrize("scope", [0, 2])
 @pytest.mark.parametrize("S", [2, 4, 8, 16, 32, 64, 128, 256])
-def test_half_octets_equal_whole_ones(S, scope):
-    """Two models with the same tensor, in the second one repeated until the update takes half octets: the same bits."""
-    n, times = 2048 * 8 * 40 + 1700, 61          # 41 tiles, 2501
+def test_parts_of_octets_equal_whole_ones(S, scope):
+    """The same tensor alone (two blocks a wave), 15 times (whole octets, mostly) and 61 times (half octets): the same bits."""
+    n, K = 2048 * 8 * 40 + 1700, 3          # 41, 615 and 2501 tiles
     got = []
-    for reps in (1, times):
-        m = gm([n] * reps, [0] * reps, [S], 1, seed=4, norm_scope=scope)
+    for reps in (1, 15, 61):
+        m = gm([n] * reps, [0] * reps, [S], K, seed=4, norm_scope=scope)
         g = torch.Generator(device="cuda")
         g.manual_seed(1)
-        x = torch.randn(n, device="cuda", generator=g)
-        for o in m.off[:1] if reps == 1 else m.off:
-            m.grad_flat[0][int(o): int(o) + n] = x
+        for k in range(K):
+            x = torch.randn(n, device="cuda", generator=g)
+            for o in m.off:
+                m.grad_flat[k][int(o): int(o) + n] = x
         m.quantize_all(1)
         rates = torch.tensor([0.37, 0.53], device="cuda")
         m.ctx.step_rates(m.msg[0], m.layer_ptrs(m.x1), m.layer_ptrs(m.y), m.layer_ptrs(m.x_half), rates, None)
         m.ctx.extrapolate(m.msg[0], m.layer_ptrs(m.x1), m.layer_ptrs(m.x_next), rates[1:])
         m.aggregate()
         got.append([t[:n].cpu().numpy().copy() for t in (m.y, m.x_half, m.x_next, m.mean)])
-    for a, b in zip(*got):
-        assert np.array_equal(a, b)
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("scope", [0, 2])
 @pytest.mark.parametrize("S", [4, 32, 256])
 def test_distance_of_the_iterates(oracle, S, scope):
-    """eq. (Alt), two rounds, tiles whose octets end at every wave: the sum of squares over slots and tiles."""
+    """eq. (Alt), three rounds, tiles whose octets end at every wave: the sum of squares over slots and tiles."""
     K, L = 3, len(RAGGED)
     m = gm(RAGGED, [0] * L, [S], K, seed=4, norm_scope=scope)
     rng = np.random.default_rng(S)

@@ -49,4 +49,10 @@ def kernels(tmp_path_factory):
 @pytest.mark.parametrize("bucket", ["false", "true"])
 @pytest.mark.parametrize("bits", range(2, 10))
 def test_alt_decode_in_eight_waves_fits_a_cu_twice(kernels, bits, bucket):
-    assert kernels[f"k_decode<{bits}, 2, {bucket}, 8>"][0] <= 128
+    early = "true" if bits <= 6 else "false"
+    assert kernels[f"k_decode<{bits}, 2, {bucket}, 8, {early}>"][0] <= 128
+
+
+@pytest.mark.parametrize("mode", [0, 1, 3])
+def test_whole_octets_of_five_bits_under_bucket_scope_run_six_waves(kernels, mode):
+    assert kernels[f"k_decode<5, {mode}, true, 8, false>"][0] <= 80
