@@ -41,6 +41,7 @@ struct qoda_ctx {
   double *d_partial = nullptr, *d_dpartial = nullptr, *d_sumsq = nullptr, *d_delta = nullptr;
   float *d_norm = nullptr, *d_inv = nullptr, *d_lev = nullptr, *d_rgap = nullptr, *d_eta = nullptr;
   float4 *d_bins = nullptr;
+  unsigned char *d_lut = nullptr;
   unsigned int *d_hist = nullptr, *d_hist_last = nullptr, *d_status = nullptr;
   int *d_type_first = nullptr;   // the layers of every type
   int3 *d_type_layers = nullptr;
@@ -262,7 +263,7 @@ Dev base_args(const qoda_ctx *c) {
   a.readers = c->d_readers;
   a.exch = c->d_exch; a.finished = c->d_finished; a.tries = c->tries;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
-  a.lev = c->d_lev; a.rgap = c->d_rgap; a.bins = c->d_bins; a.walk = c->d_walk;
+  a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.bins = c->d_bins; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
   a.hist = c->d_hist + (c->d_hist ? c->stat_set * (size_t)c->K * c->L * kHistBins : 0);
   a.sumsq += c->stat_set * (size_t)c->K * c->L;
@@ -303,7 +304,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_runs[0], c->d_runs[1], c->d_runs[2], c->d_runs[3], c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
-                  c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_bins, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
+                  c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_bins, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
                   c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
                   c->d_type_first, c->d_type_layers};
   for (void *p : ptrs)
@@ -567,6 +568,7 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   A(dev_alloc(&c->d_lev, (size_t)c->M * kMaxPoints));
   A(dev_alloc(&c->d_rgap, (size_t)c->M * kMaxPoints));
   A(dev_alloc(&c->d_eta, 3));
+  A(dev_alloc(&c->d_lut, (size_t)c->M * kLutSize));
   A(dev_alloc(&c->d_bins, (size_t)c->M * kGridPoints));
   A(dev_alloc(&c->d_status, 2));   // the status word, and a word no kernel result depends on
   A(dev_alloc(&c->d_pooled, (size_t)c->M * kGridPoints));

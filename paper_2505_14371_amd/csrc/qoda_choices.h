@@ -80,4 +80,21 @@ inline int alt_blocks(int G, int K, bool bucket, int bits) {
   return !bucket && bits <= 5 && G <= 1024 && K <= 2 ? 16 : 8;
 }
 
+// Whether k_quantize looks levels up by grid bin (one read of 128 bits, 4 KiB of table to fetch per workgroup) rather than by byte and
+// tau (two reads one after the other, 1 KiB), for n tiles of all nodes of the launch.  Without a previous message and with codes of up
+// to 6 bits the bins take 82 to 84 registers, the bytes at most 80: five against six workgroups a CU, which shows where 1281 to 1536
+// tiles are one wave of the chip with bytes and two with bins.  With the previous message and 9 bits it is 98 against 96 registers, four
+// workgroups a CU against five.  us with bins / with bytes: no previous message, 3 bits, 400 tiles 12.2 / 12.0, 1280 19.5 / 20.1, 1500
+// 26.4 / 23.4, 1700 28.7 / 29.1, 10 k 123.9 / 125.9, 74 k 886 / 907; 5 bits, 400 12.3 / 12.3, 1500 27.3 / 24.5, 10 k 130.5 / 133.0; 6 bits,
+// 400 12.5 / 13.1, 1280 20.6 / 20.9, 1500 27.8 / 24.7, 10 k 134.6 / 137.4; previous message, 8 bits, 400 14.2 / 14.8, 1280 25.1 / 25.9,
+// 3100 56.6 / 57.5, 10 k 165.8 / 166.3; 9 bits, 400 14.5 / 14.8, 1280 29.3 / 26.6, 2000 40.1 / 40.8, 3100 61.8 / 60.5, 74 k 1218 / 1300.
+// Elsewhere both take the same time, within 1 %, or the bytes less.
+constexpr bool quantize_bins_width(bool prev, int bits) { return prev ? bits >= 8 : bits <= 6; }   // widths that have the form
+constexpr bool quantize_bytes_width(bool prev, int bits) { return !prev || bits != 8; }
+inline bool quantize_bins(long long n, bool prev, int bits) {
+  if (!quantize_bins_width(prev, bits)) return false;
+  if (prev) return bits == 8 || n <= 1024 || n > 4096;
+  return n > 1536 || (bits == 6 && n <= 1280);
+}
+
 }  // namespace qoda

@@ -22,6 +22,7 @@ constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
 constexpr int kGridPoints = 257;     // normalised grid g_0 = 2^-32 ... g_256 = 1
 constexpr int kMaxPoints = 256;
+constexpr int kLutSize = 1024;       // table of tau by bits(u) >> 20 (u in [0,1] -> 0..1016)
 constexpr int kTypeSkip = 0x7fffffff;
 constexpr int kBucketCoords = 128;   // coordinates per bucket when every bucket carries its own norm
 
@@ -70,6 +71,7 @@ struct Dev {
   double *delta;      // [K]
   float *lev;         // [M*256]
   float *rgap;        // [M*256]
+  unsigned char *lut;  // [M*1024] level-search table by bits(u) >> 20: tau at the lower edge of the bin
   float4 *bins;       // [M*257] level-search table by grid bin: {l_tau, 1/gap, l_tau+1, tau} at the bin's lower edge
   int *walk;          // [M] some interior level of the type lies inside a bin, or not above the first one
   unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit

@@ -188,6 +188,19 @@ __device__ __forceinline__ void load_tables(const Dev &a, int type, int S, int w
   if (walk && t < S) tab[t] = make_float4(lj, rj, t + 1 < S ? ln : __builtin_inff(), u2f((unsigned int)t));   // rgap is 0 from S-1 on
 }
 
+// What k_quantize finds a value's level with: {l_tau, 1/gap, l_tau+1} for the tau of its bin's lower edge, and the entries by tau to
+// walk on from there (the last one with the upper neighbour +infinity, which stops every walk).
+//   BINS   one 128-bit read from the table by grid bin, which has tau in its last word
+//   !BINS  tau from a table of bytes by bits(u) >> 20, then the entry of tau: two reads one after the other
+// quantize_bins says which, with the times.  The byte form keeps room for 256 entries at every width: with as many as there are levels
+// the pass over 74 k tiles (8 levels, K = 8, previous message) takes 1024 to 1032 us instead of 993 to 1009, for the same instructions.
+template <int C1, bool BINS>
+struct QuantTables {
+  float4 bins[BINS ? kGridPoints : 1];
+  unsigned int lut[BINS ? 1 : kLutSize / 4];
+  float4 tab[BINS ? 1 << (C1 - 1) : kMaxPoints];
+};
+
 // The lane's number in its wave, from no register that would have to be kept for it.
 __device__ __forceinline__ int lane_id() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
@@ -481,27 +494,38 @@ __global__ void __launch_bounds__(kThreads) k_norm_vector(Dev a) {
 // Quantize the four coordinates a lane owns in one block (Sec. 3.1), append their codes to the record and add
 // their squared distance to the previous decoded message (eq. (general_stepsize)).  jl0 = 0 or 4: position of
 // the block inside its pair.
-template <int C1, bool PREV>
+template <int C1, bool PREV, bool BINS>
 __device__ __forceinline__ void quantize_block(const float (&x)[4], const unsigned int (&o)[4], int half, float inv,
-                                               float norm, const float4 *bins, const float4 *tab, bool walk,
+                                               float norm, const QuantTables<C1, BINS> &T, bool walk,
                                                const float *tprev, unsigned int (&D)[C1], const unsigned int (&Dp)[C1],
                                                float &acc) {
   float u[4];
-  float4 lv[4];
+  float4 lv[4];   // {l_tau, 1/gap, l_tau+1, tau (BINS)}
+  unsigned int tau[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     // min(|v| * inv, 1): the product is never negative or NaN for finite input, so the [0, 1] clamp of the
     // multiply instruction is the same thing
     u[j] = __builtin_amdgcn_fmed3f(fabsf(x[j]) * inv, 0.0f, 1.0f);
-    lv[j] = bin_entry(bins, u[j]);
+    if (BINS) lv[j] = bin_entry(T.bins, u[j]);
+    else tau[j] = reinterpret_cast<const unsigned char *>(T.lut)[f2u(u[j]) >> 20];
+  }
+  if (!BINS) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lv[j] = T.tab[tau[j]];
   }
   // A level inside a bin (walk; never the case for fitted levels, which sit on bin edges) makes some lanes walk on from the
   // entry of its lower edge.  At u = 1 the walk ends on the entry of the last level itself (xi = 0, never rounds up), which
   // yields the same code and value as tau = S-2 rounding up: there xi is 1 - 2^-23 at least, above every 16-bit draw.
   if (walk && __ballot((lv[0].z <= u[0]) | (lv[1].z <= u[1]) | (lv[2].z <= u[2]) | (lv[3].z <= u[3])) != 0ull) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      while (lv[j].z <= u[j]) lv[j] = tab[f2u(lv[j].w) + 1u];
+    for (int j = 0; j < 4; ++j) {
+      if (BINS) {
+        while (lv[j].z <= u[j]) lv[j] = T.tab[f2u(lv[j].w) + 1u];
+      } else {
+        while (lv[j].z <= u[j]) { ++tau[j]; lv[j] = T.tab[tau[j]]; }
+      }
+    }
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -511,7 +535,7 @@ __device__ __forceinline__ void quantize_block(const float (&x)[4], const unsign
     // (w16 + 0.5) < xi * 65536  <=>  w16 < xi * 65536 - 0.5 : the scaling by 2^16 is exact, and the subtraction
     // is exact whenever its result is not negative, so one fused operation decides the same.
     const bool up = (float)w16 < __builtin_fmaf(xi, 65536.0f, -0.5f);
-    const unsigned int h = f2u(lv[j].w) + (up ? 1u : 0u);
+    const unsigned int h = (BINS ? f2u(lv[j].w) : tau[j]) + (up ? 1u : 0u);
     // norm * l_h, the value the decoder will rebuild (the +inf of the last entry is never selected: there xi = 0)
     const float mag = norm * (up ? lv[j].z : lv[j].x);
     const float cur = __builtin_copysignf(mag, x[j]);
@@ -535,11 +559,11 @@ __device__ __forceinline__ void load_block_fast(const float *__restrict__ v, lon
 // unrolled: unrolled, the compiler interleaves the pairs and needs more than 256 registers.  The next pair's
 // gradient values are requested before the current pair is processed.
 // FAST: the whole octet lies inside the layer (no bounds checks anywhere).
-template <int C1, bool FAST, bool PREV>
+template <int C1, bool FAST, bool PREV, bool BINS>
 __device__ __forceinline__ void quantize_octet(const Dev &a, const LayerMeta &m, int l, int k, long long O,
                                                const float *__restrict__ v, unsigned char *body,
-                                               const unsigned char *prevbody, float inv, float norm, const float4 *bins,
-                                               const float4 *tab, bool walk, const float *tprev, int i, float &acc) {
+                                               const unsigned char *prevbody, float inv, float norm,
+                                               const QuantTables<C1, BINS> &T, bool walk, const float *tprev, int i, float &acc) {
   const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
   unsigned int D[C1], Dp[C1];
 #pragma unroll
@@ -571,19 +595,18 @@ __device__ __forceinline__ void quantize_octet(const Dev &a, const LayerMeta &m,
       }
       unsigned int o[4];
       philox4x32_10((unsigned int)((B0 >> 1) * 64 + i), (unsigned int)l, a.round, (unsigned int)k, k0, k1, o);
-      quantize_block<C1, PREV>(x0, o, 0, inv, norm, bins, tab, walk, tprev, D, Dp, acc);
+      quantize_block<C1, PREV, BINS>(x0, o, 0, inv, norm, T, walk, tprev, D, Dp, acc);
       // a block past the end of the layer is all padding: +0 inputs give code 0 and add nothing, as required
-      quantize_block<C1, PREV>(x1, o, 1, inv, norm, bins, tab, walk, tprev, D, Dp, acc);
+      quantize_block<C1, PREV, BINS>(x1, o, 1, inv, norm, T, walk, tprev, D, Dp, acc);
     }
     if (PREV) shift_out_pair<C1>(Dp);
   }
   store_record<C1>(body + O * 256 * C1, i, D);
 }
 
-template <int C1, bool PREV>
+template <int C1, bool PREV, bool BINS>
 __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, int l, int k, int chunk,
-                                              const float4 *bins, const float4 *tab, bool walk, const float *tprev,
-                                              double *red) {
+                                              const QuantTables<C1, BINS> &T, bool walk, const float *tprev, double *red) {
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int i = t & 63;
@@ -599,18 +622,17 @@ __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, 
     const long long O = (long long)chunk * 8 + w * 2 + oo;   // octet index inside the layer
     if (O >= noct) break;
     if ((O + 1) * 2048 <= m.d)
-      quantize_octet<C1, true, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, bins, tab, walk, tprev, i, acc);
+      quantize_octet<C1, true, PREV, BINS>(a, m, l, k, O, v, body, prevbody, inv, norm, T, walk, tprev, i, acc);
     else
-      quantize_octet<C1, false, PREV>(a, m, l, k, O, v, body, prevbody, inv, norm, bins, tab, walk, tprev, i, acc);
+      quantize_octet<C1, false, PREV, BINS>(a, m, l, k, O, v, body, prevbody, inv, norm, T, walk, tprev, i, acc);
   }
   const double total = block_tree((double)acc, red);
   if (t == 0) a.dpartial[(size_t)kr * a.G + blockIdx.x] = total;
 }
 
-template <int C1, bool PREV>
+template <int C1, bool PREV, bool BINS>
 __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
-  __shared__ float4 bins[kGridPoints];
-  __shared__ float4 tab[1 << (C1 - 1)];
+  __shared__ QuantTables<C1, BINS> T;
   __shared__ float tprev[1 << C1];   // previous message's decode table indexed by code = sign | h << 1
   __shared__ double red[kThreads];
   const int2 tile = a.tiles[blockIdx.x];
@@ -623,8 +645,15 @@ __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
   const int kr = k - a.row0;
   const float norm = a.norm[(size_t)kr * a.L + l];
   const unsigned char *prevmsg = (a.prev != nullptr) ? a.prev[kr] : nullptr;
-  const bool walk = a.walk[m.type] != 0;
-  load_tables(a, m.type, m.S, walk, bins, tab);
+  // (without a previous message, 6 bits: the test of the flag would take the sixth wave of a SIMD, 82 registers instead of 80)
+  const bool walk = (!BINS && !PREV && C1 == 6) || a.walk[m.type] != 0;
+  if constexpr (BINS) {
+    load_tables(a, m.type, m.S, walk, T.bins, T.tab);
+  } else {
+    const float *rg = a.rgap + (size_t)m.type * kMaxPoints;
+    T.lut[t] = reinterpret_cast<const unsigned int *>(a.lut + (size_t)m.type * kLutSize)[t];
+    if (t < m.S) T.tab[t] = make_float4(lev[t], rg[t], t + 1 < m.S ? lev[t + 1] : __builtin_inff(), 0.0f);
+  }
   if (tile.y == 0) {   // message header of this layer: {norm, levels[S]} (Sec. 3.2: the norm in C_q = 32 bits)
     float *h = reinterpret_cast<float *>(a.msg[kr] + m.hdr_off);
     for (int j = t; j <= m.S; j += kThreads) h[j] = (j == 0) ? norm : lev[j - 1];
@@ -639,7 +668,7 @@ __global__ void __launch_bounds__(kThreads) k_quantize(Dev a) {
     tprev[c] = pv;
   }
   __syncthreads();
-  quantize_tile<C1, PREV>(a, m, l, k, tile.y, bins, tab, walk, tprev, red);
+  quantize_tile<C1, PREV, BINS>(a, m, l, k, tile.y, T, walk, tprev, red);
 }
 
 // ------------------------------------------------------------------------------------------------ octets in registers
@@ -2032,9 +2061,10 @@ __global__ void __launch_bounds__(kThreads) k_fit_pool_b(Dev a) {
 
 __device__ __forceinline__ float grid_value(int j) { return u2f((unsigned int)(j + kGridBase) << 20); }
 
-// Search tables of one type from its levels (in shared memory; sgap: room for kMaxPoints): reciprocal gaps, and for every
-// grid bin the entry {l_tau, 1/gap, l_tau+1, tau} of its lower edge, tau = the largest j <= S-2 with l_j <= edge (the levels
-// increase, so that j is found by halving).  Bin 0 also serves all values below it: its entry is that of tau = 0.
+// Search tables of one type from its levels (in shared memory; sgap: room for kMaxPoints): reciprocal gaps, tau of the lower edge of
+// every bin of values whose top bits are the same, tau = the largest j <= S-2 with l_j <= edge (the levels increase, so that j is found
+// by halving), and for every grid bin the entry {l_tau, 1/gap, l_tau+1, tau}.  Grid bin 0 also serves all values below it: its
+// entry is that of tau = 0.
 __device__ void build_tables(const Dev &a, int mtype, int S, const float *slev, float *sgap) {
   float *rg = a.rgap + (size_t)mtype * kMaxPoints;
   for (int j = threadIdx.x; j < kMaxPoints; j += (int)blockDim.x) {
@@ -2049,14 +2079,18 @@ __device__ void build_tables(const Dev &a, int mtype, int S, const float *slev, 
     inside |= (f2u(slev[j]) & 0xFFFFFu) != 0u || f2u(slev[j]) <= (unsigned int)kGridBase << 20;
   const int walk = __syncthreads_or(inside);
   if (threadIdx.x == 0) a.walk[mtype] = walk;
-  for (int g = threadIdx.x; g < kGridPoints; g += (int)blockDim.x) {
-    const float lo = u2f((unsigned int)(g + kGridBase) << 20);
+  for (int q = threadIdx.x; q < kLutSize; q += (int)blockDim.x) {
+    const float lo = u2f((unsigned int)min(q, kGridBase + kGridPoints - 1) << 20);   // the last bins are beyond 1
     int tau = 0;
-    for (int n = g == 0 ? 0 : S - 2; n > 0;) {   // the answer lies in tau .. tau + n
+    for (int n = S - 2; n > 0;) {   // the answer lies in tau .. tau + n
       const int h = (n + 1) >> 1;
       if (slev[tau + h] <= lo) { tau += h; n -= h; }
       else n = h - 1;
     }
+    a.lut[(size_t)mtype * kLutSize + q] = (unsigned char)tau;
+    const int g = q - kGridBase;
+    if (g < 0 || g >= kGridPoints) continue;
+    if (g == 0) tau = 0;
     a.bins[(size_t)mtype * kGridPoints + g] = make_float4(slev[tau], sgap[tau], slev[tau + 1], u2f((unsigned int)tau));
   }
 }
@@ -2550,6 +2584,20 @@ hipError_t launch_norm_finalize(const Dev &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int C1, bool PREV>
+static void launch_quantize_tables(const Dev &a, hipStream_t s) {
+  constexpr bool bins = quantize_bins_width(PREV, C1), bytes = quantize_bytes_width(PREV, C1);
+  static_assert(bins || bytes, "a form for every width");
+  const dim3 grid(a.G, a.nnodes), block(kThreads);
+  if constexpr (bins) {
+    if (!bytes || quantize_bins((long long)a.G * a.nnodes, PREV, C1)) {
+      hipLaunchKernelGGL((k_quantize<C1, PREV, true>), grid, block, 0, s, a);
+      return;
+    }
+  }
+  if constexpr (bytes) hipLaunchKernelGGL((k_quantize<C1, PREV, false>), grid, block, 0, s, a);
+}
+
 // planes_mask: bit p set when some layer has code width p (2..9); one launch per width present.
 template <int C1>
 static void launch_quantize_width(const Dev &a, hipStream_t s) {
@@ -2568,9 +2616,8 @@ static void launch_quantize_width(const Dev &a, hipStream_t s) {
       else hipLaunchKernelGGL((k_quantize_b<C1, false, kNormLinf>), grid, block, 0, s, a);
     }
   } else {
-    const dim3 grid(a.G, a.nnodes);
-    if (prev) hipLaunchKernelGGL((k_quantize<C1, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_quantize<C1, false>), grid, block, 0, s, a);
+    if (prev) launch_quantize_tables<C1, true>(a, s);
+    else launch_quantize_tables<C1, false>(a, s);
   }
 }
 

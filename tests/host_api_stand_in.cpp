@@ -31,6 +31,7 @@ void stand_in_fail_at(int n) { g_fail_at = n; }
 void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); }
 int stand_in_alt_blocks(int G, int K, int bucket, int bits) { return alt_blocks(G, K, bucket != 0, bits); }
 int stand_in_decode_blocks(int G, int K, int mode, int bucket, int bits) { return decode_blocks(G, K, mode, bucket != 0, bits); }
+int stand_in_quantize_bins(long long n, int prev, int bits) { return quantize_bins(n, prev != 0, bits); }
 void stand_in_replay() { for (auto &f : g_graph) f(); }
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }

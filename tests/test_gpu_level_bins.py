@@ -79,3 +79,34 @@ def test_bucket_norms_next_to_floats(oracle, kind):
     x[2::4, 6:9] = np.float32(2.0 ** -12) * v[2::4, None]               # the root moves by about a unit of its last place
     x[3::4, 100] = np.float32(2.0 ** -11.5) * v[3::4]
     check(oracle, [n], np.array([0.0, 0.1, 0.5, 1.0], np.float32), [[x.reshape(-1)]], qoda.SCOPE_BUCKET, kind, False)
+
+
+@pytest.mark.parametrize("S", [2, 4, 8, 16, 32, 64, 128, 256])
+@pytest.mark.parametrize("walk", [False, True])
+def test_both_tables_of_every_width(oracle, S, walk):
+    """1700 tiles in the call of both nodes and 850 in each node's own: what one call looks up by grid bin, without a previous message
+    up to 6 bits and with it from 9 on, the other looks up by byte.  Levels on bin edges or inside bins."""
+    rng = np.random.default_rng(S)
+    sizes = [int(x) for x in rng.integers(1, 700, 848)] + [16384 + 77]
+    grads = [[(rng.choice([-1, 1], s) * 2.0 ** rng.uniform(-36, 0, s)).astype(np.float32) for s in sizes] for _ in range(2)]
+    edge = np.sort(rng.choice(254, S - 2, replace=False)) + 1
+    lev = np.concatenate([[0.0], (np.uint32(760) + edge.astype(np.uint32) << 20).view(np.float32), [1.0]]).astype(np.float32)
+    if walk and S > 2:
+        lev[1:-1] *= np.float32(1.03)
+    L = len(sizes)
+    want, prev = [[None] * 2, [None] * 2], [None] * 2
+    for t in (1, 2):
+        for k in range(2):
+            want[t - 1][k] = oracle.quantize(sizes, [S] * L, [lev] * L, grads[k], 9, t, k, msg_prev=prev[k])
+            prev[k] = want[t - 1][k][0]
+    for each in (False, True):
+        m = gm(sizes, [0] * L, [S], 2, seed=9)
+        assert sum((s + 16383) // 16384 for s in sizes) == 850
+        m.set_grads(grads)
+        m.ctx.set_levels(0, lev)
+        for t in (1, 2):
+            (m.quantize_each if each else m.quantize_all)(t)
+            msgs, delta = m.messages(), m.ctx.read_buffer(qoda.BUF_DELTA)
+            for k in range(2):
+                assert np.array_equal(msgs[k], want[t - 1][k][0]) and delta[k] == want[t - 1][k][2], (each, t, k)
+            m.cur, m.have_prev = 1 - m.cur, True

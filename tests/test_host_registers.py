@@ -56,3 +56,12 @@ def test_alt_decode_in_eight_waves_fits_a_cu_twice(kernels, bits, bucket):
 @pytest.mark.parametrize("mode", [0, 1, 3])
 def test_whole_octets_of_five_bits_under_bucket_scope_run_six_waves(kernels, mode):
     assert kernels[f"k_decode<5, {mode}, true, 8, false>"][0] <= 80
+
+
+@pytest.mark.parametrize("bits", range(2, 7))
+def test_quantize_without_previous_message_runs_six_waves(kernels, bits):
+    assert kernels[f"k_quantize<{bits}, false, false>"][0] <= 80
+
+
+def test_quantize_of_nine_bits_with_previous_message_runs_five_waves(kernels):
+    assert kernels["k_quantize<9, true, false>"][0] <= 96
