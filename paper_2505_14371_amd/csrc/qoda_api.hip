@@ -54,13 +54,16 @@ struct qoda_ctx {
   int *d_type_exp_next = nullptr;   // bucket scope: the weight scales the next gathering pass will use
   int *d_type_skip = nullptr;       // bucket scope: "no scale" for every type (passes that gather no histogram)
   bool gather = true;               // bucket scope: quantize passes gather the fit's histogram
-  // Bucket scope: two sets of statistics (d_hist, d_sumsq hold both).  stat_set is that of the last pass; while stat_swap
+  // Bucket scope: two sets of statistics, the halves of every (node, layer) pair's histogram (257 sums of 8 bytes in kStatWords words
+  // each) and of d_sumsq.  stat_set is that of the last pass; while stat_swap
   // holds the other one is zero, so that a pass over all nodes gathers into it without a launch that clears, and has the
   // old one cleared by its last kernel.  Captured work can be replayed at any time and must find its set where it left it: from
   // the first captured call on (and after one that failed between its launches) the sets stay and every pass clears its own.
   int stat_set = 0;
   bool stat_swap = false;
-  static constexpr size_t kStatPairs = 8192;   // (node, layer) pairs up to which there are two sets (64 MiB each)
+  static constexpr size_t kStatPairs = 8192;   // (node, layer) pairs up to which the sets take turns (larger tables were not timed)
+  static constexpr size_t kStatWords = kHistBins / 2;
+  static_assert(kStatWords * sizeof(unsigned int) >= kGridPoints * sizeof(unsigned long long), "a set fits half a histogram");
   unsigned long long *d_index_counts = nullptr;   // [M*256], allocated by the first qoda_index_counts
   // device pointer tables (uploaded when their host shadow changes)
   // A few device copies per table, each remembering the host array it was filled from: a caller that alternates
@@ -265,7 +268,7 @@ Dev base_args(const qoda_ctx *c) {
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.bins = c->d_bins; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
-  a.hist = c->d_hist + (c->d_hist ? c->stat_set * (size_t)c->K * c->L * kHistBins : 0);
+  a.hist = c->d_hist + (c->d_hist ? c->stat_set * qoda_ctx::kStatWords : 0);
   a.sumsq += c->stat_set * (size_t)c->K * c->L;
   a.pooled = c->d_pooled; a.type_exp = c->d_type_exp;
   a.dp_arg = c->d_dp_arg; a.dp_arg_off = c->d_dp_arg_off;
@@ -403,7 +406,7 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
       a.hist_old = a.hist;
       a.sumsq_old = a.sumsq;
       c->stat_set = 1 - c->stat_set;
-      a.hist = c->d_hist + c->stat_set * KL * kHistBins;
+      a.hist = c->d_hist + c->stat_set * qoda_ctx::kStatWords;
       a.sumsq = c->d_sumsq + c->stat_set * KL;
     } else {
       LAUNCH(c, kIdZero, s, launch_zero_stats(a.hist + n0 * kHistBins, a.sumsq + n0, nn, s));
@@ -583,8 +586,8 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
   if (c->scope == kScopeBucket) {   // the quantize pass gathers the fit's statistics itself
     A(dev_alloc(&c->d_type_exp_next, (size_t)c->M));
     A(dev_alloc(&c->d_type_skip, (size_t)c->M));
-    A(dev_alloc(&c->d_hist, sets * KL * kHistBins));
-    if (e == hipSuccess) A(hipMemset(c->d_hist, 0, sets * KL * kHistBins * sizeof(unsigned int)));
+    A(dev_alloc(&c->d_hist, KL * kHistBins));
+    if (e == hipSuccess) A(hipMemset(c->d_hist, 0, KL * kHistBins * sizeof(unsigned int)));
     if (e == hipSuccess) A(hipMemset(c->d_sumsq, 0, sets * KL * sizeof(double)));
     c->stat_swap = sets == 2;
   }
@@ -1198,7 +1201,7 @@ int qoda_read_buffer(qoda_ctx *c, int32_t which, void *dst, size_t bytes, void *
       case QODA_BUF_INV: src = c->d_inv; have = KL * sizeof(float); break;
       case QODA_BUF_DELTA: src = c->d_delta; have = c->K * sizeof(double); break;
       case QODA_BUF_HIST:
-        src = c->scope == kScopeBucket ? c->d_hist + c->stat_set * KL * kHistBins : c->d_hist_last;
+        src = c->scope == kScopeBucket ? c->d_hist : c->d_hist_last;
         have = src ? KL * kHistBins * sizeof(unsigned int) : 0;
         break;
       case QODA_BUF_POOLED: src = c->d_pooled; have = (size_t)c->M * kGridPoints * sizeof(unsigned long long); break;
@@ -1208,6 +1211,14 @@ int qoda_read_buffer(qoda_ctx *c, int32_t which, void *dst, size_t bytes, void *
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
+    if (which == QODA_BUF_HIST && c->scope == kScopeBucket) {   // of the two sets the last pass's, in front
+      constexpr size_t w = qoda_ctx::kStatWords;
+      unsigned int *row = static_cast<unsigned int *>(dst);
+      for (size_t p = 0; p < KL; ++p, row += kHistBins) {
+        if (c->stat_set != 0) std::copy(row + w, row + 2 * w, row);
+        std::fill(row + w, row + 2 * w, 0u);
+      }
+    }
     return QODA_OK;
   });
 }

@@ -1,7 +1,8 @@
 // The host side of the library (csrc/qoda_api.hip) compiled for the CPU over stand-ins for the HIP runtime and for the kernel
 // launches, so that a test without a GPU can see which launches a call makes, let one of them fail, and capture and replay
 // them.  "Device" memory is host memory, filled with a pattern when it is allocated.  Launches are recorded by name; the only
-// effect they model is that of the level fit on its histogram: the norm pass adds to it, its consumer moves it away.
+// effects they model are those on histograms: the norm pass adds to the fit's, its consumer moves it away; under bucket scope the
+// quantize pass adds to the sums of its nodes, the clearing launches (the last kernel of the pass among them) clear theirs.
 #include "../paper_2505_14371_amd/csrc/qoda_api.hip"
 #include "../paper_2505_14371_amd/csrc/qoda_choices.h"
 
@@ -12,6 +13,7 @@ namespace {
 std::string g_log;
 int g_fail_at = -1;           // launches until one fails; -1: none
 bool g_capturing = false;
+long long g_allocated = 0;
 std::vector<std::function<void()>> g_graph;
 
 hipError_t record(const std::string &name, std::function<void()> effect = nullptr) {
@@ -32,6 +34,7 @@ void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); 
 int stand_in_alt_blocks(int G, int K, int bucket, int bits) { return alt_blocks(G, K, bucket != 0, bits); }
 int stand_in_decode_blocks(int G, int K, int mode, int bucket, int bits) { return decode_blocks(G, K, mode, bucket != 0, bits); }
 int stand_in_quantize_bins(long long n, int prev, int bits) { return quantize_bins(n, prev != 0, bits); }
+long long stand_in_allocated() { return g_allocated; }   // bytes, of all allocations so far
 void stand_in_replay() { for (auto &f : g_graph) f(); }
 
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -39,6 +42,7 @@ hipError_t hipMalloc(void **p, size_t n) {
   *p = std::malloc(n);
   if (!*p) return hipErrorOutOfMemory;
   std::memset(*p, 0xCD, n);
+  g_allocated += (long long)n;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
@@ -76,9 +80,20 @@ hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t) {
 }
 hipError_t launch_norm_finalize(const Dev &, hipStream_t) { return record("norm_finalize"); }
 hipError_t launch_norm_vector(const Dev &, hipStream_t) { return record("norm_vector"); }
-hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) { return record(a.scope == kScopeBucket ? "quantize_b:" + std::to_string(a.GS) : "quantize"); }
+static void clear_sums(unsigned int *hist, size_t pairs) {
+  for (size_t i = 0; i < pairs; ++i) std::memset(hist + i * kHistBins, 0, kGridPoints * sizeof(unsigned long long));
+}
+hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) {
+  if (a.scope != kScopeBucket) return record("quantize");
+  return record("quantize_b:" + std::to_string(a.GS), [=] {
+    for (size_t i = (size_t)a.node0 * a.L; i < (size_t)(a.node0 + a.nnodes) * a.L; ++i)
+      for (int j : {0, kGridPoints - 1}) reinterpret_cast<unsigned long long *>(a.hist + i * kHistBins)[j] += 1;
+  });
+}
 hipError_t launch_quantize_small(const Dev &, unsigned int, hipStream_t) { return record("quantize_small"); }
-hipError_t launch_delta_finalize(const Dev &, hipStream_t) { return record("delta"); }
+hipError_t launch_delta_finalize(const Dev &a, hipStream_t) {
+  return record("delta", [=] { if (a.hist_old) clear_sums(a.hist_old, (size_t)a.K * a.L); });
+}
 hipError_t launch_step_scalars(const Dev &, hipStream_t) { return record("step_scalars"); }
 hipError_t launch_decode(const Dev &, int mode, unsigned int, hipStream_t) { return record("decode:" + std::to_string(mode)); }
 hipError_t launch_alt_scalars(const Dev &, hipStream_t) { return record("alt_scalars"); }
@@ -93,7 +108,7 @@ hipError_t launch_fit_dp(const Dev &a, int source, hipStream_t) {
   if (source == kFitLayers) return record("fit_dp:layers", [=] { move_histograms(a); });
   return record(source == kFitBuckets ? "fit_dp:buckets" : "fit_dp:pooled");
 }
-hipError_t launch_zero_stats(unsigned int *, double *, size_t, hipStream_t) { return record("zero_stats"); }
+hipError_t launch_zero_stats(unsigned int *h, double *, size_t n, hipStream_t) { return record("zero_stats", [=] { clear_sums(h, n); }); }
 hipError_t launch_copy(const void *, void *, size_t, hipStream_t) { return record("copy"); }
 hipError_t launch_stream(const void *, void *, size_t, int, void *, hipStream_t) { return record("stream"); }
 hipError_t launch_build_tables(const Dev &, int, hipStream_t) { return record("build_tables"); }

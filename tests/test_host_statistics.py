@@ -1,4 +1,8 @@
-"""Bucket scope: which quantize calls clear the fit's statistics with a launch of their own (CPU, over the stand-ins)."""
+"""Bucket scope: which quantize calls clear the fit's statistics with a launch of their own, and the memory of the two
+sets (CPU, over the stand-ins)."""
+import ctypes
+
+import numpy as np
 import pytest
 
 from paper_2505_14371_amd import qoda
@@ -55,3 +59,28 @@ def test_large_tables_have_one_set(routes, layers, swaps):  # noqa: F811
     m = routes([10] * layers, K=2, norm_scope=qoda.SCOPE_BUCKET)
     names = m.launches(lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, None, stream=0))
     assert ("zero_stats" not in names) == swaps
+
+
+def test_both_sets_in_one_histogram_a_pair(routes):  # noqa: F811
+    K, L = 2, 300
+    lib = routes([10]).lib
+    lib.stand_in_allocated.restype = ctypes.c_longlong
+    before = lib.stand_in_allocated()
+    routes([10] * L, K=K, norm_scope=qoda.SCOPE_BUCKET)
+    # 2048 words a pair; all else of it is under 1 KiB: statistic and norm, partial sums, 128 B of each descriptor and of each of the
+    # copies of the pointer tables
+    assert lib.stand_in_allocated() - before < K * L * (2048 * 4 + 1024) + (1 << 18)
+
+
+def test_both_sets_read_alike(model):
+    want = np.zeros((2, 3, 1024), np.uint64)
+    want[:, :, [0, 256]] = 1
+    for call in [model.all, model.all, model.all, model.one, model.all, model.all]:
+        call()
+        assert np.array_equal(model.ctx.read_buffer(qoda.BUF_HIST, stream=0).view(np.uint64), want)
+    model.lib.stand_in_capture(1)
+    model.all()
+    model.lib.stand_in_capture(0)
+    for call in [model.lib.stand_in_replay, model.lib.stand_in_replay, model.all, model.lib.stand_in_replay, model.all]:
+        call()
+        assert np.array_equal(model.ctx.read_buffer(qoda.BUF_HIST, stream=0).view(np.uint64), want)
