@@ -74,7 +74,7 @@ struct Dev {
   unsigned char *lut;  // [M*1024] level-search table by bits(u) >> 20: tau at the lower edge of the bin
   float4 *bins;       // [M*257] level-search table by grid bin: {l_tau, 1/gap, l_tau+1, tau} at the bin's lower edge
   int *walk;          // [M] some interior level of the type lies inside a bin, or not above the first one
-  unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit
+  unsigned int *hist;          // [K*L*2048] layer and vector scope: zero after a whole fit; bucket scope: the current set, 1024 words of each 2048
   unsigned int *hist_last;     // [K*L*2048] layer and vector scope: the histogram of the last fit
   unsigned int *hist_old;      // bucket scope: statistics that k_delta_finalize clears (this and the next); or nullptr
   double *sumsq_old;

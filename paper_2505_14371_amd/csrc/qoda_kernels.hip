@@ -5,7 +5,7 @@
 // coordinates of one (node, layer).  Wave w owns the 16 consecutive 256-coordinate blocks 16w..16w+15 of the tile; in a
 // block, lane i owns coordinates 4i..4i+3 (one 128-bit load, 1 KB contiguous per wave).  Thread t = 64w+i is reduction
 // slot t of the fixed-order fp64 sums.  The decode pass keeps the lane <-> coordinate mapping but runs in shorter
-// workgroups (one octet per wave, see k_decode).  The packed message is lane-local: the codes of the 32 coordinates a lane
+// workgroups (8, 4 or 2 blocks of an octet per wave, see k_decode).  The packed message is lane-local: the codes of the 32 coordinates a lane
 // owns in 8 consecutive blocks (an octet) are shifted into C1 = 1 + b 32-bit words per lane, and word r of the
 // 64 lanes is one contiguous 256-byte store.
 //
@@ -80,10 +80,10 @@ __device__ __forceinline__ void norm_and_inverse(double s, float &n_out, float &
   // s = sp * 4^k with sp in [1, 4)
   const int k = e >> 1;
   const double sp = __longlong_as_double(bits - ((long long)(2 * k) << 52));
-  const float sf = (float)sp;                       // 1/4 unit of the root
+  const float sf = (float)sp;                       // moves the root by up to 0.36 unit
   const float y = __builtin_amdgcn_rsqf(sf);        // 1/sqrt(sp) to a few units: one Newton step leaves rounding only
   const float n0 = sf * y;
-  float n = __builtin_fmaf(__builtin_fmaf(-n0, n0, sf), 0.5f * y, n0);   // within 3/4 unit: it or the float below it
+  float n = __builtin_fmaf(__builtin_fmaf(-n0, n0, sf), 0.5f * y, n0);   // within 0.87 unit: it or the float below it
   const double nd = (double)n;
   n = step_down(n, (int)(__double_as_longlong(__builtin_fma(-nd, nd, sp)) >> 32));   // the fused operation has the exact sign
   const float q = __builtin_fmaf(__builtin_fmaf(-n, y, 1.0f), y, y);     // y is within a few units of 1/n too: 1/2 unit
@@ -167,7 +167,7 @@ __device__ __forceinline__ void philox4x32_10(unsigned int c0, unsigned int c1, 
 
 // Table entry of a value u in [0, 1], by its grid bin (bins: kGridPoints entries in shared memory, see build_tables): one
 // 128-bit read gives {l_tau, 1/gap, l_tau+1, tau}, tau being that of the bin's lower edge.  (A table of tau by bin and one of
-// {l_tau, 1/gap, l_tau+1} by tau were two reads one after the other.)
+// {l_tau, 1/gap, l_tau+1} by tau are two reads one after the other; k_quantize has that form too, see QuantTables.)
 __device__ __forceinline__ float4 bin_entry(const float4 *bins, float u) {
   return bins[__builtin_elementwise_sub_sat(f2u(u) >> 20, (unsigned int)kGridBase)];
 }
@@ -1324,9 +1324,11 @@ struct BucketHist {
 
 // Bound by the vector ALU (35.7 instructions per coordinate) together with what its waves wait for: shared memory is busy 45 % of
 // the time, and a wave spends 44 % of its own waiting for a value.  Up to 64 levels (codes of 7 bits) four waves a SIMD: 128
-// registers (none spilled up to 16 levels) and 38.1 to 39.4 KiB of shared memory a workgroup, of which the table by grid bin is 4
-// KiB; so a run has at most 4 tiles.  Wider codes have larger tables, three workgroups a CU, and the compiler takes 160 to 166
-// registers.  What made it 151 M coordinates, K = 8, 8 levels 1345 -> 1252 us and 3112 tiles, 16 levels 87 -> 79 us: one 128-bit
+// registers and 37.9 to 39.4 KiB of shared memory a workgroup, of which the table by grid bin is 4 KiB; so a run has at most 4 tiles.
+// With the previous message 6 registers are spilled at 32 levels and 8 at 64, and four waves are still the better choice: 64 levels,
+// K = 8, statistics gathered, us with four waves / with three and nothing spilled: 100 tiles a node 32.6 / 38.4, 387 77.3 / 82.6, 1250
+// 210 / 228, 9300 1404 / 1454; only launches of up to 400 tiles lose (20 tiles 20.1 / 19.4, 50 25.1 / 23.1).  Wider codes have larger
+// tables, three workgroups a CU, and the compiler takes 141 to 157 registers.  What made it 151 M coordinates, K = 8, 8 levels 1345 -> 1252 us and 3112 tiles, 16 levels 87 -> 79 us: one 128-bit
 // table read per coordinate instead of two reads one after the other; the buckets' scales in registers, broadcast along the rows
 // of 16 lanes, instead of four reads per block; root and reciprocal with one exact test each; the previous record requested at
 // the start of its octet instead of one ahead (128 registers without spills).  Entries requested a block ahead need 20 registers
@@ -2105,7 +2107,7 @@ __global__ void __launch_bounds__(kThreads) k_build_tables(Dev a, int mtype) {
 
 // Exact minimisation of eq. (Qada2) over interior levels on the grid by dynamic programming; one workgroup per type.
 // cost(a, b) = sum over bins i in [a, b) of W_i (g_b - mid_i)(mid_i - g_a), from prefix sums P0, P1, P2 of W, W*mid,
-// W*mid^2 taken sequentially in increasing bin (fp64; the same operation order as the CPU checker).
+// W*mid^2 taken sequentially in increasing bin (fp64; the same operation order as the CPU oracle).
 struct FitRow { double p0, p1, p2, g; };
 
 __device__ __forceinline__ double fit_cost(const FitRow &ra, const FitRow &rb) {

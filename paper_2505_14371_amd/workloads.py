@@ -1,7 +1,7 @@
 """Seeded synthetic inputs shaped like the paper's workloads.
 
 This module holds no arithmetic of the method (no norms, levels, rounding, packing or updates): it only
-produces layer sizes and random layer contents, for the GPU library and for the CPU checker alike.
+produces layer sizes and random layer contents, for the GPU library and for the CPU oracle alike.
 
 The paper trains a WGAN on CIFAR and Transformer-XL on WikiText-103 (Sec. 7); neither the data nor the
 models are used here.  Gradients are replaced by heavy-tailed synthetic vectors with one scale per tensor:
@@ -167,7 +167,7 @@ def bilinear_game(seed: int = 0, n: int = 512):
 def bilinear_operator(A: np.ndarray, x: np.ndarray, y: np.ndarray, node: int, round_: int, seed: int = 0,
                       sigma: float = 0.1):
     """Node ``node``'s stochastic dual vector at (x, y): (A y, -A^T x) + N(0, sigma^2), computed in fp64 and
-    rounded to fp32.  This is the user's operator, outside the library and the checker."""
+    rounded to fp32.  This is the user's operator, outside the library and the oracle."""
     rng = np.random.default_rng(np.random.SeedSequence([seed, 0x0153, round_, node]))
     gx = A.astype(np.float64) @ y.astype(np.float64) + sigma * rng.standard_normal(x.size)
     gy = -(A.astype(np.float64).T @ x.astype(np.float64)) + sigma * rng.standard_normal(y.size)

@@ -13,7 +13,7 @@ def uniform_levels(S: int) -> np.ndarray:
 
 
 class OracleQODA:
-    """State of Alg. 1 kept by the checker: X_1, Y_t, the step-size accumulator and the previous messages."""
+    """State of Alg. 1 kept by the oracle: X_1, Y_t, the step-size accumulator and the previous messages."""
 
     def __init__(self, sizes, points, levels, K: int, x1: Sequence[np.ndarray], seed: int, q_hat: Optional[float] = None):
         self.q_hat = q_hat                                                          # None: eq. (general_stepsize); else eq. (Alt)

@@ -1,6 +1,6 @@
 // Drives every routine of the CPU oracle once on ragged, empty and extreme inputs.  Built by
 // tests/test_oracle_sanitizers.py with -fsanitize=address,undefined (any finding aborts), it checks that the
-// checker itself reads and writes inside its buffers and has no undefined arithmetic.  It verifies no values: the
+// oracle itself reads and writes inside its buffers and has no undefined arithmetic.  It verifies no values: the
 // pins in tests/test_oracle_*.py do that.
 #include "../oracle/qoda_oracle.cpp"
 

@@ -1,5 +1,5 @@
 """The CPU oracle built with AddressSanitizer and UndefinedBehaviorSanitizer and driven once over all its routines on
-ragged, empty and extreme inputs (tests/oracle_sanitize_driver.cpp): the checker must itself be free of out-of-bounds
+ragged, empty and extreme inputs (tests/oracle_sanitize_driver.cpp): the oracle must itself be free of out-of-bounds
 accesses and undefined arithmetic before its outputs are used to judge anything."""
 import os
 import shutil
