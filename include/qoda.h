@@ -106,7 +106,8 @@ typedef struct {
 } qoda_config;
 
 /* Create / destroy.  qoda_create allocates all device scratch (a few MB plus 16 bytes per 16384 coordinates per
- * node, under bucket scope up to 28 more per 16384 coordinates of the model, in small models 16 more per node; the fit's
+ * node, under bucket scope up to 28 more per 16384 coordinates of the model, in models whose tiles are held (see
+ * qoda_exchange_tries) 16 more per node; the fit's
  * histograms, two of 8 KB per (node, layer), are allocated on the first qoda_fit_levels, under bucket scope one of
  * them, at once).  Levels start
  * uniform: l_j = j/(S-1).  On failure *out is NULL. */
@@ -297,8 +298,8 @@ int qoda_status(qoda_ctx *ctx, void *stream);
  *   head of each tile of dst_dev.  0 stores: the read-only ceiling; 16: a copy; 2 and 8: about the read/write mix of
  *   the quantize pass and of the decode + update pass.  The measured ceilings that bench.py prints beside the nominal
  *   HBM peak come from this kernel.
- * qoda_exchange_tries: in the one launch of small models the workgroups exchange their tiles' statistics; how often a
- *   workgroup looks for the others' before it computes the missing ones itself, with the same results (default 1024, about
+ * qoda_exchange_tries: where a launch computes norms and codes with one read of the vectors (small models, and larger ones of
+ *   small layers) the workgroups exchange their tiles' statistics; how often a workgroup looks for the others' before it computes the missing ones itself, with the same results (default 1024, about
  *   a millisecond, so that a group's workgroups that are not on the device together cannot stop it).  0: it does not look
  *   and computes all of them, which a test uses to run that path.  QODA_EINVAL for tries < 0. */
 #define QODA_NUM_KERNELS 24

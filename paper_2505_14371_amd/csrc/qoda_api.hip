@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/qoda.h"
+#include "qoda_choices.h"
 #include "qoda_kernels.h"
 
 using namespace qoda;
@@ -87,7 +88,13 @@ struct qoda_ctx {
   };
   Table t_grad, t_msg, t_prev, t_in, t_x1, t_y, t_xh, t_xn, t_mean;
   bool small = false;   // the model's size and code widths allow k_quantize_small
-  unsigned long long *d_exch = nullptr;   // its exchange area, zero between calls
+  HeldModel held = {};   // what the choice of k_quantize_held goes by
+  // where it takes the small layers only: their tiles, those of the others, and the others themselves
+  int2 *d_held = nullptr, *d_rest = nullptr;
+  int *d_rest_layers = nullptr;
+  int n_rest = 0, n_rest_layers = 0;
+  unsigned long long *d_exch = nullptr;   // the exchange area of both, zero between calls
+  bool exch_zero = true;                  // the last pass with held tiles was enqueued whole, so that it leaves d_exch zero
   unsigned int *d_finished = nullptr;
   int tries = kSmallTries;   // qoda_exchange_tries
   unsigned int *d_readers = nullptr;   // of the decode pass with its own step size; zero between calls
@@ -259,6 +266,7 @@ Dev base_args(const qoda_ctx *c) {
   a.n_empty = c->n_empty;
   a.GS = c->n_runs[3];
   a.L = c->L; a.G = c->G; a.K = c->K; a.M = c->M;
+  a.NT = c->G;
   a.scope = c->scope;
   a.kind = c->kind;
   a.type_points = c->d_type_points;
@@ -309,7 +317,7 @@ void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_runs[0], c->d_runs[1], c->d_runs[2], c->d_runs[3], c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_bins, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
                   c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
-                  c->d_type_first, c->d_type_layers};
+                  c->d_type_first, c->d_type_layers, c->d_held, c->d_rest, c->d_rest_layers};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   qoda_ctx::Table *tabs[] = {&c->t_grad, &c->t_msg, &c->t_prev, &c->t_in, &c->t_x1, &c->t_y, &c->t_xh, &c->t_xn, &c->t_mean};
@@ -357,6 +365,13 @@ bool use_small(const qoda_ctx *c, int nnodes) {
   return c->small && (long long)nnodes * c->G <= kSmallTiles && (c->prof_mask & parts) == 0u;
 }
 
+// Which tiles a call that computes the norms of `nnodes` nodes itself holds.  A caller who asks for the times of the kernels that this
+// stands for gets those kernels.
+HeldTiles use_held(const qoda_ctx *c, int nnodes) {
+  const unsigned int parts = 1u << kIdSumsq | 1u << kIdNormFinalize | 1u << kIdNormVector | 1u << kIdDeltaFinalize;
+  return (c->prof_mask & parts) == 0u ? held_tiles(c->held, nnodes) : kHoldNone;
+}
+
 // Whether k_fit_dp does the work of the kernels before it; a caller who asks for their times gets them.
 bool fit_in_one(const qoda_ctx *c) {
   const unsigned int parts = 1u << kIdNormFinalize | 1u << kIdFitTypemax | 1u << kIdFitPool;
@@ -377,6 +392,37 @@ int run_norm_pass(qoda_ctx *c, Dev a, bool with_hist, hipStream_t s) {
   LAUNCH(c, with_hist ? kIdSumsqHist : kIdSumsq, s, launch_sumsq(a, with_hist, s));
   LAUNCH(c, kIdNormFinalize, s, launch_norm_finalize(a, s));
   if (c->scope == kScopeVector) LAUNCH(c, kIdNormVector, s, launch_norm_vector(a, s));
+  return QODA_OK;
+}
+
+hipError_t clear_exchange(const qoda_ctx *c, hipStream_t s) {
+  return launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_exch), 2 * (size_t)c->K * exch_row(c->G), s);
+}
+
+// Norms, quantize and delta of the nodes of `a`, with all tiles held, or those of the small layers and the others as ever.
+int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
+  // The pass finds the exchange area zero and leaves it so.  Not after one that failed between its launches; and a captured pass,
+  // which clears for itself then, says nothing about the state now.
+  const bool captured = is_captured(s);
+  if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
+  if (!captured) c->exch_zero = false;
+  Dev rest = a;
+  if (which == kHoldSmall) {
+    rest.tiles = c->d_rest;
+    rest.NT = c->n_rest;
+    rest.stiles = nullptr;
+    rest.layers = c->d_rest_layers;
+    rest.NL = c->n_rest_layers;
+    LAUNCH(c, kIdSumsq, s, launch_sumsq(rest, false, s));
+    LAUNCH(c, kIdNormFinalize, s, launch_norm_finalize(rest, s));
+    a.tiles = c->d_held;
+    a.NT = c->G - c->n_rest;
+  }
+  LAUNCH(c, kIdQuantize, s, launch_quantize_held(a, c->planes_mask, s));
+  if (which == kHoldSmall) LAUNCH(c, kIdQuantize, s, launch_quantize(rest, c->planes_mask, s));
+  a.clear_exch = true;
+  LAUNCH(c, kIdDeltaFinalize, s, launch_delta_finalize(a, s));
+  if (!captured) c->exch_zero = true;
   return QODA_OK;
 }
 
@@ -415,8 +461,13 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
   }
   if (!cached && use_small(c, nnodes)) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
+    if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
     LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
     return QODA_OK;
+  }
+  if (!cached && use_held(c, nnodes) != kHoldNone) {
+    c->norms_valid = false;
+    return quantize_held(c, a, use_held(c, nnodes), s);
   }
   if (!cached) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
@@ -598,11 +649,37 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
     c->small = one_width && c->G > 0 && c->G <= kSmallTiles &&
                (c->scope == kScopeLayer ? most_chunks <= kSmallGroup
                                         : c->scope == kScopeVector && c->G <= kSmallGroup && c->L <= kSmallLayers);
+    HeldModel &h = c->held;
+    h.scope = c->scope == kScopeVector && !one_width ? kScopeBucket : c->scope;   // a node's tiles of several widths are not one launch
+    h.tiles = c->G;
+    h.largest = most_chunks;
+    h.slots = c->planes_mask & (1u << 9) ? kHeldSlotsWide : kHeldSlots;
+    for (const LayerMeta &m : c->meta)
+      if (m.nchunks <= held_small(h)) h.small_tiles += m.nchunks;
+    if (held_tiles(h, c->K) == kHoldSmall || held_tiles(h, 1) == kHoldSmall) {
+      std::vector<int2> some, rest;
+      std::vector<int> rest_layers;
+      for (int l = 0; l < c->L; ++l) {
+        const int n = c->meta[(size_t)l].nchunks;
+        for (int ch = 0; ch < n; ++ch) (n <= held_small(h) ? some : rest).push_back(make_int2(l, ch));
+        if (n > held_small(h)) rest_layers.push_back(l);
+      }
+      c->n_rest = (int)rest.size();
+      c->n_rest_layers = (int)rest_layers.size();
+      A(dev_alloc(&c->d_held, some.size()));
+      A(dev_alloc(&c->d_rest, rest.size()));
+      A(dev_alloc(&c->d_rest_layers, rest_layers.size()));
+      if (e == hipSuccess) A(hipMemcpy(c->d_held, some.data(), some.size() * sizeof(int2), hipMemcpyHostToDevice));
+      if (e == hipSuccess) A(hipMemcpy(c->d_rest, rest.data(), rest.size() * sizeof(int2), hipMemcpyHostToDevice));
+      if (e == hipSuccess) A(hipMemcpy(c->d_rest_layers, rest_layers.data(), rest_layers.size() * sizeof(int), hipMemcpyHostToDevice));
+    }
     if (c->small) {
-      A(dev_alloc(&c->d_exch, 2 * KG));
       A(dev_alloc(&c->d_finished, (size_t)c->K));
-      if (e == hipSuccess) A(hipMemset(c->d_exch, 0, 2 * KG * sizeof(unsigned long long)));
       if (e == hipSuccess) A(hipMemset(c->d_finished, 0, (size_t)c->K * sizeof(unsigned int)));
+    }
+    if (c->small || held_tiles(h, c->K) != kHoldNone || held_tiles(h, 1) != kHoldNone) {
+      A(dev_alloc(&c->d_exch, c->K * exch_row(c->G)));
+      if (e == hipSuccess) A(hipMemset(c->d_exch, 0, c->K * exch_row(c->G) * sizeof(unsigned long long)));
     }
   }
   A(dev_alloc(&c->d_dp_arg, (size_t)arg_total));
@@ -883,9 +960,11 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     a.inv = nb.inv;
     bool kept = of_context && c->norms_valid && c->norms_round == round;
     for (int l = 0; l < c->L && kept; ++l) kept = c->norms_grad[(size_t)node * c->L + l] == grad_dev[l];
-    if (!kept && of_context && use_small(c, 1)) {
+    if (!kept && of_context && (use_small(c, 1) || use_held(c, 1) != kHoldNone)) {
       c->norms_valid = false;   // this node's kept norms are about to be overwritten
-      a.exch = c->d_exch + (size_t)node * 2 * c->G;   // the node's row
+      a.exch = c->d_exch + (size_t)node * exch_row(c->G);   // the node's row
+      if (!use_small(c, 1)) return quantize_held(c, a, use_held(c, 1), s);
+      if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
       LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
       return QODA_OK;
     }

@@ -17,6 +17,8 @@ constexpr int kSmallThreads = 512;   // k_quantize_small: a wave per octet of a 
 constexpr int kSmallTiles = 512;     // the most tiles of a launch of k_quantize_small,
 constexpr int kSmallGroup = 416;     // of a group whose statistics it combines,
 constexpr int kSmallLayers = 64;     // and the most layers under vector scope
+constexpr int kHeldSlots = 1024;     // tiles that the device holds at once in k_quantize_held: four workgroups on each of 256 CUs,
+constexpr int kHeldSlotsWide = 768;  // three with 9-bit codes; and the most tiles of a group
 constexpr int kSmallTries = 1024;    // looks for the statistics of a group before missing ones are computed (about 1 ms)
 constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
@@ -32,6 +34,9 @@ enum NormScope { kScopeLayer = 0, kScopeVector = 1, kScopeBucket = 2 };
 // statistic over its vector (sum of squares, sum of magnitudes, largest magnitude), derives the fp32 norm from it
 // (floor root; one rounding; exact) and weighs the vector by ||v||_q^2 in the level fit.
 enum NormKind { kNormLinf = 0, kNormL1 = 1, kNormL2 = 2 };
+
+// Words of a node's row of the exchange area: statistics of the tiles, distances of the tiles or words of the layers, and the node's.
+constexpr size_t exch_row(int G) { return 2 * (size_t)G + 1; }
 
 struct LayerMeta {
   long long d;         // elements
@@ -51,6 +56,9 @@ struct Dev {
   const int2 *tiles;  // per tile: (layer, chunk inside layer)
   const int4 *stiles; // per run of up to kSuperTile tiles of one layer: (layer, first chunk inside layer, chunks, -)
   int L, G, GS, K, M; // GS = number of runs
+  int NT;             // tiles of this launch: G, or those that a table of some of them lists
+  const int *layers;  // layers of this launch (NL of them); nullptr: all
+  int NL;
   int scope;          // NormScope
   int kind;           // NormKind
   const int *type_points;          // [M]
@@ -62,9 +70,10 @@ struct Dev {
   const unsigned char *const *msgs_in;  // [K] messages to decode
   double *partial;    // [K*G] per-tile statistics (sums of squares, sums of magnitudes or largest magnitudes)
   double *dpartial;   // [K*G] per-tile squared differences
-  unsigned long long *exch;   // k_quantize_small: [K][2][G] statistics and squared distances in exchange; 0 between calls
+  unsigned long long *exch;   // [K][exch_row(G)] what the workgroups of k_quantize_small and k_quantize_held exchange; 0 between calls
+  bool clear_exch;            // k_delta_finalize clears it (k_quantize_small does so itself)
   unsigned int *finished;     // k_quantize_small: [K] workgroups that are done; 0 between calls
-  int tries;                  // k_quantize_small: looks for the others' statistics; 0: it computes all of them
+  int tries;                  // looks for the others' statistics; 0: it computes all of them
   double *sumsq;      // [K*L] the statistic of (node, layer); bucket scope: its largest bucket statistic
   float *norm;        // [K*L]
   float *inv;         // [K*L]
@@ -138,6 +147,8 @@ hipError_t launch_norm_vector(const Dev &a, hipStream_t s);
 hipError_t launch_quantize(const Dev &a, unsigned int planes_mask, hipStream_t s);
 // norms, quantize and delta in one launch (layer and vector scope, one code width, groups of at most kSmallGroup tiles)
 hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStream_t s);
+// norms and quantize in one launch, for the a.NT tiles of a.tiles, whose groups have at most kHeldSlots tiles
+hipError_t launch_quantize_held(const Dev &a, unsigned int planes_mask, hipStream_t s);
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s);
 hipError_t launch_step_scalars(const Dev &a, hipStream_t s);
 hipError_t launch_decode(const Dev &a, int mode, unsigned int planes_mask, hipStream_t s);   // mode: DecodeMode

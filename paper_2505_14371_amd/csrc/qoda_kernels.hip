@@ -423,7 +423,7 @@ __global__ void __launch_bounds__(kThreads) k_sumsq(Dev a) {
 // halving tree; then norm = sqrt_floor(sum), inv = rcp_floor(norm).
 __global__ void __launch_bounds__(kThreads) k_norm_finalize(Dev a) {
   __shared__ double red[kThreads];
-  const int l = blockIdx.x;
+  const int l = a.layers ? a.layers[blockIdx.x] : blockIdx.x;
   const int k = a.node0 + blockIdx.y - a.row0;   // row in the per-node scratch tables
   const LayerMeta m = a.meta[l];
   const double *p = a.partial + (size_t)k * a.G + m.first_chunk;
@@ -627,7 +627,7 @@ __device__ __forceinline__ void quantize_tile(const Dev &a, const LayerMeta &m, 
       quantize_octet<C1, false, PREV, BINS>(a, m, l, k, O, v, body, prevbody, inv, norm, T, walk, tprev, i, acc);
   }
   const double total = block_tree((double)acc, red);
-  if (t == 0) a.dpartial[(size_t)kr * a.G + blockIdx.x] = total;
+  if (t == 0) a.dpartial[(size_t)kr * a.G + m.first_chunk + chunk] = total;
 }
 
 template <int C1, bool PREV, bool BINS>
@@ -970,7 +970,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   __syncthreads();
   if ((w & 1) && live) slot[sl] = add_terms<32>(slot[sl], x, kind);
   __syncthreads();
-  unsigned long long *stat = a.exch + (size_t)kr * 2 * a.G;   // the node's statistics, then its squared distances
+  unsigned long long *stat = a.exch + (size_t)kr * exch_row(a.G);   // the node's statistics, then its squared distances
   unsigned long long *dist = stat + a.G;
   const bool vec = a.scope == kScopeVector;
   const int first = vec ? 0 : m.first_chunk, n = vec ? a.G : m.nchunks;   // the group
@@ -1137,6 +1137,362 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   }
   for (int g = i; g < 2 * a.G; g += 64)   // for the next call; everybody has read them
     __hip_atomic_store(&stat[g], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ------------------------------------------------------------------------------------------------ held tiles
+// Norms and quantization in one launch for models of any number of tiles, where their groups (a layer's tiles; under vector scope a
+// node's) are small enough (held_tiles): one read of the vectors instead of two.  A workgroup of four waves holds its tile: of a wave's
+// two octets the first in registers, the second in shared memory, where it goes without passing through registers.  With 32 KiB
+// of data, tables of up to 7 KiB and 107 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
+// 9-bit codes, whose tables are larger).  (k_quantize_small keeps a tile in the registers of eight waves: 512 tiles, all of a launch.)
+// Bound by what a tile waits for: of the 20 us that a tile of a long launch is on the device (3112 tiles, groups of 389, 5-bit codes)
+// it loads for 5.6, waits for its group for 10 and quantizes for 5.4; 1024 tiles pass in 17 us where groups are single tiles, in 21
+// where they are 256 tiles, where the two reads of the separate kernels take 24.  So statistics and collecting go before
+// quantizing (s_setprio: 11 k tiles 245 -> 232 us).  Tried without gain: every workgroup collects for itself (their looks
+// slow the loads: 3112 tiles 78 -> 125 us); loads let in by a window of 256 to 640 tiles, or an octet at a time; 512 workgroups that
+// stay, with the next tile's statistic out before the codes of this one (two workgroups a CU quantize at 2.8 us a tile instead of
+// 2.1, and who collects holds up the rest: 106 us).
+//
+// Exchange: a tile's statistic and a layer's sum travel as the complement of their bit pattern, a pair {norm, inverse} as the
+// complement of its two words: zero means "not there yet", and all of it is zero between calls (k_delta_finalize clears what the
+// pass used).  The last tile of a layer collects the statistics of the layer's tiles and combines them (in the order of
+// k_norm_finalize); under vector scope the last tile of the node then collects the sums of the layers (in the order of
+// k_norm_vector).  The others look at one word.
+// Workgroups start in the order of the table, so all tiles of the oldest unfinished group are on the device or done.  Still every
+// wait ends whatever else runs on the device: who has looked `tries` times does the collecting work itself, and a collector
+// that has, computes the missing statistics from the vectors, one tile a turn.  Such a value is the one that its own workgroup
+// stores, bit for bit, so it may be published too.  All accesses to the area are device-scope atomics; nothing but the value that
+// is read depends on them.
+__device__ __forceinline__ unsigned long long look(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double published(unsigned long long b) { return __longlong_as_double((long long)~b); }
+
+// What the workgroups of one node share.
+struct HeldNode {
+  unsigned long long *stat;    // [G] statistics of the tiles
+  unsigned long long *word;    // [G] at a layer's first tile: {norm, inverse} of the layer, under vector scope its sum
+  unsigned long long *scale;   // vector scope: {norm, inverse} of the node
+};
+
+// Shared memory of the collecting work.
+struct HeldShared {
+  double *slot;     // [256]
+  int *missing;
+};
+
+// The 256 slots of the workgroup by the tree; the total is valid in the first lane of the first wave.
+__device__ __forceinline__ double held_tree(double v, int kind, double *slot) {
+  __syncthreads();
+  slot[threadIdx.x] = v;
+  __syncthreads();
+  if (threadIdx.x >= 64) return 0.0;
+  return kind == kNormLinf ? wave_tree<false>(slot, threadIdx.x) : wave_tree<true>(slot, threadIdx.x);
+}
+
+// The index below n, of those for which some thread has none (have false), that is looked after first; n if there is none.
+__device__ __forceinline__ int first_missing(int mine, int *missing) {
+  __syncthreads();
+  if (threadIdx.x == 0) *missing = 0x7FFFFFFF;
+  __syncthreads();
+  if (mine != 0x7FFFFFFF) atomicMin(missing, mine);
+  __syncthreads();
+  return *missing;
+}
+
+// A store of the first thread is there for all threads of the workgroup that look after this.
+__device__ __forceinline__ void settle() {
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __syncthreads();
+}
+
+// The statistic of layer m (node row kr) from those of its tiles; valid in thread 0.  All threads call this.
+__device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v, const HeldNode &hn, const HeldShared &hs) {
+  const int t = threadIdx.x, kind = a.kind;
+  const unsigned long long *stat = hn.stat + m.first_chunk;
+  constexpr int N = kHeldSlots / kThreads;
+  unsigned long long got[N];
+  for (int tries = 0;; ++tries) {
+    int none = 0x7FFFFFFF;   // the first of this thread's tiles whose statistic is not there
+#pragma unroll
+    for (int q = N - 1; q >= 0; --q) {
+      const int j = t + q * kThreads;
+      got[q] = 0ull;
+      if (j < m.nchunks) {
+        got[q] = look(&stat[j]);
+        if (got[q] == 0ull) none = j;
+      }
+    }
+    if (__syncthreads_and(none == 0x7FFFFFFF)) break;
+    if (tries < a.tries) continue;
+    const int chunk = first_missing(none, hs.missing);
+    const double s = tile_statistic(v, m.d, chunk, kind, hs.slot, t);
+    if (t == 0) publish(&hn.stat[m.first_chunk + chunk], s);
+    settle();
+  }
+  double s = t < m.nchunks ? published(got[0]) : 0.0;
+#pragma unroll
+  for (int q = 1; q < N; ++q)
+    if (t + q * kThreads < m.nchunks) s = kind == kNormLinf ? fmax(s, published(got[q])) : s + published(got[q]);
+  return held_tree(s, kind, hs.slot);
+}
+
+// Vector scope: the node's statistic from those of its layers; valid in thread 0.  All threads call this.
+__device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const HeldShared &hs) {
+  const int t = threadIdx.x, kind = a.kind;
+  double s = 0.0;
+  for (int tries = 0;; ++tries) {
+    int none = 0x7FFFFFFF;
+    s = 0.0;
+    for (int q = t; q < a.L; q += kThreads) {
+      double v = 0.0;
+      if (a.meta[q].nchunks != 0) {
+        const unsigned long long b = look(&hn.word[a.meta[q].first_chunk]);
+        if (b == 0ull) none = min(none, q);
+        else v = published(b);
+      }
+      s = kind == kNormLinf ? fmax(s, v) : s + v;
+    }
+    if (__syncthreads_and(none == 0x7FFFFFFF)) break;
+    if (tries < a.tries) continue;
+    const int q = first_missing(none, hs.missing);
+    const LayerMeta m = a.meta[q];
+    const double sum = collect_layer(a, m, a.grad[(size_t)kr * a.L + q], hn, hs);
+    if (t == 0) publish(&hn.word[m.first_chunk], sum);
+    settle();
+  }
+  return held_tree(s, kind, hs.slot);
+}
+
+// Norm and inverse of a statistic, as k_norm_finalize has them.
+__device__ __forceinline__ void held_scale(double s, int kind, float &n, float &r) {
+  n = 0.0f;
+  r = 0.0f;
+  if (!stat_finite(s, kind)) return;
+  if (kind == kNormL2) {
+    norm_and_inverse(s, n, r);
+  } else {
+    n = __double2float_rn(s);
+    r = inverse_of(n);
+  }
+}
+
+template <int C1, bool PREV>
+__global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev a) {
+  typedef __attribute__((address_space(3))) void *lds_ptr;
+  constexpr int kTabBytes = 16 << (C1 - 1), kPrevBytes = PREV ? 4 << C1 : 0;
+  __shared__ v4f hold[kThreads / 64][8][64];   // the waves' second octets
+  __shared__ float4 bins[kGridPoints];
+  // the slots of the sums, and between the norm and the distances the tables that would not fit beside them
+  __shared__ __attribute__((aligned(16))) unsigned char area[kTabBytes + kPrevBytes > 8 * kThreads ? kTabBytes + kPrevBytes : 8 * kThreads];
+  __shared__ float scale[2];
+  __shared__ int flag[1];
+  double *slot = reinterpret_cast<double *>(area);
+  float4 *tab = reinterpret_cast<float4 *>(area);
+  float *tprev = reinterpret_cast<float *>(area + kTabBytes);
+  __builtin_amdgcn_s_setprio(3);
+  const int2 tile = a.tiles[blockIdx.x];
+  const int l = tile.x;
+  const int k = a.node0 + blockIdx.y;
+  const LayerMeta m = a.meta[l];
+  if (m.planes != C1) return;   // layers of another code width are served by another instantiation
+  const int t = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i = t & 63;
+  const int kr = k - a.row0;   // row of this node in the per-node scratch and pointer tables
+  const long long noct = (m.nblk + 7) >> 3, O0 = (long long)tile.y * 8 + 2 * w;   // octets inside the layer
+  const float *__restrict__ v = a.grad[(size_t)kr * a.L + l];
+  unsigned char *msg = a.msg[kr];
+  const unsigned char *prevmsg = (PREV && a.prev != nullptr) ? a.prev[kr] : nullptr;
+  float x[32];
+  if (O0 < noct) {
+    load_octet(v, O0, m.d, i, x);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) x[j] = 0.0f;
+  }
+  if (O0 + 1 < noct) {
+    if ((O0 + 2) * 2048 <= m.d) {
+      const auto *src = as_global(v) + (O0 + 1) * 2048 + 4 * i;
+#pragma unroll
+      for (int bb = 0; bb < 8; ++bb)   // 16 bytes a lane, nontemporal
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) void *>(src + bb * kBlockCoords),
+                                         (lds_ptr)(void *)&hold[w][bb][0], 16, 0, 2);
+    } else {   // the layer's ragged last octet
+#pragma unroll 1
+      for (int bb = 0; bb < 8; ++bb) {
+        const long long e = (O0 + 1) * 2048 + bb * kBlockCoords + 4 * i;
+        float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (e < m.d) load4(v, e, m.d, y);
+        v4f q;
+        q.x = y[0]; q.y = y[1]; q.z = y[2]; q.w = y[3];
+        hold[w][bb][i] = q;
+      }
+    }
+  }
+  // tables that do not depend on the norm: requested now, the ones that share the area of the slots stored later
+  const float *lev = a.lev + (size_t)m.type * kMaxPoints, *rg = a.rgap + (size_t)m.type * kMaxPoints;
+  const int walk = a.walk[m.type];
+  const float lj = t < m.S ? lev[t] : 0.0f, ln = t + 1 < m.S ? lev[t + 1] : __builtin_inff(), rj = t < m.S ? rg[t] : 0.0f;
+  float pl[2] = {0.0f, 0.0f};
+  if (PREV && prevmsg) {
+    const float *hp = reinterpret_cast<const float *>(prevmsg + m.hdr_off);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c = t + q * kThreads;   // codes past S-1 decode as the last level
+      if (c < (1 << C1)) {
+        const float mag = hp[0] * hp[1 + min(c >> 1, m.S - 1)];
+        pl[q] = (c & 1) ? -mag : mag;
+      }
+    }
+  }
+  {
+    const v4f *src = reinterpret_cast<const v4f *>(a.bins + (size_t)m.type * kGridPoints);
+    *reinterpret_cast<v4f *>(&bins[t]) = src[t];
+    if (t == 0) *reinterpret_cast<v4f *>(&bins[kThreads]) = src[kThreads];
+  }
+  // the tile's statistic: a slot runs through the wave's two octets
+  const int kind = a.kind;
+  double own = 0.0;
+  if (O0 < noct) own = add_terms<32>(own, x, kind);
+  if (O0 + 1 < noct) {
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+#pragma unroll
+    for (int bb = 0; bb < 8; ++bb) {
+      const v4f q = hold[w][bb][i];
+      const float y[4] = {q.x, q.y, q.z, q.w};
+      own = add_terms<4>(own, y, kind);
+    }
+  }
+  const HeldShared hs = {slot, flag};
+  const bool vec = a.scope == kScopeVector;
+  unsigned long long *row = a.exch + (size_t)kr * exch_row(a.G);
+  const HeldNode hn = {row, row + a.G, row + 2 * (size_t)a.G};
+  unsigned long long *word = vec ? hn.scale : &hn.word[m.first_chunk];   // of the group
+  double s = held_tree(own, kind, slot);   // valid in thread 0, as all totals here
+  if (m.nchunks > 1 && t == 0) publish(&hn.stat[m.first_chunk + tile.y], s);
+  // collectors: the last tile of a layer, and under vector scope that of the last layer with coordinates
+  bool collects = tile.y == m.nchunks - 1;
+  if (collects) {
+    if (m.nchunks > 1) s = collect_layer(a, m, v, hn, hs);
+    if (vec) {
+      if (t == 0) {
+        publish(&hn.word[m.first_chunk], s);
+        float n, r;   // a layer's own norm raises this flag under vector scope too
+        held_scale(s, kind, n, r);
+        if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
+      }
+      collects = m.first_chunk + m.nchunks == a.G;
+      if (collects) {
+        settle();
+        s = collect_node(a, kr, hn, hs);
+      }
+    }
+  }
+  if (!collects) {
+    if (t == 0) {
+      unsigned long long b = 0ull;
+      for (int tries = 0; tries < a.tries && b == 0ull; ++tries) {
+        if (tries) __builtin_amdgcn_s_sleep(16);
+        b = look(word);
+      }
+      scale[0] = u2f((unsigned int)(~b >> 32));
+      scale[1] = u2f((unsigned int)~b);
+      flag[0] = b != 0ull;
+    }
+    __syncthreads();
+    if (flag[0] == 0) {   // no answer: the collecting work is done here as well
+      s = vec ? collect_node(a, kr, hn, hs) : collect_layer(a, m, v, hn, hs);
+      if (t == 0) held_scale(s, kind, scale[0], scale[1]);
+    }
+  } else {
+    if (t == 0) {
+      float n, r;
+      held_scale(s, kind, n, r);
+      scale[0] = n;
+      scale[1] = r;
+      if (vec || m.nchunks > 1)
+        __hip_atomic_store(word, ~((unsigned long long)f2u(n) << 32 | f2u(r)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!stat_finite(s, kind)) atomicOr(a.status, kStatusNonFinite);
+      if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
+      if (!vec) {
+        const size_t idx = (size_t)kr * a.L + l;
+        a.sumsq[idx] = s;
+        a.norm[idx] = n;
+        a.inv[idx] = r;
+      } else {
+        slot[0] = s;
+      }
+    }
+    if (vec) {   // every layer of the node has its statistic, norm and inverse
+      __syncthreads();
+      for (int q = t; q < a.L; q += kThreads) {
+        const size_t idx = (size_t)kr * a.L + q;
+        a.sumsq[idx] = slot[0];
+        a.norm[idx] = scale[0];
+        a.inv[idx] = scale[1];
+      }
+    }
+  }
+  __syncthreads();   // scale is there, the slots are free
+  const float norm = scale[0], inv = scale[1];
+  if (t < m.S) tab[t] = make_float4(lj, rj, ln, u2f((unsigned int)t));   // the walk's entries, see load_tables
+  if (PREV) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (t + q * kThreads < (1 << C1)) tprev[t + q * kThreads] = pl[q];
+  }
+  if (tile.y == 0) {   // message header of this layer: {norm, levels[S]} (Sec. 3.2: the norm in C_q = 32 bits)
+    float *h = reinterpret_cast<float *>(msg + m.hdr_off);
+    if (t < m.S) h[1 + t] = lj;
+    if (t == 0) h[0] = norm;
+  }
+  if (!vec) {   // layers without coordinates: their header entries are written by k_delta_finalize
+    for (int q = blockIdx.x * kThreads + t; q < a.n_empty; q += gridDim.x * kThreads) {
+      const size_t idx = (size_t)kr * a.L + a.empty_layers[q];
+      a.sumsq[idx] = 0.0;
+      a.norm[idx] = 0.0f;
+      a.inv[idx] = 0.0f;
+    }
+  }
+  __syncthreads();
+  __builtin_amdgcn_s_setprio(0);
+  float dacc = 0.0f;   // this slot's squared differences: an fp32 fused multiply-add chain in increasing coordinate
+  const unsigned int k0 = (unsigned int)a.seed, k1 = (unsigned int)(a.seed >> 32);
+  unsigned int Dp[C1];
+#pragma unroll
+  for (int r = 0; r < C1; ++r) Dp[r] = 0u;
+#pragma unroll 1
+  for (int oo = 0; oo < 2; ++oo) {
+    const long long O = O0 + oo;
+    if (O >= noct) break;
+    unsigned int D[C1];
+#pragma unroll
+    for (int r = 0; r < C1; ++r) D[r] = 0u;
+    if (PREV && prevmsg != nullptr) load_record<C1>(prevmsg + m.body_off + O * 256 * C1, i, Dp);
+    const bool more = oo == 0 && O + 1 < noct;
+    const auto done = [&](int bb, float (&diff)[4]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dacc = __builtin_fmaf(diff[j], diff[j], dacc);
+      asm volatile("" : "+v"(dacc));
+      if (more) {
+        const v4f q = hold[w][bb][i];
+        x[4 * bb] = q.x; x[4 * bb + 1] = q.y; x[4 * bb + 2] = q.z; x[4 * bb + 3] = q.w;
+      }
+    };
+    const unsigned int c0 = (unsigned int)(O * 256 + i);   // counter of the octet's first pair: 64 per 512 coordinates
+    const int pairs = (int)min(4ll, (m.nblk + 1 - O * 8) >> 1);   // the layer's; the others stay code 0, distance 0
+    const Scales sc = {inv, norm, 0.0f};
+    if (walk) quantize_regs<C1, PREV, true, false>(x, c0, l, a.round, k, k0, k1, sc, bins, tab, tprev, D, Dp, NoHist(), done, pairs);
+    else quantize_regs<C1, PREV, false, false>(x, c0, l, a.round, k, k0, k1, sc, bins, tab, tprev, D, Dp, NoHist(), done, pairs);
+    store_record<C1>(msg + m.body_off + O * 256 * C1, i, D);
+  }
+  __syncthreads();   // the tables are done with
+  slot[t] = (double)dacc;
+  __syncthreads();
+  if (w != 0) return;
+  const double total = wave_tree<true>(slot, i);
+  if (i == 0) a.dpartial[(size_t)kr * a.G + m.first_chunk + tile.y] = total;
 }
 
 // ------------------------------------------------------------------------------------------------ bucket scope
@@ -1488,15 +1844,22 @@ __global__ void __launch_bounds__(kThreads, 4) k_quantize_b(Dev a) {
 }
 
 // delta_k: slot j takes the node's tiles j, j+256, ... (all layers, in order), then the halving tree.
-// Bucket scope, with a.hist_old: further workgroups clear the statistics of the pass before, for the next one.
+// Further workgroups clear what the next pass finds zero: under bucket scope, with a.hist_old, the statistics of the pass before; with
+// a.clear_exch what the held tiles of this pass exchanged.
 __global__ void __launch_bounds__(kThreads) k_delta_finalize(Dev a) {
   __shared__ double red[kThreads];
   const int k = a.node0 + blockIdx.x;
+  const int kr = k - a.row0;   // row in the per-node scratch and pointer tables
   if (blockIdx.y != 0) {
-    zero_stats(a.hist_old, a.sumsq_old, (size_t)k * a.L + blockIdx.y - 1);
+    if (a.clear_exch) {
+      unsigned long long *row = a.exch + (size_t)kr * exch_row(a.G);
+      const size_t n = exch_row(a.G);
+      for (size_t j = (blockIdx.y - 1) * (size_t)kThreads + threadIdx.x; j < n; j += (gridDim.y - 1) * (size_t)kThreads) row[j] = 0ull;
+    } else {
+      zero_stats(a.hist_old, a.sumsq_old, (size_t)k * a.L + blockIdx.y - 1);
+    }
     return;
   }
-  const int kr = k - a.row0;   // row in the per-node scratch and pointer tables
   const double *p = a.dpartial + (size_t)kr * a.G;
   double acc = 0.0;
   // the loads of a slot are independent of its running sum: requested 16 at a time, added in the slot's order
@@ -2554,14 +2917,14 @@ hipError_t launch_zero_u32(unsigned int *p, size_t n, hipStream_t s) {
 
 template <int KIND>
 static void launch_sumsq_kind(const Dev &a, bool with_hist, hipStream_t s) {
-  const dim3 runs(a.GS, a.nnodes), tiles(a.G, a.nnodes), block(kThreads);
+  const dim3 runs(a.GS, a.nnodes), tiles(a.NT, a.nnodes), block(kThreads);
   // Without a histogram nothing is kept per run, and single tiles are the most even load.  Only where they would fill the
   // device one and a half to two times (the second fill's waves come and go with too few loads in flight) fewer, longer
   // workgroups are a little faster.  us of the pass with runs / single tiles, K = 1 and K = 8: 512 tiles 20 / 10 and - ; 2048
   // 31 / 27; 2560 38 / 32 and 38 / 32; 2800 39 / 35 and 34 / 35; 3096 39 / 37 and 36 / 38; 3300 38 / 40 and 39 / 40; 3600 45 / 43
   // and 41 / 44; 3900 44 / 44 and 45 / 45; 4600 57 / 52 and 58 / 52; 8192 90 / 88 and 87 / 87; 32768 323 / 322.
-  const long long n = (long long)a.G * a.nnodes;
-  const bool long_runs = n > 4 * kTaperWorkgroups / 3 && n < 15 * kTaperWorkgroups / 8;
+  const long long n = (long long)a.NT * a.nnodes;
+  const bool long_runs = a.stiles != nullptr && n > 4 * kTaperWorkgroups / 3 && n < 15 * kTaperWorkgroups / 8;
   if (with_hist) {
     hipLaunchKernelGGL((k_sumsq<true, KIND>), runs, block, 0, s, a);
   } else if (long_runs) {
@@ -2582,7 +2945,7 @@ hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t s) {
 }
 
 hipError_t launch_norm_finalize(const Dev &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm_finalize, dim3(a.L, a.nnodes), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(k_norm_finalize, dim3(a.layers ? a.NL : a.L, a.nnodes), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -2590,9 +2953,9 @@ template <int C1, bool PREV>
 static void launch_quantize_tables(const Dev &a, hipStream_t s) {
   constexpr bool bins = quantize_bins_width(PREV, C1), bytes = quantize_bytes_width(PREV, C1);
   static_assert(bins || bytes, "a form for every width");
-  const dim3 grid(a.G, a.nnodes), block(kThreads);
+  const dim3 grid(a.NT, a.nnodes), block(kThreads);
   if constexpr (bins) {
-    if (!bytes || quantize_bins((long long)a.G * a.nnodes, PREV, C1)) {
+    if (!bytes || quantize_bins((long long)a.NT * a.nnodes, PREV, C1)) {
       hipLaunchKernelGGL((k_quantize<C1, PREV, true>), grid, block, 0, s, a);
       return;
     }
@@ -2624,7 +2987,7 @@ static void launch_quantize_width(const Dev &a, hipStream_t s) {
 }
 
 hipError_t launch_quantize(const Dev &a, unsigned int planes_mask, hipStream_t s) {
-  if (a.G == 0 || a.nnodes == 0) return hipSuccess;
+  if (a.NT == 0 || a.nnodes == 0) return hipSuccess;
   if (planes_mask & (1u << 2)) launch_quantize_width<2>(a, s);
   if (planes_mask & (1u << 3)) launch_quantize_width<3>(a, s);
   if (planes_mask & (1u << 4)) launch_quantize_width<4>(a, s);
@@ -2658,9 +3021,31 @@ hipError_t launch_quantize_small(const Dev &a, unsigned int planes_mask, hipStre
   return hipGetLastError();
 }
 
+template <int C1>
+static void launch_held_width(const Dev &a, hipStream_t s) {
+  const dim3 grid(a.NT, a.nnodes), block(kThreads);
+  if (a.prev != nullptr) hipLaunchKernelGGL((k_quantize_held<C1, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_quantize_held<C1, false>), grid, block, 0, s, a);
+}
+
+hipError_t launch_quantize_held(const Dev &a, unsigned int planes_mask, hipStream_t s) {
+  if (a.NT == 0 || a.nnodes == 0) return hipSuccess;
+  if (planes_mask & (1u << 2)) launch_held_width<2>(a, s);
+  if (planes_mask & (1u << 3)) launch_held_width<3>(a, s);
+  if (planes_mask & (1u << 4)) launch_held_width<4>(a, s);
+  if (planes_mask & (1u << 5)) launch_held_width<5>(a, s);
+  if (planes_mask & (1u << 6)) launch_held_width<6>(a, s);
+  if (planes_mask & (1u << 7)) launch_held_width<7>(a, s);
+  if (planes_mask & (1u << 8)) launch_held_width<8>(a, s);
+  if (planes_mask & (1u << 9)) launch_held_width<9>(a, s);
+  return hipGetLastError();
+}
+
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s) {
   // the layers go into grid.y: up to 65534 of them (the caller sees to it)
-  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes, a.hist_old ? 1 + a.L : 1), dim3(kThreads), 0, s, a);
+  const size_t clear = (exch_row(a.G) + 4 * kThreads - 1) / (4 * kThreads);   // workgroups, about four words a thread
+  const unsigned int more = a.clear_exch ? (unsigned int)(clear < 256 ? clear : 256) : a.hist_old ? a.L : 0;
+  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes, 1 + more), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -46,7 +46,7 @@ def _short(name: str) -> str:
     raw = [a.strip() for a in (m.group(2) or "<>")[1:-1].split(",") if a.strip()]
     if base == "k_decode" and len(raw) >= 2:
         return "k_decode<" + {"0": "false", "1": "true", "2": "alt", "3": "extrapolate", "4": "true"}.get(raw[1], raw[1]) + ">"
-    if base in ("k_quantize", "k_quantize_b", "k_quantize_small"):   # whatever the code width, with or without a previous message
+    if base in ("k_quantize", "k_quantize_b", "k_quantize_small", "k_quantize_held"):   # whatever the code width, with or without a previous message
         return "k_quantize"
     if base == "k_index_hist":
         return base
@@ -57,10 +57,12 @@ def _short(name: str) -> str:
 def _label(name: str) -> str:
     """The class name, and which of its kernels where a class has several."""
     label = _short(name)
-    if label == "k_quantize" and re.search(r"k_quantize(_b|_small)?<\d+, false", name):
+    if label == "k_quantize" and re.search(r"k_quantize(_b|_small|_held)?<\d+, false", name):
         label = "k_quantize (no prev)"   # the round-1 variant that reads no previous message
     if "k_quantize_small" in name:
         label += " [with norms and delta]"
+    if "k_quantize_held" in name:
+        label += " [with norms]"
     if re.search(r"k_decode<\d+, 4", name):
         label += " [with step size]"
     m = re.search(r"k_fit_dp<([12])>", name)
@@ -177,7 +179,7 @@ def main():
         if "qoda::" not in r["Name"]:
             continue
         label = _label(r["Name"])
-        width = re.search(r"k_(quantize|quantize_b|quantize_small|decode)<(\d+)", r["Name"])
+        width = re.search(r"k_(quantize|quantize_b|quantize_small|quantize_held|decode)<(\d+)", r["Name"])
         if width and a.bench_json:             # a run with two workloads: tell their code widths apart
             label += f" [{width.group(2)}-bit codes]"
         lines.append(f"{label:<42}{r['Calls']:>7}{float(r['AverageNs']) / 1e3:>12.1f}"

@@ -301,7 +301,7 @@ class Context:
 
     # -- measurement aids
     def exchange_tries(self, tries: int):
-        """How often a workgroup of a small model's one launch looks for the others' statistics before it computes them."""
+        """How often a workgroup of a launch that computes norms and codes looks for the others' statistics before it computes them."""
         self._check(self._lib.qoda_exchange_tries(self._h, tries))
 
     def profile_enable(self, classes=True):

@@ -91,8 +91,11 @@ hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) {
   });
 }
 hipError_t launch_quantize_small(const Dev &, unsigned int, hipStream_t) { return record("quantize_small"); }
+hipError_t launch_quantize_held(const Dev &a, unsigned int, hipStream_t) {
+  return record("quantize_held:" + std::to_string(a.NT), [=] { a.exch[0] += 1; });
+}
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t) {
-  return record("delta", [=] { if (a.hist_old) clear_sums(a.hist_old, (size_t)a.K * a.L); });
+  return record("delta", [=] { if (a.clear_exch) std::memset(a.exch, 0, 8 * a.nnodes * exch_row(a.G)); if (a.hist_old) clear_sums(a.hist_old, (size_t)a.K * a.L); });
 }
 hipError_t launch_step_scalars(const Dev &, hipStream_t) { return record("step_scalars"); }
 hipError_t launch_decode(const Dev &, int mode, unsigned int, hipStream_t) { return record("decode:" + std::to_string(mode)); }

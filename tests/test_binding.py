@@ -42,6 +42,7 @@ def test_gradients_are_compared_with_the_parameters_as_they_are():
     ("void qoda::k_quantize<4, true>(qoda::Dev)", "k_quantize", "k_quantize"),
     ("void qoda::k_quantize_b<4, false, 2>(qoda::Dev)", "k_quantize", "k_quantize (no prev)"),
     ("void qoda::k_quantize_small<4, true>(qoda::Dev)", "k_quantize", "k_quantize [with norms and delta]"),
+    ("void qoda::k_quantize_held<4, false>(qoda::Dev)", "k_quantize", "k_quantize (no prev) [with norms]"),
     ("void qoda::k_decode<4, 1, false>(qoda::Dev)", "k_decode<true>", "k_decode<true>"),
     ("void qoda::k_decode<4, 4, false>(qoda::Dev)", "k_decode<true>", "k_decode<true> [with step size]"),
     ("void qoda::k_fit_dp<1>(qoda::Dev)", "k_fit_dp", "k_fit_dp [with norms and pooling]"),

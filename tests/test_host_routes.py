@@ -260,3 +260,89 @@ def test_routes_of_the_sizes_that_the_gpu_tests_compare(routes):
         m = routes(sizes, types=types, points=points, K=K, norm_scope=2)
         names = m.launches(lambda: m.ctx.fit_levels(None, 3, stream=0))
         assert (names == ["fit_dp:buckets"]) == bucket_scope, (K, layers)
+
+
+def held(tiles):
+    return [f"quantize_held:{tiles}", "delta"]
+
+
+class TestHeldTiles:
+    """Calls that hold their tiles from the norm to the codes."""
+
+    def quantize(self, m, one=False):
+        if one:
+            return m.launches(lambda: m.ctx.quantize(0, m.grads[:m.L], 1, m.msgs[0], m.prev[0], stream=0))
+        return m.launches(lambda: m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0))
+
+    # tiles of a layer, layers, K, scope, grid points; whether all tiles of a call for all nodes are held
+    @pytest.mark.parametrize("tiles, layers, K, scope, S, all_nodes", [
+        (639, 1, 1, 0, 8, False), (640, 1, 1, 0, 8, True), (1024, 1, 1, 0, 8, True), (1025, 1, 1, 0, 8, False), (341, 1, 40, 0, 8, True),
+        (342, 1, 40, 0, 8, False), (448, 1, 6, 0, 8, True), (447, 1, 6, 0, 8, False), (512, 1, 6, 0, 8, True), (512, 1, 7, 0, 8, False),
+        (1024, 3, 1, 0, 8, True), (1024, 2, 2, 0, 8, False), (64, 30, 2, 0, 256, True), (65, 30, 2, 0, 256, False), (768, 1, 1, 0, 256, True),
+        (769, 1, 1, 0, 256, False), (416, 1, 2, 1, 8, True), (415, 1, 2, 1, 8, False), (83, 10, 1, 1, 8, False), (84, 10, 1, 1, 8, True),
+        (384, 1, 10, 1, 8, True), (384, 1, 9, 1, 8, False), (383, 1, 10, 1, 8, False), (384, 1, 12, 1, 8, False), (1025, 1, 1, 1, 8, False)])
+    def test_lines(self, routes, tiles, layers, K, scope, S, all_nodes):
+        m = routes([16384 * tiles] * layers, points=(S,), K=K, norm_scope=scope)
+        separate = VECTOR if scope else LAYERS
+        assert self.quantize(m) == (held(tiles * layers) if all_nodes else separate)
+        assert m.launches(lambda: m.ctx.quantize_noalloc(0, m.grads[:layers], 1, m.msgs[0], None, stream=0)) == separate
+        m.ctx.profile_enable(["k_norm_finalize"])
+        assert self.quantize(m) == separate
+
+    def test_large_layers_among_small_ones(self, routes):
+        m = routes([16384 * 100] * 30 + [16384 * 1000], K=1)             # a quarter of the tiles
+        assert self.quantize(m) == held(4000)
+        m = routes([16384 * 100] * 29 + [16384 * 1000], K=1)
+        assert self.quantize(m) == LAYERS
+        several = ["norms", "norm_finalize", "quantize_held:2048", "quantize", "delta"]
+        m = routes([16384 * 256] * 8 + [16384 * 2000], K=4)              # 8192 small tiles
+        assert self.quantize(m) == several and self.quantize(m, one=True) == LAYERS
+        assert self.quantize(routes([16384 * 256] * 8 + [16384 * 2000], K=3)) == LAYERS
+        assert self.quantize(routes([16384 * 256] * 8 + [16384 * 8192], K=4)) == several
+        assert self.quantize(routes([16384 * 256] * 8 + [16384 * 8193], K=4)) == LAYERS
+
+    def test_a_vector_of_several_code_widths(self, routes):
+        m = routes([16384 * 450] * 2, types=[0, 1], points=(8, 32), norm_scope=1)
+        assert self.quantize(m) == VECTOR
+        m = routes([16384 * 450] * 2, types=[0, 1], points=(8, 32))
+        assert self.quantize(m) == held(900)
+
+    def test_the_exchange_area_is_zero_when_a_pass_starts(self, routes):
+        from paper_2505_14371_amd import qoda
+
+        m = routes([16384 * 400] * 2)
+        for at in (0, 1):                                    # the pass, what clears behind it
+            with pytest.raises(qoda.QodaError):
+                m.launches(lambda: (m.lib.stand_in_fail_at(at), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
+            assert self.quantize(m) == ["zero"] + held(800) and self.quantize(m) == held(800)
+        m.lib.stand_in_capture(1)
+        assert self.quantize(m) == held(800)
+        m.lib.stand_in_capture(0)
+        with pytest.raises(qoda.QodaError):
+            m.launches(lambda: (m.lib.stand_in_fail_at(1), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
+        m.lib.stand_in_capture(1)
+        assert self.quantize(m) == ["zero"] + held(800)      # for its replays; nothing is known of the area now
+        m.lib.stand_in_capture(0)
+        assert self.quantize(m) == ["zero"] + held(800)
+        m = routes([16384 * 200, 16384 * 300], K=2)          # one node: 500 tiles in one launch, which clears what a failed pass left
+        with pytest.raises(qoda.QodaError):
+            m.launches(lambda: (m.lib.stand_in_fail_at(1), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
+        assert self.quantize(m, one=True) == ["zero"] + SMALL
+
+    def test_sizes_of_the_gpu_tests(self, routes):
+        """tests/test_gpu_held_tiles.py compares this route with the separate kernels: at its sizes it is the one that is taken."""
+        import test_gpu_held_tiles as g
+
+        def names(sizes, K, scope=0, types=None, points=(16,)):
+            return self.quantize(routes(sizes, types=types, points=points, K=K, norm_scope=scope))
+
+        tiles = lambda sizes: sum(-(-s // 16384) for s in sizes)
+        for shape, (sizes, K) in g.SIZES.items():
+            for S in (16, 130):
+                assert (names(sizes, K, points=(S,)) == held(tiles(sizes))) == (S == 16 or "1024" not in shape), (shape, S)
+        for sizes, K in g.VECTORS + [g.NODES, g.THREE]:
+            assert names(sizes, K, scope=1) == held(tiles(sizes))
+        for sizes, K in (g.NODES, g.THREE):
+            assert names(sizes, K) == held(tiles(sizes))
+        assert names(g.WIDTHS, 1, types=[0, 1, 1, 2, 2], points=(4, 16, 200)) == held(tiles(g.WIDTHS))
+        assert names(*g.BESIDE)[:3] == ["norms", "norm_finalize", f"quantize_held:{tiles(g.BESIDE[0]) - 1025}"]
