@@ -100,20 +100,22 @@ inline bool quantize_bins(long long n, bool prev, int bits) {
 // Which tiles of a call that computes norms and codes are held from the one to the other (k_quantize_held: one read of the vectors)
 // and which go through the norm pass, its combination and the quantizer.  A group (a layer's tiles; under vector scope a
 // node's) waits for its last tile, so what counts is how its tiles share the slots of the device with others that load or quantize
-// meanwhile.  us of a quantize call, separate kernels / held:
-//   * All tiles on the device at once: 5 bits 640 tiles 30 / 24, 1024 in one layer 36 / 29, in 64 tiles each 36 / 29; one norm per
+// meanwhile.  us with the separate kernels / held, of a whole pass of K nodes (quantize, decode, and what else is in it), but `call`: of
+// quantize calls one after the other:
+//   * All tiles on the device at once: call, 5 bits 640 tiles 30 / 24, 1024 in one layer 36 / 29, in layers of 64 36 / 29; one norm per
 //     vector 960 38 / 29.  (Launches of k_quantize_small and a little beyond stay as they are.)
-//   * Layers of up to a third of the slots: always some that load and some that quantize.  5 bits, previous message, 3 k and 12 k
-//     tiles: layers of 1 tile 99 / 72 and 342 / 243, 64 97 / 77 and 326 / 259, 256 96 / 80 and 309 / 285, 341 92 / 82 and 312 / 297.  A
-//     few larger ones among them do no harm (up to a quarter of the tiles: 11 k tiles, 18 % in a layer of 511, 8 bits 273 / 235).
-//   * Larger groups: up to three fills, if whole groups fill the slots.  Layers of 450 2.7 k 78 / 72, 5.9 k 146 / 150; 512 3 k 90 / 75,
-//     12 k 288 / 281; 1024 3 k 90 / 83, 6 k 152 / 160; but 389 (two of them, and a part that waits) 2 k 58 / 61, 700 2.8 k 82 / 90.
-//   * Vectors: whole fills.  200 tiles, five at once: 1.2 k 41 / 41, 2.4 k 69 / 67; 300 3.6 k 97 / 93; 389 1.9 k 60 / 64, 3.1 k 92 / 91
-//     (ten layers of unlike sizes 92 / 83), 4.7 k 122 / 132; 512 4 k 108 / 101; 700 2.8 k 83 / 95.
-//   * 9 bits (three workgroups a CU), previous message: layers of 16 to 64 tiles 3 k 105 / 100, 12 k 354 / 348; 128 3 k 104 / 102, 6 k 180 / 187.
-//   * Small layers beside such as no launch can hold (two sets of launches, two more tails): only where they are many and a good part of all.
-//     Rounds: 20 k tiles in layers of up to 53 beside 54 k, 4 bits 2223 / 2131; 11.7 k beside 5.9 k, 5 bits 587 / 534; 12 k in layers of 256
-//     beside 148 k, 3 bits 7352 / 7408; one node, 2.5 k beside 6.8 k 250 / 254.
+//   * Layers of up to two fifths of the slots, vectors of up to half: there are always some that load and some that quantize.  Vectors
+//     of 389 tiles, K = 3 60 / 55, 4 73 / 62, 7 111 / 94, 16 191 / 180, of 230 K = 3 57 / 48, 12 124 / 111, of 512 K = 8 call 108 / 101;
+//     layers of up to 389, K = 4 97 / 86, 8 152 / 133, of up to 198 with 8 bits, K = 4 1459 / 1247; call, 12 k tiles in layers of 1
+//     342 / 243, 64 326 / 259, 256 309 / 285.  Larger ones among them do no harm up to a quarter of the tiles (511 of 2815, 8 bits,
+//     K = 4 455 / 407); beyond that they do: 511 of 640 tiles, K = 4 117 / 121, 8 186 / 199.
+//   * Larger groups: up to two fills.  Vectors of 650, K = 2 97 / 92; layers of up to 700, K = 2 107 / 99, 8 242 / 246; up to 991, K = 1
+//     106 / 103, 2 138 / 143.
+//   * 9 bits (three workgroups a CU), previous message, calls: layers of 16 to 64 tiles 3 k 105 / 100, 12 k 354 / 348; 192 1.5 k 57 / 57,
+//     3 k 104 / 102, 6 k 178 / 188; 384 3 k 104 / 107.
+//   * Small layers beside such as no launch can hold (two sets of launches, two more tails): only where they are many and a good part of
+//     all.  20 k tiles in layers of up to 53 beside 54 k, 4 bits 2223 / 2131; 11.7 k beside 5.9 k, 5 bits 587 / 534; 12 k in layers
+//     of 256 beside 148 k, 3 bits 7352 / 7408; one node, 2.5 k beside 6.8 k 250 / 254.
 enum HeldTiles { kHoldNone = 0, kHoldAll = 1, kHoldSmall = 2 };
 constexpr long long kHeldLeast = 640, kHeldLeastVector = 832;   // tiles of a launch
 constexpr long long kHeldSmallLeast = 8192;
@@ -122,20 +124,18 @@ struct HeldModel {
   long long tiles, small_tiles;   // of a node; in layers of up to held_small()
   int largest;                    // tiles of the largest layer
 };
-inline int held_small(const HeldModel &h) { return h.slots == kHeldSlots ? h.slots / 3 : h.slots / 12; }
+inline int held_small(const HeldModel &h) { return h.slots != kHeldSlots ? h.slots / 12 : h.scope == kScopeVector ? h.slots / 2 : 2 * h.slots / 5; }
 inline HeldTiles held_tiles(const HeldModel &h, int nodes) {
-  const long long n = h.tiles * nodes;
-  if (h.scope == kScopeVector) {
-    if (n < kHeldLeastVector || h.tiles > h.slots) return kHoldNone;
-    const long long fill = h.slots / h.tiles;   // nodes on the device at once
-    return n <= h.slots || (n <= 4 * h.slots && nodes % fill == 0 && 4 * fill * h.tiles >= 3 * h.slots) ? kHoldAll : kHoldNone;
+  const long long n = h.tiles * nodes, least = h.scope == kScopeVector ? kHeldLeastVector : kHeldLeast;
+  const int group = h.scope == kScopeVector ? (int)(h.tiles < INT32_MAX ? h.tiles : INT32_MAX) : h.largest;
+  if (h.scope == kScopeBucket || n < least) return kHoldNone;
+  if (group <= h.slots) {
+    const bool small = h.scope == kScopeVector ? group <= held_small(h) : 4 * h.small_tiles >= 3 * h.tiles;
+    if (n <= h.slots || small) return kHoldAll;
+    if (h.slots != kHeldSlots) return 4 * group <= h.slots && n <= 4 * h.slots ? kHoldAll : kHoldNone;
+    if (n <= 2 * h.slots) return kHoldAll;
   }
-  if (h.scope != kScopeLayer || n < kHeldLeast) return kHoldNone;
-  if (h.largest <= h.slots) {
-    if (n <= h.slots || 4 * h.small_tiles >= 3 * h.tiles) return kHoldAll;
-    if (h.slots == kHeldSlots && n <= 3 * h.slots && 8 * (h.slots / h.largest) * h.largest >= 7 * h.slots) return kHoldAll;
-  }
-  return h.small_tiles * nodes >= kHeldSmallLeast && 5 * h.small_tiles >= h.tiles ? kHoldSmall : kHoldNone;
+  return h.scope == kScopeLayer && h.small_tiles * nodes >= kHeldSmallLeast && 5 * h.small_tiles >= h.tiles ? kHoldSmall : kHoldNone;
 }
 
 }  // namespace qoda

@@ -276,11 +276,12 @@ class TestHeldTiles:
 
     # tiles of a layer, layers, K, scope, grid points; whether all tiles of a call for all nodes are held
     @pytest.mark.parametrize("tiles, layers, K, scope, S, all_nodes", [
-        (639, 1, 1, 0, 8, False), (640, 1, 1, 0, 8, True), (1024, 1, 1, 0, 8, True), (1025, 1, 1, 0, 8, False), (341, 1, 40, 0, 8, True),
-        (342, 1, 40, 0, 8, False), (448, 1, 6, 0, 8, True), (447, 1, 6, 0, 8, False), (512, 1, 6, 0, 8, True), (512, 1, 7, 0, 8, False),
-        (1024, 3, 1, 0, 8, True), (1024, 2, 2, 0, 8, False), (64, 30, 2, 0, 256, True), (65, 30, 2, 0, 256, False), (768, 1, 1, 0, 256, True),
-        (769, 1, 1, 0, 256, False), (416, 1, 2, 1, 8, True), (415, 1, 2, 1, 8, False), (83, 10, 1, 1, 8, False), (84, 10, 1, 1, 8, True),
-        (384, 1, 10, 1, 8, True), (384, 1, 9, 1, 8, False), (383, 1, 10, 1, 8, False), (384, 1, 12, 1, 8, False), (1025, 1, 1, 1, 8, False)])
+        (639, 1, 1, 0, 8, False), (640, 1, 1, 0, 8, True), (1024, 1, 1, 0, 8, True), (1025, 1, 1, 0, 8, False), (409, 1, 40, 0, 8, True),
+        (410, 1, 40, 0, 8, False), (682, 1, 3, 0, 8, True), (683, 1, 3, 0, 8, False), (1024, 2, 1, 0, 8, True), (1024, 3, 1, 0, 8, False),
+        (64, 30, 2, 0, 256, True), (65, 48, 1, 0, 256, False), (192, 16, 1, 0, 256, True),
+        (193, 10, 1, 0, 256, False), (192, 17, 1, 0, 256, False), (768, 1, 1, 0, 256, True), (769, 1, 1, 0, 256, False), (83, 10, 1, 1, 8, False),
+        (84, 10, 1, 1, 8, True), (512, 1, 16, 1, 8, True), (513, 1, 4, 1, 8, False), (513, 1, 3, 1, 8, True), (1024, 1, 3, 1, 8, False),
+        (1024, 1, 2, 1, 8, True), (1025, 1, 1, 1, 8, False)])
     def test_lines(self, routes, tiles, layers, K, scope, S, all_nodes):
         m = routes([16384 * tiles] * layers, points=(S,), K=K, norm_scope=scope)
         separate = VECTOR if scope else LAYERS
