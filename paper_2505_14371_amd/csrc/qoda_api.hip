@@ -420,7 +420,7 @@ int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
   }
   LAUNCH(c, kIdQuantize, s, launch_quantize_held(a, c->planes_mask, s));
   if (which == kHoldSmall) LAUNCH(c, kIdQuantize, s, launch_quantize(rest, c->planes_mask, s));
-  a.clear_exch = true;
+  a.clear_exch = (int)std::min<size_t>(256, (exch_row(c->G) + 4 * kThreads - 1) / (4 * kThreads));   // about four words a thread
   LAUNCH(c, kIdDeltaFinalize, s, launch_delta_finalize(a, s));
   if (!captured) c->exch_zero = true;
   return QODA_OK;

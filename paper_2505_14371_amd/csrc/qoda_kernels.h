@@ -56,9 +56,6 @@ struct Dev {
   const int2 *tiles;  // per tile: (layer, chunk inside layer)
   const int4 *stiles; // per run of up to kSuperTile tiles of one layer: (layer, first chunk inside layer, chunks, -)
   int L, G, GS, K, M; // GS = number of runs
-  int NT;             // tiles of this launch: G, or those that a table of some of them lists
-  const int *layers;  // layers of this launch (NL of them); nullptr: all
-  int NL;
   int scope;          // NormScope
   int kind;           // NormKind
   const int *type_points;          // [M]
@@ -71,7 +68,6 @@ struct Dev {
   double *partial;    // [K*G] per-tile statistics (sums of squares, sums of magnitudes or largest magnitudes)
   double *dpartial;   // [K*G] per-tile squared differences
   unsigned long long *exch;   // [K][exch_row(G)] what the workgroups of k_quantize_small and k_quantize_held exchange; 0 between calls
-  bool clear_exch;            // k_delta_finalize clears it (k_quantize_small does so itself)
   unsigned int *finished;     // k_quantize_small: [K] workgroups that are done; 0 between calls
   int tries;                  // looks for the others' statistics; 0: it computes all of them
   double *sumsq;      // [K*L] the statistic of (node, layer); bucket scope: its largest bucket statistic
@@ -117,6 +113,11 @@ struct Dev {
                 // statistics of bucket scope (hist, sumsq) are always indexed by the node.
   float invK;
   double invK2;
+  // (at the end: the kernels' arguments are read from host memory, line by line, and the fields above are laid out by use)
+  int NT;             // tiles of this launch: G, or those that a table of some of them lists
+  int NL;             // layers of this launch, if not all:
+  const int *layers;  // which; nullptr: all
+  int clear_exch;     // workgroups of k_delta_finalize that clear exch for a node (k_quantize_small does so itself)
 };
 
 // What the decode kernel does after the K-way mean: store it, apply eq. (ODA), apply eq. (ODA) with the two

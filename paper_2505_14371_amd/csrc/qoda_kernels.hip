@@ -1854,7 +1854,7 @@ __global__ void __launch_bounds__(kThreads) k_delta_finalize(Dev a) {
     if (a.clear_exch) {
       unsigned long long *row = a.exch + (size_t)kr * exch_row(a.G);
       const size_t n = exch_row(a.G);
-      for (size_t j = (blockIdx.y - 1) * (size_t)kThreads + threadIdx.x; j < n; j += (gridDim.y - 1) * (size_t)kThreads) row[j] = 0ull;
+      for (size_t j = (blockIdx.y - 1) * (size_t)kThreads + threadIdx.x; j < n; j += a.clear_exch * (size_t)kThreads) row[j] = 0ull;
     } else {
       zero_stats(a.hist_old, a.sumsq_old, (size_t)k * a.L + blockIdx.y - 1);
     }
@@ -3043,9 +3043,8 @@ hipError_t launch_quantize_held(const Dev &a, unsigned int planes_mask, hipStrea
 
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t s) {
   // the layers go into grid.y: up to 65534 of them (the caller sees to it)
-  const size_t clear = (exch_row(a.G) + 4 * kThreads - 1) / (4 * kThreads);   // workgroups, about four words a thread
-  const unsigned int more = a.clear_exch ? (unsigned int)(clear < 256 ? clear : 256) : a.hist_old ? a.L : 0;
-  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes, 1 + more), dim3(kThreads), 0, s, a);
+  const int more = a.clear_exch ? a.clear_exch : a.hist_old ? a.L : 0;
+  hipLaunchKernelGGL(k_delta_finalize, dim3(a.nnodes, (unsigned int)(1 + more)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
