@@ -933,9 +933,7 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
   if (rc) return rc;
   if (msg_prev_dev == msg_dev) return fail(c, QODA_EINVAL, "%s: msg_prev_dev aliases msg_dev", who);
   // the node's pointers reach the device as kernel arguments: no staging buffer, no copy, nothing to wait for
-  HIP_TRY(c, launch_stage_pointers(nb.tab, reinterpret_cast<const void *const *>(grad_dev), (size_t)c->L, s));
-  HIP_TRY(c, launch_stage_pointers(nb.tab + c->L, mp, 1, s));
-  HIP_TRY(c, launch_stage_pointers(nb.tab + c->L + 1, pp, 1, s));
+  HIP_TRY(c, launch_stage_node(nb.tab, reinterpret_cast<const void *const *>(grad_dev), (size_t)c->L, msg_dev, msg_prev_dev, s));
   Dev a = base_args(c);
   a.grad = reinterpret_cast<const float *const *>(nb.tab);
   a.msg = reinterpret_cast<unsigned char *const *>(nb.tab + c->L);

@@ -121,5 +121,11 @@ hipError_t launch_stage_pointers(void **dst, const void *const *src, size_t n, h
   std::memcpy(dst, src, n * sizeof(void *));
   return hipSuccess;
 }
+hipError_t launch_stage_node(void **dst, const void *const *src, size_t n, const void *msg, const void *prev, hipStream_t) {
+  std::memcpy(dst, src, n * sizeof(void *));
+  dst[n] = const_cast<void *>(msg);
+  dst[n + 1] = const_cast<void *>(prev);
+  return hipSuccess;
+}
 
 }  // namespace qoda
