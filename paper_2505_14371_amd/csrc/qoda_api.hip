@@ -34,7 +34,7 @@ struct qoda_ctx {
   // device memory owned by the context
   LayerMeta *d_meta = nullptr;
   int2 *d_tiles = nullptr;
-  int4 *d_runs[4] = {};   // runs of at most 1, 2, 4 and kSuperTile tiles (the first three under bucket scope only)
+  int4 *d_runs[4] = {};   // runs of at most 1, 2, 4 and kSuperTile tiles (of the first three those that use_runs may choose)
   int *d_empty = nullptr;
   int n_empty = 0;
   int n_runs[4] = {};
@@ -339,14 +339,24 @@ void free_all(qoda_ctx *c) {
 //                  3096 167 / 166 / - / 369; 10000 403 / 380 / - / 449; 40 k 1423 / 1273 / 1280 / 1362; 75 k 2607 / 2335 / 2315 / 2320
 //   kRunsCount     us of qoda_index_counts, S = 8 (128), with 1 / 2 / 8: 512 tiles 34 (41) / 32 (36) / 40 (43); 1024 40 (55) / 35 (42)
 //                  / 40 (43); 1536 47 (65) / 39 (48) / 40 (45); 3096 66 (99) / 49 (67) / 43 (50)
-enum RunUse { kRunsQuantize, kRunsFit, kRunsCount };
+//   kRunsHist      the norm pass with the histogram, layer and vector scope.  us of a fit with runs of 1 / 2 / 4 / 8, 16 levels: 27 tiles 53
+//                  / 52 / 55 / 64; 108 56 / 56 / 60 / 65; 316 58 / 59 / 59 / 69; 632 61 / 64 / 61 / 71; 1024 in one layer 62 / 57 / 54 / 60;
+//                  1930 76 / 70 / 70 / 80; 2064 76 / 79 / 81 / 91; 2986 90 / 85 / 82 / 87; 3112 80 / 79 / 80 / 79; 3860 96 / 90 / 88 / 99; 4770
+//                  117 / 110 / 100 / 105; 17 k 250 / 239 / 239 / 239.  Whole rounds with 2 / 4 / 8: ten layers, K = 8 (3112 tiles) 163 / 166 / 165,
+//                  K = 16 252 / 252 / 260; 3 k tiles, K = 12 170 / 173 / 178; 7.2 k, K = 4 - / 339 to 343 / 335
+int hist_runs(long long G, int nodes) {
+  const long long n = G * nodes;
+  return n <= 256 || (n > 1600 && n <= 8192 && G <= 640) ? 1 : n <= 5120 ? 2 : 3;
+}
+enum RunUse { kRunsQuantize, kRunsFit, kRunsCount, kRunsHist };
 void use_runs(const qoda_ctx *c, Dev &a, RunUse use, int nnodes) {
-  if (c->scope != kScopeBucket) return;   // the long runs
   const long long n = (long long)nnodes * c->G;
+  if (c->scope != kScopeBucket && use != kRunsHist) return;   // the long runs
   int i = 3;
   if (use == kRunsQuantize) i = n <= 1024 ? 0 : n <= 10000 ? 1 : 2;   // at most kQuantRun tiles
   if (use == kRunsFit) i = n <= 2048 ? 0 : n <= 65536 ? 1 : 3;
   if (use == kRunsCount) i = n <= 1024 ? 1 : 3;
+  if (use == kRunsHist) i = hist_runs(c->G, nnodes);
   a.stiles = c->d_runs[i];
   a.GS = c->n_runs[i];
 }
@@ -563,6 +573,9 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
     if (chunks <= 2048) runs[0] = list_runs(1);
     runs[1] = list_runs(2);
     runs[2] = list_runs(kQuantRun);
+  } else {
+    const int i = hist_runs(chunks, c->K);
+    if (i != 3) runs[i] = list_runs(1 << i);
   }
   runs[3] = list_runs(kSuperTile);
   std::vector<int> empty;
@@ -847,6 +860,7 @@ static int fit_levels_impl(qoda_ctx *c, const float *const *grad_dev, uint32_t r
     const bool captured = is_captured(s);
     if (captured || !c->hist_zero) LAUNCH(c, kIdZero, s, launch_zero_u32(c->d_hist, KL * kHistBins, s));
     if (!captured) c->hist_zero = false;
+    use_runs(c, a, kRunsHist, c->K);
     if (fit_in_one(c)) {
       LAUNCH(c, kIdSumsqHist, s, launch_sumsq(a, true, s));
       LAUNCH(c, kIdFitDp, s, launch_fit_dp(a, kFitLayers, s));
