@@ -12,11 +12,17 @@ object; ``state_point()`` returns X_{t+1} when asked for.
 """
 from __future__ import annotations
 
+import ctypes
 from typing import List, Optional, Sequence
 
 import torch
 
 from . import qoda
+
+try:   # built with the library; without it (another torch, say) every tensor is looked at in Python
+    from . import _qoda_torch
+except ImportError:
+    _qoda_torch = None
 
 
 class QODA:
@@ -70,7 +76,11 @@ class QODA:
         self.t = 0
 
     def _check_grads(self, node_grads):
-        """The pointer array of the K x L gradients, every tensor looked at: this loop is most of a small model's host time."""
+        """The pointer array of the K x L gradients, every tensor looked at, in native code where that suffices."""
+        if _qoda_torch is not None:
+            out = (ctypes.c_void_p * (self.K * len(self.params)))()
+            if _qoda_torch.gather(node_grads, self.params, self.K, ctypes.addressof(out)):
+                return out
         if len(node_grads) != self.K:
             raise ValueError(f"QODA.step: {len(node_grads)} gradient lists for {self.K} nodes")
         sizes, f32, ptrs = [p.numel() for p in self.params], torch.float32, []

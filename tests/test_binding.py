@@ -38,6 +38,36 @@ def test_gradients_are_compared_with_the_parameters_as_they_are():
         opt._check_grads(grads)
 
 
+def test_native_look_at_the_gradients_leaves_the_rest_to_the_python_one():
+    """What is not a list of lists of plain contiguous fp32 CUDA tensors of the parameters' sizes is not accepted (these are on the CPU)."""
+    import ctypes
+
+    from paper_2505_14371_amd import solver
+
+    if solver._qoda_torch is None:
+        from paper_2505_14371_amd import build
+
+        build.build_torch()
+        from paper_2505_14371_amd import _qoda_torch as native
+    else:
+        native = solver._qoda_torch
+
+    class Sub(torch.Tensor):
+        is_cuda = True
+
+    params = [torch.nn.Parameter(torch.zeros(4, 3)), torch.zeros(5)]
+    out = (ctypes.c_void_p * 4)()
+    good = [[torch.zeros(4, 3), torch.zeros(5)] for _ in range(2)]
+    for grads in (good, [[g.as_subclass(Sub) for g in node] for node in good], good[:1], [[*good[0], good[0][0]], good[1]], iter(good),
+                  [iter(good[0]), good[1]], [[None, None], good[1]], [[1, 2], good[1]], [], None):
+        assert native.gather(grads, params, 2, ctypes.addressof(out)) is False
+    assert list(out) == [None] * 4
+    with pytest.raises(TypeError):
+        native.gather(good, params)
+    with pytest.raises(TypeError):
+        native.gather(good, params, "2", 0)
+
+
 @pytest.mark.parametrize("symbol, cls, label", [
     ("void qoda::k_quantize<4, true>(qoda::Dev)", "k_quantize", "k_quantize"),
     ("void qoda::k_quantize_b<4, false, 2>(qoda::Dev)", "k_quantize", "k_quantize (no prev)"),

@@ -102,3 +102,30 @@ def test_argument_checks():
     with pytest.raises(RuntimeError):
         opt.state_point()
     opt.close()
+
+
+def test_gradients_are_refused_or_taken_as_before_by_the_native_look(monkeypatch):
+    """Lists, tuples, views at any offset of 16 bytes, parameters as gradients: the same addresses as the look in Python; wrong sizes,
+    types, layouts and places raise."""
+    from paper_2505_14371_amd import solver
+
+    assert solver._qoda_torch is not None
+    dev = torch.device("cuda:0")
+    params = [torch.zeros(6, 4, device=dev), torch.zeros(7, device=dev)]
+    opt = solver.QODA(params, num_nodes=2, points=4)
+    flat = torch.zeros(64, device=dev)
+    for grads in ([[torch.ones_like(p) for p in params] for _ in range(2)], tuple(tuple(torch.ones_like(p) for p in params) for _ in range(2)),
+                  [[flat[4:28].view(6, 4), flat[28:35]], [flat[36:60], torch.nn.Parameter(flat[0:7])]]):
+        got = list(opt._check_grads(grads))
+        with monkeypatch.context() as m:
+            m.setattr(solver, "_qoda_torch", None)
+            assert got == list(opt._check_grads(grads)) == [g.data_ptr() for node in grads for g in node]
+    ok = [torch.ones_like(p) for p in params]
+    for bad in (torch.zeros(6, 3, device=dev), torch.zeros(6, 4, device=dev, dtype=torch.float64), torch.zeros(4, 6, device=dev).t(),
+                torch.zeros(6, 4)):
+        with pytest.raises(ValueError):
+            opt._check_grads([ok, [bad, ok[1]]])
+    for lists in ([ok], [ok, ok[:1]], [ok, ok, ok]):
+        with pytest.raises(ValueError):
+            opt._check_grads(lists)
+    opt.close()
