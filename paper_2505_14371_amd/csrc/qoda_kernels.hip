@@ -148,6 +148,20 @@ __device__ __forceinline__ float inverse_of(float n) {
   return step_down(q, (int)f2u(__builtin_fmaf(-n, q, 1.0f)));
 }
 
+// Norm and inverse of a statistic (0 where it is not finite), by straight-line code where that will do: the general routines are 0.5 us
+// on the way of a short kernel.
+__device__ __forceinline__ void stat_scale(double s, int kind, float &n, float &r) {
+  n = 0.0f;
+  r = 0.0f;
+  if (!stat_finite(s, kind)) return;
+  if (kind == kNormL2) {
+    norm_and_inverse(s, n, r);
+  } else {
+    n = __double2float_rn(s);
+    r = inverse_of(n);
+  }
+}
+
 // Philox4x32-10 (Salmon et al., SC'11).
 __device__ __forceinline__ void philox4x32_10(unsigned int c0, unsigned int c1, unsigned int c2, unsigned int c3,
                                                unsigned int k0, unsigned int k1, unsigned int out[4]) {
@@ -448,11 +462,12 @@ __global__ void __launch_bounds__(kThreads) k_norm_finalize(Dev a) {
   }
   if (threadIdx.x == 0) {
     const bool finite = stat_finite(s, a.kind);
-    const float n = finite ? norm_of(s, a.kind) : 0.0f;
+    float n, r;
+    stat_scale(s, a.kind, n, r);
     const size_t idx = (size_t)k * a.L + l;
     a.sumsq[idx] = s;
     a.norm[idx] = n;
-    a.inv[idx] = rcp_floor(n);
+    a.inv[idx] = r;
     if (!finite) atomicOr(a.status, kStatusNonFinite);
     if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
   }
@@ -478,8 +493,8 @@ __global__ void __launch_bounds__(kThreads) k_norm_vector(Dev a) {
   __syncthreads();
   const double total = tot[0];
   const bool finite = stat_finite(total, a.kind);
-  const float n = finite ? norm_of(total, a.kind) : 0.0f;
-  const float r = rcp_floor(n);
+  float n, r;
+  stat_scale(total, a.kind, n, r);
   for (int l = threadIdx.x; l < a.L; l += kThreads) {
     const size_t idx = (size_t)k * a.L + l;
     a.sumsq[idx] = total;
@@ -849,10 +864,10 @@ __device__ __forceinline__ void sum_tiles(const Dev &a, const float *chain, cons
 // What the workgroups exchange are the values themselves: a statistic is stored as the complement of its bit pattern, so
 // that the zeros left by the call before mean "not there yet" (no double that these sums produce has all bits set).  Every
 // access to them is a device-scope atomic, so no cache keeps an old value; a value is all that a reader needs, so no fence
-// goes with it.  Only one order matters, that of a workgroup's stores and its count in `finished`: thread 0 makes both
-// stores and the count, and waits for the stores before it counts.  So who finds that all workgroups of a node have been
-// counted also finds all their values, and nothing but its own zeros is written there after that, in this call.
-// A group of one tile has nothing to exchange and waits for nothing (2 x 512 entries, K = 4: 0.6 us less).
+// goes with it.  Thread 0 of a workgroup makes both stores and then counts the workgroup in `finished`; who finds that all
+// workgroups of a node have been counted waits until all their values are there, and clears: nothing but its zeros is written
+// there after that, in this call.  (When each workgroup waited for its stores before it counted, 2 x 512 entries took 0.4 us more.)
+// A group of one tile has nothing to exchange and waits for nothing; its tile's statistic is the layer's.
 // Waiting ends: after `tries` looks a workgroup computes the missing statistics itself, one per turn, from the vectors, with
 // the same operations in the same order, and keeps them to itself.
 // Bound by latency: tile -> layer -> pointers -> values, the exchange, four pairs of blocks one after the other.  A quantize
@@ -976,16 +991,15 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   unsigned long long *dist = stat + a.G;
   const bool vec = a.scope == kScopeVector;
   const int first = vec ? 0 : m.first_chunk, n = vec ? a.G : m.nchunks;   // the group
+  const bool alone = !vec && n == 1;   // the tile's statistic is the layer's
+  double own = 0.0;
   if (w == 0) {
-    const double own = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
-    if (i == 0) {
-      if (n == 1) group[0] = own;   // nobody else needs it
-      else publish(&stat[m.first_chunk + tile.y], own);
-    }
+    own = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
+    if (i == 0) publish(&stat[m.first_chunk + tile.y], own);   // (nobody else needs it where the tile is alone; see the end)
   }
   // the group's statistics; n <= kSmallGroup, one thread each
-  bool have = t >= n || n == 1;
-  for (int tries = 0;; ++tries) {
+  bool have = t >= n;
+  for (int tries = 0; !alone; ++tries) {
     if (!have && a.tries > 0) {
       const unsigned long long b = __hip_atomic_load(&stat[first + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       have = b != 0ull;
@@ -1005,7 +1019,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
     if (t == q) have = true;
   }
   // combine: slot j takes items j, j + 256, ... in increasing order, then the tree
-  if (!vec) {
+  if (alone) {
+  } else if (!vec) {
     if (t < kThreads) {
       double s = t < n ? group[t] : 0.0;
       if (t + kThreads < n) s = kind == kNormLinf ? fmax(s, group[t + kThreads]) : s + group[t + kThreads];
@@ -1042,13 +1057,13 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
       slot[t] = s;
     }
   }
-  __syncthreads();
+  if (!alone) __syncthreads();
   if (w == 0) {
-    const double s = kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
+    const double s = alone ? own : kind == kNormLinf ? wave_tree<false>(slot, i) : wave_tree<true>(slot, i);
     if (i == 0) {
       const bool finite = stat_finite(s, kind);
-      const float nn = finite ? norm_of(s, kind) : 0.0f;
-      const float rr = rcp_floor(nn);
+      float nn, rr;
+      stat_scale(s, kind, nn, rr);
       scale[0] = nn;
       scale[1] = rr;
       total_stat[0] = s;
@@ -1118,16 +1133,21 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
   unsigned int done = 0u;
   if (i == 0) {
     publish(&dist[m.first_chunk + tile.y], total);
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // both of this thread's stores are done before the count
     done = __hip_atomic_fetch_add(&a.finished[k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (__builtin_amdgcn_readfirstlane(done) != (unsigned int)a.G - 1u) return;
   asm volatile("" : : : "memory");   // the distances are read after the count
+  // Who has been counted has both stores on their way: they are waited for here, and nothing is stored to the area after that but
+  // the zeros below.
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     double s = 0.0;
     for (int g = i + 64 * r; g < a.G; g += kThreads) {
-      const unsigned long long b = __hip_atomic_load(&dist[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long b, c;
+      do {
+        b = __hip_atomic_load(&dist[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        c = __hip_atomic_load(&stat[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } while (b == 0ull || c == 0ull);
       s = s + __longlong_as_double((long long)~b);
     }
     slot[i + 64 * r] = s;
@@ -1266,19 +1286,6 @@ __device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const H
   return held_tree(s, kind, hs.slot);
 }
 
-// Norm and inverse of a statistic, as k_norm_finalize has them.
-__device__ __forceinline__ void held_scale(double s, int kind, float &n, float &r) {
-  n = 0.0f;
-  r = 0.0f;
-  if (!stat_finite(s, kind)) return;
-  if (kind == kNormL2) {
-    norm_and_inverse(s, n, r);
-  } else {
-    n = __double2float_rn(s);
-    r = inverse_of(n);
-  }
-}
-
 template <int C1, bool PREV>
 __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev a) {
   typedef __attribute__((address_space(3))) void *lds_ptr;
@@ -1381,7 +1388,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
       if (t == 0) {
         publish(&hn.word[m.first_chunk], s);
         float n, r;   // a layer's own norm raises this flag under vector scope too
-        held_scale(s, kind, n, r);
+        stat_scale(s, kind, n, r);
         if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
       }
       collects = m.first_chunk + m.nchunks == a.G;
@@ -1405,12 +1412,12 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
     __syncthreads();
     if (flag[0] == 0) {   // no answer: the collecting work is done here as well
       s = vec ? collect_node(a, kr, hn, hs) : collect_layer(a, m, v, hn, hs);
-      if (t == 0) held_scale(s, kind, scale[0], scale[1]);
+      if (t == 0) stat_scale(s, kind, scale[0], scale[1]);
     }
   } else {
     if (t == 0) {
       float n, r;
-      held_scale(s, kind, n, r);
+      stat_scale(s, kind, n, r);
       scale[0] = n;
       scale[1] = r;
       if (vec || m.nchunks > 1)
@@ -1894,6 +1901,11 @@ __device__ __forceinline__ double sum_distances(const Dev &a) {
   for (int k = 1; k < a.K; ++k) sum = sum + a.delta[k];
   return *a.acc + sum * a.invK2;
 }
+__device__ __forceinline__ float step_size(double acc) {
+  float n, r;
+  norm_and_inverse(1.0 + acc, n, r);   // 1 + acc is 1 at least, or not a number
+  return r;
+}
 __device__ __forceinline__ void store_scalars(const Dev &a, double acc, float eta) {
   *a.acc = acc;
   a.eta[0] = eta;
@@ -1903,7 +1915,7 @@ __device__ __forceinline__ void store_scalars(const Dev &a, double acc, float et
 __global__ void k_step_scalars(Dev a) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const double acc = sum_distances(a);
-  store_scalars(a, acc, rcp_floor(sqrt_floor(1.0 + acc)));
+  store_scalars(a, acc, step_size(acc));
 }
 
 // eq. (Alt), Sec. 6: the rates for the update of this round from the sums over the rounds before it,
@@ -2014,10 +2026,17 @@ struct Part {
   }
 };
 
+// The update of a few tiles requests its part of the state before the tables are set up: there is no other wave to fill the wait for it.
+template <int MODE, int NB>
+struct StatePart {
+  static constexpr bool early = MODE == kDecodeUpdateScalars;
+  float y[early ? 4 * NB : 1], x1[early ? 4 * NB : 1];
+};
+
 // EARLY: cur is node 0's part already, requested before the tables were set up.
 template <int C1, int MODE, bool FAST, bool BUCKET, int NB, bool EARLY, bool CHAIN>
 __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, int l, long long O, int part, const float *T, int i,
-                                            float eta, float gamma, float eta_prev, Part<C1, NB, BUCKET> cur,
+                                            float eta, float gamma, float eta_prev, const StatePart<MODE, NB> &st, Part<C1, NB, BUCKET> cur,
                                             float (&diffs)[MODE == kDecodeUpdateAlt ? 4 * NB : 1], float &chain) {
   constexpr int TS = 1 << C1;   // table entries per node, indexed by code = sign | h << 1
   constexpr long long OS = 256 * C1 + (BUCKET ? 64 : 0);   // bytes per octet (bucket scope: codes + 16 norms)
@@ -2060,8 +2079,13 @@ __device__ __forceinline__ void decode_part(const Dev &a, const LayerMeta &m, in
         store4(a.x_half[l], e, dlim, out);
       } else {
         float y[4], x1[4], xn[4], xh[4];
-        load4(a.y[l], e, dlim, y);      // coordinates past the end of the layer read as 0 and add nothing below
-        load4(a.x1[l], e, dlim, x1);
+        if constexpr (StatePart<MODE, NB>::early) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { y[j] = st.y[4 * bb + j]; x1[j] = st.x1[4 * bb + j]; }
+        } else {
+          load4(a.y[l], e, dlim, y);      // coordinates past the end of the layer read as 0 and add nothing below
+          load4(a.x1[l], e, dlim, x1);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float xt = 0.0f;
@@ -2120,6 +2144,20 @@ __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDec
   const bool live = O < noct;
   Part<C1, PB, BUCKET> first = {};
   if (EARLY && live) first.load(a.msgs_in[0] + m.body_off + O * (256 * C1 + (BUCKET ? 64 : 0)), piece, i);
+  StatePart<MODE, PB> state;
+  if constexpr (StatePart<MODE, PB>::early) {
+#pragma unroll
+    for (int bb = 0; bb < PB; ++bb) {
+      const long long e = (O * 8 + piece * PB + bb) * kBlockCoords + 4 * i;
+      float q[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (e < m.d) {
+        load4(a.y[l], e, m.d, q);
+        load4(a.x1[l], e, m.d, v);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { state.y[4 * bb + j] = q[j]; state.x1[4 * bb + j] = v[j]; }
+    }
+  }
   const int TS = 1 << C1;
   double new_acc = 0.0;
   if (MODE == kDecodeUpdateScalars) new_acc = sum_distances(a);   // every wave computes what k_step_scalars computes
@@ -2140,7 +2178,7 @@ __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDec
   unsigned int readers = 0u;
   if (MODE == kDecodeUpdateScalars) {
     if (t == 0) readers = __hip_atomic_fetch_add(a.readers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    eta = gamma = rcp_floor(sqrt_floor(1.0 + new_acc));
+    eta = gamma = step_size(new_acc);
   }
   if (ALT) eta_prev = a.eta[2];
   if (MODE == kDecodeExtrapolate) gamma = a.gamma_in[0];
@@ -2149,14 +2187,14 @@ __global__ void __launch_bounds__(NB > 8 ? kThreads : 2 * kThreads, MODE != kDec
     for (int oo = 0; oo < NB / 8; ++oo) {
       const long long Oc = O + oo;
       if (Oc >= noct) break;
-      if ((Oc + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
-      else decode_part<C1, MODE, false, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, first, diffs, accx);
+      if ((Oc + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, state, first, diffs, accx);
+      else decode_part<C1, MODE, false, BUCKET, PB, EARLY, true>(a, m, l, Oc, 0, T, i, eta, gamma, eta_prev, state, first, diffs, accx);
     }
     const double total = block_tree((double)accx, red);
     if (t == 0) a.dpartial[g] = total;
   } else if (live) {
-    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
-    else decode_part<C1, MODE, false, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, first, diffs, accx);
+    if ((O + 1) * 2048 <= m.d) decode_part<C1, MODE, true, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, state, first, diffs, accx);
+    else decode_part<C1, MODE, false, BUCKET, PB, EARLY, false>(a, m, l, O, piece, T, i, eta, gamma, eta_prev, state, first, diffs, accx);
   }
   if (ALT && NB == 8) {
     // a slot's fp32 fused chain in increasing coordinate: even waves first
