@@ -93,8 +93,9 @@ struct qoda_ctx {
   int2 *d_held = nullptr, *d_rest = nullptr;
   int *d_rest_layers = nullptr;
   int n_rest = 0, n_rest_layers = 0;
-  unsigned long long *d_exch = nullptr;   // the exchange area of both, zero between calls
-  bool exch_zero = true;                  // the last pass with held tiles was enqueued whole, so that it leaves d_exch zero
+  unsigned long long *d_exch = nullptr;         // exchange area of the held tiles, zero between calls that are enqueued whole
+  bool exch_zero = true;                        // the last of them was
+  unsigned long long *d_small_exch = nullptr;   // that of k_quantize_small, which leaves it zero by itself
   unsigned int *d_finished = nullptr;
   int tries = kSmallTries;   // qoda_exchange_tries
   unsigned int *d_readers = nullptr;   // of the decode pass with its own step size; zero between calls
@@ -272,7 +273,7 @@ Dev base_args(const qoda_ctx *c) {
   a.type_points = c->d_type_points;
   a.partial = c->d_partial; a.dpartial = c->d_dpartial; a.sumsq = c->d_sumsq;
   a.readers = c->d_readers;
-  a.exch = c->d_exch; a.finished = c->d_finished; a.tries = c->tries;
+  a.finished = c->d_finished; a.tries = c->tries;
   a.norm = c->d_norm; a.inv = c->d_inv; a.delta = c->d_delta;
   a.lev = c->d_lev; a.rgap = c->d_rgap; a.lut = c->d_lut; a.bins = c->d_bins; a.walk = c->d_walk;
   a.hist_last = c->d_hist_last; a.type_first = c->d_type_first; a.type_layers = c->d_type_layers;
@@ -316,7 +317,7 @@ int check_msg_ptrs(qoda_ctx *c, const void *const *p, size_t n, const char *what
 void free_all(qoda_ctx *c) {
   void *ptrs[] = {c->d_meta, c->d_tiles, c->d_runs[0], c->d_runs[1], c->d_runs[2], c->d_runs[3], c->d_empty, c->d_type_points, c->d_partial, c->d_dpartial, c->d_sumsq, c->d_delta,
                   c->d_norm, c->d_inv, c->d_lev, c->d_rgap, c->d_eta, c->d_lut, c->d_bins, c->d_hist, c->d_status, c->d_pooled, c->d_index_counts, c->d_type_exp_next,
-                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_finished, c->d_readers, c->d_hist_last,
+                  c->d_type_exp, c->d_dp_arg, c->d_dp_arg_off, c->d_node_tab, c->d_type_skip, c->d_walk, c->d_exch, c->d_small_exch, c->d_finished, c->d_readers, c->d_hist_last,
                   c->d_type_first, c->d_type_layers, c->d_held, c->d_rest, c->d_rest_layers};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -405,16 +406,16 @@ int run_norm_pass(qoda_ctx *c, Dev a, bool with_hist, hipStream_t s) {
   return QODA_OK;
 }
 
-hipError_t clear_exchange(const qoda_ctx *c, hipStream_t s) {
-  return launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_exch), 2 * (size_t)c->K * exch_row(c->G), s);
-}
-
-// Norms, quantize and delta of the nodes of `a`, with all tiles held, or those of the small layers and the others as ever.
+// Norms, quantize and delta of the nodes of `a` (rows row0 of the tables on), with all tiles held, or those of the small layers and the
+// others as ever.
 int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
-  // The pass finds the exchange area zero and leaves it so.  Not after one that failed between its launches; and a captured pass,
-  // which clears for itself then, says nothing about the state now.
+  // The pass finds the exchange area zero and leaves it so, but for one that fails between its launches: the next one clears all of the
+  // area.  A captured pass can be replayed after such a failure too, whatever the state is now, so it always clears its rows.
   const bool captured = is_captured(s);
-  if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
+  const size_t row = exch_row(c->G);
+  a.exch = c->d_exch + (size_t)a.row0 * row;
+  if (captured) LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(a.exch), 2 * (size_t)a.nnodes * row, s));
+  else if (!c->exch_zero) LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_exch), 2 * (size_t)c->K * row, s));
   if (!captured) c->exch_zero = false;
   Dev rest = a;
   if (which == kHoldSmall) {
@@ -430,7 +431,7 @@ int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
   }
   LAUNCH(c, kIdQuantize, s, launch_quantize_held(a, c->planes_mask, s));
   if (which == kHoldSmall) LAUNCH(c, kIdQuantize, s, launch_quantize(rest, c->planes_mask, s));
-  a.clear_exch = (int)std::min<size_t>(256, (exch_row(c->G) + 4 * kThreads - 1) / (4 * kThreads));   // about four words a thread
+  a.clear_exch = (int)std::min<size_t>(256, (row + 4 * kThreads - 1) / (4 * kThreads));   // about four words a thread
   LAUNCH(c, kIdDeltaFinalize, s, launch_delta_finalize(a, s));
   if (!captured) c->exch_zero = true;
   return QODA_OK;
@@ -471,7 +472,7 @@ int quantize_impl(qoda_ctx *c, int node0, int nnodes, const float *const *grad_f
   }
   if (!cached && use_small(c, nnodes)) {
     c->norms_valid = false;   // the cached norms of these nodes are about to be overwritten
-    if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
+    a.exch = c->d_small_exch;
     LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
     return QODA_OK;
   }
@@ -687,10 +688,12 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
       if (e == hipSuccess) A(hipMemcpy(c->d_rest_layers, rest_layers.data(), rest_layers.size() * sizeof(int), hipMemcpyHostToDevice));
     }
     if (c->small) {
+      A(dev_alloc(&c->d_small_exch, c->K * exch_row(c->G)));
       A(dev_alloc(&c->d_finished, (size_t)c->K));
+      if (e == hipSuccess) A(hipMemset(c->d_small_exch, 0, c->K * exch_row(c->G) * sizeof(unsigned long long)));
       if (e == hipSuccess) A(hipMemset(c->d_finished, 0, (size_t)c->K * sizeof(unsigned int)));
     }
-    if (c->small || held_tiles(h, c->K) != kHoldNone || held_tiles(h, 1) != kHoldNone) {
+    if (held_tiles(h, c->K) != kHoldNone || held_tiles(h, 1) != kHoldNone) {
       A(dev_alloc(&c->d_exch, c->K * exch_row(c->G)));
       if (e == hipSuccess) A(hipMemset(c->d_exch, 0, c->K * exch_row(c->G) * sizeof(unsigned long long)));
     }
@@ -974,9 +977,8 @@ static int quantize_node(qoda_ctx *c, int32_t node, const float *const *grad_dev
     for (int l = 0; l < c->L && kept; ++l) kept = c->norms_grad[(size_t)node * c->L + l] == grad_dev[l];
     if (!kept && of_context && (use_small(c, 1) || use_held(c, 1) != kHoldNone)) {
       c->norms_valid = false;   // this node's kept norms are about to be overwritten
-      a.exch = c->d_exch + (size_t)node * exch_row(c->G);   // the node's row
       if (!use_small(c, 1)) return quantize_held(c, a, use_held(c, 1), s);
-      if (!c->exch_zero) LAUNCH(c, kIdZero, s, clear_exchange(c, s));
+      a.exch = c->d_small_exch + (size_t)node * exch_row(c->G);   // the node's row
       LAUNCH(c, kIdQuantize, s, launch_quantize_small(a, c->planes_mask, s));
       return QODA_OK;
     }

@@ -1,8 +1,9 @@
 // The host side of the library (csrc/qoda_api.hip) compiled for the CPU over stand-ins for the HIP runtime and for the kernel
 // launches, so that a test without a GPU can see which launches a call makes, let one of them fail, and capture and replay
 // them.  "Device" memory is host memory, filled with a pattern when it is allocated.  Launches are recorded by name; the only
-// effects they model are those on histograms: the norm pass adds to the fit's, its consumer moves it away; under bucket scope the
-// quantize pass adds to the sums of its nodes, the clearing launches (the last kernel of the pass among them) clear theirs.
+// effects they model are those on statistics: the norm pass adds to the fit's, its consumer moves it away; under bucket scope the
+// quantize pass adds to the sums of its nodes, the clearing launches (the last kernel of the pass among them) clear theirs; held tiles
+// leave a mark in their nodes' rows of the exchange area.
 #include "../paper_2505_14371_amd/csrc/qoda_api.hip"
 #include "../paper_2505_14371_amd/csrc/qoda_choices.h"
 
@@ -14,6 +15,7 @@ std::string g_log;
 int g_fail_at = -1;           // launches until one fails; -1: none
 bool g_capturing = false;
 long long g_allocated = 0;
+int g_stale = 0;              // rows of the exchange area that a pass with held tiles found in use
 std::vector<std::function<void()>> g_graph;
 
 hipError_t record(const std::string &name, std::function<void()> effect = nullptr) {
@@ -31,6 +33,7 @@ void stand_in_reset() { g_log.clear(); g_fail_at = -1; }
 const char *stand_in_log() { return g_log.c_str(); }
 void stand_in_fail_at(int n) { g_fail_at = n; }
 void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); }
+int stand_in_stale() { return g_stale; }
 int stand_in_alt_blocks(int G, int K, int bucket, int bits) { return alt_blocks(G, K, bucket != 0, bits); }
 int stand_in_decode_blocks(int G, int K, int mode, int bucket, int bits) { return decode_blocks(G, K, mode, bucket != 0, bits); }
 int stand_in_quantize_bins(long long n, int prev, int bits) { return quantize_bins(n, prev != 0, bits); }
@@ -90,9 +93,13 @@ hipError_t launch_quantize(const Dev &a, unsigned int, hipStream_t) {
       for (int j : {0, kGridPoints - 1}) reinterpret_cast<unsigned long long *>(a.hist + i * kHistBins)[j] += 1;
   });
 }
-hipError_t launch_quantize_small(const Dev &, unsigned int, hipStream_t) { return record("quantize_small"); }
+hipError_t launch_quantize_small(const Dev &a, unsigned int, hipStream_t) {
+  return record("quantize_small", [=] { for (size_t i = 0; i < a.nnodes * exch_row(a.G); ++i) g_stale += a.exch[i] != 0; });
+}
 hipError_t launch_quantize_held(const Dev &a, unsigned int, hipStream_t) {
-  return record("quantize_held:" + std::to_string(a.NT), [=] { a.exch[0] += 1; });
+  return record("quantize_held:" + std::to_string(a.NT), [=] {
+    for (int k = a.node0 - a.row0; k < a.node0 - a.row0 + a.nnodes; ++k) g_stale += a.exch[k * exch_row(a.G)]++ != 0;
+  });
 }
 hipError_t launch_delta_finalize(const Dev &a, hipStream_t) {
   return record("delta", [=] { if (a.clear_exch) std::memset(a.exch, 0, 8 * a.nnodes * exch_row(a.G)); if (a.hist_old) clear_sums(a.hist_old, (size_t)a.K * a.L); });

@@ -317,18 +317,51 @@ class TestHeldTiles:
                 m.launches(lambda: (m.lib.stand_in_fail_at(at), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
             assert self.quantize(m) == ["zero"] + held(800) and self.quantize(m) == held(800)
         m.lib.stand_in_capture(1)
-        assert self.quantize(m) == held(800)
+        assert self.quantize(m) == ["zero"] + held(800)      # for its replays, whatever comes before them
         m.lib.stand_in_capture(0)
         with pytest.raises(qoda.QodaError):
             m.launches(lambda: (m.lib.stand_in_fail_at(1), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
         m.lib.stand_in_capture(1)
-        assert self.quantize(m) == ["zero"] + held(800)      # for its replays; nothing is known of the area now
+        assert self.quantize(m) == ["zero"] + held(800)      # says nothing about the area now
         m.lib.stand_in_capture(0)
         assert self.quantize(m) == ["zero"] + held(800)
-        m = routes([16384 * 200, 16384 * 300], K=2)          # one node: 500 tiles in one launch, which clears what a failed pass left
+
+    @pytest.mark.parametrize("one", [False, True])
+    def test_replays_after_a_pass_that_failed(self, routes, one):
+        """A graph captured while all was well, replayed after an eager pass that failed between its launches."""
+        from paper_2505_14371_amd import qoda
+
+        m = routes([16384 * 400] * 2, K=2)
+        stale = m.lib.stand_in_stale()
+        self.quantize(m)
+        m.lib.stand_in_capture(1)
+        self.quantize(m, one)
+        m.lib.stand_in_capture(0)
+        m.lib.stand_in_replay()
+        for at in (1, 2):                                    # behind the pass that holds tiles; the second call clears first
+            with pytest.raises(qoda.QodaError):
+                m.launches(lambda: (m.lib.stand_in_fail_at(at), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
+            m.lib.stand_in_replay()
+        assert self.quantize(m) == ["zero"] + held(800)      # all of the area, the rows that the graph does not clear among them
+        m.lib.stand_in_replay()
+        assert self.quantize(m) == held(800)
+        assert m.lib.stand_in_stale() == stale
+
+    def test_small_launches_have_an_area_of_their_own(self, routes):
+        """One node's 500 tiles in one launch, all nodes' 1000 held: a held pass that fails leaves nothing to the small ones, nor they to clear."""
+        from paper_2505_14371_amd import qoda
+
+        m = routes([16384 * 200, 16384 * 300], K=2)
+        stale = m.lib.stand_in_stale()
+        m.lib.stand_in_capture(1)
+        assert self.quantize(m, one=True) == SMALL
+        m.lib.stand_in_capture(0)
         with pytest.raises(qoda.QodaError):
             m.launches(lambda: (m.lib.stand_in_fail_at(1), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
-        assert self.quantize(m, one=True) == ["zero"] + SMALL
+        m.lib.stand_in_replay()
+        assert self.quantize(m, one=True) == SMALL and self.quantize(m, one=True) == SMALL
+        assert self.quantize(m) == ["zero"] + held(500)
+        assert m.lib.stand_in_stale() == stale
 
     def test_sizes_of_the_gpu_tests(self, routes):
         """tests/test_gpu_held_tiles.py compares this route with the separate kernels: at its sizes it is the one that is taken."""
