@@ -849,7 +849,10 @@ struct NoHist {
   __device__ __forceinline__ void operator()(const float *, const float (&)[4], int) const {}
 };
 
-// The lane's 32 coordinates of octet O of a layer of d entries (zeros past the end).
+// The lane's 32 coordinates of octet O of a layer of d entries (zeros past the end).  TOGETHER: the loads of a ragged last octet are all on
+// their way at once too, where otherwise a block waits for the one before it; for k_quantize_held, where a group waits for its last
+// tile.  (In the bucket quantizer it costs up to ten more spilled registers, in k_quantize_small five more registers.)
+template <bool TOGETHER = false>
 __device__ __forceinline__ void load_octet(const float *__restrict__ v, long long O, long long d, int i, float (&x)[32]) {
   const long long e0 = O * 2048 + 4 * i;
   if ((O + 1) * 2048 <= d) {
@@ -859,6 +862,26 @@ __device__ __forceinline__ void load_octet(const float *__restrict__ v, long lon
       q[bb] = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) v4f *>(as_global(v) + e0 + bb * kBlockCoords));
 #pragma unroll
     for (int bb = 0; bb < 8; ++bb) { x[4 * bb] = q[bb].x; x[4 * bb + 1] = q[bb].y; x[4 * bb + 2] = q[bb].z; x[4 * bb + 3] = q[bb].w; }
+  } else if constexpr (TOGETHER) {
+    // Lanes past the layer's end request its last whole quad again and drop it; the coordinates behind that quad are loaded by every lane.
+    const auto *g = as_global(v) + O * 2048;
+    const int n = (int)(d - O * 2048), whole = n & ~3;   // coordinates of the octet (1 at least), those in whole quads
+    v4f q[8] = {};
+    if (d >= 4) {
+#pragma unroll
+      for (int bb = 0; bb < 8; ++bb)
+        q[bb] = __builtin_nontemporal_load(reinterpret_cast<const __attribute__((address_space(1))) v4f *>(g + min(bb * kBlockCoords + 4 * i, whole - 4)));
+    }
+    float p[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) p[j] = g[min(whole + j, n - 1)];
+#pragma unroll
+    for (int bb = 0; bb < 8; ++bb) {
+      const int e = bb * kBlockCoords + 4 * i;
+      const float y[4] = {q[bb].x, q[bb].y, q[bb].z, q[bb].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * bb + j] = e < whole ? y[j] : e + j < n && j < 3 ? p[j] : 0.0f;
+    }
   } else {
 #pragma unroll
     for (int bb = 0; bb < 8; ++bb) {
@@ -1192,7 +1215,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 // Norms and quantization in one launch for models of any number of tiles, where their groups (a layer's tiles; under vector scope a
 // node's) are small enough (held_tiles): one read of the vectors instead of two.  A workgroup of four waves holds its tile: of a wave's
 // two octets the first in registers, the second in shared memory, where it goes without passing through registers.  With 32 KiB
-// of data, tables of up to 7 KiB and 107 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
+// of data, tables of up to 7 KiB and 109 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
 // 9-bit codes, whose tables are larger).  (k_quantize_small keeps a tile in the registers of eight waves: 512 tiles, all of a launch.)
 // Bound by what a tile waits for: of the 20 us that a tile of a long launch is on the device (3112 tiles, groups of 389, 5-bit codes)
 // it loads for 5.6, waits for its group for 10 and quantizes for 5.4; 1024 tiles pass in 17 us where groups are single tiles, in 21
@@ -1342,7 +1365,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
   const unsigned char *prevmsg = (PREV && a.prev != nullptr) ? a.prev[kr] : nullptr;
   float x[32];
   if (O0 < noct) {
-    load_octet(v, O0, m.d, i, x);
+    load_octet<true>(v, O0, m.d, i, x);
   } else {
 #pragma unroll
     for (int j = 0; j < 32; ++j) x[j] = 0.0f;
@@ -1354,15 +1377,26 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
       for (int bb = 0; bb < 8; ++bb)   // 16 bytes a lane, nontemporal
         __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) void *>(src + bb * kBlockCoords),
                                          (lds_ptr)(void *)&hold[w][bb][0], 16, 0, 2);
-    } else {   // the layer's ragged last octet
-#pragma unroll 1
+    } else {
+      // The layer's ragged last octet, its loads together too (when they were one after the other the group waited for this tile: 16
+      // nodes of one layer of 350 tiles less 3 entries 161 -> 142 us, separate kernels 148; 12 k layers of a tile less 3 entries 233 -> 201).
+      const auto *src = as_global(v) + (O0 + 1) * 2048;
+      const int n = (int)(m.d - (O0 + 1) * 2048);
+#pragma unroll
       for (int bb = 0; bb < 8; ++bb) {
-        const long long e = (O0 + 1) * 2048 + bb * kBlockCoords + 4 * i;
-        float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (e < m.d) load4(v, e, m.d, y);
-        v4f q;
-        q.x = y[0]; q.y = y[1]; q.z = y[2]; q.w = y[3];
-        hold[w][bb][i] = q;
+        const int e = bb * kBlockCoords + 4 * i;
+        if (e + 4 <= n) {
+          __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) void *>(src + e),
+                                           (lds_ptr)(void *)&hold[w][bb][0], 16, 0, 2);
+        } else {
+          v4f q = {0.0f, 0.0f, 0.0f, 0.0f};
+          if (e < n) {
+            q.x = src[e];
+            if (e + 1 < n) q.y = src[e + 1];
+            if (e + 2 < n) q.z = src[e + 2];
+          }
+          hold[w][bb][i] = q;
+        }
       }
     }
   }

@@ -51,6 +51,8 @@ SIZES = {
     "a group of 1024": ([T * 1023 + 5], 1),
     "a group of 768": ([T * 767 + 2047], 1),
     "257 and 500 in a group": ([T * 256 + 2049, 0, T * 500 + 2047, 3], 1),
+    # every remainder of a quad, in the first and in the second octet of every wave, and layers of less than two quads
+    "ends": ([T * 2 + 2048 * o + r for o in range(8) for r in (1, 2, 3, 4, 6, 255, 1021, 2047)] + [1, 2, 3, 4, 5, 6, 7], 4),
     "small layers": ([1, 0, 255, 2049, 4097, T, T + 1, T * 3 + 6145, T * 40, 300000] * 4 + [0] * 70, 5),
 }
 VECTORS = [([T * 350 + 5, 0, 9, T * 46 + 2049], 4), ([T, 5, 0, T * 3 - 1] * 60 + [0], 3), ([T * 1000 + 1, 77], 1)]
