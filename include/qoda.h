@@ -284,9 +284,11 @@ int qoda_status(qoda_ctx *ctx, void *stream);
 /* Measurement aids (no part of the method).
  * qoda_profile_enable: launches of the kernel classes whose bit is set in class_mask (bit i = class i, see
  *   qoda_kernel_name; 0 = off, 0xFFFFFFFF = all) are bracketed by two HIP events on the launch stream.  Each timed
- *   launch costs a few microseconds of idle time around it.  Small models run several classes in one launch (norms,
- *   quantizer and delta: timed as the quantizer; step size and update: timed as the update); a call made while one of the
- *   classes inside is asked for runs them as kernels of their own, with the same results.
+ *   launch costs a few microseconds of idle time around it.  Some calls run several classes in one launch (small models:
+ *   norms, quantizer and delta, timed as the quantizer; step size and update, timed as the update; larger models of small
+ *   layers: norms and quantizer, timed as the quantizer, for all layers or for the small ones); a call made while one of the
+ *   other classes inside is asked for runs them as kernels of their own, with the same results.  What a call launches of one
+ *   class (a kernel a code width, held tiles and the others) is one timed launch.
  * qoda_profile_read: waits for `stream`, then returns, per kernel class, the summed elapsed milliseconds and the
  *   number of launches since the last read (host arrays of QODA_NUM_KERNELS entries) and resets both.
  * qoda_kernel_name: the kernel's name for a class index (as it appears in a profiler's kernel trace), "" if out

@@ -377,7 +377,7 @@ bool use_small(const qoda_ctx *c, int nnodes) {
 }
 
 // Which tiles a call that computes the norms of `nnodes` nodes itself holds.  A caller who asks for the times of the kernels that this
-// stands for gets those kernels.
+// stands for gets those kernels; the quantizer's time holds the norms of the held tiles otherwise.
 HeldTiles use_held(const qoda_ctx *c, int nnodes) {
   const unsigned int parts = 1u << kIdSumsq | 1u << kIdNormFinalize | 1u << kIdNormVector | 1u << kIdDeltaFinalize;
   return (c->prof_mask & parts) == 0u ? held_tiles(c->held, nnodes) : kHoldNone;
@@ -429,8 +429,12 @@ int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
     a.tiles = c->d_held;
     a.NT = c->G - c->n_rest;
   }
-  LAUNCH(c, kIdQuantize, s, launch_quantize_held(a, c->planes_mask, s));
-  if (which == kHoldSmall) LAUNCH(c, kIdQuantize, s, launch_quantize(rest, c->planes_mask, s));
+  // one launch of the class: its time is that of all the call's codes
+  const auto codes = [&]() {
+    const hipError_t e = launch_quantize_held(a, c->planes_mask, s);
+    return e == hipSuccess && which == kHoldSmall ? launch_quantize(rest, c->planes_mask, s) : e;
+  };
+  LAUNCH(c, kIdQuantize, s, codes());
   a.clear_exch = (int)std::min<size_t>(256, (row + 4 * kThreads - 1) / (4 * kThreads));   // about four words a thread
   LAUNCH(c, kIdDeltaFinalize, s, launch_delta_finalize(a, s));
   if (!captured) c->exch_zero = true;

@@ -302,6 +302,15 @@ class TestHeldTiles:
         assert self.quantize(routes([16384 * 256] * 8 + [16384 * 8192], K=4)) == several
         assert self.quantize(routes([16384 * 256] * 8 + [16384 * 8193], K=4)) == LAYERS
 
+    @pytest.mark.parametrize("sizes, K", [([16384 * 256] * 8 + [16384 * 2000], 4), ([16384 * 400] * 2, 1)])   # small layers held; all
+    def test_the_quantizers_time_is_one_launch_a_call(self, routes, sizes, K):
+        m = routes(sizes, K=K)
+        names = self.quantize(m)
+        m.ctx.profile_enable(["k_quantize"])
+        for _ in range(3):
+            assert self.quantize(m) == names         # the calls that run otherwise
+        assert m.ctx.profile_read(stream=0)["k_quantize"][1] == 3
+
     def test_a_vector_of_several_code_widths(self, routes):
         m = routes([16384 * 450] * 2, types=[0, 1], points=(8, 32), norm_scope=1)
         assert self.quantize(m) == VECTOR
