@@ -302,7 +302,8 @@ int qoda_status(qoda_ctx *ctx, void *stream);
  *   HBM peak come from this kernel.
  * qoda_exchange_tries: where a launch computes norms and codes with one read of the vectors (small models, and larger ones of
  *   small layers) the workgroups exchange their tiles' statistics; how often a workgroup looks for the others' before it computes the missing ones itself, with the same results (default 1024, about
- *   a millisecond, so that a group's workgroups that are not on the device together cannot stop it).  0: it does not look
+ *   a millisecond, in small models, and never more than 64 in larger ones, so that a group's workgroups that are not on the device
+ *   together, because other work holds a part of it, cannot stop it).  0: it does not look
  *   and computes all of them, which a test uses to run that path.  QODA_EINVAL for tries < 0. */
 #define QODA_NUM_KERNELS 24
 int qoda_exchange_tries(qoda_ctx *ctx, int32_t tries);

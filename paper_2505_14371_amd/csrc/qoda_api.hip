@@ -414,6 +414,7 @@ int quantize_held(qoda_ctx *c, Dev a, HeldTiles which, hipStream_t s) {
   const bool captured = is_captured(s);
   const size_t row = exch_row(c->G);
   a.exch = c->d_exch + (size_t)a.row0 * row;
+  a.tries = std::min(c->tries, kHeldTries);
   if (captured) LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(a.exch), 2 * (size_t)a.nnodes * row, s));
   else if (!c->exch_zero) LAUNCH(c, kIdZero, s, launch_zero_u32(reinterpret_cast<unsigned int *>(c->d_exch), 2 * (size_t)c->K * row, s));
   if (!captured) c->exch_zero = false;

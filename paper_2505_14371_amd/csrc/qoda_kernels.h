@@ -20,6 +20,7 @@ constexpr int kSmallLayers = 64;     // and the most layers under vector scope
 constexpr int kHeldSlots = 1024;     // tiles that the device holds at once in k_quantize_held: four workgroups on each of 256 CUs,
 constexpr int kHeldSlotsWide = 768;  // three with 9-bit codes; and the most tiles of a group
 constexpr int kSmallTries = 1024;    // looks for the statistics of a group before missing ones are computed (about 1 ms)
+constexpr int kHeldTries = 64;       // the most of k_quantize_held (about 0.1 ms; the kernel's comment has the times)
 constexpr int kHistBins = 2048;      // top 11 magnitude bits of an fp32 value
 constexpr int kGridBase = 760;       // (127 - 32) << 3
 constexpr int kGridPoints = 257;     // normalised grid g_0 = 2^-32 ... g_256 = 1

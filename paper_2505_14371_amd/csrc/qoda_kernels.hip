@@ -962,7 +962,8 @@ __device__ __forceinline__ double add_terms(double acc, const float *x, int kind
   return acc;
 }
 
-// The statistic of any tile, from memory: what its own workgroup publishes.  All 512 threads call this (256 slots work).
+// The statistic of any tile, from memory: what its own workgroup publishes.  All threads of the workgroup call this, 256 at least, of which
+// the first 256 work.
 __device__ double tile_statistic(const float *__restrict__ v, long long d, int chunk, int kind, double *slot, int t) {
   __syncthreads();
   if (t < kThreads) {
@@ -1215,7 +1216,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 // Norms and quantization in one launch for models of any number of tiles, where their groups (a layer's tiles; under vector scope a
 // node's) are small enough (held_tiles): one read of the vectors instead of two.  A workgroup of four waves holds its tile: of a wave's
 // two octets the first in registers, the second in shared memory, where it goes without passing through registers.  With 32 KiB
-// of data, tables of up to 7 KiB and 109 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
+// of data, tables of up to 7 KiB and 113 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
 // 9-bit codes, whose tables are larger).  (k_quantize_small keeps a tile in the registers of eight waves: 512 tiles, all of a launch.)
 // Bound by what a tile waits for: of the 20 us that a tile of a long launch is on the device (3112 tiles, groups of 389, 5-bit codes)
 // it loads for 5.6, waits for its group for 10 and quantizes for 5.4; 1024 tiles pass in 17 us where groups are single tiles, in 21
@@ -1230,15 +1231,22 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 // pass used).  The last tile of a layer collects the statistics of the layer's tiles and combines them (in the order of
 // k_norm_finalize); under vector scope the last tile of the node then collects the sums of the layers (in the order of
 // k_norm_vector).  The others look at one word.
-// Workgroups start in the order of the table, so all tiles of the oldest unfinished group are on the device or done.  Still every
-// wait ends whatever else runs on the device: who has looked `tries` times does the collecting work itself, and a collector
-// that has, computes the missing statistics from the vectors, one tile a turn.  Such a value is the one that its own workgroup
-// stores, bit for bit, so it may be published too.  All accesses to the area are device-scope atomics; nothing but the value that
-// is read depends on them.
+// Workgroups start in the order of the table, so on an empty device all tiles of the oldest unfinished group are there or done.  Other
+// streams' work may hold a part of the device, and then workgroups wait for such as cannot start before they end.  So every wait ends:
+// who has looked `tries` times does the collecting work itself, and computes missing statistics from the vectors, one tile a turn and
+// each workgroup another one.  Such a value is the one that its own workgroup stores, bit for bit, so it is published too, for all.
+// (us beside a stream of elementwise additions; separate kernels / 1024 looks, the same tile in all workgroups, and as many looks again
+// for every layer that is missing / 256, 64, 32 and 16 looks, shared out: one layer of 1024 tiles 101 / 1884 / 288, 153, 148, 147;
+// a vector of 900 layers of a tile 104 / 461, one call 6973 / 112, 141, 152, 170; two layers of 400 tiles 91 / 71 / 71, 74, 71, 96; 8 vectors of
+// 389 216 / 221 / 217, 218, 226, 271.  Alone 16 looks are too few: the vectors of 389 take 112 instead of 92.)
+// All accesses to the area are device-scope atomics; nothing but the value that is read depends on them.
 __device__ __forceinline__ unsigned long long look(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ double published(unsigned long long b) { return __longlong_as_double((long long)~b); }
+__device__ __forceinline__ void publish_scale(unsigned long long *p, float n, float r) {
+  __hip_atomic_store(p, ~((unsigned long long)f2u(n) << 32 | f2u(r)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // What the workgroups of one node share.
 struct HeldNode {
@@ -1262,14 +1270,27 @@ __device__ __forceinline__ double held_tree(double v, int kind, double *slot) {
   return kind == kNormLinf ? wave_tree<false>(slot, threadIdx.x) : wave_tree<true>(slot, threadIdx.x);
 }
 
-// The index below n, of those for which some thread has none (have false), that is looked after first; n if there is none.
-__device__ __forceinline__ int first_missing(int mine, int *missing) {
+constexpr int kNothing = 0x7FFFFFFF;
+
+// One of the threads' indices (at least one has one; the others kNothing): the `who`-th of them in turn, so that workgroups that look for the
+// same ones share them out.  total: how many there were.
+__device__ __forceinline__ int share_missing(int mine, unsigned int who, const HeldShared &hs, unsigned int &total) {
+  unsigned int *count = reinterpret_cast<unsigned int *>(hs.slot);
+  const int w = threadIdx.x >> 6;
+  const unsigned long long has = __ballot(mine != kNothing);
   __syncthreads();
-  if (threadIdx.x == 0) *missing = 0x7FFFFFFF;
+  if ((threadIdx.x & 63) == 0) count[w] = (unsigned int)__popcll(has);
   __syncthreads();
-  if (mine != 0x7FFFFFFF) atomicMin(missing, mine);
+  unsigned int rank = (unsigned int)__popcll(has & ((1ull << (threadIdx.x & 63)) - 1ull));
+  total = 0u;
+#pragma unroll
+  for (int q = 0; q < kThreads / 64; ++q) {
+    if (q < w) rank += count[q];
+    total += count[q];
+  }
+  if (mine != kNothing && rank == who % total) *hs.missing = mine;
   __syncthreads();
-  return *missing;
+  return *hs.missing;
 }
 
 // A store of the first thread is there for all threads of the workgroup that look after this.
@@ -1278,14 +1299,16 @@ __device__ __forceinline__ void settle() {
   __syncthreads();
 }
 
-// The statistic of layer m (node row kr) from those of its tiles; valid in thread 0.  All threads call this.
-__device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v, const HeldNode &hn, const HeldShared &hs) {
+// The statistic of layer m from those of its tiles; valid in thread 0.  All threads call this.  After `looks` looks the missing ones are
+// computed here, the `who`-th first.
+__device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v, const HeldNode &hn, const HeldShared &hs, int looks,
+                                unsigned int who) {
   const int t = threadIdx.x, kind = a.kind;
   const unsigned long long *stat = hn.stat + m.first_chunk;
   constexpr int N = kHeldSlots / kThreads;
   unsigned long long got[N];
   for (int tries = 0;; ++tries) {
-    int none = 0x7FFFFFFF;   // the first of this thread's tiles whose statistic is not there
+    int none = kNothing;   // the first of this thread's tiles whose statistic is not there
 #pragma unroll
     for (int q = N - 1; q >= 0; --q) {
       const int j = t + q * kThreads;
@@ -1295,9 +1318,10 @@ __device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v
         if (got[q] == 0ull) none = j;
       }
     }
-    if (__syncthreads_and(none == 0x7FFFFFFF)) break;
-    if (tries < a.tries) continue;
-    const int chunk = first_missing(none, hs.missing);
+    if (__syncthreads_and(none == kNothing)) break;
+    if (tries < looks) continue;
+    unsigned int total;
+    const int chunk = share_missing(none, who, hs, total);
     const double s = tile_statistic(v, m.d, chunk, kind, hs.slot, t);
     if (t == 0) publish(&hn.stat[m.first_chunk + chunk], s);
     settle();
@@ -1310,11 +1334,11 @@ __device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v
 }
 
 // Vector scope: the node's statistic from those of its layers; valid in thread 0.  All threads call this.
-__device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const HeldShared &hs) {
+__device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const HeldShared &hs, int looks) {
   const int t = threadIdx.x, kind = a.kind;
   double s = 0.0;
   for (int tries = 0;; ++tries) {
-    int none = 0x7FFFFFFF;
+    int none = kNothing;
     s = 0.0;
     for (int q = t; q < a.L; q += kThreads) {
       double v = 0.0;
@@ -1325,11 +1349,12 @@ __device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const H
       }
       s = kind == kNormLinf ? fmax(s, v) : s + v;
     }
-    if (__syncthreads_and(none == 0x7FFFFFFF)) break;
-    if (tries < a.tries) continue;
-    const int q = first_missing(none, hs.missing);
+    if (__syncthreads_and(none == kNothing)) break;
+    if (tries < looks) continue;
+    unsigned int total;
+    const int q = share_missing(none, blockIdx.x, hs, total);
     const LayerMeta m = a.meta[q];
-    const double sum = collect_layer(a, m, a.grad[(size_t)kr * a.L + q], hn, hs);
+    const double sum = collect_layer(a, m, a.grad[(size_t)kr * a.L + q], hn, hs, 0, blockIdx.x / total);
     if (t == 0) publish(&hn.word[m.first_chunk], sum);
     settle();
   }
@@ -1444,7 +1469,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
   // collectors: the last tile of a layer, and under vector scope that of the last layer with coordinates
   bool collects = tile.y == m.nchunks - 1;
   if (collects) {
-    if (m.nchunks > 1) s = collect_layer(a, m, v, hn, hs);
+    if (m.nchunks > 1) s = collect_layer(a, m, v, hn, hs, a.tries, blockIdx.x);
     if (vec) {
       if (t == 0) {
         publish(&hn.word[m.first_chunk], s);
@@ -1455,7 +1480,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
       collects = m.first_chunk + m.nchunks == a.G;
       if (collects) {
         settle();
-        s = collect_node(a, kr, hn, hs);
+        s = collect_node(a, kr, hn, hs, a.tries);
       }
     }
   }
@@ -1471,9 +1496,15 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
       flag[0] = b != 0ull;
     }
     __syncthreads();
-    if (flag[0] == 0) {   // no answer: the collecting work is done here as well
-      s = vec ? collect_node(a, kr, hn, hs) : collect_layer(a, m, v, hn, hs);
-      if (t == 0) stat_scale(s, kind, scale[0], scale[1]);
+    if (flag[0] == 0) {   // no answer: the collecting work is done here as well, and its result is the group's
+      s = vec ? collect_node(a, kr, hn, hs, 0) : collect_layer(a, m, v, hn, hs, 0, blockIdx.x);
+      if (t == 0) {
+        float n, r;
+        stat_scale(s, kind, n, r);
+        scale[0] = n;
+        scale[1] = r;
+        publish_scale(word, n, r);
+      }
     }
   } else {
     if (t == 0) {
@@ -1481,8 +1512,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
       stat_scale(s, kind, n, r);
       scale[0] = n;
       scale[1] = r;
-      if (vec || m.nchunks > 1)
-        __hip_atomic_store(word, ~((unsigned long long)f2u(n) << 32 | f2u(r)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (vec || m.nchunks > 1) publish_scale(word, n, r);
       if (!stat_finite(s, kind)) atomicOr(a.status, kStatusNonFinite);
       if (n > 0.0f && n < kFltMin) atomicOr(a.status, kStatusTinyNorm);
       if (!vec) {
