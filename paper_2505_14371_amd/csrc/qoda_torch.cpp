@@ -45,4 +45,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_qoda_torch", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__qoda_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__qoda_torch() {
+  PyObject *m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", QODA_BUILT_FOR) != 0) {   // the caller compares it with what is running
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -17,12 +17,19 @@ from typing import List, Optional, Sequence
 
 import torch
 
-from . import qoda
+from . import build, qoda
 
-try:   # built with the library; without it (another torch, say) every tensor is looked at in Python
-    from . import _qoda_torch
-except ImportError:
-    _qoda_torch = None
+
+def _native_look():
+    """The native part of the loop, if it is there and was built for this torch; without it every tensor is looked at in Python."""
+    try:
+        from . import _qoda_torch as native
+    except ImportError:
+        return None
+    return native if getattr(native, "built_for", None) == build.built_for() else None
+
+
+_qoda_torch = _native_look()
 
 
 class QODA:

@@ -68,6 +68,38 @@ def test_native_look_at_the_gradients_leaves_the_rest_to_the_python_one():
         native.gather(good, params, "2", 0)
 
 
+@pytest.mark.parametrize("why", [ImportError("no torch"), FileNotFoundError("g++"), None])
+def test_the_library_is_built_without_the_loops_native_part(monkeypatch, tmp_path, why):
+    import subprocess
+
+    from paper_2505_14371_amd import build
+
+    left = tmp_path / "_qoda_torch.so"          # of a build with another torch
+    left.write_bytes(b"")
+    ran = []
+
+    def run(cmd):
+        ran.append(cmd[-1] if build.TORCH_SRC not in cmd else "torch")
+        if ran[-1] == "torch":
+            raise subprocess.CalledProcessError(1, cmd) if why is None else why
+
+    monkeypatch.setattr(build, "TORCH_LIB", str(left))
+    monkeypatch.setattr(build.subprocess, "check_call", run)
+    with pytest.warns(UserWarning, match="_qoda_torch.so was not built"):
+        assert build.build() == build.LIB
+    assert len(ran) == 3 and ran[-1] == "torch" and not left.exists()
+
+
+def test_a_native_part_built_for_another_torch_is_not_used(monkeypatch):
+    import paper_2505_14371_amd as package
+    from paper_2505_14371_amd import build, solver
+
+    for has, used in ((types.SimpleNamespace(), False), (types.SimpleNamespace(built_for="2.0.0 cpython-310"), False),
+                      (types.SimpleNamespace(built_for=build.built_for()), True)):
+        monkeypatch.setattr(package, "_qoda_torch", has, raising=False)
+        assert (solver._native_look() is has) == used and (solver._native_look() is None) != used
+
+
 @pytest.mark.parametrize("symbol, cls, label", [
     ("void qoda::k_quantize<4, true>(qoda::Dev)", "k_quantize", "k_quantize"),
     ("void qoda::k_quantize_b<4, false, 2>(qoda::Dev)", "k_quantize", "k_quantize (no prev)"),
