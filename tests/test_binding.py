@@ -39,7 +39,8 @@ def test_gradients_are_compared_with_the_parameters_as_they_are():
 
 
 def test_native_look_at_the_gradients_leaves_the_rest_to_the_python_one():
-    """What is not a list of lists of plain contiguous fp32 CUDA tensors of the parameters' sizes is not accepted (these are on the CPU)."""
+    """Nothing on the CPU is accepted, in whatever form it comes, and nothing breaks.  (What else is refused, one cause at a time:
+    tests/test_gpu_solver.py.)"""
     import ctypes
 
     from paper_2505_14371_amd import solver

@@ -129,3 +129,40 @@ def test_gradients_are_refused_or_taken_as_before_by_the_native_look(monkeypatch
         with pytest.raises(ValueError):
             opt._check_grads(lists)
     opt.close()
+
+
+def test_the_native_look_refuses_each_deviation_by_itself():
+    """Tensors on the GPU that are accepted but for one thing."""
+    import ctypes
+
+    from paper_2505_14371_amd import solver
+
+    dev = torch.device("cuda:0")
+    gather = solver._qoda_torch.gather
+
+    class Sub(torch.Tensor):
+        pass
+
+    params = [torch.zeros(6, 4, device=dev), torch.zeros(7, device=dev)]
+    good = [[torch.ones_like(p) for p in params] for _ in range(2)]
+
+    def look(grads):
+        out = (ctypes.c_void_p * 8)()          # room for a list too many, should it be taken
+        return gather(grads, params, 2, ctypes.addressof(out)), list(out)
+
+    def second(i, g):                          # the second node's i-th gradient is g
+        return [good[0], [g if j == i else x for j, x in enumerate(good[1])]]
+
+    taken = [g.data_ptr() for node in good for g in node]
+    for grads in (good, tuple(tuple(n) for n in good), second(1, good[1][1])):
+        assert look(grads) == (True, taken + [None] * 4)
+    for grads in (good[:1], [*good, good[0]], [good[0], good[1][:1]], [good[0], [*good[1], good[1][0]]],      # numbers of lists and of tensors
+                  iter(good), [good[0], iter(good[1])], {0: good[0], 1: good[1]}, None,                       # kinds of lists
+                  second(0, good[1][0].as_subclass(Sub)), second(0, None), second(0, good[1][0].data_ptr()),  # kinds of gradients
+                  second(0, torch.ones(6, 3, device=dev)), second(1, torch.ones(8, device=dev)),              # sizes
+                  second(0, good[1][0].double()), second(0, good[1][0].half()), second(0, good[1][0].int()),  # types
+                  second(0, torch.ones(4, 6, device=dev).t()), second(1, torch.ones(14, device=dev)[::2]),    # layouts
+                  second(0, torch.ones(6, 4, device=dev).to_sparse()),
+                  second(0, good[1][0].cpu()), second(1, torch.ones(7, device="meta"))):                      # places
+        assert look(grads)[0] is False
+    assert look(good)[0] is True
