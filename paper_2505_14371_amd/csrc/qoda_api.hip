@@ -340,14 +340,15 @@ void free_all(qoda_ctx *c) {
 //                  3096 167 / 166 / - / 369; 10000 403 / 380 / - / 449; 40 k 1423 / 1273 / 1280 / 1362; 75 k 2607 / 2335 / 2315 / 2320
 //   kRunsCount     us of qoda_index_counts, S = 8 (128), with 1 / 2 / 8: 512 tiles 34 (41) / 32 (36) / 40 (43); 1024 40 (55) / 35 (42)
 //                  / 40 (43); 1536 47 (65) / 39 (48) / 40 (45); 3096 66 (99) / 49 (67) / 43 (50)
-//   kRunsHist      the norm pass with the histogram, layer and vector scope.  us of a fit with runs of 1 / 2 / 4 / 8, 16 levels: 27 tiles 53
-//                  / 52 / 55 / 64; 108 56 / 56 / 60 / 65; 316 58 / 59 / 59 / 69; 632 61 / 64 / 61 / 71; 1024 in one layer 62 / 57 / 54 / 60;
-//                  1930 76 / 70 / 70 / 80; 2064 76 / 79 / 81 / 91; 2986 90 / 85 / 82 / 87; 3112 80 / 79 / 80 / 79; 3860 96 / 90 / 88 / 99; 4770
-//                  117 / 110 / 100 / 105; 17 k 250 / 239 / 239 / 239.  Whole rounds with 2 / 4 / 8: ten layers, K = 8 (3112 tiles) 163 / 166 / 165,
-//                  K = 16 252 / 252 / 260; 3 k tiles, K = 12 170 / 173 / 178; 7.2 k, K = 4 - / 339 to 343 / 335
+//   kRunsHist      the norm pass with the histogram, layer and vector scope.  us of a fit with runs of 2 / 4 / 8, 16 levels, nodes x tiles of a
+//                  node in one layer (in 40): up to 640 tiles of a node, 1 x 316 46 (51) / 49 (56) / 58 (65); 8 x 128 54 (75) / 55 (76) / 62 (77); 8 x
+//                  193 61 (72) / 61 (77) / 64 (75); 16 x 194 78 (98) / 81 (105) / 81 (100); 8 x 482 86 (101) / 86 (102) / 86 (111); 16 x 500 130
+//                  (161) / 130 (165) / 136 (167).  Beyond, where the runs of a large layer meet in one histogram, 1 x
+//                  1930 70 (65) / 65 (67) / 65 (68); 1 x 3860 92 (84) / 84 (85) / 85 (86); 1 x 4770 108 (94) / 100 (96) / 101 (103); 1 x 5300 115
+//                  (101) / 109 (103) / 106 (104); 8 x 2200 237 (238) / 232 (237) / 233 (241)
 int hist_runs(long long G, int nodes) {
   const long long n = G * nodes;
-  return n <= 256 || (n > 1600 && n <= 8192 && G <= 640) ? 1 : n <= 5120 ? 2 : 3;
+  return G <= 640 && n <= 8192 ? 1 : n <= 5120 ? 2 : 3;
 }
 enum RunUse { kRunsQuantize, kRunsFit, kRunsCount, kRunsHist };
 void use_runs(const qoda_ctx *c, Dev &a, RunUse use, int nnodes) {

@@ -15,6 +15,7 @@ std::string g_log;
 int g_fail_at = -1;           // launches until one fails; -1: none
 bool g_capturing = false;
 long long g_allocated = 0;
+int g_hist_runs = 0;          // workgroups a node of the last norm pass with a histogram
 int g_stale = 0;              // rows of the exchange area that a pass with held tiles found in use
 std::vector<std::function<void()>> g_graph;
 
@@ -33,6 +34,7 @@ void stand_in_reset() { g_log.clear(); g_fail_at = -1; }
 const char *stand_in_log() { return g_log.c_str(); }
 void stand_in_fail_at(int n) { g_fail_at = n; }
 void stand_in_capture(int on) { g_capturing = on != 0; if (on) g_graph.clear(); }
+int stand_in_hist_runs() { return g_hist_runs; }
 int stand_in_stale() { return g_stale; }
 int stand_in_alt_blocks(int G, int K, int bucket, int bits) { return alt_blocks(G, K, bucket != 0, bits); }
 int stand_in_decode_blocks(int G, int K, int mode, int bucket, int bits) { return decode_blocks(G, K, mode, bucket != 0, bits); }
@@ -79,6 +81,7 @@ static void move_histograms(const Dev &a) {   // what the consumer of the histog
 hipError_t launch_zero_u32(unsigned int *p, size_t n, hipStream_t) { return record("zero", [=] { std::memset(p, 0, 4 * n); }); }
 hipError_t launch_sumsq(const Dev &a, bool with_hist, hipStream_t) {
   if (!with_hist) return record("norms");
+  g_hist_runs = a.GS;
   return record("norms+hist", [=] { for (size_t i = 0; i < (size_t)a.K * a.L; ++i) a.hist[i * kHistBins + 1] += 1; });
 }
 hipError_t launch_norm_finalize(const Dev &, hipStream_t) { return record("norm_finalize"); }
