@@ -674,8 +674,12 @@ static int create_impl(const qoda_config *cfg, qoda_ctx *c) {
     h.tiles = c->G;
     h.largest = most_chunks;
     h.slots = c->planes_mask & (1u << 9) ? kHeldSlotsWide : kHeldSlots;
-    for (const LayerMeta &m : c->meta)
+    h.whole = true;
+    for (const LayerMeta &m : c->meta) {
       if (m.nchunks <= held_small(h)) h.small_tiles += m.nchunks;
+      if (2 * m.nchunks > h.slots) ++h.over_half;
+      if (m.d % 2048 != 0) h.whole = false;
+    }
     if (held_tiles(h, c->K) == kHoldSmall || held_tiles(h, 1) == kHoldSmall) {
       std::vector<int2> some, rest;
       std::vector<int> rest_layers;

@@ -101,7 +101,7 @@ inline bool quantize_bins(long long n, bool prev, int bits) {
 // and which go through the norm pass, its combination and the quantizer.  A group (a layer's tiles; under vector scope a
 // node's) waits for its last tile, so what counts is how its tiles share the slots of the device with others that load or quantize
 // meanwhile.  us with the separate kernels / held, of a whole pass of K nodes (quantize, decode, and what else is in it), but `call`: of
-// quantize calls one after the other:
+// quantize calls one after the other (most of these with a layer whose end is ragged):
 //   * All tiles on the device at once: call, 5 bits 640 tiles 30 / 24, 1024 in one layer 36 / 29, in layers of 64 36 / 29; one norm per
 //     vector 960 38 / 29.  (Launches of k_quantize_small and a little beyond stay as they are.)
 //   * Layers of up to two fifths of the slots, vectors of up to half: there are always some that load and some that quantize.  Vectors
@@ -110,7 +110,14 @@ inline bool quantize_bins(long long n, bool prev, int bits) {
 //     342 / 243, 64 326 / 259, 256 309 / 285.  Larger ones among them do no harm up to a quarter of the tiles (511 of 2815, 8 bits,
 //     K = 4 455 / 407); beyond that they do: 511 of 640 tiles, K = 4 117 / 121, 8 186 / 199.
 //   * Larger groups: up to two fills.  Vectors of 650, K = 2 97 / 92; layers of up to 700, K = 2 107 / 99, 8 242 / 246; up to 991, K = 1
-//     106 / 103, 2 138 / 143.
+//     106 / 103, 2 138 / 143.  Not three or more groups of over half of the slots, which come one after the other: vectors of 560, K = 3
+//     67 / 74, with ragged ends 75 / 77; layers of 650, K = 3 72 / 79.  (Layers with ragged ends 600, K = 3 77 / 76, 650 77 / 79.)
+//   * Layers that all end with a whole octet: the separate kernels, which take a ragged one block by block, are 5 to 8 us faster there.  Little
+//     more than a fill is not held then.  One layer a node: 342 tiles, K = 3 43 / 46, with ragged ends 48 / 44; 513, K = 2 43 / 47; 409,
+//     K = 3 48 / 50; 150, K = 7 44 / 46, 9 56 / 52; 300, K = 4 46 / 48, 5 58 / 54; 256, K = 5 47 / 47; layers of 16 and fewer 1030 tiles 57 / 57 and
+//     55 / 51.  9 bits: layers of 16, 780 tiles 48 / 54, 1152 61 / 65, 1300 69 / 66; of 64, 1000 tiles 53 / 56, 1152 59 / 60.
+//     Left as they are: whole vectors of a third of the slots (342, K = 5 67 / 69, 8 100 / 96, 12 132 / 133), 9 bits with layers of 16, 2.1
+//     to 2.6 fills (1650 tiles 87 / 92, 2000 99 / 101).
 //   * 9 bits (three workgroups a CU), previous message, calls: layers of 16 to 64 tiles 3 k 105 / 100, 12 k 354 / 348; 192 1.5 k 57 / 57,
 //     3 k 104 / 102, 6 k 178 / 188; 384 3 k 104 / 107.
 //   * Small layers beside such as no launch can hold (two sets of launches, two more tails): only where they are many and a good part of
@@ -123,6 +130,8 @@ struct HeldModel {
   int scope, slots;
   long long tiles, small_tiles;   // of a node; in layers of up to held_small()
   int largest;                    // tiles of the largest layer
+  int over_half;                  // layers of more than half of the slots
+  bool whole;                     // every layer ends with a whole octet
 };
 inline int held_small(const HeldModel &h) { return h.slots != kHeldSlots ? h.slots / 12 : h.scope == kScopeVector ? h.slots / 2 : 2 * h.slots / 5; }
 inline HeldTiles held_tiles(const HeldModel &h, int nodes) {
@@ -130,10 +139,13 @@ inline HeldTiles held_tiles(const HeldModel &h, int nodes) {
   const int group = h.scope == kScopeVector ? (int)(h.tiles < INT32_MAX ? h.tiles : INT32_MAX) : h.largest;
   if (h.scope == kScopeBucket || n < least) return kHoldNone;
   if (group <= h.slots) {
-    const bool small = h.scope == kScopeVector ? group <= held_small(h) : 4 * h.small_tiles >= 3 * h.tiles;
-    if (n <= h.slots || small) return kHoldAll;
-    if (h.slots != kHeldSlots) return 4 * group <= h.slots && n <= 4 * h.slots ? kHoldAll : kHoldNone;
-    if (n <= 2 * h.slots) return kHoldAll;
+    const bool vec = h.scope == kScopeVector, wide = h.slots != kHeldSlots;
+    if (n <= h.slots) return kHoldAll;
+    if (h.whole && (wide ? 2 * n <= 3 * h.slots : group > 16 && 8 * n < (4 * group > h.slots ? 10 : 9) * h.slots)) return kHoldNone;
+    if (vec ? group <= held_small(h) : 4 * h.small_tiles >= 3 * h.tiles) return kHoldAll;
+    if (wide) return 4 * group <= h.slots && n <= 4 * h.slots ? kHoldAll : kHoldNone;
+    const long long over_half = (vec ? 1ll : h.over_half) * nodes;   // (a vector that comes here is)
+    if (n <= 2 * h.slots && (over_half <= 2 || !(vec || h.whole))) return kHoldAll;
   }
   return h.scope == kScopeLayer && h.small_tiles * nodes >= kHeldSmallLeast && 5 * h.small_tiles >= h.tiles ? kHoldSmall : kHoldNone;
 }

@@ -277,10 +277,10 @@ class TestHeldTiles:
     # tiles of a layer, layers, K, scope, grid points; whether all tiles of a call for all nodes are held
     @pytest.mark.parametrize("tiles, layers, K, scope, S, all_nodes", [
         (639, 1, 1, 0, 8, False), (640, 1, 1, 0, 8, True), (1024, 1, 1, 0, 8, True), (1025, 1, 1, 0, 8, False), (409, 1, 40, 0, 8, True),
-        (410, 1, 40, 0, 8, False), (682, 1, 3, 0, 8, True), (683, 1, 3, 0, 8, False), (1024, 2, 1, 0, 8, True), (1024, 3, 1, 0, 8, False),
+        (410, 1, 40, 0, 8, False), (682, 1, 3, 0, 8, False), (1023, 1, 2, 0, 8, True), (1024, 2, 1, 0, 8, True), (1024, 3, 1, 0, 8, False),
         (64, 30, 2, 0, 256, True), (65, 48, 1, 0, 256, False), (192, 16, 1, 0, 256, True),
         (193, 10, 1, 0, 256, False), (192, 17, 1, 0, 256, False), (768, 1, 1, 0, 256, True), (769, 1, 1, 0, 256, False), (83, 10, 1, 1, 8, False),
-        (84, 10, 1, 1, 8, True), (512, 1, 16, 1, 8, True), (513, 1, 4, 1, 8, False), (513, 1, 3, 1, 8, True), (1024, 1, 3, 1, 8, False),
+        (84, 10, 1, 1, 8, True), (512, 1, 16, 1, 8, True), (513, 1, 4, 1, 8, False), (513, 1, 3, 1, 8, False), (1024, 1, 3, 1, 8, False),
         (1024, 1, 2, 1, 8, True), (1025, 1, 1, 1, 8, False)])
     def test_lines(self, routes, tiles, layers, K, scope, S, all_nodes):
         m = routes([16384 * tiles] * layers, points=(S,), K=K, norm_scope=scope)
@@ -289,6 +289,19 @@ class TestHeldTiles:
         assert m.launches(lambda: m.ctx.quantize_noalloc(0, m.grads[:layers], 1, m.msgs[0], None, stream=0)) == separate
         m.ctx.profile_enable(["k_norm_finalize"])
         assert self.quantize(m) == separate
+
+    # tiles of a layer, layers, K, scope, grid points; whether all tiles are held when layers are whole, and when one ends within an octet
+    @pytest.mark.parametrize("tiles, layers, K, scope, S, whole, ragged", [
+        (513, 1, 2, 0, 8, False, True), (640, 2, 1, 0, 8, True, True), (639, 2, 1, 0, 8, False, True), (256, 1, 5, 0, 8, True, True),
+        (257, 1, 4, 0, 8, False, True), (255, 5, 1, 0, 8, True, True), (17, 61, 1, 0, 8, False, True), (17, 68, 1, 0, 8, True, True),
+        (16, 65, 1, 0, 8, True, True), (342, 1, 3, 1, 8, False, True), (320, 1, 4, 1, 8, True, True), (682, 1, 3, 0, 8, False, True),
+        (683, 1, 3, 0, 8, False, False), (513, 3, 1, 0, 8, False, True), (513, 1, 3, 1, 8, False, False), (700, 1, 2, 1, 8, True, True),
+        (1, 769, 1, 0, 256, False, True), (16, 72, 1, 0, 256, False, True), (1, 1153, 1, 0, 256, True, True)])
+    def test_ends_of_layers(self, routes, tiles, layers, K, scope, S, whole, ragged):
+        separate = VECTOR if scope else LAYERS
+        for less, holds in ((0, whole), (2048, whole), (3, ragged), (2047, ragged)):
+            m = routes([16384 * tiles] * (layers - 1) + [16384 * tiles - less], points=(S,), K=K, norm_scope=scope)
+            assert self.quantize(m) == (held(tiles * layers) if holds else separate), less
 
     def test_large_layers_among_small_ones(self, routes):
         m = routes([16384 * 100] * 30 + [16384 * 1000], K=1)             # a quarter of the tiles
