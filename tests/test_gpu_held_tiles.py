@@ -58,6 +58,13 @@ SIZES = {
 VECTORS = [([T * 350 + 5, 0, 9, T * 46 + 2049], 4), ([T, 5, 0, T * 3 - 1] * 60 + [0], 3), ([T * 1000 + 1, 77], 1)]
 WIDTHS = [T * 200 + 5, 1000, T * 300, 0, T * 250 + 3]
 BESIDE = [T * 1025 - 3, 5, 0, T * 100 + 7, T * 300, 20000], 21     # 8463 small tiles, 29 % of all
+# more of small layers beside others: sizes, K, types, grid points, kind of norm
+SOME = {
+    "several code widths": (*BESIDE, [0, 1, 1, 0, 1, 0], [4, 32], qoda.NORM_L2),
+    "the largest would fit": ([T * 1000 - 3, 5, 0, T * 100 + 7, T * 300, 20000], 21, [0] * 6, [16], qoda.NORM_L1),
+    "nine bits": ([T * 800 + 1] + [T * 60 + 7] * 10 + [9, 0], 14, [0] * 13, [200], qoda.NORM_LINF),
+    "one node is enough": ([T * 1025 + 5] + [T * 256 + 3] * 33 + [0, 77], 2, [0] * 36, [8], qoda.NORM_L2),
+}
 NODES = [T * 20 + 5, 1, T * 10, 0, T], 30
 THREE = [T * 200 + 5, 300, T * 100], 3
 
@@ -107,6 +114,22 @@ def test_small_layers_beside_a_large_one():
         for m in ms:
             fill(m, t)
         assert same(*[call(m, t) for m in ms]), t
+
+
+@pytest.mark.parametrize("name", SOME)
+def test_more_of_small_layers_beside_others(name):
+    sizes, K, types, points, kind = SOME[name]
+    ms = [gm(sizes, types, points, K, seed=3, norm_kind=kind) for _ in range(2)]
+    ms[1].ctx.profile_enable(PARTS)
+    for t in (1, 2, 3):
+        for m in ms:
+            fill(m, t)
+        assert same(*[call(m, t, each=t == 3) for m in ms]), t
+
+
+def test_replays_of_a_captured_call_that_holds_small_layers():
+    sizes, K = BESIDE
+    replays(sizes, K, [0] * len(sizes), LAYER)
 
 
 @pytest.mark.parametrize("scope", [LAYER, VECTOR])
@@ -179,7 +202,11 @@ def test_flags(scope, bad):
 def test_replays_of_a_captured_call(scope):
     """A captured pass leaves its exchange area ready for the next replay and for eager passes between."""
     sizes, K = THREE
-    ms = [gm(sizes, [0] * 3, [8], K, seed=3, norm_scope=scope) for _ in range(2)]
+    replays(sizes, K, [0] * 3, scope)
+
+
+def replays(sizes, K, types, scope):
+    ms = [gm(sizes, types, [8], K, seed=3, norm_scope=scope) for _ in range(2)]
     ms[1].ctx.profile_enable(PARTS)
 
     def one(m):

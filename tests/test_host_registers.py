@@ -65,3 +65,11 @@ def test_quantize_without_previous_message_runs_six_waves(kernels, bits):
 
 def test_quantize_of_nine_bits_with_previous_message_runs_five_waves(kernels):
     assert kernels["k_quantize<9, true, false>"][0] <= 96
+
+
+@pytest.mark.parametrize("prev", ["false", "true"])
+@pytest.mark.parametrize("bits", range(2, 10))
+def test_held_tiles_four_workgroups_a_cu_and_nothing_spilled(kernels, bits, prev):
+    """Three with nine bits; a workgroup is a wave on each SIMD."""
+    registers, scratch = kernels[f"k_quantize_held<{bits}, {prev}>"]
+    assert registers <= (168 if bits == 9 else 128) and scratch == 0

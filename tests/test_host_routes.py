@@ -369,6 +369,26 @@ class TestHeldTiles:
         assert self.quantize(m) == held(800)
         assert m.lib.stand_in_stale() == stale
 
+    @pytest.mark.parametrize("one", [False, True])
+    def test_small_layers_beside_others_after_a_launch_that_failed(self, routes, one):
+        """Every launch of such a call fails once; a graph captured while all was well is replayed after each failure."""
+        from paper_2505_14371_amd import qoda
+
+        m = routes([16384 * 256] * 33 + [16384 * 1025], K=2)
+        names = ["norms", "norm_finalize", f"quantize_held:{256 * 33}", "quantize", "delta"]
+        stale = m.lib.stand_in_stale()
+        assert self.quantize(m, one) == names
+        m.lib.stand_in_capture(1)
+        assert self.quantize(m, one) == ["zero"] + names
+        m.lib.stand_in_capture(0)
+        for at in range(5):
+            with pytest.raises(qoda.QodaError):
+                m.launches(lambda: (m.lib.stand_in_fail_at(at), m.ctx.quantize_all(m.grads, 1, m.msgs, m.prev, stream=0)))
+            m.lib.stand_in_replay()
+            assert self.quantize(m, one) == ["zero"] + names and self.quantize(m, one) == names
+            m.lib.stand_in_replay()
+        assert m.lib.stand_in_stale() == stale
+
     def test_small_launches_have_an_area_of_their_own(self, routes):
         """One node's 500 tiles in one launch, all nodes' 1000 held: a held pass that fails leaves nothing to the small ones, nor they to clear."""
         from paper_2505_14371_amd import qoda
@@ -401,4 +421,10 @@ class TestHeldTiles:
         for sizes, K in (g.NODES, g.THREE):
             assert names(sizes, K) == held(tiles(sizes))
         assert names(g.WIDTHS, 1, types=[0, 1, 1, 2, 2], points=(4, 16, 200)) == held(tiles(g.WIDTHS))
+        for name, (sizes, K, types, points, _) in g.SOME.items():
+            limit = 64 if "nine" in name else 409
+            some = [f"quantize_held:{sum(-(-s // 16384) for s in sizes if s <= 16384 * limit)}", "quantize", "delta"]
+            assert names(sizes, K, types=types, points=points) == ["norms", "norm_finalize"] + some, name
+            m = routes(sizes, types=types, points=points, K=K)
+            assert (self.quantize(m, one=True)[2:] == some) == ("one node" in name), name
         assert names(*g.BESIDE)[:3] == ["norms", "norm_finalize", f"quantize_held:{tiles(g.BESIDE[0]) - 1025}"]
