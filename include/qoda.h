@@ -107,7 +107,7 @@ typedef struct {
 
 /* Create / destroy.  qoda_create allocates all device scratch (a few MB plus 16 bytes per 16384 coordinates per
  * node, under bucket scope up to 28 more per 16384 coordinates of the model, in models whose tiles are held (see
- * qoda_exchange_tries) 16 more per node; the fit's
+ * qoda_exchange_tries) 16 more per node, and 16 more (8 KB a node at most) in small models; the fit's
  * histograms, two of 8 KB per (node, layer), are allocated on the first qoda_fit_levels, under bucket scope one of
  * them, at once).  Levels start
  * uniform: l_j = j/(S-1).  On failure *out is NULL. */
