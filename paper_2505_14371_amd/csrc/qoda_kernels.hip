@@ -1216,7 +1216,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 // Norms and quantization in one launch for models of any number of tiles, where their groups (a layer's tiles; under vector scope a
 // node's) are small enough (held_tiles): one read of the vectors instead of two.  A workgroup of four waves holds its tile: of a wave's
 // two octets the first in registers, the second in shared memory, where it goes without passing through registers.  With 32 KiB
-// of data, tables of up to 7 KiB and 113 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
+// of data, tables of up to 7 KiB and 109 to 125 registers four workgroups fit a CU, 1024 tiles the device (three, 768 tiles, with
 // 9-bit codes, whose tables are larger).  (k_quantize_small keeps a tile in the registers of eight waves: 512 tiles, all of a launch.)
 // Bound by what a tile waits for: of the 20 us that a tile of a long launch is on the device (3112 tiles, groups of 389, 5-bit codes)
 // it loads for 5.6, waits for its group for 10 and quantizes for 5.4; 1024 tiles pass in 17 us where groups are single tiles, in 21
@@ -1236,8 +1236,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_quantize_small(Dev a) {
 // who has looked `tries` times does the collecting work itself, and computes missing statistics from the vectors, one tile a turn and
 // each workgroup another one.  Such a value is the one that its own workgroup stores, bit for bit, so it is published too, for all.
 // (us beside a stream of elementwise additions; separate kernels / 1024 looks, the same tile in all workgroups, and as many looks again
-// for every layer that is missing / 256, 64, 32 and 16 looks, shared out: one layer of 1024 tiles 101 / 1884 / 288, 153, 148, 147;
-// a vector of 900 layers of a tile 104 / 461, one call 6973 / 112, 141, 152, 170; two layers of 400 tiles 91 / 71 / 71, 74, 71, 96; 8 vectors of
+// for every layer that is missing / 256, 64, 32 and 16 looks, shared out: one layer of 1024 tiles 101 / 1884 / 288, 153 to 165, 148, 147;
+// a vector of 900 layers of a tile 104 / 461, one call 6973 / 112, 130 to 144, 152, 170; two layers of 400 tiles 91 / 71 / 71, 74, 71, 96; 8 vectors of
 // 389 216 / 221 / 217, 218, 226, 271.  Alone 16 looks are too few: the vectors of 389 take 112 instead of 92.)
 // All accesses to the area are device-scope atomics; nothing but the value that is read depends on them.
 __device__ __forceinline__ unsigned long long look(const unsigned long long *p) {
@@ -1272,25 +1272,21 @@ __device__ __forceinline__ double held_tree(double v, int kind, double *slot) {
 
 constexpr int kNothing = 0x7FFFFFFF;
 
-// One of the threads' indices (at least one has one; the others kNothing): the `who`-th of them in turn, so that workgroups that look for the
-// same ones share them out.  total: how many there were.
-__device__ __forceinline__ int share_missing(int mine, unsigned int who, const HeldShared &hs, unsigned int &total) {
-  unsigned int *count = reinterpret_cast<unsigned int *>(hs.slot);
-  const int w = threadIdx.x >> 6;
-  const unsigned long long has = __ballot(mine != kNothing);
+// One of the threads' indices (at least one has one; the others kNothing), which each workgroup takes in an order of its own, so that those
+// that look for the same ones share them out.  (By rank, workgroup after workgroup: no faster beside other work, and 1 % slower without
+// any, vectors of 389 79.4 instead of 78.1 us.)
+__device__ __forceinline__ int pick_missing(int mine, int *missing) {
+  const unsigned int order = ((unsigned int)mine * 0x9E3779B1u ^ blockIdx.x * 0x85EBCA77u) * 0xC2B2AE3Du;   // odd multipliers
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) count[w] = (unsigned int)__popcll(has);
+  if (threadIdx.x == 0) *missing = kNothing;
   __syncthreads();
-  unsigned int rank = (unsigned int)__popcll(has & ((1ull << (threadIdx.x & 63)) - 1ull));
-  total = 0u;
-#pragma unroll
-  for (int q = 0; q < kThreads / 64; ++q) {
-    if (q < w) rank += count[q];
-    total += count[q];
-  }
-  if (mine != kNothing && rank == who % total) *hs.missing = mine;
+  if (mine != kNothing) atomicMin(missing, (int)((order >> 1 & ~(unsigned int)(kThreads - 1)) | threadIdx.x));
   __syncthreads();
-  return *hs.missing;
+  const int first = *missing & (kThreads - 1);   // the thread
+  __syncthreads();
+  if (first == (int)threadIdx.x) *missing = mine;
+  __syncthreads();
+  return *missing;
 }
 
 // A store of the first thread is there for all threads of the workgroup that look after this.
@@ -1300,9 +1296,8 @@ __device__ __forceinline__ void settle() {
 }
 
 // The statistic of layer m from those of its tiles; valid in thread 0.  All threads call this.  After `looks` looks the missing ones are
-// computed here, the `who`-th first.
-__device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v, const HeldNode &hn, const HeldShared &hs, int looks,
-                                unsigned int who) {
+// computed here.
+__device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v, const HeldNode &hn, const HeldShared &hs, int looks) {
   const int t = threadIdx.x, kind = a.kind;
   const unsigned long long *stat = hn.stat + m.first_chunk;
   constexpr int N = kHeldSlots / kThreads;
@@ -1320,8 +1315,7 @@ __device__ double collect_layer(const Dev &a, const LayerMeta &m, const float *v
     }
     if (__syncthreads_and(none == kNothing)) break;
     if (tries < looks) continue;
-    unsigned int total;
-    const int chunk = share_missing(none, who, hs, total);
+    const int chunk = pick_missing(none, hs.missing);
     const double s = tile_statistic(v, m.d, chunk, kind, hs.slot, t);
     if (t == 0) publish(&hn.stat[m.first_chunk + chunk], s);
     settle();
@@ -1351,10 +1345,9 @@ __device__ double collect_node(const Dev &a, int kr, const HeldNode &hn, const H
     }
     if (__syncthreads_and(none == kNothing)) break;
     if (tries < looks) continue;
-    unsigned int total;
-    const int q = share_missing(none, blockIdx.x, hs, total);
+    const int q = pick_missing(none, hs.missing);
     const LayerMeta m = a.meta[q];
-    const double sum = collect_layer(a, m, a.grad[(size_t)kr * a.L + q], hn, hs, 0, blockIdx.x / total);
+    const double sum = collect_layer(a, m, a.grad[(size_t)kr * a.L + q], hn, hs, 0);
     if (t == 0) publish(&hn.word[m.first_chunk], sum);
     settle();
   }
@@ -1469,7 +1462,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
   // collectors: the last tile of a layer, and under vector scope that of the last layer with coordinates
   bool collects = tile.y == m.nchunks - 1;
   if (collects) {
-    if (m.nchunks > 1) s = collect_layer(a, m, v, hn, hs, a.tries, blockIdx.x);
+    if (m.nchunks > 1) s = collect_layer(a, m, v, hn, hs, a.tries);
     if (vec) {
       if (t == 0) {
         publish(&hn.word[m.first_chunk], s);
@@ -1497,7 +1490,7 @@ __global__ void __launch_bounds__(kThreads, C1 == 9 ? 3 : 4) k_quantize_held(Dev
     }
     __syncthreads();
     if (flag[0] == 0) {   // no answer: the collecting work is done here as well, and its result is the group's
-      s = vec ? collect_node(a, kr, hn, hs, 0) : collect_layer(a, m, v, hn, hs, 0, blockIdx.x);
+      s = vec ? collect_node(a, kr, hn, hs, 0) : collect_layer(a, m, v, hn, hs, 0);
       if (t == 0) {
         float n, r;
         stat_scale(s, kind, n, r);

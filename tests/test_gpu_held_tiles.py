@@ -147,7 +147,7 @@ def test_workgroups_that_do_the_collecting_themselves(scope):
 
 @pytest.mark.parametrize("sizes, scope", [([T * 1024], LAYER), ([T] * 900, VECTOR)])
 def test_a_device_that_others_use_too(sizes, scope):
-    """A group that would fill the device, beside a stream of large additions: it does not wait for what cannot start.  (The bound: held 1.5
+    """A group that would fill the device, beside a stream of large additions: it does not wait for what cannot start.  (The bound: held 1.6
     and 1.4 times the separate kernels' time; 19 and 4.4 times, with calls of 7 ms, when every workgroup computed all that was missing.)"""
     import time
 
