@@ -121,8 +121,9 @@ inline bool quantize_bins(long long n, bool prev, int bits) {
 //   * 9 bits (three workgroups a CU), previous message, calls: layers of 16 to 64 tiles 3 k 105 / 100, 12 k 354 / 348; 192 1.5 k 57 / 57,
 //     3 k 104 / 102, 6 k 178 / 188; 384 3 k 104 / 107.
 //   * Where not all are held: layers of up to held_small() are, beside larger ones (whether the device could hold those or not) that go
-//     through the separate kernels.  Two sets of launches, two more tails: only where the small ones are many and a good part of all.  20 k tiles in layers of up to 53 beside 54 k, 4 bits 2223 / 2131; 11.7 k beside 5.9 k, 5 bits 587 / 534; 12 k in layers
-//     of 256 beside 148 k, 3 bits 7352 / 7408; one node, 2.5 k beside 6.8 k 250 / 254.
+//     through the separate kernels.  Two sets of launches, two more tails: only where the small ones are many and a good part of all.  20
+//     k tiles in layers of up to 53 beside 54 k, 4 bits 2223 / 2131; 11.7 k beside 5.9 k, 5 bits 587 / 534; 12 k in layers of 256 beside
+//     148 k, 3 bits 7352 / 7408; one node, 2.5 k beside 6.8 k 250 / 254.
 enum HeldTiles { kHoldNone = 0, kHoldAll = 1, kHoldSmall = 2 };
 constexpr long long kHeldLeast = 640, kHeldLeastVector = 832;   // tiles of a launch
 constexpr long long kHeldSmallLeast = 8192;
